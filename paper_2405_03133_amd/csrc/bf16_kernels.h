@@ -40,23 +40,6 @@ __device__ __forceinline__ void unpack4(u32x2 p, float (&f)[4])
 template <bool SAVE, bool ACT>
 struct EpiGUT {
     static constexpr int NOUT = 3;
-    // The ring GEMM forms the activation alone from the bf16 values of both operand sets
-    // (combine) instead of calling pack() on the accumulators.
-    static constexpr bool COMBINE = ACT && !SAVE;
-    static constexpr int COMBINED_PLANE = 0;
-    __device__ __forceinline__ gemm::u32x4 combine(gemm::u32x4 g, gemm::u32x4 u) const
-    {
-        gemm::u32x4 r;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            const float g0 = __uint_as_float(g[w] << 16), g1 = __uint_as_float(g[w] & 0xffff0000u);
-            const float u0 = __uint_as_float(u[w] << 16), u1 = __uint_as_float(u[w] & 0xffff0000u);
-            r[w] = gemm::cvt_pk_bf16(g0 * __builtin_amdgcn_rcpf(1.0f + __expf(-g0)) * u0,
-                                     g1 * __builtin_amdgcn_rcpf(1.0f + __expf(-g1)) * u1);
-        }
-        return r;
-    }
-    static constexpr bool HAS_IN = false;
     typedef NoIn In;
     uint16_t *G, *U, *Act;  // [tokens, d_ff]
     int T, dff, n_off;
@@ -71,6 +54,7 @@ struct EpiGUT {
         for (int e = 0; e < 4; ++e) a[e] = v[0][e] * __builtin_amdgcn_rcpf(1.0f + __expf(-v[0][e])) * v[1][e];
         return pack4(a[0], a[1], a[2], a[3]);
     }
+    __device__ __forceinline__ long row_bytes() const { return 2L * dff; }
     __device__ __forceinline__ uint16_t *ptr(int o, int s, int m, int n) const
     {
         uint16_t *base = (o == 0) ? Act : (o == 1) ? G : U;
@@ -87,8 +71,6 @@ struct EpiGU {
 // C[batch][m][n] = bf16(v)
 struct EpiStore {
     static constexpr int NOUT = 1;
-    static constexpr bool COMBINE = false;
-    static constexpr bool HAS_IN = false;
     typedef NoIn In;
     uint16_t *C;
     long c_batch;
@@ -99,6 +81,7 @@ struct EpiStore {
     {
         return pack4(v[0][0], v[0][1], v[0][2], v[0][3]);
     }
+    __device__ __forceinline__ long row_bytes() const { return 2L * ldc; }
     __device__ __forceinline__ uint16_t *ptr(int, int b, int m, int n) const
     {
         return C + (size_t)b * c_batch + (size_t)m * ldc + n;
@@ -107,8 +90,6 @@ struct EpiStore {
 
 struct EpiStore2 {
     static constexpr int NOUT = 2;
-    static constexpr bool COMBINE = false;
-    static constexpr bool HAS_IN = false;
     typedef NoIn In;
     uint16_t *C0, *C1;
     long c_batch;

@@ -1,20 +1,27 @@
-// Persistent batched bf16 MFMA GEMM for gfx950: 256 x 256 tiles fed by a
-// four-stage LDS ring that is filled with direct global->LDS loads
-// (global_load_lds_dwordx4), so that two to three K steps of operands are in
-// flight while one is being multiplied.  Same problem statement, operand layouts and
-// epilogue interface as gemm_bf16.h (the dense contractions of the merged FFN,
-// paper Section 3.1 / Appendix B); this variant needs M % 256 == 0 and
-// N % (256 / NSET) == 0 and is used whenever the shape allows.
+// Persistent batched bf16 MFMA GEMM for gfx950: 256-column tiles fed by an LDS ring that is filled
+// with direct global->LDS loads (global_load_lds_dwordx4), so that two to three K steps of operands are
+// in flight while one is being multiplied.  Every dense contraction of the merged FFN and of its backward
+// (paper Section 3.1: o_x = FFN(h_x; theta_bar) for all tokens of a segment; Appendix B counts them as
+// 6*L*d*d' FLOPs) is an instance of
 //
-// Per K step (BK = 32) a stage holds A (16 KB) and B (16 KB).  A direct load
-// writes the 64 lanes' 16-byte chunks to 1 KB of consecutive LDS, so the
-// swizzles below are applied on the global side: each lane fetches the chunk
-// that belongs at its LDS position.
+//     C_b[M,N] = sum over sources q of  A_{q,b}[M,K] * B_{q,b}[K,N]
+//
+// with one batch item per segment and fp32 accumulation on v_mfma_f32_32x32x16_bf16.
+//
+// Operand layouts, chosen per instance by template flags:
+//   A: "KC" = stored [M][K] (K contiguous)   or "MC" = stored [K][M]
+//   B: "KC" = stored [N][K] (K contiguous)   or "NC" = stored [K][N]
+//
+// Any M and N (N a multiple of 8, M too for an MC operand): the loads of an edge tile are clamped to the
+// last row or 16-byte chunk of the matrix and its stores are masked.  K % 32 == 0, at least two K steps.
+//
+// Per K step (BK = 32) a stage holds A (64 bytes per row of the tile) and B (16 KB).  A direct load
+// writes the 64 lanes' 16-byte chunks to 1 KB of consecutive LDS, so the swizzles below are applied on
+// the global side: each lane fetches the chunk that belongs at its LDS position.
 //   K-contiguous operand: rows of 32 bf16 = 4 chunks; chunk c of row r lives in
 //     slot c ^ f(r), f(r) = ((r>>1 ^ r>>3) & 1) | ((r>>2 & 1) << 1).
-//   operand stored with K as the slow index (read with ds_read_b64_tr_b16):
-//     32 K rows of W bf16, dense; the 64-byte granule g of row k lives at
-//     granule g ^ (k & 3).
+//   operand stored with K as the slow index (read with ds_read_b64_tr_b16, i.e. transposed by the LDS
+//     read): 32 K rows of W bf16, dense; the 64-byte granule g of row k lives at granule g ^ ftr(k).
 #pragma once
 
 #include "gemm_bf16.h"
@@ -29,22 +36,29 @@ using gemm::s16x4;
 using gemm::u32x2;
 using gemm::u32x4;
 
-constexpr int kThreads = 256;
-constexpr int BM = 256;
 constexpr int BK = 32;
-constexpr int kStages = 4;
-constexpr int kOperandBytes = 16 * 1024;        // one operand of one stage
-constexpr int kStageBytes = 2 * kOperandBytes;  // A + B
 
-template <int NSET>
-struct Smem {
-    static constexpr int BN = 256;  // columns of the tile over all operand sets
-    static constexpr int BNS = BN / NSET;
-    static constexpr int ring = kStages * kStageBytes;
-    // epilogue staging: every wave owns 32 rows x 128 columns of bf16 (one plane of 128 columns, or
-    // the two 64-column planes of a combining epilogue), no padding
-    static constexpr int stage_out = 32 * 128 * 2;
-    static constexpr int total = ring + 4 * stage_out;
+// A tile shape: WMV x WNV wavefronts, each with MI x NB blocks of 32 x 32 outputs (NB counted through the
+// operand sets), the stages of its ring and how many workgroups share a CU.
+template <int WMV_, int WNV_, int MI_, int NB_, int STAGES, int WGS>
+struct Tile {
+    static constexpr int WMV = WMV_, WNV = WNV_, MI = MI_, NB = NB_;
+    static constexpr int NW = WMV * WNV;
+    static constexpr int threads = NW * 64;
+    static constexpr int BM = WMV * MI * 32;        // rows
+    static constexpr int BN = WNV * NB * 32;        // columns over all operand sets
+    static constexpr int stages = STAGES;
+    static constexpr int wgs = WGS;
+    static constexpr int waves_per_simd = NW * WGS / 4;
+    static constexpr int a_bytes = BM * 64;
+    static constexpr int b_bytes = BN * 64;
+    static constexpr int stage = a_bytes + b_bytes;
+    static constexpr int ring = stages * stage;
+    static constexpr int JG = 2;                    // 32-column blocks staged at a time in the epilogue
+    static constexpr int stage_out = 32 * JG * 64;  // bytes per wave
+    static constexpr int total = ring + NW * stage_out;
+    static_assert(a_bytes % (NW * 1024) == 0 && b_bytes % (NW * 1024) == 0, "every wave fetches whole kilobytes");
+    static_assert(WGS * total <= 160 * 1024, "LDS of a CU");
 };
 
 __device__ __forceinline__ int fkc(int row)
@@ -52,22 +66,13 @@ __device__ __forceinline__ int fkc(int row)
     return (((row >> 1) ^ (row >> 3)) & 1) | (((row >> 2) & 1) << 1);
 }
 
-// Element offset (relative to the operand's base pointer at K step 0) of the chunk that belongs
-// at LDS chunk position L of a K-contiguous tile.
-__device__ __forceinline__ long chunk_off_kc(int L, int ld, int row0)
-{
-    const int row = L >> 2, slot = L & 3;
-    return (long)(row0 + row) * ld + ((slot ^ fkc(row)) << 3);
-}
-
-// Same for a tile stored with K as the slow index, W columns wide.
+// XOR of the 64-byte granule index in row k of a K-slow tile W columns wide: the four rows that half a
+// wave of a transposing read touches then lie in different banks.
 template <int W>
-__device__ __forceinline__ long chunk_off_tr(int L, int ld, int col0)
+__device__ __forceinline__ int ftr(int k)
 {
-    constexpr int cpr = W / 8;
-    const int k = L / cpr, pchunk = L % cpr;
-    const int g = (pchunk >> 2) ^ (k & 3);
-    return (long)k * ld + col0 + (((g << 2) | (pchunk & 3)) << 3);
+    static_assert(W == 64 || W % 128 == 0, "a K-slow tile is 64 or a multiple of 128 columns wide");
+    return W == 64 ? ((k >> 1) & 1) : (k & 3);
 }
 
 __device__ __forceinline__ bf16x8 frag_kc(const char *lds, int row0, int kk, int lane)
@@ -77,16 +82,11 @@ __device__ __forceinline__ bf16x8 frag_kc(const char *lds, int row0, int kk, int
     return *reinterpret_cast<const bf16x8 *>(lds + row * 64 + ((c ^ fkc(row)) << 4));
 }
 
-template <int W>
-__device__ __forceinline__ bf16x8 frag_tr(const char *lds, int col0, int kk, int lane)
+__device__ __forceinline__ bf16x8 frag_tr(const char *p, int hi_off)
 {
     typedef __attribute__((address_space(3))) s16x4 *lds_ptr;
-    const int g16 = lane >> 4, r = lane & 15;
-    const int coloff = (col0 + 16 * (g16 & 1) + 4 * (r & 3)) * 2;
-    const int krow = kk * 16 + 8 * (g16 >> 1) + (r >> 2);
-    const char *p = lds + krow * (W * 2) + ((((coloff >> 6) ^ (krow & 3)) << 6) | (coloff & 63));
     const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p));
-    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p + 4 * W * 2));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr)(p + hi_off));
     union {
         s16x4 h[2];
         bf16x8 v;
@@ -109,6 +109,16 @@ __device__ __forceinline__ void dma16(const uint16_t *g, uint32_t lds_addr)
                  : "memory", "m0");
 }
 
+// The same with a wave-uniform base in scalar registers and a 32-bit byte offset per lane: a K step
+// advances the base with one scalar addition and the lanes' offsets stay as they are.
+__device__ __forceinline__ void dma16s(const char *base, uint32_t off, uint32_t lds_addr)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 :
+                 : "s"(lds_addr), "v"(off), "s"(base)
+                 : "memory", "m0");
+}
+
 template <int N>
 __device__ __forceinline__ void wait_vmcnt()
 {
@@ -127,36 +137,37 @@ __device__ __forceinline__ void ring_barrier()
     asm volatile("" ::: "memory");
 }
 
-// Persistent kernel: the grid is one workgroup per CU (a multiple of 8); every workgroup walks
-// its own list of tiles, and the K steps of consecutive tiles form one stream through the
-// ring, so the first operands of the next tile are already in flight while the current tile
-// is multiplied and written out.
-template <int NSET, int NSRC, bool A_MC, bool B_NC, class Epi>
-__global__ __launch_bounds__(kThreads, 1) void gemm2_kernel(const Params p, const Epi epi)
+// Persistent kernel: the grid is one workgroup per CU (two where the tile's LDS allows); every workgroup walks its own list of
+// tiles, and the K steps of consecutive tiles form one stream through the ring, so the first operands of
+// the next tile are already in flight while the current tile is multiplied and written out.
+template <int NSET, int NSRC, bool A_MC, bool B_NC, class TL, class Epi>
+__global__ __launch_bounds__(TL::threads, TL::waves_per_simd) void gemm2_kernel(const Params p, const Epi epi)
 {
     static_assert(NSET == 1 || NSRC == 1, "either two operand sets or two sources");
-    using SM = Smem<NSET>;
-    constexpr int BNS = SM::BNS;          // columns per operand set
-    constexpr int WN = BNS / 2;           // columns per wave and set
-    constexpr int MI = 4, NI = WN / 32;   // 128 x WN per wave and set
-    constexpr int BSET_BYTES = kOperandBytes / NSET;
-    static_assert(NSET * NI == 4, "a wave multiplies 4 A blocks with 4 B blocks per K slice");
+    constexpr int MI = TL::MI, NB = TL::NB;
+    constexpr int BM = TL::BM;
+    constexpr int BNS = TL::BN / NSET;    // columns per operand set
+    constexpr int NI = NB / NSET;         // 32-column blocks per wave and set
+    constexpr int WM = MI * 32;           // rows per wave
+    constexpr int WN = NI * 32;           // columns per wave and set
+    constexpr int S = TL::stages;
+    constexpr int BSET_BYTES = TL::b_bytes / NSET;
+    constexpr int LA = TL::a_bytes / (TL::NW * 1024), LB = TL::b_bytes / (TL::NW * 1024);  // direct loads of a wave per K step
 
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
-    const int wm0 = (wave >> 1) * 128;
-    const int wn0 = (wave & 1) * WN;
-    const uint32_t wave_u = __builtin_amdgcn_readfirstlane(wave);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm0 = (wave / TL::WNV) * WM;
+    const int wn0 = (wave % TL::WNV) * WN;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
 
     // Workgroups are dealt round-robin to the 8 XCDs (each with its own L2).  Every XCD gets a
     // contiguous range of tiles, shared cyclically by its workgroups, so that the tiles of one
     // segment, which share the A operand, meet in the same L2.
-    const int tiles_n = p.N / BNS;
-    const int tiles_m = p.M / BM;
+    const int tiles_n = (p.N + BNS - 1) / BNS;
+    const int tiles_m = (p.M + BM - 1) / BM;
     const int ntiles = p.batches * tiles_m * tiles_n;
     const int per_xcd = (ntiles + 7) >> 3;
     const int wg_per_xcd = gridDim.x >> 3;
@@ -167,20 +178,7 @@ __global__ __launch_bounds__(kThreads, 1) void gemm2_kernel(const Params p, cons
     if (my_tiles == 0) return;
 
     const int ktiles = p.K / BK;
-    const int total = ktiles * NSRC;   // K steps per tile
-    const int G = my_tiles * total;    // K steps of this workgroup
-
-    // per-lane element offsets of this wave's 4 + 4 chunks per stage, relative to the tile origin
-    long offA[4], offB[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int L = (wave * 4 + i) * 64 + lane;  // LDS chunk position inside a 16 KB operand tile
-        offA[i] = A_MC ? chunk_off_tr<BM>(L, p.lda[0], 0) : chunk_off_kc(L, p.lda[0], 0);
-        const int Ls = (NSET == 2) ? (L & 511) : L;
-        offB[i] = B_NC ? chunk_off_tr<BNS>(Ls, p.ldb[0], 0) : chunk_off_kc(Ls, p.ldb[0], 0);
-    }
-    const long kstepA = A_MC ? (long)BK * p.lda[0] : BK;
-    const long kstepB = B_NC ? (long)BK * p.ldb[0] : BK;
+    const int total = ktiles * NSRC;   // K steps per tile, at least two
 
     auto tile_coords = [&](int i, int &batch, int &m0, int &n0) {
         int id = xcd * per_xcd + qx + i * wg_per_xcd;
@@ -192,44 +190,109 @@ __global__ __launch_bounds__(kThreads, 1) void gemm2_kernel(const Params p, cons
         n0 = nt * BNS;
     };
 
-    // The A and the B operand of a K step are fetched at different times (see step()), so each
-    // load stream keeps the origin (in elements) of the tile it is currently in.
-    int ldA_tile = -1, ldB_tile = -1;
-    long tileA = 0, tileB = 0;
-    int ldA_batch = 0, ldB_batch = 0;
-    auto enter_tile_A = [&](int i) {
-        int m0, n0;
-        tile_coords(i, ldA_batch, m0, n0);
-        tileA = A_MC ? (long)m0 : (long)m0 * p.lda[0];
-        ldA_tile = i;
-    };
-    auto enter_tile_B = [&](int i) {
-        int m0, n0;
-        tile_coords(i, ldB_batch, m0, n0);
-        tileB = B_NC ? (long)n0 : (long)n0 * p.ldb[0];
-        ldB_tile = i;
-    };
+    // ---- the two load streams.  A and B of a K step are fetched at different times, so each stream keeps
+    // its own position: a wave-uniform pointer that advances by one K step, the K steps left in the current
+    // source, and the lanes' byte offsets inside the tile (recomputed when a tile is entered, because an
+    // edge tile clamps them).  All per-step work is a handful of scalar instructions: with one wave per
+    // SIMD, whatever is issued between MFMAs and does not fit under them is lost matrix time (an earlier
+    // version that derived the addresses of every load from the K step's number, i.e. from integer
+    // divisions, spent more scalar instructions on them than the step has MFMA issue slots).
+    const char *ptrA, *ptrB;
+    int leftA, leftB, srcA = 0, srcB = 0, iA = 0, iB = 0;
+    long bA = 0, bB = 0;     // byte offset of the current tile inside a source (second source: same offset)
+    uint32_t offA[LA], offB[LB];
+    const long kA = 2 * (A_MC ? (long)BK * p.lda[0] : (long)BK);
+    const long kB = 2 * (B_NC ? (long)BK * p.ldb[0] : (long)BK);
+    const int bset = (NSET == 2) ? wave / (TL::NW / 2) : 0;   // the first half of the waves fetches set 0
 
-    // The 4 + 4 direct loads this wave contributes to K step gsrc of its stream (A chunk i, B
-    // chunk j); gslot = K step whose ring slot receives them.
-    auto issue_A = [&](int gsrc, int gslot, int i) {
-        const int t = gsrc % total;
-        const int src = (NSRC == 2) ? (t / ktiles) : 0;
-        const int ks = t % ktiles;
-        const uint32_t stage = lds0 + (gslot & (kStages - 1)) * kStageBytes + wave_u * 4096;
-        const uint16_t *a = p.A[src] + (size_t)ldA_batch * p.a_batch[src] + tileA + ks * kstepA;
-        dma16(a + offA[i], stage + i * 1024);
+    auto enter_A = [&](int i) {
+        int batch, m0, n0;
+        tile_coords(i, batch, m0, n0);
+        const int rem = p.M - m0;
+#pragma unroll
+        for (int q = 0; q < LA; ++q) {
+            const int L = (wave * LA + q) * 64 + lane;   // LDS chunk position inside the operand tile
+            if constexpr (A_MC) {
+                constexpr int cpr = BM / 8;
+                const int k = L / cpr, pc = L % cpr;
+                int c = ((((pc >> 2) ^ ftr<BM>(k)) << 2) | (pc & 3)) << 3;
+                c = c < rem ? c : rem - 8;
+                offA[q] = 2u * ((uint32_t)k * (uint32_t)p.lda[0] + (uint32_t)c);
+            } else {
+                const int r = L >> 2, c = (L & 3) ^ fkc(r);
+                const int rr = r < rem ? r : rem - 1;
+                offA[q] = 2u * ((uint32_t)rr * (uint32_t)p.lda[0] + 8u * c);
+            }
+        }
+        bA = 2 * ((long)batch * p.a_batch[0] + (A_MC ? (long)m0 : (long)m0 * p.lda[0]));
+        ptrA = reinterpret_cast<const char *>(p.A[0]) + bA;
+        if constexpr (NSRC == 2) bA = 2 * ((long)batch * p.a_batch[1] + (A_MC ? (long)m0 : (long)m0 * p.lda[0]));
+        leftA = ktiles;
+        srcA = 0;
     };
-    auto issue_B = [&](int gsrc, int gslot, int j) {
-        const int t = gsrc % total;
-        const int src = (NSRC == 2) ? (t / ktiles) : 0;
-        const int ks = t % ktiles;
-        const uint32_t stage = lds0 + (gslot & (kStages - 1)) * kStageBytes + wave_u * 4096;
-        const int set = (NSET == 2) ? ((wave * 4 + j) >> 3) : 0;  // 8 KB = 8 wave-loads per set
-        const int bi = (NSRC == 2) ? src : set;
-        const uint16_t *b = p.B[bi] + (size_t)ldB_batch * p.b_batch[bi] + tileB + ks * kstepB;
-        dma16(b + offB[j], stage + kOperandBytes + j * 1024);
+    auto enter_B = [&](int i) {
+        int batch, m0, n0;
+        tile_coords(i, batch, m0, n0);
+        const int rem = p.N - n0;
+#pragma unroll
+        for (int q = 0; q < LB; ++q) {
+            const int L = ((wave * LB + q) * 64 + lane) & (TL::BN * 4 / NSET - 1);
+            if constexpr (B_NC) {
+                constexpr int cpr = BNS / 8;
+                const int k = L / cpr, pc = L % cpr;
+                int c = ((((pc >> 2) ^ ftr<BNS>(k)) << 2) | (pc & 3)) << 3;
+                c = c < rem ? c : rem - 8;
+                offB[q] = 2u * ((uint32_t)k * (uint32_t)p.ldb[0] + (uint32_t)c);
+            } else {
+                const int r = L >> 2, c = (L & 3) ^ fkc(r);
+                const int rr = r < rem ? r : rem - 1;
+                offB[q] = 2u * ((uint32_t)rr * (uint32_t)p.ldb[0] + 8u * c);
+            }
+        }
+        const long in_b = B_NC ? (long)n0 : (long)n0 * p.ldb[0];
+        const int s = (NSET == 2) ? bset : 0;
+        ptrB = reinterpret_cast<const char *>(s ? p.B[1] : p.B[0]) + 2 * ((long)batch * (s ? p.b_batch[1] : p.b_batch[0]) + in_b);
+        if constexpr (NSRC == 2) bB = 2 * ((long)batch * p.b_batch[1] + in_b);
+        leftB = ktiles;
+        srcB = 0;
     };
+    // One K step further.  Past the end of the stream the last K step is fetched again, into slots nobody
+    // reads, so that the wait counts below always hold.
+    auto advance_A = [&]() {
+        ptrA += kA;
+        if (--leftA == 0) {
+            if (NSRC == 2 && srcA == 0) {
+                srcA = 1;
+                ptrA = reinterpret_cast<const char *>(p.A[1]) + bA;
+                leftA = ktiles;
+            } else if (iA + 1 < my_tiles) {
+                enter_A(++iA);
+            } else {
+                ptrA -= kA;
+                leftA = 1;
+            }
+        }
+    };
+    auto advance_B = [&]() {
+        ptrB += kB;
+        if (--leftB == 0) {
+            if (NSRC == 2 && srcB == 0) {
+                srcB = 1;
+                ptrB = reinterpret_cast<const char *>(p.B[1]) + bB;
+                leftB = ktiles;
+            } else if (iB + 1 < my_tiles) {
+                enter_B(++iB);
+            } else {
+                ptrB -= kB;
+                leftB = 1;
+            }
+        }
+    };
+    const uint32_t ldsA = lds0 + wave * (LA * 1024);
+    const uint32_t ldsB = lds0 + TL::a_bytes + wave * (LB * 1024);
+    auto issue_A = [&](uint32_t slot, int i) { dma16s(ptrA, offA[i], ldsA + slot + i * 1024); };
+    auto issue_B = [&](uint32_t slot, int j) { dma16s(ptrB, offB[j], ldsB + slot + j * 1024); };
+    auto next_slot = [&](uint32_t s) -> uint32_t { return s + TL::stage == TL::ring ? 0u : s + TL::stage; };
 
     f32x16 acc[NSET][MI][NI];
     auto zero_acc = [&]() {
@@ -243,239 +306,323 @@ __global__ __launch_bounds__(kThreads, 1) void gemm2_kernel(const Params p, cons
                     for (int r = 0; r < 16; ++r) acc[s][i][j][r] = 0.f;
     };
 
-    for (int g = 0; g < kStages; ++g) {  // the whole ring: K steps 0 .. 3
-        const int gsrc = g < G ? g : G - 1;
-        if (gsrc / total != ldA_tile) enter_tile_A(gsrc / total);
-        if (gsrc / total != ldB_tile) enter_tile_B(gsrc / total);
+    enter_A(0);
+    enter_B(0);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) issue_A(gsrc, g, i);
+    for (int g = 0; g < S; ++g) {  // the whole ring: K steps 0 .. S-1
 #pragma unroll
-        for (int j = 0; j < 4; ++j) issue_B(gsrc, g, j);
+        for (int i = 0; i < LA; ++i) issue_A(g * TL::stage, i);
+#pragma unroll
+        for (int j = 0; j < LB; ++j) issue_B(g * TL::stage, j);
+        advance_A();
+        advance_B();
     }
 
-    // Fragment f of a 16-wide K slice: f < 4 -> A rows block f, else B columns block f - 4
-    // (blocks of B count through the operand sets).
-    auto load_frag = [&](const char *la, int kk, int f, bf16x8 (&af)[MI], bf16x8 (&bfr)[NSET * NI]) {
-        if (f < 4) {
+    // LDS offsets of the lane's fragments inside a stage.  KC: one per 16-wide slice, blocks 2 KB apart.
+    // K-slow: one per block, slices 16 rows apart.
+    constexpr int NFA = A_MC ? MI : 2, NFB = B_NC ? NI : 2;
+    int fragA[NFA], fragB[NFB];
+    {
+        const int g16 = lane >> 4, r = lane & 15, krow = 8 * (g16 >> 1) + (r >> 2);
+#pragma unroll
+        for (int f = 0; f < NFA; ++f) {
+            if constexpr (A_MC) {
+                const int co = (wm0 + f * 32 + 16 * (g16 & 1) + 4 * (r & 3)) * 2;
+                fragA[f] = krow * (BM * 2) + ((((co >> 6) ^ ftr<BM>(krow)) << 6) | (co & 63));
+            } else {
+                const int row = wm0 + (lane & 31);
+                fragA[f] = row * 64 + (((2 * f + (lane >> 5)) ^ fkc(lane & 31)) << 4);
+            }
+        }
+#pragma unroll
+        for (int f = 0; f < NFB; ++f) {
+            if constexpr (B_NC) {
+                const int co = (wn0 + f * 32 + 16 * (g16 & 1) + 4 * (r & 3)) * 2;
+                fragB[f] = TL::a_bytes + krow * (BNS * 2) + ((((co >> 6) ^ ftr<BNS>(krow)) << 6) | (co & 63));
+            } else {
+                const int row = wn0 + (lane & 31);
+                fragB[f] = TL::a_bytes + row * 64 + (((2 * f + (lane >> 5)) ^ fkc(lane & 31)) << 4);
+            }
+        }
+    }
+    // Fragments of a 16-wide K slice in the order their first MFMA needs them: A block 0, the B
+    // blocks (counted through the operand sets), A blocks 1 ..
+    constexpr int NF = MI + NB;
+    auto load_frag = [&](uint32_t slot, int kk, int f, bf16x8 (&af)[MI], bf16x8 (&bfr)[NB]) {
+        const char *la = smem + slot;
+        if (f == 0 || f > NB) {
+            const int i = f == 0 ? 0 : f - NB;
             if constexpr (A_MC)
-                af[f] = frag_tr<BM>(la, wm0 + f * 32, kk, lane);
+                af[i] = frag_tr(la + fragA[i % NFA] + kk * 16 * (BM * 2), 4 * BM * 2);
             else
-                af[f] = frag_kc(la, wm0 + f * 32, kk, lane);
+                af[i] = *reinterpret_cast<const bf16x8 *>(la + fragA[kk] + i * 2048);
         } else {
-            const int q = f - 4, s = q / NI, j = q % NI;
-            const char *lb = la + kOperandBytes + s * BSET_BYTES;
+            const int q = f - 1, s = q / NI, j = q % NI;
             if constexpr (B_NC)
-                bfr[q] = frag_tr<BNS>(lb, wn0 + j * 32, kk, lane);
+                bfr[q] = frag_tr(la + fragB[j % NFB] + s * BSET_BYTES + kk * 16 * (BNS * 2), 4 * BNS * 2);
             else
-                bfr[q] = frag_kc(lb, wn0 + j * 32, kk, lane);
+                bfr[q] = *reinterpret_cast<const bf16x8 *>(la + fragB[kk] + s * BSET_BYTES + j * 2048);
         }
     };
 
-    // The 16 MFMAs of a K slice are issued one per "slot"; every slot also carries one LDS
-    // fragment read for the next slice or one direct load for the ring, so that those issue
-    // in the shadow of the matrix pipe instead of between bursts.  Fragments are double
-    // buffered in registers.  The single barrier of a K step sits between its two slices: by
-    // then every wave has finished reading step g-1 (its ring slot may be refilled with step
-    // g+3) and step g+1 has landed for everyone (its first slice can be fetched behind the
-    // second slice's MFMAs).
-    bf16x8 a0[MI], b0[NSET * NI], a1[MI], b1[NSET * NI];
-    wait_vmcnt<(kStages - 1) * 8>();  // steps 1 .. 3 may still be in flight
+    // The MI * NB MFMAs of a K slice are issued one per "slot"; the first slots also carry the LDS fragment
+    // reads of the next slice, the later ones this wave's direct loads for the ring, so that those issue in
+    // the shadow of the matrix pipe and the fragments have arrived when the slice ends.  Fragments are
+    // double buffered in registers.  The single barrier of a K step sits between its two slices: by then
+    // every wave has finished reading step g-1 (its ring slot may be refilled with step g+S-1) and step
+    // g+1 has landed for everyone (its first slice can be fetched behind the second slice's MFMAs).
+    constexpr int NM = NB * MI;
+    bf16x8 a0[MI], b0[NB], a1[MI], b1[NB];
+    wait_vmcnt<(S - 1) * (LA + LB)>();  // steps 1 .. S-1 may still be in flight
     ring_barrier();
 #pragma unroll
-    for (int f = 0; f < 8; ++f) load_frag(smem, 0, f, a0, b0);
+    for (int f = 0; f < NF; ++f) load_frag(0, 0, f, a0, b0);
 
-    // One K step g.  Its 32 MFMA slots also carry the LDS fragment reads of the next slice (even
-    // slots) and this wave's eight direct loads for the ring, one every fourth slot, spread over
-    // the whole step: the four waves issue theirs at the same time, and the memory pipeline takes
-    // about 16 cycles per load, so loads in adjacent slots (as when all eight sat in one half
-    // step) stalled the waves for longer than the MFMAs they hide behind.  (Giving every wave
-    // slots of its own was tried: the wave-dependent branches cost far more than they saved.)
-    //   first half:  A chunks of step g+3 (into the slot step g-1 left at the previous barrier)
-    //   second half: B chunks of step g+4 (into the slot step g itself left at this step's
-    //                barrier: every wave has fetched its last fragments of step g by then)
-    // so that, with the four ring slots, up to three and a half K steps of operands are in
-    // flight.  The B operand is the one that streams from HBM, hence the longer lead.  Across a
-    // tile boundary the A chunks that the next tile's first step would issue are issued half a
-    // step early, in the last step of the tile, so that everything the next tile's first three
-    // steps wait for is older than the epilogue's stores: loads and stores share vmcnt and
-    // retire in order, and a wait may only leave younger operations pending.
-    // Past the end of the stream the loads re-fetch the last K step into slots nobody reads, so
-    // "all but the newest 16 loads have landed" (vmcnt(16)) always means "step g+1 is complete".
-    // extra_now: store instructions of the previous tile's epilogue that may still be pending
-    // (only non-zero for the first three steps of a tile).
-    auto step = [&](int g, int extra_now, bool first_of_tile, bool last_of_tile) {
-        const char *la = smem + (g & (kStages - 1)) * kStageBytes;
-        const char *ln = smem + ((g + 1) & (kStages - 1)) * kStageBytes;
-        const int srcA = (g + 3 < G) ? (g + 3) : (G - 1);
-        if (!first_of_tile && srcA / total != ldA_tile) enter_tile_A(srcA / total);
+    uint32_t cur = 0, nxt = TL::stage;          // ring slots of step g and g+1
+    uint32_t slotA = (S - 1) * TL::stage;       // slot of step g+S-1: the next one A refills
+    // One K step g:
+    //   first half:  A chunks of step g+S-1 (into the slot step g-1 left at the previous barrier)
+    //   second half: B chunks of step g+S (into the slot step g itself left at this step's barrier:
+    //                every wave has fetched its last fragments of step g by then)
+    // The B operand is the one that streams from HBM, hence the longer lead.  Across a tile boundary the A
+    // chunks that the next tile's first step would issue are issued half a step early, in the last step of
+    // the tile, so that everything the next tile's first S-1 steps wait for is older than the epilogue's
+    // stores: loads and stores share vmcnt and retire in order, and a wait may only leave younger
+    // operations pending.  "All but the newest (S-2)(LA+LB) loads have landed" means "step g+1 is
+    // complete".  extra: store instructions of the previous tile's epilogue that may still be pending.
+    auto step = [&](auto first_c, auto last_c, int extra) {
+        constexpr bool first = decltype(first_c)::value, last = decltype(last_c)::value;
+        constexpr int kWait = (S - 2) * (LA + LB);
 #pragma unroll
-        for (int sl = 0; sl < 16; ++sl) {
-            const int i = sl >> 2, q = sl & 3;
+        for (int sl = 0; sl < NM; ++sl) {
+            const int i = sl / NB, q = sl % NB;
             acc[q / NI][i][q % NI] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b0[q], a0[i], acc[q / NI][i][q % NI], 0, 0, 0);
-            if ((sl & 1) == 0) load_frag(la, 1, sl >> 1, a1, b1);
-            if (!first_of_tile && (sl & 3) == 1) issue_A(srcA, g + 3, sl >> 2);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        if (extra_now == 32)
-            wait_vmcnt<48>();
-        else if (extra_now == 16)
-            wait_vmcnt<32>();
-        else
-            wait_vmcnt<16>();
-        ring_barrier();
-        const int srcB = (g + 4 < G) ? (g + 4) : (G - 1);  // K step to fetch
-        if (srcB / total != ldB_tile) enter_tile_B(srcB / total);
-        if (last_of_tile && srcB / total != ldA_tile) enter_tile_A(srcB / total);
 #pragma unroll
-        for (int sl = 0; sl < 16; ++sl) {
-            const int i = sl >> 2, q = sl & 3;
-            acc[q / NI][i][q % NI] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b1[q], a1[i], acc[q / NI][i][q % NI], 0, 0, 0);
-            if ((sl & 1) == 0) load_frag(ln, 0, sl >> 1, a0, b0);
-            if ((sl & 3) == 1) issue_B(srcB, g + 4, sl >> 2);
-            if (last_of_tile && (sl & 3) == 3) issue_A(srcB, g + 4, sl >> 2);
+            for (int f = 0; f < NF; ++f)
+                if (f * NM / (2 * NF) == sl) load_frag(cur, 1, f, a1, b1);
+            if constexpr (!first) {
+#pragma unroll
+                for (int l = 0; l < LA; ++l)
+                    if (NM / 2 + l * (NM / 2) / LA == sl) issue_A(slotA, l);
+            }
             __builtin_amdgcn_sched_barrier(0);
         }
+        if constexpr (!first) advance_A();
+        if (extra >= 32)
+            wait_vmcnt<kWait + 32>();
+        else if (extra >= 16)
+            wait_vmcnt<kWait + 16>();
+        else
+            wait_vmcnt<kWait>();
+        ring_barrier();
+#pragma unroll
+        for (int sl = 0; sl < NM; ++sl) {
+            const int i = sl / NB, q = sl % NB;
+            acc[q / NI][i][q % NI] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b1[q], a1[i], acc[q / NI][i][q % NI], 0, 0, 0);
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+                if (f * NM / (2 * NF) == sl) load_frag(nxt, 0, f, a0, b0);
+#pragma unroll
+            for (int l = 0; l < LB; ++l)
+                if (NM / 2 + l * (NM / 2) / LB == sl) issue_B(cur, l);
+            if constexpr (last) {
+#pragma unroll
+                for (int l = 0; l < LA; ++l)
+                    if (NM / 2 + l * (NM / 2) / LA == sl) issue_A(cur, l);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        advance_B();
+        if constexpr (last) advance_A();
+        slotA = cur;
+        cur = nxt;
+        nxt = next_slot(nxt);
     };
 
-    // Epilogue of one tile, wave-local: the wave's 128 x WN sub-tile leaves in blocks of 32 rows
+    // Epilogue of one tile, wave-local: the wave's WM x WN sub-tile leaves in blocks of 32 rows
     // through the wave's own staging area (XOR-swizzled 16-byte chunks), as 16-byte stores that
     // are contiguous along n.  Accumulator element r of a 32x32 block is row m = lane & 31,
-    // column n = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3).
-    char *stg = smem + SM::ring + wave * SM::stage_out;
-    constexpr int CP = WN / 8;  // 16-byte chunks per staged row
-    auto epilogue = [&](int tile_i) {
-        int batch, m0, n0;
-        tile_coords(tile_i, batch, m0, n0);
-        const int r = lane & 31, h = lane >> 5;
+    // column n = 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3).  Edge tiles (not full) mask the rows and chunks
+    // beyond the matrix.
+    char *stg = smem + TL::ring + wave * TL::stage_out;
+    constexpr int JG = TL::JG < NI ? TL::JG : NI;   // 32-column blocks staged at a time
+    constexpr int CP = JG * 4;             // 16-byte chunks per staged row
+    auto epilogue = [&](auto full_c, int batch, int m0, int n0) {
+        constexpr bool full = decltype(full_c)::value;
+        // keeps the two instances apart: merged, their common part would hold every packed value at once
+        if constexpr (full)
+            asm volatile("; interior tile" ::: "memory");
+        else
+            asm volatile("; edge tile" ::: "memory");
+        int el = lane;
+        asm volatile("" : "+v"(el));   // lane constants of the epilogue are formed here, not kept across the K loop
+        const int r = el & 31, h = el >> 5;
+        // The lane's position in the stores: row lane / CP of every RPI rows, chunk lane % CP.  The
+        // address of every plane is a running pointer.
+        constexpr int RPI = 64 / CP;
+        const int srow = el / CP, sc = el % CP;
+        const int ncol = n0 + wn0 + sc * 8;
+        const long step_bytes = (long)RPI * epi.row_bytes();
+        char *out[Epi::NOUT];
+#pragma unroll
+        for (int o = 0; o < Epi::NOUT; ++o)
+            if (epi.enabled(o)) out[o] = reinterpret_cast<char *>(epi.ptr(o, batch, m0 + wm0 + srow, ncol));
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
-            if constexpr (Epi::COMBINE) {
-                // One output plane computed from both operand sets: both are staged as bf16 and
-                // combined on the way out.  (Combined straight from the accumulators, the compiler
-                // copied the whole second set to VGPRs at the top of the epilogue and spilled.)
-                static_assert(NSET == 2, "a combining epilogue has two operand sets");
-                constexpr int PLB = 32 * WN * 2;
-#pragma unroll
-                for (int s = 0; s < NSET; ++s)
-#pragma unroll
-                    for (int j = 0; j < NI; ++j)
-#pragma unroll
-                        for (int rq = 0; rq < 4; ++rq) {
-                            const int c = (j * 32 + 8 * rq) >> 3;
-                            u32x2 pk;
-                            pk.x = gemm::cvt_pk_bf16(acc[s][i][j][rq * 4 + 0], acc[s][i][j][rq * 4 + 1]);
-                            pk.y = gemm::cvt_pk_bf16(acc[s][i][j][rq * 4 + 2], acc[s][i][j][rq * 4 + 3]);
-                            *reinterpret_cast<u32x2 *>(stg + s * PLB + r * (WN * 2) + ((c ^ (r & (CP - 1))) << 4) + h * 8) = pk;
-                            __builtin_amdgcn_sched_barrier(0);
-                        }
-                __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                for (int it = 0; it < (32 * CP) / 64; ++it) {
-                    const int idx = it * 64 + lane;
-                    const int row = idx / CP, c = idx % CP;
-                    const int off = row * (WN * 2) + ((c ^ (row & (CP - 1))) << 4);
-                    const u32x4 v0 = *reinterpret_cast<const u32x4 *>(stg + off);
-                    const u32x4 v1 = *reinterpret_cast<const u32x4 *>(stg + PLB + off);
-                    __builtin_nontemporal_store(
-                        epi.combine(v0, v1),
-                        reinterpret_cast<u32x4 *>(epi.ptr(Epi::COMBINED_PLANE, batch, m0 + wm0 + i * 32 + row, n0 + wn0 + c * 8)));
-                }
-                __builtin_amdgcn_wave_barrier();
-                continue;
-            }
+            const int mb = m0 + wm0 + i * 32;
             // all planes of one 32-row block before the next block: its accumulators are read
             // into registers once
 #pragma unroll
             for (int o = 0; o < Epi::NOUT; ++o) {
                 if (!epi.enabled(o)) continue;
+                char *dst = out[o];
 #pragma unroll
-                for (int j = 0; j < NI; ++j)
+                for (int jg = 0; jg < NI; jg += JG) {
 #pragma unroll
-                    for (int rq = 0; rq < 4; ++rq) {
-                        const int nl = j * 32 + 8 * rq + 4 * h;  // column inside the wave's WN columns
-                        float v[NSET][4];
+                    for (int jj = 0; jj < JG; ++jj)
 #pragma unroll
-                        for (int s = 0; s < NSET; ++s)
+                        for (int rq = 0; rq < 4; ++rq) {
+                            const int j = jg + jj;
+                            const int nl = j * 32 + 8 * rq + 4 * h;  // column inside the wave's WN columns
+                            float v[NSET][4];
 #pragma unroll
-                            for (int e = 0; e < 4; ++e) v[s][e] = acc[s][i][j][rq * 4 + e];
-                        const u32x2 pk = epi.pack(o, batch, m0 + wm0 + i * 32 + r, n0 + wn0 + nl, typename Epi::In(), v);
-                        const int c = nl >> 3;
-                        *reinterpret_cast<u32x2 *>(stg + r * (WN * 2) + ((c ^ (r & (CP - 1))) << 4) + h * 8) = pk;
-                        __builtin_amdgcn_sched_barrier(0);  // one quad at a time: keeps register use flat
+                            for (int s = 0; s < NSET; ++s)
+#pragma unroll
+                                for (int e = 0; e < 4; ++e) v[s][e] = acc[s][i][j][rq * 4 + e];
+                            const u32x2 pk = epi.pack(o, batch, mb + r, n0 + wn0 + nl, typename Epi::In(), v);
+                            const int c = jj * 4 + rq;
+                            *reinterpret_cast<u32x2 *>(stg + r * (CP * 16) + ((c ^ (r & (CP - 1))) << 4) + h * 8) = pk;
+                            __builtin_amdgcn_sched_barrier(0);  // one quad at a time: keeps register use flat
+                        }
+                    __builtin_amdgcn_wave_barrier();
+                    dst = out[o] + jg * 64;
+#pragma unroll
+                    for (int it = 0; it < 32 / RPI; ++it) {
+                        const int row = it * RPI + srow;
+                        const u32x4 val = *reinterpret_cast<const u32x4 *>(stg + row * (CP * 16) + ((sc ^ (row & (CP - 1))) << 4));
+                        // streamed output: non-temporal, so that it does not push the operands that later
+                        // tiles share (activations of the segment) out of the caches
+                        if (full || (mb + row < p.M && ncol + jg * 32 < p.N))
+                            __builtin_nontemporal_store(val, reinterpret_cast<u32x4 *>(dst));
+                        dst += step_bytes;
+                        asm volatile("" : "+v"(dst));
                     }
-                __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                for (int it = 0; it < (32 * CP) / 64; ++it) {
-                    const int idx = it * 64 + lane;
-                    const int row = idx / CP, c = idx % CP;
-                    const u32x4 val = *reinterpret_cast<const u32x4 *>(stg + row * (WN * 2) + ((c ^ (row & (CP - 1))) << 4));
-                    // streamed output: non-temporal, so that it does not push the operands that later
-                    // tiles share (activations of the segment) out of the caches
-                    __builtin_nontemporal_store(
-                        val, reinterpret_cast<u32x4 *>(epi.ptr(o, batch, m0 + wm0 + i * 32 + row, n0 + wn0 + c * 8)));
+                    __builtin_amdgcn_wave_barrier();
                 }
-                __builtin_amdgcn_wave_barrier();
+                out[o] = dst - (NI - JG) * 64;
             }
         }
     };
 
-    // 16-byte store instructions a wave issues per tile epilogue
+    // 16-byte store instructions a wave issues per interior tile
     int nst = 0;
 #pragma unroll
     for (int o = 0; o < Epi::NOUT; ++o)
-        if (epi.enabled(o)) nst += MI * ((32 * CP) / 64);
-    const int extra = (total >= 2) ? (nst >= 32 ? 32 : (nst >= 16 ? 16 : 0)) : 0;
-    int g = 0;
+        if (epi.enabled(o)) nst += MI * NI * 2;
+    using T = std::true_type;
+    using F = std::false_type;
+    int extra = 0;
     for (int tile_i = 0; tile_i < my_tiles; ++tile_i) {
         zero_acc();
-        // the first three K steps of a tile run while the previous tile's stores drain
-        const int relaxed = (tile_i > 0) ? 3 : 0;
-        for (int t = 0; t < total; ++t, ++g) step(g, t < relaxed ? extra : 0, t == 0, t == total - 1);
-        epilogue(tile_i);
+        // the first S-1 K steps of a tile run while the previous tile's stores drain
+        step(T(), F(), extra);
+        for (int t = 1; t < total - 1; ++t) step(F(), F(), t < S - 1 ? extra : 0);
+        step(F(), T(), total - 1 < S - 1 ? extra : 0);
+        int batch, m0, n0;
+        tile_coords(tile_i, batch, m0, n0);
+        if (m0 + BM <= p.M && n0 + BNS <= p.N) {
+            epilogue(T(), batch, m0, n0);
+            extra = nst;
+        } else {
+            epilogue(F(), batch, m0, n0);
+            extra = 0;   // masked stores may not have been issued: wait as if there were none
+        }
     }
     wait_vmcnt<0>();  // no direct load may still be writing LDS when the workgroup retires
 }
 
-// Shapes this kernel accepts.
-template <int NSET, int NSRC>
-inline bool fits(const Params &p)
+inline int cu_count()
 {
-    if (p.M % BM != 0 || p.N % (256 / NSET) != 0 || p.K % BK != 0) return false;
-    if (NSRC == 2 && (p.lda[0] != p.lda[1] || p.ldb[0] != p.ldb[1])) return false;
-    if (NSET == 2 && p.ldb[0] != p.ldb[1]) return false;
-    return true;
-}
-
-inline int persistent_grid()
-{
-    static int grid = 0;
-    if (grid == 0) {
+    static int n = 0;
+    if (n == 0) {
         int dev = 0, cus = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 8)
             cus = 256;
-        grid = cus / 8 * 8;
+        n = cus / 8 * 8;
     }
-    return grid;
+    return n;
 }
 
-template <int NSET, int NSRC, bool A_MC, bool B_NC, class Epi>
+inline int persistent_grid() { return cu_count(); }
+
+template <int NSET, int NSRC, bool A_MC, bool B_NC, class TL, class Epi>
 inline hipError_t launch(const Params &p, const Epi &epi, hipStream_t st)
 {
-    using SM = Smem<NSET>;
-    auto kern = gemm2_kernel<NSET, NSRC, A_MC, B_NC, Epi>;
+    if (p.K % BK != 0 || p.K < 2 * BK || p.N % 8 != 0 || p.M < 1 || p.N < 8 || (A_MC && p.M % 8 != 0)) return hipErrorInvalidValue;
+    if (NSRC == 2 && (p.lda[0] != p.lda[1] || p.ldb[0] != p.ldb[1])) return hipErrorInvalidValue;
+    if (NSET == 2 && p.ldb[0] != p.ldb[1]) return hipErrorInvalidValue;
+    auto kern = gemm2_kernel<NSET, NSRC, A_MC, B_NC, TL, Epi>;
     static bool configured = false;  // per instantiation
     if (!configured) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, SM::total);
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, TL::total);
         if (e != hipSuccess) return e;
         configured = true;
     }
-    const long ntiles = (long)p.batches * (p.M / BM) * (p.N / SM::BNS);
+    constexpr int BNS = TL::BN / NSET;
+    const long ntiles = (long)p.batches * ((p.M + TL::BM - 1) / TL::BM) * ((p.N + BNS - 1) / BNS);
+    const long slots = (long)cu_count() * TL::wgs;
     long blocks = (ntiles + 7) / 8 * 8;
-    if (blocks > persistent_grid()) blocks = persistent_grid();  // one workgroup per CU walks several tiles
-    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kThreads), SM::total, st, p, epi);
+    if (blocks > slots) blocks = slots;  // every workgroup walks several tiles
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(TL::threads), TL::total, st, p, epi);
     return hipGetLastError();
+}
+
+// Tile shapes in use.  Eight waves (two per SIMD) where the tile is 256 rows tall: with four waves of
+// 128 x 128 the CU's vector-memory path delivered 16 bytes per cycle at one wave per SIMD, and weight
+// gradients (short contractions) waited for their own epilogues.  Sustained rates on N(0,1) data,
+// TFLOP/s, four-wave kernel -> this one: X_s^T dG_s of 64 segments of 256 tokens at d = 2048, d_ff = 5632:
+// 695 -> 860; dY Wd_bar^T of the same: 840 -> 930; a single 8192^3 product: 1300, where the chip is at
+// its power limit.  192 rows need four waves (12 KB of A do not divide by eight); 128 rows ran faster
+// with four waves and three stages than with eight and four (A Wd_bar of 32 segments at d = 1024: 45
+// against 53 us).
+using T256 = Tile<2, 4, 4, 2, 4, 1>;
+using T192 = Tile<2, 2, 3, 4, 4, 1>;
+using T128 = Tile<2, 2, 2, 4, 3, 1>;
+using T64 = Tile<2, 2, 1, 4, 4, 1>;
+using W128 = Tile<2, 4, 2, 2, 4, 1>;   // 128 rows of a weight gradient
+
+// Rounds of tiles over the CUs, in units of the time of one round.
+inline double rounds_of(const Params &p, int bm, int bns)
+{
+    const long tiles = (long)p.batches * ((p.M + bm - 1) / bm) * ((p.N + bns - 1) / bns);
+    return (double)((tiles + cu_count() - 1) / cu_count());
+}
+
+// Tile height of a contraction whose rows are the tokens of a segment: the shortest estimated time,
+// i.e. rounds of tiles over the CUs times the measured time of a tile's K step (us, all CUs busy:
+// 0.90, 0.72, 0.55 and 0.42 for 256, 192, 128 and 64 rows).  A taller tile costs less per row, a lower one
+// wastes fewer rows of a segment and fewer CUs of the last round.
+template <int NSET, int NSRC, bool A_MC, bool B_NC, class Epi>
+inline hipError_t launch_rows(const Params &p, const Epi &e, hipStream_t st)
+{
+    const int bns = 256 / NSET;
+    const double t256 = 0.90 * rounds_of(p, 256, bns), t192 = 0.72 * rounds_of(p, 192, bns);
+    const double t128 = 0.55 * rounds_of(p, 128, bns), t64 = 0.42 * rounds_of(p, 64, bns);
+    if (t256 <= t192 && t256 <= t128 && t256 <= t64) return launch<NSET, NSRC, A_MC, B_NC, T256>(p, e, st);
+    if (t192 <= t128 && t192 <= t64) return launch<NSET, NSRC, A_MC, B_NC, T192>(p, e, st);
+    if (t128 <= t64) return launch<NSET, NSRC, A_MC, B_NC, T128>(p, e, st);
+    return launch<NSET, NSRC, A_MC, B_NC, T64>(p, e, st);
+}
+
+// Tile of a weight gradient (K = tokens of a segment): both heights take the same time per element
+// (bound by their stores), so the one that wastes less of the last round.
+template <int NSET, int NSRC, bool A_MC, bool B_NC, class Epi>
+inline hipError_t launch_weight(const Params &p, const Epi &e, hipStream_t st)
+{
+    if (rounds_of(p, 256, 256) <= 0.51 * rounds_of(p, 128, 256)) return launch<NSET, NSRC, A_MC, B_NC, T256>(p, e, st);
+    return launch<NSET, NSRC, A_MC, B_NC, W128>(p, e, st);
 }
 
 }  // namespace gemm2

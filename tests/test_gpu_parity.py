@@ -189,6 +189,24 @@ def test_bf16_small_shapes(cfg, budget, default_budget):
     compare(cfg, got, ref, ALL, TOL["bf16"])
 
 
+# Shapes whose GEMMs need edge tiles of every height (T or d_ff no multiple of the tile) and several tiles
+# per workgroup, so that edge tiles sit inside the stream of K steps.
+RING_EDGE_CASES = [
+    LoryConfig("ring_192_rows", B=4, L=4608, T=192, d=320, d_ff=832, E=3, dtype="bf16", seed=45),
+    LoryConfig("ring_128_rows_clamped", B=2, L=3840, T=320, d=320, d_ff=832, E=3, dtype="bf16", seed=46),
+    LoryConfig("ring_256_rows_clamped", B=2, L=4032, T=448, d=320, d_ff=832, E=3, dtype="bf16", seed=47),
+    LoryConfig("ring_64_rows", B=2, L=1280, T=64, d=192, d_ff=704, E=20, dtype="bf16", seed=48),
+    LoryConfig("ring_smallest", B=1, L=64, T=64, d=64, d_ff=64, E=2, dtype="bf16", seed=49),
+]
+
+
+@pytest.mark.parametrize("cfg", RING_EDGE_CASES, ids=lambda c: c.name)
+def test_bf16_ring_gemm_edge_tiles(cfg):
+    t = make_inputs(cfg, structured=True)
+    got = run_layer(cfg, t)
+    compare(cfg, got, oracle_layer(cfg, t, got["w_used"]), ALL, TOL["bf16"])
+
+
 def test_bf16_recompute_bf16_grads_and_accumulate(default_budget):
     cfg = BF16_CASES[0][0]
     lb.lory_set_slab_budget(1 << 20)
