@@ -224,8 +224,9 @@ int lory_prompt_merge(const lory_shape *shape, const void *X_prompt, const int32
  * shape: L = tokens per sequence in this call (1 for a decode step), T = L.
  * in:  X [B, L, d] (dtype); Wbar as lory_prompt_merge wrote it
  * out: Y [B, L, d] (dtype)
- * LORY_BF16 with L % 64 == 0 runs on the batched matrix-core GEMMs; every other
- * case runs HBM-bound kernels that read each weight once per 8 tokens.
+ * LORY_BF16 runs on the batched matrix-core GEMMs (contractions split over K when
+ * few tokens would leave the chip idle); LORY_F32 runs HBM-bound kernels that read
+ * each weight once per 8 tokens.
  * workspace: lory_workspace_bytes(shape, LORY_PASS_DENSE).
  */
 int lory_dense_ffn_fwd(const lory_shape *shape, const void *X, const void *Wbar, void *Y,

@@ -83,7 +83,67 @@ __global__ __launch_bounds__(256) void swiglu_fwd_kernel(const uint16_t *__restr
     }
 }
 
+// Sums of fp32 partial products over the K slices of a split contraction, in slice order; four
+// consecutive elements per thread.  HBM-bound (the parts of a small call sit in the memory-side cache).
+__device__ __forceinline__ float4 sum_parts(const float *p, int ksplit, size_t pitch)
+{
+    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+    int s = 0;
+    for (; s + 4 <= ksplit; s += 4) {  // loads overlap, adds stay in order
+        float4 v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = *reinterpret_cast<const float4 *>(p + (size_t)(s + i) * pitch);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            a.x += v[i].x; a.y += v[i].y; a.z += v[i].z; a.w += v[i].w;
+        }
+    }
+    for (; s < ksplit; ++s) {
+        const float4 v = *reinterpret_cast<const float4 *>(p + (size_t)s * pitch);
+        a.x += v.x; a.y += v.y; a.z += v.z; a.w += v.w;
+    }
+    return a;
+}
+
+// part [ksplit][batches][2][mn] -> Act [batches][mn]
+__global__ __launch_bounds__(256) void sum_act_kernel(const float *__restrict__ part, int ksplit, long batches, long mn,
+                                                      uint16_t *__restrict__ Act)
+{
+    const long i = ((long)blockIdx.x * 256 + threadIdx.x) * 4;
+    if (i >= batches * mn) return;
+    const long b = i / mn, e = i - b * mn;
+    const float *p = part + (size_t)b * 2 * mn + e;
+    const size_t pitch = (size_t)batches * 2 * mn;
+    const float4 g = sum_parts(p, ksplit, pitch), u = sum_parts(p + mn, ksplit, pitch);
+    auto act = [](float x, float y) { return x * __builtin_amdgcn_rcpf(1.0f + __expf(-x)) * y; };
+    *reinterpret_cast<u32x2 *>(Act + i) = pack4(act(g.x, u.x), act(g.y, u.y), act(g.z, u.z), act(g.w, u.w));
+}
+
+// part [ksplit][n] -> Y [n]
+__global__ __launch_bounds__(256) void sum_store_kernel(const float *__restrict__ part, int ksplit, long n,
+                                                        uint16_t *__restrict__ Y)
+{
+    const long i = ((long)blockIdx.x * 256 + threadIdx.x) * 4;
+    if (i >= n) return;
+    const float4 y = sum_parts(part + i, ksplit, (size_t)n);
+    *reinterpret_cast<u32x2 *>(Y + i) = pack4(y.x, y.y, y.z, y.w);
+}
+
 }  // namespace
+
+hipError_t launch_sum_act(hipStream_t st, const float *part, int ksplit, long batches, long mn, uint16_t *Act)
+{
+    const long blocks = (batches * mn / 4 + 255) / 256;
+    hipLaunchKernelGGL(sum_act_kernel, dim3((unsigned)blocks), dim3(256), 0, st, part, ksplit, batches, mn, Act);
+    return hipGetLastError();
+}
+
+hipError_t launch_sum_store(hipStream_t st, const float *part, int ksplit, long n, uint16_t *Y)
+{
+    const long blocks = (n / 4 + 255) / 256;
+    hipLaunchKernelGGL(sum_store_kernel, dim3((unsigned)blocks), dim3(256), 0, st, part, ksplit, n, Y);
+    return hipGetLastError();
+}
 
 hipError_t launch_swiglu_fwd(hipStream_t st, const uint16_t *G, const uint16_t *U, uint16_t *Act, long rows,
                              int dff, int n0, int nf)

@@ -27,5 +27,17 @@ hipError_t launch_down(hipStream_t st, const gemm::Params &p, const EpiStore &e)
     return gemm2::launch_rows<1, 1, false, true>(p, e, st);
 }
 
+hipError_t launch_gu_split(hipStream_t st, const gemm::Params &p, const EpiPart<2> &e, int rows)
+{
+    if (rows == 128) return gemm2::launch<2, 1, false, true, gemm2::T128>(p, e, st);
+    return gemm2::launch<2, 1, false, true, gemm2::T64>(p, e, st);
+}
+
+hipError_t launch_down_split(hipStream_t st, const gemm::Params &p, const EpiPart<1> &e, int rows)
+{
+    if (rows == 128) return gemm2::launch<1, 1, false, true, gemm2::T128>(p, e, st);
+    return gemm2::launch<1, 1, false, true, gemm2::T64>(p, e, st);
+}
+
 }  // namespace k
 }  // namespace lory

@@ -40,6 +40,7 @@ __device__ __forceinline__ void unpack4(u32x2 p, float (&f)[4])
 template <bool SAVE, bool ACT>
 struct EpiGUT {
     static constexpr int NOUT = 3;
+    static constexpr bool SPLIT = false;
     typedef NoIn In;
     uint16_t *G, *U, *Act;  // [tokens, d_ff]
     int T, dff, n_off;
@@ -71,6 +72,7 @@ struct EpiGU {
 // C[batch][m][n] = bf16(v)
 struct EpiStore {
     static constexpr int NOUT = 1;
+    static constexpr bool SPLIT = false;
     typedef NoIn In;
     uint16_t *C;
     long c_batch;
@@ -90,6 +92,7 @@ struct EpiStore {
 
 struct EpiStore2 {
     static constexpr int NOUT = 2;
+    static constexpr bool SPLIT = false;
     typedef NoIn In;
     uint16_t *C0, *C1;
     long c_batch;
@@ -103,6 +106,25 @@ struct EpiStore2 {
     __device__ __forceinline__ uint16_t *ptr(int o, int b, int m, int n) const
     {
         return (o == 0 ? C0 : C1) + (size_t)b * c_batch + (size_t)m * ldc + n;
+    }
+};
+
+// fp32 partial sums of one K slice: part[slice][batch][set][m][n]
+template <int NSET>
+struct EpiPart {
+    static constexpr int NOUT = 1;
+    static constexpr bool SPLIT = true;
+    typedef NoIn In;
+    float *P;
+    int ksplit, batches, M, N;   // batches: items before the split
+    __device__ __forceinline__ bool enabled(int) const { return false; }
+    __device__ __forceinline__ long row_bytes() const { return 0; }
+    __device__ __forceinline__ uint16_t *ptr(int, int, int, int) const { return nullptr; }
+    __device__ __forceinline__ u32x2 pack(int, int, int, int, const In &, const float (&)[NSET][4]) const { return u32x2{0, 0}; }
+    __device__ __forceinline__ float *part(int set, int bs, int m, int n) const
+    {
+        const int sl = bs % ksplit, b = bs / ksplit;
+        return P + ((((size_t)sl * batches + b) * NSET + set) * M + m) * N + n;
     }
 };
 
@@ -127,6 +149,14 @@ hipError_t launch_fused_dw(hipStream_t st, const fsg::Params &p);
 
 hipError_t launch_gu(hipStream_t st, const gemm::Params &p, const EpiGU &e);     // X * [Wg_bar | Wu_bar]
 hipError_t launch_down(hipStream_t st, const gemm::Params &p, const EpiStore &e);  // A * Wd_bar
+// The same two projections with the contraction split into p.ksplit slices (p.batches already counts them);
+// rows: tile height, 64 or 128.
+hipError_t launch_gu_split(hipStream_t st, const gemm::Params &p, const EpiPart<2> &e, int rows);
+hipError_t launch_down_split(hipStream_t st, const gemm::Params &p, const EpiPart<1> &e, int rows);
+// Sums of the K slices in slice order: part [ksplit][batches][2][M][N] -> Act = silu(G) * U, or
+// part [ksplit][batches][1][M][N] -> Y; n = batches * M * N elements, N a multiple of 4.
+hipError_t launch_sum_act(hipStream_t st, const float *part, int ksplit, long batches, long mn, uint16_t *Act);
+hipError_t launch_sum_store(hipStream_t st, const float *part, int ksplit, long n, uint16_t *Y);
 hipError_t launch_da(hipStream_t st, const gemm::Params &p, const EpiStore &e);  // dY * Wd_bar^T
 hipError_t launch_swiglu_fwd(hipStream_t st, const uint16_t *G, const uint16_t *U, uint16_t *Act, long rows,
                              int dff, int n0, int nf);

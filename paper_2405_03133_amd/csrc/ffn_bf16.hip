@@ -340,14 +340,88 @@ int bf16_merge_all(const Dims &m, const float *w, const void *Wgv, const void *W
     return LORY_OK;
 }
 
-size_t bf16_dense_workspace_bytes(const Dims &m) { return align_up((size_t)m.tokens * m.dff * 2, 256); }
+namespace {
+
+// Tile height and K slices of one projection of the dense FFN.
+struct DenseSplit {
+    int rows;    // 0: not split, launch_rows picks the tile
+    int ks;
+};
+
+// M rows per sequence, N columns per operand set, nset operand sets.  A few dozen rows against one weight
+// matrix per sequence leave most CUs without a tile, and the pass is then bound by how many CUs stream the
+// weights, so the contraction is cut into slices until the tiles fill the chip once; what a slice costs is its
+// fp32 partial sums (written once, read once).  Estimate, us: K steps of a CU (0.55 / 0.42 each for 128 / 64
+// rows, plus six for the fill of the ring and the epilogue) + the partial sums at 4 TB/s.
+// max_floats bounds the partial sums.  Measured at d = 2048, d_ff = 5632, 2 sequences (140 MB of weights), us
+// per call against kernels that read the weights once per 8 tokens on the vector ALUs: 1 token 33.6 / 36.7, 8
+// tokens 34.7 / 89, 32: 36 / 357, 100: 49 / 1126, 400: 81 / 4452; blocks of 64 and 256 tokens on the unsplit
+// GEMM took 79 and 91, split 40 and 67.
+DenseSplit dense_split(const Dims &m, int M, int N, int K, int nset, size_t max_floats)
+{
+    const int cus = gemm2::cu_count(), bns = 256 / nset, steps = K / gemm2::BK;
+    DenseSplit best = {0, 1};
+    const long tiles256 = (long)m.B * ((M + 255) / 256) * ((N + bns - 1) / bns);
+    double best_t = 0.9 * (double)((tiles256 + cus - 1) / cus) * (steps + 6);
+    for (int rows = 64; rows <= 256; rows += rows) {
+        const double step = rows == 64 ? 0.42 : rows == 128 ? 0.55 : 0.90;
+        const long tiles = (long)m.B * ((M + rows - 1) / rows) * ((N + bns - 1) / bns);
+        const double t1 = step * (double)((tiles + cus - 1) / cus) * (steps + 6);
+        if (t1 < best_t) {
+            best_t = t1;
+            best = {0, 1};
+        }
+        if (rows == 256) break;   // few tiles of this height means short blocks: lower tiles do the same
+        for (int ks = 2; ks <= steps / 4 && tiles * ks <= cus; ++ks) {
+            const double parts = (double)ks * nset * m.B * M * N;
+            if (parts > (double)max_floats) break;
+            const double t = step * ((steps + ks - 1) / ks + 6) + parts * 8.0 / 4e6 + 3.0;
+            if (t < best_t) {
+                best_t = t;
+                best = {rows, ks};
+            }
+        }
+    }
+    return best;
+}
+
+struct DensePlan {
+    DenseSplit gu, down;
+    size_t act, parts;   // bytes
+};
+
+DensePlan dense_plan(const Dims &m, size_t budget)
+{
+    DensePlan p;
+    p.act = align_up((size_t)m.tokens * m.dff * 2, 256);
+    const size_t fl = budget > p.act ? (budget - p.act) / sizeof(float) : 0;
+    p.gu = dense_split(m, m.L, m.dff, m.d, 2, fl);
+    p.down = dense_split(m, m.L, m.d, m.dff, 1, fl);
+    size_t a = p.gu.rows ? (size_t)p.gu.ks * 2 * m.tokens * m.dff : 0;
+    const size_t b = p.down.rows ? (size_t)p.down.ks * m.tokens * m.d : 0;
+    if (b > a) a = b;
+    p.parts = align_up(a * sizeof(float), 256);
+    return p;
+}
+
+}  // namespace
+
+// `budget`: the partial sums of split contractions are kept within this many bytes (activations included).
+size_t bf16_dense_workspace_bytes(const Dims &m, size_t budget)
+{
+    const DensePlan p = dense_plan(m, budget);
+    return p.act + p.parts;
+}
 
 // Dense SwiGLU FFN of every sequence with its own materialised merged parameters
-// (m.T == m.L: one parameter set per sequence, T a multiple of 64).
-int bf16_dense_ffn_fwd(const Dims &m, const void *Xv, const void *Wbarv, void *Yv, void *ws, hipStream_t st)
+// (m.T == m.L: one parameter set per sequence, any number of rows).
+int bf16_dense_ffn_fwd(const Dims &m, const void *Xv, const void *Wbarv, void *Yv, void *ws, size_t budget,
+                       hipStream_t st)
 {
     const bf *X = (const bf *)Xv, *Wbar = (const bf *)Wbarv;
+    const DensePlan pl = dense_plan(m, budget);
     bf *Y = (bf *)Yv, *Act = (bf *)ws;
+    float *parts = (float *)((char *)ws + pl.act);
     const long TD = (long)m.T * m.d, TF = (long)m.T * m.dff;
     {
         Params p = {};
@@ -355,20 +429,36 @@ int bf16_dense_ffn_fwd(const Dims &m, const void *Xv, const void *Wbarv, void *Y
         p.B[0] = Wbar; p.b_batch[0] = m.D; p.ldb[0] = m.dff;
         p.B[1] = Wbar + (size_t)m.S * m.D; p.b_batch[1] = m.D; p.ldb[1] = m.dff;
         p.M = m.T; p.N = m.dff; p.K = m.d; p.batches = m.S;
-        EpiGU epi = {nullptr, nullptr, Act, m.T, m.dff, 0};
         prof::Range r(st, prof::kGemmGU, gemm_flops(p, 2, 1),
                       2.0 * ((double)m.S * TD + 2.0 * m.S * m.D + (double)m.S * TF));
-        LORY_TRY(k::launch_gu(st, p, epi));
+        if (pl.gu.rows) {
+            p.ksplit = pl.gu.ks;
+            p.batches = m.S * pl.gu.ks;
+            const k::EpiPart<2> epi = {parts, pl.gu.ks, m.S, m.T, m.dff};
+            LORY_TRY(k::launch_gu_split(st, p, epi, pl.gu.rows));
+            LORY_TRY(k::launch_sum_act(st, parts, pl.gu.ks, m.S, TF, Act));
+        } else {
+            EpiGU epi = {nullptr, nullptr, Act, m.T, m.dff, 0};
+            LORY_TRY(k::launch_gu(st, p, epi));
+        }
     }
     {
         Params p = {};
         p.A[0] = Act; p.a_batch[0] = TF; p.lda[0] = m.dff;
         p.B[0] = Wbar + (size_t)2 * m.S * m.D; p.b_batch[0] = m.D; p.ldb[0] = m.d;
         p.M = m.T; p.N = m.d; p.K = m.dff; p.batches = m.S;
-        EpiStore epi = {Y, TD, m.d};
         prof::Range r(st, prof::kGemmDown, gemm_flops(p, 1, 1),
                       2.0 * ((double)m.S * TF + (double)m.S * m.D + (double)m.S * TD));
-        LORY_TRY(k::launch_down(st, p, epi));
+        if (pl.down.rows) {
+            p.ksplit = pl.down.ks;
+            p.batches = m.S * pl.down.ks;
+            const k::EpiPart<1> epi = {parts, pl.down.ks, m.S, m.T, m.d};
+            LORY_TRY(k::launch_down_split(st, p, epi, pl.down.rows));
+            LORY_TRY(k::launch_sum_store(st, parts, pl.down.ks, m.S * TD, Y));
+        } else {
+            EpiStore epi = {Y, TD, m.d};
+            LORY_TRY(k::launch_down(st, p, epi));
+        }
     }
     return LORY_OK;
 }

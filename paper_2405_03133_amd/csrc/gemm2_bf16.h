@@ -178,7 +178,10 @@ __global__ __launch_bounds__(TL::threads, TL::waves_per_simd) void gemm2_kernel(
     if (my_tiles == 0) return;
 
     const int ktiles = p.K / BK;
-    const int total = ktiles * NSRC;   // K steps per tile, at least two
+    // K steps of a tile, at least two.  Epi::SPLIT: a batch item's contraction is cut into ksplit slices that
+    // count as batch items of their own (index b * ksplit + slice) and leave as fp32 partial sums.
+    static_assert(!Epi::SPLIT || NSRC == 1, "a split contraction has one source");
+    auto slice_begin = [&](int sl) { return (int)((uint32_t)ktiles * (uint32_t)sl / (uint32_t)p.ksplit); };
 
     auto tile_coords = [&](int i, int &batch, int &m0, int &n0) {
         int id = xcd * per_xcd + qx + i * wg_per_xcd;
@@ -229,6 +232,12 @@ __global__ __launch_bounds__(TL::threads, TL::waves_per_simd) void gemm2_kernel(
         if constexpr (NSRC == 2) bA = 2 * ((long)batch * p.a_batch[1] + (A_MC ? (long)m0 : (long)m0 * p.lda[0]));
         leftA = ktiles;
         srcA = 0;
+        if constexpr (Epi::SPLIT) {
+            const int sl = batch % p.ksplit, k0 = slice_begin(sl);
+            ptrA = reinterpret_cast<const char *>(p.A[0]) + kA * k0 +
+                   2 * ((long)(batch / p.ksplit) * p.a_batch[0] + (A_MC ? (long)m0 : (long)m0 * p.lda[0]));
+            leftA = slice_begin(sl + 1) - k0;
+        }
     };
     auto enter_B = [&](int i) {
         int batch, m0, n0;
@@ -255,6 +264,12 @@ __global__ __launch_bounds__(TL::threads, TL::waves_per_simd) void gemm2_kernel(
         if constexpr (NSRC == 2) bB = 2 * ((long)batch * p.b_batch[1] + in_b);
         leftB = ktiles;
         srcB = 0;
+        if constexpr (Epi::SPLIT) {
+            const int sl = batch % p.ksplit, k0 = slice_begin(sl);
+            ptrB = reinterpret_cast<const char *>(s ? p.B[1] : p.B[0]) + kB * k0 +
+                   2 * ((long)(batch / p.ksplit) * (s ? p.b_batch[1] : p.b_batch[0]) + in_b);
+            leftB = slice_begin(sl + 1) - k0;
+        }
     };
     // One K step further.  Past the end of the stream the last K step is fetched again, into slots nobody
     // reads, so that the wait counts below always hold.
@@ -457,6 +472,27 @@ __global__ __launch_bounds__(TL::threads, TL::waves_per_simd) void gemm2_kernel(
         int el = lane;
         asm volatile("" : "+v"(el));   // lane constants of the epilogue are formed here, not kept across the K loop
         const int r = el & 31, h = el >> 5;
+        if constexpr (Epi::SPLIT) {
+            // fp32 partial sums straight from the accumulators: 16 bytes per lane, 128 bytes of a row over
+            // four stores
+#pragma unroll
+            for (int i = 0; i < MI; ++i) {
+                const int m = m0 + wm0 + i * 32 + r;
+#pragma unroll
+                for (int s = 0; s < NSET; ++s)
+#pragma unroll
+                    for (int j = 0; j < NI; ++j)
+#pragma unroll
+                        for (int rq = 0; rq < 4; ++rq) {
+                            const int n = n0 + wn0 + j * 32 + 8 * rq + 4 * h;
+                            if (full || (m < p.M && n < p.N))
+                                *reinterpret_cast<float4 *>(epi.part(s, batch, m, n)) =
+                                    make_float4(acc[s][i][j][rq * 4 + 0], acc[s][i][j][rq * 4 + 1],
+                                                acc[s][i][j][rq * 4 + 2], acc[s][i][j][rq * 4 + 3]);
+                        }
+            }
+            return;
+        }
         // The lane's position in the stores: row lane / CP of every RPI rows, chunk lane % CP.  The
         // address of every plane is a running pointer.
         constexpr int RPI = 64 / CP;
@@ -515,7 +551,7 @@ __global__ __launch_bounds__(TL::threads, TL::waves_per_simd) void gemm2_kernel(
     };
 
     // 16-byte store instructions a wave issues per interior tile
-    int nst = 0;
+    int nst = Epi::SPLIT ? MI * NB * 4 : 0;
 #pragma unroll
     for (int o = 0; o < Epi::NOUT; ++o)
         if (epi.enabled(o)) nst += MI * NI * 2;
@@ -524,12 +560,14 @@ __global__ __launch_bounds__(TL::threads, TL::waves_per_simd) void gemm2_kernel(
     int extra = 0;
     for (int tile_i = 0; tile_i < my_tiles; ++tile_i) {
         zero_acc();
+        int batch, m0, n0;
+        tile_coords(tile_i, batch, m0, n0);
+        int total = ktiles * NSRC;
+        if constexpr (Epi::SPLIT) total = slice_begin(batch % p.ksplit + 1) - slice_begin(batch % p.ksplit);
         // the first S-1 K steps of a tile run while the previous tile's stores drain
         step(T(), F(), extra);
         for (int t = 1; t < total - 1; ++t) step(F(), F(), t < S - 1 ? extra : 0);
         step(F(), T(), total - 1 < S - 1 ? extra : 0);
-        int batch, m0, n0;
-        tile_coords(tile_i, batch, m0, n0);
         if (m0 + BM <= p.M && n0 + BNS <= p.N) {
             epilogue(T(), batch, m0, n0);
             extra = nst;
@@ -562,6 +600,7 @@ inline hipError_t launch(const Params &p, const Epi &epi, hipStream_t st)
     if (p.K % BK != 0 || p.K < 2 * BK || p.N % 8 != 0 || p.M < 1 || p.N < 8 || (A_MC && p.M % 8 != 0)) return hipErrorInvalidValue;
     if (NSRC == 2 && (p.lda[0] != p.lda[1] || p.ldb[0] != p.ldb[1])) return hipErrorInvalidValue;
     if (NSET == 2 && p.ldb[0] != p.ldb[1]) return hipErrorInvalidValue;
+    if (Epi::SPLIT && (p.ksplit < 1 || p.ksplit > 1024 || p.K > (1 << 24) || p.batches % p.ksplit != 0 || p.K / BK < 2 * p.ksplit)) return hipErrorInvalidValue;
     auto kern = gemm2_kernel<NSET, NSRC, A_MC, B_NC, TL, Epi>;
     static bool configured = false;  // per instantiation
     if (!configured) {

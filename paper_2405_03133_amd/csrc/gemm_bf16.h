@@ -23,7 +23,8 @@ struct Params {
     long b_batch[2];
     int ldb[2];
     int M, N, K;           // per batch item; K per source
-    int batches;
+    int batches;           // split contraction: ksplit entries per batch item
+    int ksplit;            // K slices per batch item (split epilogues only)
 };
 
 __device__ __forceinline__ float bf16_bits_to_float(uint16_t b)

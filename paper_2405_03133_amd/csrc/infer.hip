@@ -3,9 +3,8 @@
 // inference"; Appendix G.1).  After one routing decision per layer the merged
 // FFN of a sequence is an ordinary dense FFN,
 //   Y_b = (silu(X_b Wg_bar_b) (.) X_b Wu_bar_b) Wd_bar_b .
-// Long token blocks (bf16, a multiple of 64 tokens per sequence) go through the
-// batched MFMA GEMMs.  Everything else (decode steps of one or a few tokens,
-// fp32, ragged token counts) goes through the "skinny" kernels below, which are
+// bf16 runs on the ring GEMM for every number of tokens (bf16_dense_ffn_fwd: contractions split over K
+// where the tiles would leave the chip idle).  fp32 goes through the "skinny" kernels below, which are
 // HBM-bound: every weight is read once per pass of up to 8 tokens.
 //
 // Skinny pass, per matrix product out[t][n] = sum_k x[t][k] W[k][n], W row-major:
@@ -27,11 +26,10 @@ namespace {
 constexpr int kSkThreads = 256;
 constexpr int kMaxTok = 8;        // tokens per skinny pass
 constexpr int kMaxSlice = 512;    // rows of W per workgroup (x slice in LDS: 8 * 512 floats)
+constexpr size_t kStaticScratchBytes = (size_t)16 << 20;  // scratch of lory_dense_ffn_fwd_static
+constexpr size_t kGemmBudget = (size_t)64 << 20;          // scratch of the matrix-core path in larger calls
 
 template <typename T> using Ld = Elem<T>;
-
-__device__ __forceinline__ float to_f32(float v) { return v; }
-__device__ __forceinline__ float to_f32(__hip_bfloat16 v) { return Ld<__hip_bfloat16>::one(&v); }
 
 // TW: storage type of the weights.  MT tokens, NMAT matrices sharing x (2 = gate and up), VEC
 // columns per lane (Ld<TW>::vec, or 1 when N is not a multiple of it).
@@ -59,7 +57,7 @@ __global__ __launch_bounds__(kSkThreads) void skinny_kernel(const TW *__restrict
     for (int i = tid; i < MT * (k1 - k0); i += kSkThreads) {
         const int t = i / (k1 - k0), k = i - t * (k1 - k0);
         if constexpr (NMAT == 2) {
-            xs[t * kMaxSlice + k] = to_f32(x[((size_t)b * x_rows + t) * K + k0 + k]);
+            xs[t * kMaxSlice + k] = x[((size_t)b * x_rows + t) * K + k0 + k];
         } else {
             const float *pg = gu + ((size_t)b * 2 * MT + t) * K + k0 + k;   // split 0, gate
             const size_t pitch = (size_t)B * 2 * MT * K, up = (size_t)MT * K;
@@ -268,14 +266,28 @@ int skinny_ffn(const Dims &m, const T *X, const T *Wbar, T *Y, void *ws, hipStre
     return LORY_OK;
 }
 
-bool gemm_path(const Dims &m) { return m.dtype == LORY_BF16 && m.L % 64 == 0; }
+// Partial sums of the skinny plan.  For bf16 it is the size that calls of other than a multiple of 64
+// tokens report (the ring GEMM needs less or as much): which calls fit the library-held scratch is part of
+// the interface.
+size_t base_bytes(const Dims &m)
+{
+    if (m.dtype == LORY_BF16 && m.L % 64 == 0) return align_up((size_t)m.tokens * m.dff * 2, 256);
+    const SkinnyPlan pl = (m.dtype == LORY_F32) ? skinny_plan<float>(m) : skinny_plan<__hip_bfloat16>(m);
+    return align_up(sizeof(float) * (pl.part1 + pl.part2), 256);
+}
+
+// Bound on the scratch of the matrix-core path: calls that fit the library-held array keep fitting it.
+size_t gemm_budget(const Dims &m)
+{
+    const size_t base = base_bytes(m);
+    return base <= kStaticScratchBytes ? kStaticScratchBytes : (base > kGemmBudget ? base : kGemmBudget);
+}
 
 // Scratch of lory_dense_ffn_fwd_static: the partial sums (or the activation block) that
 // lory_dense_ffn_fwd keeps in the caller's workspace, held by the library instead.  Every GPU
 // the library runs on holds its own copy of the array at its own address until the process
 // ends; in host code the array's name is only a handle for hipGetSymbolAddress, the address
 // looked up per device is what launches receive.
-constexpr size_t kStaticScratchBytes = (size_t)16 << 20;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 constexpr int kMaxDevices = 64;
 void *g_scratch_addr[kMaxDevices];  // device address of `scratch` per device ordinal, looked up once
@@ -310,17 +322,16 @@ int dense_ffn_fwd_static(const Dims &m, const void *X, const void *Wbar, void *Y
 
 size_t dense_workspace_bytes(const Dims &m)
 {
-    if (gemm_path(m)) return bf16_dense_workspace_bytes(m);
-    const SkinnyPlan pl = (m.dtype == LORY_F32) ? skinny_plan<float>(m) : skinny_plan<__hip_bfloat16>(m);
-    return align_up(sizeof(float) * (pl.part1 + pl.part2), 256);
+    const size_t base = base_bytes(m);
+    if (m.dtype == LORY_F32) return base;
+    const size_t n = bf16_dense_workspace_bytes(m, gemm_budget(m));
+    return n > base ? n : base;
 }
 
 int dense_ffn_fwd(const Dims &m, const void *X, const void *Wbar, void *Y, void *ws, hipStream_t st)
 {
-    if (gemm_path(m)) return bf16_dense_ffn_fwd(m, X, Wbar, Y, ws, st);
-    if (m.dtype == LORY_F32) return skinny_ffn<float>(m, (const float *)X, (const float *)Wbar, (float *)Y, ws, st);
-    return skinny_ffn<__hip_bfloat16>(m, (const __hip_bfloat16 *)X, (const __hip_bfloat16 *)Wbar,
-                                      (__hip_bfloat16 *)Y, ws, st);
+    if (m.dtype == LORY_BF16) return bf16_dense_ffn_fwd(m, X, Wbar, Y, ws, gemm_budget(m), st);
+    return skinny_ffn<float>(m, (const float *)X, (const float *)Wbar, (float *)Y, ws, st);
 }
 
 }  // namespace lory

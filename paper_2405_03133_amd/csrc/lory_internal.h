@@ -94,8 +94,8 @@ int dense_ffn_fwd_static(const Dims &m, const void *X, const void *Wbar, void *Y
 // ---- bf16 path (ffn_bf16.hip)
 int bf16_merge_all(const Dims &m, const float *w, const void *Wg, const void *Wu, const void *Wd,
                    void *Wbar, hipStream_t st);
-size_t bf16_dense_workspace_bytes(const Dims &m);
-int bf16_dense_ffn_fwd(const Dims &m, const void *X, const void *Wbar, void *Y, void *ws, hipStream_t st);
+size_t bf16_dense_workspace_bytes(const Dims &m, size_t budget);
+int bf16_dense_ffn_fwd(const Dims &m, const void *X, const void *Wbar, void *Y, void *ws, size_t budget, hipStream_t st);
 int set_slab_budget(size_t bytes);
 int set_fused_mode(int mode);
 size_t bf16_workspace_bytes(const Dims &m, int pass);

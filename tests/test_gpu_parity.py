@@ -497,6 +497,21 @@ def test_prompt_only_routing_inference(cfg, Lp, steps):
         assert np.isfinite(err) and err <= tol, (cfg.name, n_tok, err)
 
 
+# One row, the edges of the 64- and 128-row tiles, K slices of different lengths (d / 32 and d_ff / 32 not
+# multiples of the slice count), the smallest widths, and enough sequences that nothing is split.
+@pytest.mark.parametrize("B,d,d_ff", [(1, 320, 832), (3, 64, 64), (2, 1088, 2880), (40, 192, 1728)])
+@pytest.mark.parametrize("n_tok", [1, 63, 65, 128, 200])
+def test_dense_block_split_contractions(B, d, d_ff, n_tok):
+    cfg = LoryConfig("dense_block", B=B, L=n_tok, T=n_tok, d=d, d_ff=d_ff, E=B, dtype="bf16", seed=61)
+    t = make_inputs(cfg, with_dy=False)
+    # sequence b uses "expert" b: the oracle's one-hot routing, and the library's parameter set b
+    Wbar = torch.stack([to_dev(t[k], cfg).reshape(B, d * d_ff) for k in ("Wg", "Wu", "Wd")]).contiguous()
+    Y = lb.lory_dense_ffn_fwd(to_dev(t["X"], cfg), Wbar, d_ff)
+    torch.cuda.synchronize()
+    ref = orc.ffn_fwd(t["X"], np.eye(B), t["Wg"], t["Wu"], t["Wd"], n_tok)["Y"]
+    check(f"dense B={B} d={d} d_ff={d_ff} tokens={n_tok}", host(Y), ref, TOL["bf16"])
+
+
 def test_prefill_with_saved_merged_parameters_feeds_decode(default_budget):
     """lory_merged_ffn_fwd with T = L and Wbar_save leaves the same buffer lory_prompt_merge writes."""
     cfg = LoryConfig("inf_prefill", B=2, L=128, T=128, d=128, d_ff=256, E=8, dtype="bf16", seed=55)
