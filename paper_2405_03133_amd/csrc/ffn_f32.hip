@@ -1,153 +1,230 @@
 // fp32 instantiation of the merged FFN (paper Eq. 1 / Eq. 2, SwiGLU experts)
-// and of its backward.  This path exists for the small fp32 configuration
-// whose tolerance (rel-L2 <= 1e-5) needs fp32 operands; it is written for
-// clarity and arbitrary shapes, not for speed: LDS-tiled FMA GEMMs, explicit
-// per-segment merged weights in a workspace slab, processed a chunk of
-// segments at a time so that the workspace stays bounded.
+// and of its backward, for arbitrary shapes at fp32 accuracy (rel-L2 <= 1e-5).
+//
+// Every stage is a small dense contraction - the merge is w [S,E] x stack [E,n], the scatter
+// w^T [E,S] x slab [S,n], the inner products slab [S,n] x stack^T [n,E], the rest are the layer's token
+// GEMMs - so one kernel on the fp32 matrix instruction (v_mfma_f32_32x32x2_f32, full fp32 products and
+// sums) runs them all, and independent ones share a launch: the shapes of this configuration are small and
+// a pass is bound by the number of dependent launches (B=2, L=512, T=128, d=64, d_ff=256, E=4: 27 launches
+// of 4-30 us each took 325 us per training step, 12 launches take 70 us; B=8, L=1024, T=256, d=256, d_ff=640,
+// E=16: 1787 -> 616 us, 42 TFLOP/s).  SwiGLU and its derivative
+// are epilogues.  Merged weights of a chunk of segments live in a workspace slab, so that the workspace
+// stays bounded.
 #include "lory_internal.h"
 
 namespace lory {
+
+namespace k {
+hipError_t launch_dw_reduce(hipStream_t st, const float *partials, int slots, int rows, int cols, float *dw, int S,
+                            int E);
+}
 
 namespace {
 
 constexpr size_t kF32ChunkBudget = (size_t)512 << 20;  // workspace target per chunk of segments
 
-// ---------------------------------------------------------------- kernels
+// ---------------------------------------------------------------- the contraction kernel
 
-// slab[s][i] = sum_e w[s][e] * stack[e][i]      grid (ceil(n/256), Sc)
-__global__ void merge_f32_kernel(const float *__restrict__ w, const float *__restrict__ stack,
-                                 float *__restrict__ slab, long n, int E)
-{
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    const int s = blockIdx.y;
-    if (i >= n) return;
-    float acc = 0.f;
-    for (int e = 0; e < E; ++e) acc = fmaf(w[(size_t)s * E + e], stack[(size_t)e * n + i], acc);
-    slab[(size_t)s * n + i] = acc;
-}
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-// Batched C = op(A) * op(B) (+ C), 64x64x16 tiles, 256 threads, 4x4 per thread.
-//   op(A)(m,k) = TA ? A[k*lda + m] : A[m*lda + k]
-//   op(B)(k,n) = TB ? B[n*ldb + k] : B[k*ldb + n]
-template <bool TA, bool TB>
-__global__ __launch_bounds__(256) void sgemm_kernel(int M, int N, int K, const float *__restrict__ A,
-                                                    int lda, long strideA,
-                                                    const float *__restrict__ B, int ldb,
-                                                    long strideB, float *__restrict__ C, int ldc,
-                                                    long strideC, int add)
-{
-    __shared__ float As[16][64 + 4];
-    __shared__ float Bs[16][64 + 4];
-    A += (size_t)blockIdx.z * strideA;
-    B += (size_t)blockIdx.z * strideB;
-    C += (size_t)blockIdx.z * strideC;
-    const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-    const int tid = threadIdx.x;
-    const int tm = (tid / 16) * 4, tn = (tid % 16) * 4;
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < K; k0 += 16) {
-        for (int i = tid; i < 64 * 16; i += 256) {
-            int mm, kk;
-            if (TA) { mm = i % 64; kk = i / 64; } else { kk = i % 16; mm = i / 16; }
-            const int gm = m0 + mm, gk = k0 + kk;
-            float v = 0.f;
-            if (gm < M && gk < K) v = TA ? A[(size_t)gk * lda + gm] : A[(size_t)gm * lda + gk];
-            As[kk][mm] = v;
-        }
-        for (int i = tid; i < 64 * 16; i += 256) {
-            int nn, kk;
-            if (TB) { kk = i % 16; nn = i / 16; } else { nn = i % 64; kk = i / 64; }
-            const int gn = n0 + nn, gk = k0 + kk;
-            float v = 0.f;
-            if (gn < N && gk < K) v = TB ? B[(size_t)gn * ldb + gk] : B[(size_t)gk * ldb + gn];
-            Bs[kk][nn] = v;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < 16; ++kk) {
-            float a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = As[kk][tm + i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = Bs[kk][tn + j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-    for (int i = 0; i < 4; ++i) {
-        const int gm = m0 + tm + i;
-        if (gm >= M) continue;
-        for (int j = 0; j < 4; ++j) {
-            const int gn = n0 + tn + j;
-            if (gn >= N) continue;
-            float *c = C + (size_t)gm * ldc + gn;
-            *c = add ? (*c + acc[i][j]) : acc[i][j];
-        }
-    }
-}
+enum Mode { kStore = 0, kGateUp = 1, kGradAct = 2 };
+
+// C_b[m][n] (+)= sum over sources q, k of A_{q,b}(m,k) * B_{q,b}(k,n); operand element (i,k) at
+// base + i * s_i + k * s_k, one of the two strides being 1.
+struct Problem {
+    const float *A[2], *B[2];   // second source, or NULL; kGateUp: B[1] is the up projection's operand
+    long a_batch, b_batch;      // elements between batch items
+    long sAm, sAk, sBn, sBk;
+    float *C;
+    long c_batch;
+    long ldc;
+    long M, N, K;
+    int batches;
+    int ksplit;                 // slices of K; slice j writes C + j * c_slice
+    long c_slice;
+    int add;
+    int vecA, vecB;             // 16-byte loads along k are aligned
+    int split_waves;            // the four wavefronts share a 32 x 32 block (else a 64 x 64 tile)
+    int blocks;                 // workgroups of this problem
+};
+
+constexpr int kMaxProblems = 7;
+struct Group {
+    Problem p[kMaxProblems];
+    int n;
+};
+
+// Elementwise operands of the epilogues, all with the layout of C.
+struct Elementwise {
+    float *U, *A;               // kGateUp: C receives G
+    const float *G_in, *U_in;   // kGradAct: C receives dG
+    float *dU;
+};
+
+constexpr int TK = 32;   // contraction indices of a step
 
 __device__ inline float sigmoidf_(float z) { return 1.0f / (1.0f + expf(-z)); }
 
-// A = G * sigmoid(G) * U
-__global__ void swiglu_fwd_kernel(const float *__restrict__ G, const float *__restrict__ U,
-                                  float *__restrict__ A, long n)
+// One lane's share of 32 rows x 32 contraction indices of an operand, straight from memory: row lane & 31,
+// indices 8 j + 4 (lane >> 5) + e for j, e = 0..3 (the matrix instruction pairs element (j, e) of both lane
+// halves; any order does as long as A and B agree).  base: element (row of the lane, index 4 (lane >> 5) of the
+// step); left: indices left from there (elements beyond are zero); rows: 16-byte loads along k are possible.
+__device__ __forceinline__ void load_frag(float (&v)[16], const float *base, long s_k, int left, bool rows)
 {
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const float g = G[i];
-    A[i] = g * sigmoidf_(g) * U[i];
-}
-
-// dG = dA * U * sig(G) * (1 + G (1 - sig(G))),  dU = dA * G * sig(G); also A (needed for dWd_bar)
-__global__ void swiglu_bwd_kernel(const float *__restrict__ G, const float *__restrict__ U,
-                                  const float *__restrict__ dA, float *__restrict__ A,
-                                  float *__restrict__ dG, float *__restrict__ dU, long n)
-{
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const float g = G[i], u = U[i], da = dA[i];
-    const float sg = sigmoidf_(g);
-    A[i] = g * sg * u;
-    dG[i] = da * u * sg * (1.0f + g * (1.0f - sg));
-    dU[i] = da * g * sg;
-}
-
-// dW[e][i] (+)= sum_{s in chunk} w[s][e] * slab[s][i]      grid (ceil(n/256), E)
-__global__ void scatter_f32_kernel(const float *__restrict__ w, const float *__restrict__ slab,
-                                   float *__restrict__ dW, long n, int E, int Sc, int add)
-{
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    const int e = blockIdx.y;
-    if (i >= n) return;
-    float acc = 0.f;
-    for (int s = 0; s < Sc; ++s) acc = fmaf(w[(size_t)s * E + e], slab[(size_t)s * n + i], acc);
-    float *p = dW + (size_t)e * n + i;
-    *p = add ? (*p + acc) : acc;
-}
-
-// dw[s][e] (+)= <stack[e], slab[s]>      grid (E, Sc), 256 threads, fixed-order tree reduction
-__global__ __launch_bounds__(256) void dots_f32_kernel(const float *__restrict__ stack,
-                                                       const float *__restrict__ slab,
-                                                       float *__restrict__ dw, long n, int E, int add)
-{
-    __shared__ float red[256];
-    const int e = blockIdx.x, s = blockIdx.y;
-    const float *a = stack + (size_t)e * n;
-    const float *b = slab + (size_t)s * n;
-    float acc = 0.f;
-    for (long i = threadIdx.x; i < n; i += 256) acc = fmaf(a[i], b[i], acc);
-    red[threadIdx.x] = acc;
-    __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off) red[threadIdx.x] += red[threadIdx.x + off];
-        __syncthreads();
+    if (rows && left >= TK - 4) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float4 f = *reinterpret_cast<const float4 *>(base + 8 * j);
+            v[4 * j] = f.x; v[4 * j + 1] = f.y; v[4 * j + 2] = f.z; v[4 * j + 3] = f.w;
+        }
+    } else {
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            const int k = 8 * (q >> 2) + (q & 3);
+            v[q] = 0.f;
+            if (k < left) v[q] = base[k * s_k];
+        }
     }
-    if (threadIdx.x == 0) {
-        float *p = dw + (size_t)s * E + e;
-        *p = add ? (*p + red[0]) : red[0];
+}
+
+// 256 threads = 4 wavefronts of one 32 x 32 block (two in kGateUp: both operand sets share A).  Operands go
+// straight from memory to the matrix instruction, one step ahead: no barrier in the loop, and a short
+// contraction costs one memory latency.  p.split_waves: the wavefronts share one block and take a quarter
+// of its steps each, added in LDS (few blocks); else they form a 64 x 64 tile.
+template <int MODE>
+__global__ __launch_bounds__(256) void contract_kernel(const Group grp, const Elementwise ew)
+{
+    constexpr int NSET = MODE == kGateUp ? 2 : 1;
+    __shared__ float red[3][NSET][16][64];
+    int bid = blockIdx.x, pi = 0;
+    while (bid >= grp.p[pi].blocks) bid -= grp.p[pi++].blocks;
+    const Problem &p = grp.p[pi];
+    const int tile = p.split_waves ? 32 : 64;
+    const int tiles_n = (int)((p.N + tile - 1) / tile), tiles_m = (int)((p.M + tile - 1) / tile);
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l31 = lane & 31, lh = lane >> 5;
+    long n0 = (long)(bid % tiles_n) * tile;
+    bid /= tiles_n;
+    long m0 = (long)(bid % tiles_m) * tile;
+    bid /= tiles_m;
+    const int sl = bid % p.ksplit, b = bid / p.ksplit;
+    const long steps_all = (p.K + TK - 1) / TK;
+    int kb = (int)(steps_all * sl / p.ksplit), ke = (int)(steps_all * (sl + 1) / p.ksplit);
+    const int nsrc = (MODE != kGateUp && p.A[1]) ? 2 : 1;
+    int per_src = ke - kb, t0 = 0, t1 = per_src * nsrc;
+    if (p.split_waves) {
+        const int t = t1;
+        t0 = t * wave / 4;
+        t1 = t * (wave + 1) / 4;
+    } else {
+        m0 += (wave >> 1) * 32;
+        n0 += (wave & 1) * 32;
+        if (m0 >= p.M || n0 >= p.N) return;   // no barrier follows in this form
+    }
+
+    // rows and columns beyond the matrix repeat the last one; their results are not stored
+    const long mrow = m0 + l31 < p.M ? m0 + l31 : p.M - 1, ncol = n0 + l31 < p.N ? n0 + l31 : p.N - 1;
+    const long offA = b * p.a_batch + mrow * p.sAm + 4 * lh * p.sAk, offB = b * p.b_batch + ncol * p.sBn + 4 * lh * p.sBk;
+    const bool rowsA = p.vecA && p.sAk == 1, rowsB = p.vecB && p.sBk == 1;
+    f32x16 acc[NSET];
+#pragma unroll
+    for (int s = 0; s < NSET; ++s)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[s][r] = 0.f;
+    // One step ahead, with one copy of the loading code: these launches are short enough to be bound by
+    // instruction fetch (two unrolled buffers, 19-30 KB of code, took 12 us where this takes 5).
+    float ca[16], cb[NSET][16];
+    int cleft = 0;
+#pragma unroll 1
+    for (int t = t0; t <= t1; ++t) {
+        float na[16], nb[NSET][16];
+        int nleft = 0;
+        if (t < t1) {
+            const int src = t >= per_src ? 1 : 0;
+            const long k0 = (long)(kb + t - src * per_src) * TK;
+            nleft = p.K - k0 < TK ? (int)(p.K - k0) : TK;
+            load_frag(na, p.A[src] + offA + k0 * p.sAk, p.sAk, nleft - 4 * lh, rowsA);
+#pragma unroll
+            for (int s = 0; s < NSET; ++s)
+                load_frag(nb[s], p.B[NSET == 2 ? s : src] + offB + k0 * p.sBk, p.sBk, nleft - 4 * lh, rowsB);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (8 * j < cleft) {   // short contractions (few experts or segments) skip the zero padding
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int s = 0; s < NSET; ++s)
+                        acc[s] = __builtin_amdgcn_mfma_f32_32x32x2f32(ca[4 * j + e], cb[s][4 * j + e], acc[s], 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+            ca[q] = na[q];
+#pragma unroll
+            for (int s = 0; s < NSET; ++s) cb[s][q] = nb[s][q];
+        }
+        cleft = nleft;
+    }
+    if (p.split_waves) {
+        if (wave > 0) {
+#pragma unroll
+            for (int s = 0; s < NSET; ++s)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) red[wave - 1][s][r][lane] = acc[s][r];
+        }
+        __syncthreads();
+        if (wave > 0) return;
+#pragma unroll
+        for (int s = 0; s < NSET; ++s)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                acc[s][r] = ((acc[s][r] + red[0][s][r][lane]) + red[1][s][r][lane]) + red[2][s][r][lane];
+    }
+
+    // accumulator element r: row 8 (r >> 2) + 4 (lane >> 5) + (r & 3), column lane & 31
+    const long n = n0 + l31;
+    if (n >= p.N) return;
+    const long rows = p.M - m0 - 4 * lh;   // rows left from the lane's first
+    const size_t base = (size_t)(b * p.c_batch + (m0 + 4 * lh) * p.ldc + n);
+    auto at = [&](int r) { return base + (size_t)((8 * (r >> 2) + (r & 3)) * p.ldc); };
+    auto ok = [&](int r) { return 8 * (r >> 2) + (r & 3) < rows; };
+    float x[16], y[16];   // what the epilogue reads, fetched together
+    if constexpr (MODE == kGradAct) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            if (ok(r)) {
+                x[r] = ew.G_in[at(r)];
+                y[r] = ew.U_in[at(r)];
+            }
+    }
+    float *C = p.C + (size_t)sl * p.c_slice;
+    if (MODE == kStore && p.add) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            if (ok(r)) x[r] = C[at(r)];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[0][r] += x[r];
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        if (!ok(r)) continue;
+        const size_t o = at(r);
+        const float v = acc[0][r];
+        if constexpr (MODE == kStore) {
+            C[o] = v;
+        } else if constexpr (MODE == kGateUp) {
+            const float u = acc[1][r];
+            C[o] = v;
+            ew.U[o] = u;
+            if (ew.A) ew.A[o] = v * sigmoidf_(v) * u;
+        } else {
+            // v = dA:  dG = dA U sig(G) (1 + G (1 - sig(G))),  dU = dA G sig(G); also A (needed for dWd_bar)
+            const float g = x[r], u = y[r], sg = sigmoidf_(g);
+            ew.A[o] = g * sg * u;
+            C[o] = v * u * sg * (1.0f + g * (1.0f - sg));
+            ew.dU[o] = v * g * sg;
+        }
     }
 }
 
@@ -172,19 +249,73 @@ F32Plan plan(const Dims &m)
     return p;
 }
 
-template <bool TA, bool TB>
-void gemm(hipStream_t st, int batch, int M, int N, int K, const float *A, int lda, long sA,
-          const float *B, int ldb, long sB, float *C, int ldc, long sC, int add)
+bool aligned(const float *q, long a, long b) { return ((uintptr_t)q & 15) == 0 && a % 4 == 0 && b % 4 == 0; }
+
+// Operand strides: a row-major matrix with `ld` elements between rows; trans: the contraction runs along
+// its rows' index (the stored matrix is [K][M] for A, [K][N] is the plain B).
+Problem problem(int batches, long M, long N, long K, const float *A, long lda, long a_batch, bool ta, const float *B,
+                long ldb, long b_batch, bool tb, float *C, long ldc, long c_batch)
 {
-    const dim3 grid((N + 63) / 64, (M + 63) / 64, batch);
-    hipLaunchKernelGGL((sgemm_kernel<TA, TB>), grid, dim3(256), 0, st, M, N, K, A, lda, sA, B, ldb,
-                       sB, C, ldc, sC, add);
+    Problem p = {};
+    p.A[0] = A; p.a_batch = a_batch;
+    p.sAm = ta ? 1 : lda; p.sAk = ta ? lda : 1;
+    p.B[0] = B; p.b_batch = b_batch;
+    p.sBn = tb ? ldb : 1; p.sBk = tb ? 1 : ldb;
+    p.C = C; p.ldc = ldc; p.c_batch = c_batch;
+    p.M = M; p.N = N; p.K = K; p.batches = batches; p.ksplit = 1;
+    p.vecA = aligned(A, lda, a_batch);
+    p.vecB = aligned(B, ldb, b_batch);
+    return p;
 }
 
-void merge(hipStream_t st, const float *w, const float *stack, float *slab, long n, int E, int Sc)
+void second_source(Problem &p, const float *A, const float *B)
 {
-    const dim3 grid((unsigned)((n + 255) / 256), Sc);
-    hipLaunchKernelGGL(merge_f32_kernel, grid, dim3(256), 0, st, w, stack, slab, n, E);
+    p.A[1] = A; p.B[1] = B;
+    p.vecA = p.vecA && aligned(A, 0, 0);
+    p.vecB = p.vecB && aligned(B, 0, 0);
+}
+
+template <int MODE>
+void launch(hipStream_t st, Group &g, const Elementwise &ew = Elementwise())
+{
+    long blocks = 0;
+    for (int i = 0; i < g.n; ++i) {
+        Problem &p = g.p[i];
+        const long big = ((p.N + 63) / 64) * ((p.M + 63) / 64) * p.ksplit * p.batches;
+        const long small = ((p.N + 31) / 32) * ((p.M + 31) / 32) * p.ksplit * p.batches;
+        // Fewer tiles than CUs: split the steps of a block over the wavefronts instead (down projection of 8 segments
+        // of 128 tokens, d_ff = 256: 18.6 -> 6.6 us); a contraction of one step has nothing to split.
+        p.split_waves = big < 512 && p.K > TK;
+        p.blocks = (int)(p.split_waves ? small : big);
+        blocks += p.blocks;
+    }
+    hipLaunchKernelGGL(contract_kernel<MODE>, dim3((unsigned)blocks), dim3(256), 0, st, g, ew);
+}
+
+// slab_x[s][i] = sum_e w[s][e] stack_x[e][i]  for the given matrices
+void merge(hipStream_t st, const float *w, int E, int Sc, long n, const float *const *stacks, float *const *slabs,
+           int count)
+{
+    Group g = {};
+    g.n = count;
+    for (int x = 0; x < count; ++x)
+        g.p[x] = problem(1, Sc, n, E, w, E, 0, false, stacks[x], n, 0, false, slabs[x], n, 0);
+    launch<kStore>(st, g);
+}
+
+void gate_up(hipStream_t st, const Dims &m, int sc, const float *X, const float *mg, const float *mu, float *G,
+             float *U, float *A)
+{
+    const long TD = (long)m.T * m.d, TF = (long)m.T * m.dff;
+    Group g = {};
+    g.n = 1;
+    g.p[0] = problem(sc, m.T, m.dff, m.d, X, m.d, TD, false, mg, m.dff, m.D, false, G, m.dff, TF);
+    g.p[0].B[1] = mu;
+    g.p[0].vecB = g.p[0].vecB && aligned(mu, 0, 0);
+    Elementwise ew = {};
+    ew.U = U;
+    ew.A = A;
+    launch<kGateUp>(st, g, ew);
 }
 
 }  // namespace
@@ -203,22 +334,17 @@ int f32_ffn_fwd(const Dims &m, const float *X, const float *w, const float *Wg, 
     float *mg = (float *)ws, *mu = mg + p.slab, *md = mu + p.slab;
     float *Gb = md + p.slab, *Ub = Gb + p.act, *Ab = Ub + p.act;
     const long TD = (long)m.T * m.d, TF = (long)m.T * m.dff;
+    const float *stacks[3] = {Wg, Wu, Wd};
+    float *slabs[3] = {mg, mu, md};
     for (int s0 = 0; s0 < m.S; s0 += p.Sc) {
         const int sc = (m.S - s0 < p.Sc) ? (m.S - s0) : p.Sc;
-        const float *wc = w + (size_t)s0 * m.E;
-        const float *Xc = X + (size_t)s0 * TD;
-        float *G = G_save ? G_save + (size_t)s0 * TF : Gb;
-        float *U = U_save ? U_save + (size_t)s0 * TF : Ub;
-        merge(st, wc, Wg, mg, m.D, m.E, sc);
-        merge(st, wc, Wu, mu, m.D, m.E, sc);
-        merge(st, wc, Wd, md, m.D, m.E, sc);
-        gemm<false, false>(st, sc, m.T, m.dff, m.d, Xc, m.d, TD, mg, m.dff, m.D, G, m.dff, TF, 0);
-        gemm<false, false>(st, sc, m.T, m.dff, m.d, Xc, m.d, TD, mu, m.dff, m.D, U, m.dff, TF, 0);
-        const long n = (long)sc * TF;
-        hipLaunchKernelGGL(swiglu_fwd_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, G,
-                           U, Ab, n);
-        gemm<false, false>(st, sc, m.T, m.d, m.dff, Ab, m.dff, TF, md, m.d, m.D,
-                           Y + (size_t)s0 * TD, m.d, TD, 0);
+        merge(st, w + (size_t)s0 * m.E, m.E, sc, m.D, stacks, slabs, 3);
+        gate_up(st, m, sc, X + (size_t)s0 * TD, mg, mu, G_save ? G_save + (size_t)s0 * TF : Gb,
+                U_save ? U_save + (size_t)s0 * TF : Ub, Ab);
+        Group g = {};
+        g.n = 1;
+        g.p[0] = problem(sc, m.T, m.d, m.dff, Ab, m.dff, TF, false, md, m.d, m.D, false, Y + (size_t)s0 * TD, m.d, TD);
+        launch<kStore>(st, g);
     }
     return launch_status();
 }
@@ -228,11 +354,8 @@ int f32_merge_all(const Dims &m, const float *w, const float *Wg, const float *W
                   float *Wbar, hipStream_t st)
 {
     const float *stacks[3] = {Wg, Wu, Wd};
-    for (int x = 0; x < 3; ++x)
-        for (int s0 = 0; s0 < m.S; s0 += 32768) {  // grid.y limit
-            const int sc = (m.S - s0 < 32768) ? (m.S - s0) : 32768;
-            merge(st, w + (size_t)s0 * m.E, stacks[x], Wbar + ((size_t)x * m.S + s0) * m.D, m.D, m.E, sc);
-        }
+    float *slabs[3] = {Wbar, Wbar + (size_t)m.S * m.D, Wbar + (size_t)2 * m.S * m.D};
+    merge(st, w, m.E, m.S, m.D, stacks, slabs, 3);
     return launch_status();
 }
 
@@ -245,50 +368,80 @@ int f32_ffn_bwd(const Dims &m, const float *X, const float *w, const float *Wg, 
     float *mg = (float *)ws, *mu = mg + p.slab, *md = mu + p.slab;
     float *gg = md + p.slab, *gu = gg + p.slab, *gd = gu + p.slab;
     float *Gb = gd + p.slab, *Ub = Gb + p.act, *Ab = Ub + p.act;
-    float *dAb = Ab + p.act, *dGb = dAb + p.act, *dUb = dGb + p.act;
+    float *parts = Ab + p.act, *dGb = parts + p.act, *dUb = dGb + p.act;
     const long TD = (long)m.T * m.d, TF = (long)m.T * m.dff;
+    const float *stacks[3] = {Wg, Wu, Wd};
+    float *slabs[3] = {mg, mu, md};
+    const float *grads[3] = {gg, gu, gd};
+    float *dW[3] = {dWg, dWu, dWd};
     for (int s0 = 0; s0 < m.S; s0 += p.Sc) {
         const int sc = (m.S - s0 < p.Sc) ? (m.S - s0) : p.Sc;
         const float *wc = w + (size_t)s0 * m.E;
         const float *Xc = X + (size_t)s0 * TD;
         const float *dYc = dY + (size_t)s0 * TD;
-        merge(st, wc, Wg, mg, m.D, m.E, sc);
-        merge(st, wc, Wu, mu, m.D, m.E, sc);
-        merge(st, wc, Wd, md, m.D, m.E, sc);
-        const float *G, *U;
+        merge(st, wc, m.E, sc, m.D, stacks, slabs, 3);
+        const float *G = Gb, *U = Ub;
         if (G_save && U_save) {
             G = G_save + (size_t)s0 * TF;
             U = U_save + (size_t)s0 * TF;
         } else {
-            gemm<false, false>(st, sc, m.T, m.dff, m.d, Xc, m.d, TD, mg, m.dff, m.D, Gb, m.dff, TF, 0);
-            gemm<false, false>(st, sc, m.T, m.dff, m.d, Xc, m.d, TD, mu, m.dff, m.D, Ub, m.dff, TF, 0);
-            G = Gb;
-            U = Ub;
+            gate_up(st, m, sc, Xc, mg, mu, Gb, Ub, nullptr);
         }
-        // dA = dY Wd_bar^T
-        gemm<false, true>(st, sc, m.T, m.dff, m.d, dYc, m.d, TD, md, m.d, m.D, dAb, m.dff, TF, 0);
-        const long n = (long)sc * TF;
-        hipLaunchKernelGGL(swiglu_bwd_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, G,
-                           U, dAb, Ab, dGb, dUb, n);
-        // dWd_bar = A^T dY ; dWg_bar = X^T dG ; dWu_bar = X^T dU
-        gemm<true, false>(st, sc, m.dff, m.d, m.T, Ab, m.dff, TF, dYc, m.d, TD, gd, m.d, m.D, 0);
-        gemm<true, false>(st, sc, m.d, m.dff, m.T, Xc, m.d, TD, dGb, m.dff, TF, gg, m.dff, m.D, 0);
-        gemm<true, false>(st, sc, m.d, m.dff, m.T, Xc, m.d, TD, dUb, m.dff, TF, gu, m.dff, m.D, 0);
-        // dX = dG Wg_bar^T + dU Wu_bar^T
-        float *dXc = dX + (size_t)s0 * TD;
-        gemm<false, true>(st, sc, m.T, m.d, m.dff, dGb, m.dff, TF, mg, m.dff, m.D, dXc, m.d, TD, 0);
-        gemm<false, true>(st, sc, m.T, m.d, m.dff, dUb, m.dff, TF, mu, m.dff, m.D, dXc, m.d, TD, 1);
-        // scatter to the experts and router-weight inner products
-        const int add = (accumulate || s0 > 0) ? 1 : 0;
-        const dim3 sgrid((unsigned)((m.D + 255) / 256), m.E);
-        hipLaunchKernelGGL(scatter_f32_kernel, sgrid, dim3(256), 0, st, wc, gg, dWg, m.D, m.E, sc, add);
-        hipLaunchKernelGGL(scatter_f32_kernel, sgrid, dim3(256), 0, st, wc, gu, dWu, m.D, m.E, sc, add);
-        hipLaunchKernelGGL(scatter_f32_kernel, sgrid, dim3(256), 0, st, wc, gd, dWd, m.D, m.E, sc, add);
-        float *dwc = dw + (size_t)s0 * m.E;
-        const dim3 dgrid(m.E, sc);
-        hipLaunchKernelGGL(dots_f32_kernel, dgrid, dim3(256), 0, st, Wg, gg, dwc, m.D, m.E, 0);
-        hipLaunchKernelGGL(dots_f32_kernel, dgrid, dim3(256), 0, st, Wu, gu, dwc, m.D, m.E, 1);
-        hipLaunchKernelGGL(dots_f32_kernel, dgrid, dim3(256), 0, st, Wd, gd, dwc, m.D, m.E, 1);
+        // dA = dY Wd_bar^T, and from it dG, dU and A
+        {
+            Group g = {};
+            g.n = 1;
+            g.p[0] = problem(sc, m.T, m.dff, m.d, dYc, m.d, TD, false, md, m.d, m.D, true, dGb, m.dff, TF);
+            Elementwise ew = {};
+            ew.G_in = G; ew.U_in = U; ew.A = Ab; ew.dU = dUb;
+            launch<kGradAct>(st, g, ew);
+        }
+        // dWg_bar = X^T dG ; dWu_bar = X^T dU ; dWd_bar = A^T dY
+        {
+            Group g = {};
+            g.n = 3;
+            g.p[0] = problem(sc, m.d, m.dff, m.T, Xc, m.d, TD, true, dGb, m.dff, TF, false, gg, m.dff, m.D);
+            g.p[1] = problem(sc, m.d, m.dff, m.T, Xc, m.d, TD, true, dUb, m.dff, TF, false, gu, m.dff, m.D);
+            g.p[2] = problem(sc, m.dff, m.d, m.T, Ab, m.dff, TF, true, dYc, m.d, TD, false, gd, m.d, m.D);
+            launch<kStore>(st, g);
+        }
+        // dX = dG Wg_bar^T + dU Wu_bar^T; dWx[e] (+)= sum_s w[s,e] dWx_bar(s); partial sums of
+        // <Wx[e], dWx_bar(s)> over slices of the matrix, at least 8 K steps each
+        long slices = (m.D + 8 * TK - 1) / (8 * TK);
+        const long room = (long)(p.act / ((size_t)3 * sc * m.E));
+        if (slices > room) slices = room;
+        if (slices > 128) slices = 128;
+        const bool in_parts = slices >= 1;   // else (a few tokens) there is no room for partial sums
+        {
+            Group g = {};
+            g.n = in_parts ? 7 : 4;
+            g.p[0] = problem(sc, m.T, m.d, m.dff, dGb, m.dff, TF, false, mg, m.dff, m.D, true, dX + (size_t)s0 * TD, m.d, TD);
+            second_source(g.p[0], dUb, mu);
+            for (int x = 0; x < 3; ++x) {
+                g.p[1 + x] = problem(1, m.E, m.D, sc, wc, m.E, 0, true, grads[x], m.D, 0, false, dW[x], m.D, 0);
+                g.p[1 + x].add = (accumulate || s0 > 0) ? 1 : 0;
+            }
+            for (int x = 0; in_parts && x < 3; ++x) {
+                Problem &q = g.p[4 + x];
+                q = problem(1, sc, m.E, m.D, grads[x], m.D, 0, false, stacks[x], m.D, 0, true,
+                            parts + (size_t)x * slices * sc * m.E, m.E, 0);
+                q.ksplit = (int)slices;
+                q.c_slice = (long)sc * m.E;
+            }
+            launch<kStore>(st, g);
+            for (int x = 0; !in_parts && x < 3; ++x) {
+                Group h = {};
+                h.n = 1;
+                h.p[0] = problem(1, sc, m.E, m.D, grads[x], m.D, 0, false, stacks[x], m.D, 0, true,
+                                 dw + (size_t)s0 * m.E, m.E, 0);
+                h.p[0].add = x > 0;
+                launch<kStore>(st, h);
+            }
+        }
+        if (in_parts) {
+            if (k::launch_dw_reduce(st, parts, (int)(3 * slices), sc, m.E, dw + (size_t)s0 * m.E, sc, m.E) != hipSuccess)
+                return LORY_ERR_DEVICE;
+        }
     }
     return launch_status();
 }

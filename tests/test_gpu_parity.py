@@ -109,6 +109,22 @@ def test_fp32_edge_shapes(cfg):
     compare(cfg, got, ref, names, TOL["f32"])
 
 
+# The contraction kernel where it can go wrong: no room for partial inner products (fewer activations than
+# routing weights), more than one step over experts and segments with rows that are not 16-byte aligned, and
+# enough tiles that the wavefronts of a workgroup work on blocks of their own.
+@pytest.mark.parametrize("cfg", [
+    LoryConfig("f32_no_room", B=3, L=4, T=1, d=8, d_ff=8, E=16, dtype="f32", seed=27),
+    LoryConfig("f32_two_steps", B=4, L=400, T=40, d=72, d_ff=130, E=40, dtype="f32", seed=28),
+    LoryConfig("f32_many_tiles", B=8, L=1024, T=128, d=96, d_ff=200, E=9, dtype="f32", seed=29),
+], ids=lambda c: c.name)
+@pytest.mark.parametrize("save", [True, False], ids=["saved_GU", "recompute_GU"])
+def test_fp32_contraction_forms(cfg, save):
+    t = make_inputs(cfg, structured=True)
+    got = run_layer(cfg, t, save=save)
+    names = ALL if save else ("Y", "dX", "dWg", "dWu", "dWd", "dw")
+    compare(cfg, got, oracle_layer(cfg, t, got["w_used"]), names, TOL["f32"])
+
+
 def test_fp32_given_routing_weights_onehot_and_accumulate():
     cfg = CONFIGS["C1"]
     t = make_inputs(cfg)
