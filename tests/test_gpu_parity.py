@@ -125,6 +125,30 @@ def test_fp32_contraction_forms(cfg, save):
     compare(cfg, got, oracle_layer(cfg, t, got["w_used"]), names, TOL["f32"])
 
 
+# Routing where its thread layout changes: expert counts around 16, 32 and 64 lanes per row of R; widths around the
+# 64, 128 and 256 column threads (one column each when a row is not a multiple of a 16-byte load); segments of fewer,
+# as many and more rows than the rounds of eight; the path that returns the means and the one that does not; and
+# the mean of a whole prompt, whose last chunk of 64 rows is short.  The bound is the one of fp32 sums.
+@pytest.mark.parametrize("dtype,d,T,E", [
+    ("f32", 63, 5, 1), ("f32", 255, 33, 15), ("f32", 260, 40, 17), ("f32", 513, 70, 64), ("f32", 1028, 300, 33),
+    ("bf16", 64, 64, 16), ("bf16", 512, 128, 32), ("bf16", 576, 192, 33), ("bf16", 1088, 320, 12),
+    ("bf16", 2112, 64, 64),
+])
+def test_route_forms(dtype, d, T, E):
+    cfg = LoryConfig("route", B=2, L=3 * T, T=T, d=d, d_ff=64, E=E, dtype=dtype, seed=31)
+    t = make_inputs(cfg, structured=True, with_dy=False)
+    X, R = to_dev(t["X"], cfg), to_dev(t["R"], cfg)
+    hbar = torch.empty((cfg.S, d), dtype=torch.float32, device="cuda")
+    print(f"[gpu] {cfg}", flush=True)
+    w_h, w = lb.lory_route(X, R, T, hbar=hbar, d_ff=64), lb.lory_route(X, R, T, d_ff=64)
+    w_p, _ = lb.lory_prompt_merge(X, R, *(to_dev(t[k], cfg) for k in ("Wg", "Wu", "Wd")))
+    ref = orc.route(t["X"], t["R"], T)
+    check("w, means returned", host(w_h), ref["w"], TOL["f32"])
+    check("hbar", host(hbar), ref["hbar"], TOL["f32"])
+    check("w", host(w), ref["w"], TOL["f32"])
+    check("w, prompt", host(w_p), orc.route(t["X"], t["R"], cfg.L)["w"], TOL["f32"])
+
+
 def test_fp32_given_routing_weights_onehot_and_accumulate():
     cfg = CONFIGS["C1"]
     t = make_inputs(cfg)
