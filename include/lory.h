@@ -225,8 +225,10 @@ int lory_prompt_merge(const lory_shape *shape, const void *X_prompt, const int32
  * in:  X [B, L, d] (dtype); Wbar as lory_prompt_merge wrote it
  * out: Y [B, L, d] (dtype)
  * LORY_BF16 runs on the batched matrix-core GEMMs (contractions split over K when
- * few tokens would leave the chip idle); LORY_F32 runs HBM-bound kernels that read
- * each weight once per 8 tokens.
+ * few tokens would leave the chip idle).  The activation between the projections
+ * is rounded to bf16 when L is a multiple of 64 and keeps fp32 precision (two bf16
+ * terms) for every other L.  LORY_F32 runs HBM-bound kernels that read each weight
+ * once per 8 tokens.
  * workspace: lory_workspace_bytes(shape, LORY_PASS_DENSE).
  */
 int lory_dense_ffn_fwd(const lory_shape *shape, const void *X, const void *Wbar, void *Y,

@@ -83,29 +83,37 @@ __global__ __launch_bounds__(256) void swiglu_fwd_kernel(const uint16_t *__restr
     }
 }
 
-// Sums of fp32 partial products over the K slices of a split contraction, in slice order; four
-// consecutive elements per thread.  HBM-bound (the parts of a small call sit in the memory-side cache).
-__device__ __forceinline__ float4 sum_parts(const float *p, int ksplit, size_t pitch)
+// Sums of fp32 partial products over the K slices of a split contraction, in slice order, of NP planes `plane`
+// apart; four consecutive elements per thread.  HBM-bound (the parts of a small call sit in the memory-side cache).
+template <int NP>
+__device__ __forceinline__ void sum_parts(const float *p, size_t plane, int ksplit, size_t pitch, float4 (&a)[NP])
 {
-    float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int j = 0; j < NP; ++j) a[j] = make_float4(0.f, 0.f, 0.f, 0.f);
     int s = 0;
     for (; s + 4 <= ksplit; s += 4) {  // loads overlap, adds stay in order
-        float4 v[4];
+        float4 v[4][NP];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = *reinterpret_cast<const float4 *>(p + (size_t)(s + i) * pitch);
+        for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            a.x += v[i].x; a.y += v[i].y; a.z += v[i].z; a.w += v[i].w;
+            for (int j = 0; j < NP; ++j) v[i][j] = *reinterpret_cast<const float4 *>(p + (size_t)(s + i) * pitch + j * plane);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < NP; ++j) {
+                a[j].x += v[i][j].x; a[j].y += v[i][j].y; a[j].z += v[i][j].z; a[j].w += v[i][j].w;
+            }
+    }
+    for (; s < ksplit; ++s)
+#pragma unroll
+        for (int j = 0; j < NP; ++j) {
+            const float4 v = *reinterpret_cast<const float4 *>(p + (size_t)s * pitch + j * plane);
+            a[j].x += v.x; a[j].y += v.y; a[j].z += v.z; a[j].w += v.w;
         }
-    }
-    for (; s < ksplit; ++s) {
-        const float4 v = *reinterpret_cast<const float4 *>(p + (size_t)s * pitch);
-        a.x += v.x; a.y += v.y; a.z += v.z; a.w += v.w;
-    }
-    return a;
 }
 
-// part [ksplit][batches][2][mn] -> Act [batches][mn]
+// part [ksplit][batches][2][mn] -> Act [batches][TERMS][mn]
+template <int TERMS>
 __global__ __launch_bounds__(256) void sum_act_kernel(const float *__restrict__ part, int ksplit, long batches, long mn,
                                                       uint16_t *__restrict__ Act)
 {
@@ -114,34 +122,61 @@ __global__ __launch_bounds__(256) void sum_act_kernel(const float *__restrict__ 
     const long b = i / mn, e = i - b * mn;
     const float *p = part + (size_t)b * 2 * mn + e;
     const size_t pitch = (size_t)batches * 2 * mn;
-    const float4 g = sum_parts(p, ksplit, pitch), u = sum_parts(p + mn, ksplit, pitch);
-    auto act = [](float x, float y) { return x * __builtin_amdgcn_rcpf(1.0f + __expf(-x)) * y; };
-    *reinterpret_cast<u32x2 *>(Act + i) = pack4(act(g.x, u.x), act(g.y, u.y), act(g.z, u.z), act(g.w, u.w));
+    float4 gu[2];
+    sum_parts<2>(p, mn, ksplit, pitch, gu);
+    const float4 g = gu[0], u = gu[1];
+    if constexpr (TERMS == 1) {
+        auto act = [](float x, float y) { return x * __builtin_amdgcn_rcpf(1.0f + __expf(-x)) * y; };
+        *reinterpret_cast<u32x2 *>(Act + i) = pack4(act(g.x, u.x), act(g.y, u.y), act(g.z, u.z), act(g.w, u.w));
+    } else {
+        float h[4], l[4];
+        act_terms(g.x, u.x, h[0], l[0]);
+        act_terms(g.y, u.y, h[1], l[1]);
+        act_terms(g.z, u.z, h[2], l[2]);
+        act_terms(g.w, u.w, h[3], l[3]);
+        uint16_t *dst = Act + (size_t)b * 2 * mn + e;
+        *reinterpret_cast<u32x2 *>(dst) = pack4(h[0], h[1], h[2], h[3]);
+        *reinterpret_cast<u32x2 *>(dst + mn) = pack4(l[0], l[1], l[2], l[3]);
+    }
 }
 
-// part [ksplit][n] -> Y [n]
-__global__ __launch_bounds__(256) void sum_store_kernel(const float *__restrict__ part, int ksplit, long n,
+// part [ksplit][batches][TERMS][mn] -> Y [batches][mn]
+template <int TERMS>
+__global__ __launch_bounds__(256) void sum_store_kernel(const float *__restrict__ part, int ksplit, long batches, long mn,
                                                         uint16_t *__restrict__ Y)
 {
     const long i = ((long)blockIdx.x * 256 + threadIdx.x) * 4;
-    if (i >= n) return;
-    const float4 y = sum_parts(part + i, ksplit, (size_t)n);
-    *reinterpret_cast<u32x2 *>(Y + i) = pack4(y.x, y.y, y.z, y.w);
+    if (i >= batches * mn) return;
+    const long b = i / mn, e = i - b * mn;
+    const float *p = part + (size_t)b * TERMS * mn + e;
+    float4 y[TERMS];
+    sum_parts<TERMS>(p, mn, ksplit, (size_t)batches * TERMS * mn, y);
+#pragma unroll
+    for (int j = 1; j < TERMS; ++j) {
+        y[0].x += y[j].x; y[0].y += y[j].y; y[0].z += y[j].z; y[0].w += y[j].w;
+    }
+    *reinterpret_cast<u32x2 *>(Y + i) = pack4(y[0].x, y[0].y, y[0].z, y[0].w);
 }
 
 }  // namespace
 
-hipError_t launch_sum_act(hipStream_t st, const float *part, int ksplit, long batches, long mn, uint16_t *Act)
+hipError_t launch_sum_act(hipStream_t st, const float *part, int ksplit, long batches, long mn, int terms, uint16_t *Act)
 {
-    const long blocks = (batches * mn / 4 + 255) / 256;
-    hipLaunchKernelGGL(sum_act_kernel, dim3((unsigned)blocks), dim3(256), 0, st, part, ksplit, batches, mn, Act);
+    const dim3 grid((unsigned)((batches * mn / 4 + 255) / 256));
+    if (terms == 1)
+        hipLaunchKernelGGL(sum_act_kernel<1>, grid, dim3(256), 0, st, part, ksplit, batches, mn, Act);
+    else
+        hipLaunchKernelGGL(sum_act_kernel<2>, grid, dim3(256), 0, st, part, ksplit, batches, mn, Act);
     return hipGetLastError();
 }
 
-hipError_t launch_sum_store(hipStream_t st, const float *part, int ksplit, long n, uint16_t *Y)
+hipError_t launch_sum_store(hipStream_t st, const float *part, int ksplit, long batches, long mn, int terms, uint16_t *Y)
 {
-    const long blocks = (n / 4 + 255) / 256;
-    hipLaunchKernelGGL(sum_store_kernel, dim3((unsigned)blocks), dim3(256), 0, st, part, ksplit, n, Y);
+    const dim3 grid((unsigned)((batches * mn / 4 + 255) / 256));
+    if (terms == 1)
+        hipLaunchKernelGGL(sum_store_kernel<1>, grid, dim3(256), 0, st, part, ksplit, batches, mn, Y);
+    else
+        hipLaunchKernelGGL(sum_store_kernel<2>, grid, dim3(256), 0, st, part, ksplit, batches, mn, Y);
     return hipGetLastError();
 }
 

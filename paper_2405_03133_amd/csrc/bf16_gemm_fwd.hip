@@ -21,10 +21,21 @@ hipError_t launch_gu(hipStream_t st, const gemm::Params &p, const EpiGU &d)
     return gemm2::launch_rows<2, 1, false, true>(p, e, st);
 }
 
+hipError_t launch_gu2(hipStream_t st, const gemm::Params &p, const EpiAct2 &e)
+{
+    return gemm2::launch_rows<2, 1, false, true>(p, e, st);
+}
+
 hipError_t launch_down(hipStream_t st, const gemm::Params &p, const EpiStore &e)
 {
     // A = Act_s [T][d_ff], B = merged slab [d_ff][jf] (N contiguous)
     return gemm2::launch_rows<1, 1, false, true>(p, e, st);
+}
+
+hipError_t launch_down2(hipStream_t st, const gemm::Params &p, const EpiStore &e)
+{
+    // A = the two terms of Act_s, both with the same merged slab
+    return gemm2::launch_rows<1, 2, false, true>(p, e, st);
 }
 
 hipError_t launch_gu_split(hipStream_t st, const gemm::Params &p, const EpiPart<2> &e, int rows)

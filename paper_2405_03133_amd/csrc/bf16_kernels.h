@@ -69,6 +69,44 @@ struct EpiGU {
     int T, dff, n_off;
 };
 
+// An activation of fp32 precision as two bf16 terms, hi + lo (relative error up to 2^-18): the matrix instruction
+// multiplies both with the same weights.  hi is the rounded value, or the truncated one where rounding would
+// overflow; infinities and NaN go into hi alone.  Error of the dense FFN against 64 bits, activation in fp32 on the
+// vector ALUs / these two terms / rounded to bf16, 1e-3: 2 x 100 tokens at d = 2048, d_ff = 5632 1.659371 / 1.659373 /
+// 2.344863, one token at d = 1024, d_ff = 2816 1.611728 / 1.611738 / 2.262393 (the rounding of the output is 1.66).
+__device__ __forceinline__ void act_terms(float g, float u, float &hi, float &lo)
+{
+    const float a = g * __builtin_amdgcn_rcpf(1.0f + __expf(-g)) * u;   // 32 bits: 3e-7 for |g| < 4
+    const uint32_t bits = __float_as_uint(a);
+    uint32_t h = gemm::cvt_pk_bf16(a, 0.f) << 16;
+    const bool finite = (bits & 0x7f800000u) != 0x7f800000u;
+    if (finite && (h & 0x7f800000u) == 0x7f800000u) h = bits & 0xffff0000u;
+    hi = __uint_as_float(h);
+    lo = finite ? a - hi : 0.f;
+}
+
+// Gate/up projections, activation as two terms: Act[batch][hi rows | lo rows][d_ff].
+struct EpiAct2 {
+    static constexpr int NOUT = 2;
+    static constexpr bool SPLIT = false;
+    typedef NoIn In;
+    uint16_t *Act;
+    int T, dff;
+    __device__ __forceinline__ bool enabled(int) const { return true; }
+    __device__ __forceinline__ u32x2 pack(int o, int, int, int, const In &, const float (&v)[2][4]) const
+    {
+        float t[2][4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) act_terms(v[0][e], v[1][e], t[0][e], t[1][e]);
+        return o == 0 ? pack4(t[0][0], t[0][1], t[0][2], t[0][3]) : pack4(t[1][0], t[1][1], t[1][2], t[1][3]);
+    }
+    __device__ __forceinline__ long row_bytes() const { return 2L * dff; }
+    __device__ __forceinline__ uint16_t *ptr(int o, int s, int m, int n) const
+    {
+        return Act + ((size_t)(2 * s + o) * T + m) * dff + n;
+    }
+};
+
 // C[batch][m][n] = bf16(v)
 struct EpiStore {
     static constexpr int NOUT = 1;
@@ -148,15 +186,17 @@ int fused_dw_slots(const fsg::Params &p);
 hipError_t launch_fused_dw(hipStream_t st, const fsg::Params &p);
 
 hipError_t launch_gu(hipStream_t st, const gemm::Params &p, const EpiGU &e);     // X * [Wg_bar | Wu_bar]
+hipError_t launch_gu2(hipStream_t st, const gemm::Params &p, const EpiAct2 &e);   // the same, activation as two terms
 hipError_t launch_down(hipStream_t st, const gemm::Params &p, const EpiStore &e);  // A * Wd_bar
+hipError_t launch_down2(hipStream_t st, const gemm::Params &p, const EpiStore &e);  // A_hi * Wd_bar + A_lo * Wd_bar
 // The same two projections with the contraction split into p.ksplit slices (p.batches already counts them);
 // rows: tile height, 64 or 128.
 hipError_t launch_gu_split(hipStream_t st, const gemm::Params &p, const EpiPart<2> &e, int rows);
 hipError_t launch_down_split(hipStream_t st, const gemm::Params &p, const EpiPart<1> &e, int rows);
-// Sums of the K slices in slice order: part [ksplit][batches][2][M][N] -> Act = silu(G) * U, or
-// part [ksplit][batches][1][M][N] -> Y; n = batches * M * N elements, N a multiple of 4.
-hipError_t launch_sum_act(hipStream_t st, const float *part, int ksplit, long batches, long mn, uint16_t *Act);
-hipError_t launch_sum_store(hipStream_t st, const float *part, int ksplit, long n, uint16_t *Y);
+// Sums of the K slices in slice order.  part [ksplit][batches][2][mn] -> Act [batches][terms][mn], silu(G) * U
+// rounded (terms = 1) or as two terms; part [ksplit][batches][terms][mn] -> Y [batches][mn].
+hipError_t launch_sum_act(hipStream_t st, const float *part, int ksplit, long batches, long mn, int terms, uint16_t *Act);
+hipError_t launch_sum_store(hipStream_t st, const float *part, int ksplit, long batches, long mn, int terms, uint16_t *Y);
 hipError_t launch_da(hipStream_t st, const gemm::Params &p, const EpiStore &e);  // dY * Wd_bar^T
 hipError_t launch_swiglu_fwd(hipStream_t st, const uint16_t *G, const uint16_t *U, uint16_t *Act, long rows,
                              int dff, int n0, int nf);

@@ -348,7 +348,8 @@ struct DenseSplit {
     int ks;
 };
 
-// M rows per sequence, N columns per operand set, nset operand sets.  A few dozen rows against one weight
+// M rows per sequence, N columns per operand set, nset operand sets, the row operand in `terms` bf16 terms (unsplit: one
+// source each; split: rows of their own, whose sums are added with those of the slices).  A few dozen rows against one weight
 // matrix per sequence leave most CUs without a tile, and the pass is then bound by how many CUs stream the
 // weights, so the contraction is cut into slices until the tiles fill the chip once; what a slice costs is its
 // fp32 partial sums (written once, read once).  Estimate, us: K steps of a CU (0.55 / 0.42 each for 128 / 64
@@ -357,23 +358,23 @@ struct DenseSplit {
 // per call against kernels that read the weights once per 8 tokens on the vector ALUs: 1 token 33.6 / 36.7, 8
 // tokens 34.7 / 89, 32: 36 / 357, 100: 49 / 1126, 400: 81 / 4452; blocks of 64 and 256 tokens on the unsplit
 // GEMM took 79 and 91, split 40 and 67.
-DenseSplit dense_split(const Dims &m, int M, int N, int K, int nset, size_t max_floats)
+DenseSplit dense_split(const Dims &m, int M, int N, int K, int nset, int terms, size_t max_floats)
 {
     const int cus = gemm2::cu_count(), bns = 256 / nset, steps = K / gemm2::BK;
     DenseSplit best = {0, 1};
-    const long tiles256 = (long)m.B * ((M + 255) / 256) * ((N + bns - 1) / bns);
-    double best_t = 0.9 * (double)((tiles256 + cus - 1) / cus) * (steps + 6);
+    double best_t = 1e30;
     for (int rows = 64; rows <= 256; rows += rows) {
         const double step = rows == 64 ? 0.42 : rows == 128 ? 0.55 : 0.90;
-        const long tiles = (long)m.B * ((M + rows - 1) / rows) * ((N + bns - 1) / bns);
-        const double t1 = step * (double)((tiles + cus - 1) / cus) * (steps + 6);
+        const long tiles1 = (long)m.B * ((M + rows - 1) / rows) * ((N + bns - 1) / bns);
+        const double t1 = step * (double)((tiles1 + cus - 1) / cus) * (terms * steps + 6);
         if (t1 < best_t) {
             best_t = t1;
             best = {0, 1};
         }
         if (rows == 256) break;   // few tiles of this height means short blocks: lower tiles do the same
-        for (int ks = 2; ks <= steps / 4 && tiles * ks <= cus; ++ks) {
-            const double parts = (double)ks * nset * m.B * M * N;
+        const long tiles = (long)m.B * ((terms * M + rows - 1) / rows) * ((N + bns - 1) / bns);
+        for (int ks = 1; ks <= steps / 4 && tiles * ks <= cus; ++ks) {
+            const double parts = (double)ks * nset * terms * m.B * M * N;
             if (parts > (double)max_floats) break;
             const double t = step * ((steps + ks - 1) / ks + 6) + parts * 8.0 / 4e6 + 3.0;
             if (t < best_t) {
@@ -386,6 +387,7 @@ DenseSplit dense_split(const Dims &m, int M, int N, int K, int nset, size_t max_
 }
 
 struct DensePlan {
+    int terms;           // bf16 terms of the activation
     DenseSplit gu, down;
     size_t act, parts;   // bytes
 };
@@ -393,12 +395,15 @@ struct DensePlan {
 DensePlan dense_plan(const Dims &m, size_t budget)
 {
     DensePlan p;
-    p.act = align_up((size_t)m.tokens * m.dff * 2, 256);
+    // Blocks of 64 k tokens (prefill) round the activation to bf16 like the training forward; every other
+    // number of tokens, decode steps among them, keeps it in fp32 precision.
+    p.terms = m.L % 64 == 0 ? 1 : 2;
+    p.act = align_up((size_t)m.tokens * m.dff * 2 * p.terms, 256);
     const size_t fl = budget > p.act ? (budget - p.act) / sizeof(float) : 0;
-    p.gu = dense_split(m, m.L, m.dff, m.d, 2, fl);
-    p.down = dense_split(m, m.L, m.d, m.dff, 1, fl);
+    p.gu = dense_split(m, m.L, m.dff, m.d, 2, 1, fl);
+    p.down = dense_split(m, m.L, m.d, m.dff, 1, p.terms, fl);
     size_t a = p.gu.rows ? (size_t)p.gu.ks * 2 * m.tokens * m.dff : 0;
-    const size_t b = p.down.rows ? (size_t)p.down.ks * m.tokens * m.d : 0;
+    const size_t b = p.down.rows ? (size_t)p.down.ks * p.terms * m.tokens * m.d : 0;
     if (b > a) a = b;
     p.parts = align_up(a * sizeof(float), 256);
     return p;
@@ -436,28 +441,35 @@ int bf16_dense_ffn_fwd(const Dims &m, const void *Xv, const void *Wbarv, void *Y
             p.batches = m.S * pl.gu.ks;
             const k::EpiPart<2> epi = {parts, pl.gu.ks, m.S, m.T, m.dff};
             LORY_TRY(k::launch_gu_split(st, p, epi, pl.gu.rows));
-            LORY_TRY(k::launch_sum_act(st, parts, pl.gu.ks, m.S, TF, Act));
-        } else {
+            LORY_TRY(k::launch_sum_act(st, parts, pl.gu.ks, m.S, TF, pl.terms, Act));
+        } else if (pl.terms == 1) {
             EpiGU epi = {nullptr, nullptr, Act, m.T, m.dff, 0};
             LORY_TRY(k::launch_gu(st, p, epi));
+        } else {
+            LORY_TRY(k::launch_gu2(st, p, k::EpiAct2{Act, m.T, m.dff}));
         }
     }
     {
+        // the two terms of an activation are blocks of rows of one matrix, or two sources
+        const int nt = pl.terms;
         Params p = {};
-        p.A[0] = Act; p.a_batch[0] = TF; p.lda[0] = m.dff;
-        p.B[0] = Wbar + (size_t)2 * m.S * m.D; p.b_batch[0] = m.D; p.ldb[0] = m.d;
+        p.A[0] = Act; p.A[1] = Act + TF; p.a_batch[0] = p.a_batch[1] = nt * TF; p.lda[0] = p.lda[1] = m.dff;
+        p.B[0] = p.B[1] = Wbar + (size_t)2 * m.S * m.D; p.b_batch[0] = p.b_batch[1] = m.D; p.ldb[0] = p.ldb[1] = m.d;
         p.M = m.T; p.N = m.d; p.K = m.dff; p.batches = m.S;
         prof::Range r(st, prof::kGemmDown, gemm_flops(p, 1, 1),
                       2.0 * ((double)m.S * TF + (double)m.S * m.D + (double)m.S * TD));
+        EpiStore epi = {Y, TD, m.d};
         if (pl.down.rows) {
+            p.M = nt * m.T;
             p.ksplit = pl.down.ks;
             p.batches = m.S * pl.down.ks;
-            const k::EpiPart<1> epi = {parts, pl.down.ks, m.S, m.T, m.d};
-            LORY_TRY(k::launch_down_split(st, p, epi, pl.down.rows));
-            LORY_TRY(k::launch_sum_store(st, parts, pl.down.ks, m.S * TD, Y));
-        } else {
-            EpiStore epi = {Y, TD, m.d};
+            const k::EpiPart<1> part = {parts, pl.down.ks, m.S, nt * m.T, m.d};
+            LORY_TRY(k::launch_down_split(st, p, part, pl.down.rows));
+            LORY_TRY(k::launch_sum_store(st, parts, pl.down.ks, m.S, TD, nt, Y));
+        } else if (nt == 1) {
             LORY_TRY(k::launch_down(st, p, epi));
+        } else {
+            LORY_TRY(k::launch_down2(st, p, epi));
         }
     }
     return LORY_OK;

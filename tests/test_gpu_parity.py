@@ -552,6 +552,42 @@ def test_dense_block_split_contractions(B, d, d_ff, n_tok):
     check(f"dense B={B} d={d} d_ff={d_ff} tokens={n_tok}", host(Y), ref, TOL["bf16"])
 
 
+# Token counts other than multiples of 64 (decode steps, ragged blocks) keep the activation in fp32 precision into the
+# down projection: what separates the output from the exact one is its own rounding to bf16.  The bound is the error of
+# the rounded oracle (1.7e-3) with 3 % for rows whose fp32 sums round the other way; an activation rounded to bf16 is
+# 1.4 times as far off.  The shapes split both, one or none of the projections, over tiles of every height.
+@pytest.mark.parametrize("B,n_tok,d,d_ff", [
+    (1, 1, 320, 832), (5, 7, 320, 832), (1, 65, 1664, 2816), (2, 100, 512, 1408), (3, 200, 64, 64),
+    (130, 100, 64, 64), (150, 129, 64, 128), (130, 250, 64, 64),
+])
+def test_dense_block_rounds_only_its_output(B, n_tok, d, d_ff):
+    cfg = LoryConfig("dense_exact", B=B, L=n_tok, T=n_tok, d=d, d_ff=d_ff, E=B, dtype="bf16", seed=62)
+    print(f"[gpu] {cfg}", flush=True)
+    t = make_inputs(cfg, with_dy=False)
+    Wbar = torch.stack([to_dev(t[k], cfg).reshape(B, d * d_ff) for k in ("Wg", "Wu", "Wd")]).contiguous()
+    Y = host(lb.lory_dense_ffn_fwd(to_dev(t["X"], cfg), Wbar, d_ff))
+    ref = orc.ffn_fwd(t["X"], np.eye(B), t["Wg"], t["Wu"], t["Wd"], n_tok)["Y"]
+    rounded = np.linalg.norm(round_to_bf16(ref.astype(np.float32)) - ref)
+    err = np.linalg.norm(Y - ref)
+    assert err <= 1.03 * rounded, (err / rounded, rounded / np.linalg.norm(ref))
+
+
+@pytest.mark.parametrize("d,d_ff", [(64, 64), (256, 512)], ids=["two sources", "split"])
+def test_dense_block_activation_at_the_end_of_the_range(d, d_ff):
+    """An activation above the largest bf16 but finite in fp32 stays finite; an infinite one stays infinite."""
+    X = torch.zeros((1, 2, d), device="cuda")
+    W = torch.zeros((3, d * d_ff), device="cuda")
+    Wg, Wu = W[0].view(d, d_ff), W[1].view(d, d_ff)
+    X[0, 0, :2] = 2.0 ** 32
+    X[0, 1, 0] = float("inf")
+    Wg[0], Wu[0], Wu[1] = 2.0 ** 32, 2.0 ** 31 * 1.9921875, 2.0 ** 31 * 0.005859375
+    W[2] = 2.0 ** -100
+    a = 2.0 ** 127 * 1.998046875   # silu(2^64) * u; the largest bf16 is 1.9921875 * 2^127
+    Y = lb.lory_dense_ffn_fwd(X.bfloat16(), W.bfloat16().reshape(3, 1, d * d_ff).contiguous(), d_ff).double().cpu()
+    assert bool(((Y[0, 0] / (d_ff * a * 2.0 ** -100) - 1).abs() < 2.0 ** -8).all()), Y[0, 0, :4]
+    assert bool((Y[0, 1] == float("inf")).all()), Y[0, 1, :4]
+
+
 def test_prefill_with_saved_merged_parameters_feeds_decode(default_budget):
     """lory_merged_ffn_fwd with T = L and Wbar_save leaves the same buffer lory_prompt_merge writes."""
     cfg = LoryConfig("inf_prefill", B=2, L=128, T=128, d=128, d_ff=256, E=8, dtype="bf16", seed=55)
