@@ -229,7 +229,11 @@ int lory_prompt_merge(const lory_shape *shape, const void *X_prompt, const int32
  * is rounded to bf16 when L is a multiple of 64 and keeps fp32 precision (two bf16
  * terms) for every other L.  LORY_F32 runs HBM-bound kernels that read each weight
  * once per 8 tokens.
- * workspace: lory_workspace_bytes(shape, LORY_PASS_DENSE).
+ * workspace: lory_workspace_bytes(shape, LORY_PASS_DENSE).  LORY_BF16 calls also
+ * take less, down to B L d_ff elements when L is a multiple of 64 and to the
+ * partial sums of one pass of up to 8 tokens otherwise: contractions are then
+ * split less and rows walked in blocks, which is slower and adds the same
+ * products in another order.
  */
 int lory_dense_ffn_fwd(const lory_shape *shape, const void *X, const void *Wbar, void *Y,
                        void *workspace, size_t workspace_bytes, void *stream);

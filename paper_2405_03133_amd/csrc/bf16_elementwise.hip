@@ -140,10 +140,10 @@ __global__ __launch_bounds__(256) void sum_act_kernel(const float *__restrict__ 
     }
 }
 
-// part [ksplit][batches][TERMS][mn] -> Y [batches][mn]
+// part [ksplit][batches][TERMS][mn] -> Y, mn elements every y_batch
 template <int TERMS>
 __global__ __launch_bounds__(256) void sum_store_kernel(const float *__restrict__ part, int ksplit, long batches, long mn,
-                                                        uint16_t *__restrict__ Y)
+                                                        uint16_t *__restrict__ Y, long y_batch)
 {
     const long i = ((long)blockIdx.x * 256 + threadIdx.x) * 4;
     if (i >= batches * mn) return;
@@ -155,7 +155,7 @@ __global__ __launch_bounds__(256) void sum_store_kernel(const float *__restrict_
     for (int j = 1; j < TERMS; ++j) {
         y[0].x += y[j].x; y[0].y += y[j].y; y[0].z += y[j].z; y[0].w += y[j].w;
     }
-    *reinterpret_cast<u32x2 *>(Y + i) = pack4(y[0].x, y[0].y, y[0].z, y[0].w);
+    *reinterpret_cast<u32x2 *>(Y + (size_t)b * y_batch + e) = pack4(y[0].x, y[0].y, y[0].z, y[0].w);
 }
 
 }  // namespace
@@ -170,13 +170,14 @@ hipError_t launch_sum_act(hipStream_t st, const float *part, int ksplit, long ba
     return hipGetLastError();
 }
 
-hipError_t launch_sum_store(hipStream_t st, const float *part, int ksplit, long batches, long mn, int terms, uint16_t *Y)
+hipError_t launch_sum_store(hipStream_t st, const float *part, int ksplit, long batches, long mn, int terms, uint16_t *Y,
+                            long y_batch)
 {
     const dim3 grid((unsigned)((batches * mn / 4 + 255) / 256));
     if (terms == 1)
-        hipLaunchKernelGGL(sum_store_kernel<1>, grid, dim3(256), 0, st, part, ksplit, batches, mn, Y);
+        hipLaunchKernelGGL(sum_store_kernel<1>, grid, dim3(256), 0, st, part, ksplit, batches, mn, Y, y_batch);
     else
-        hipLaunchKernelGGL(sum_store_kernel<2>, grid, dim3(256), 0, st, part, ksplit, batches, mn, Y);
+        hipLaunchKernelGGL(sum_store_kernel<2>, grid, dim3(256), 0, st, part, ksplit, batches, mn, Y, y_batch);
     return hipGetLastError();
 }
 

@@ -194,9 +194,10 @@ hipError_t launch_down2(hipStream_t st, const gemm::Params &p, const EpiStore &e
 hipError_t launch_gu_split(hipStream_t st, const gemm::Params &p, const EpiPart<2> &e, int rows);
 hipError_t launch_down_split(hipStream_t st, const gemm::Params &p, const EpiPart<1> &e, int rows);
 // Sums of the K slices in slice order.  part [ksplit][batches][2][mn] -> Act [batches][terms][mn], silu(G) * U
-// rounded (terms = 1) or as two terms; part [ksplit][batches][terms][mn] -> Y [batches][mn].
+// rounded (terms = 1) or as two terms; part [ksplit][batches][terms][mn] -> Y, mn elements every y_batch.
 hipError_t launch_sum_act(hipStream_t st, const float *part, int ksplit, long batches, long mn, int terms, uint16_t *Act);
-hipError_t launch_sum_store(hipStream_t st, const float *part, int ksplit, long batches, long mn, int terms, uint16_t *Y);
+hipError_t launch_sum_store(hipStream_t st, const float *part, int ksplit, long batches, long mn, int terms, uint16_t *Y,
+                            long y_batch);
 hipError_t launch_da(hipStream_t st, const gemm::Params &p, const EpiStore &e);  // dY * Wd_bar^T
 hipError_t launch_swiglu_fwd(hipStream_t st, const uint16_t *G, const uint16_t *U, uint16_t *Act, long rows,
                              int dff, int n0, int nf);

@@ -386,90 +386,115 @@ DenseSplit dense_split(const Dims &m, int M, int N, int K, int nset, int terms, 
     return best;
 }
 
+// Rows of the dense FFN are walked in blocks of `rows` per sequence (all of them unless the scratch is too small).
 struct DensePlan {
     int terms;           // bf16 terms of the activation
-    DenseSplit gu, down;
-    size_t act, parts;   // bytes
+    int rows;
+    size_t act;          // bytes of a block's activation
+    size_t floats;       // bound on the partial sums of split contractions
+    DenseSplit gate_up(const Dims &m, int r) const { return dense_split(m, r, m.dff, m.d, 2, 1, floats); }
+    DenseSplit down(const Dims &m, int r) const { return dense_split(m, r, m.d, m.dff, 1, terms, floats); }
+    size_t parts(const Dims &m, int r) const   // floats that a block of r rows uses
+    {
+        const DenseSplit g = gate_up(m, r), w = down(m, r);
+        const size_t a = g.rows ? (size_t)g.ks * 2 * m.B * r * m.dff : 0;
+        const size_t b = w.rows ? (size_t)w.ks * terms * m.B * r * m.d : 0;
+        return a > b ? a : b;
+    }
 };
 
-DensePlan dense_plan(const Dims &m, size_t budget)
+DensePlan dense_plan(const Dims &m, const DenseScratch &scratch)
 {
     DensePlan p;
     // Blocks of 64 k tokens (prefill) round the activation to bf16 like the training forward; every other
     // number of tokens, decode steps among them, keeps it in fp32 precision.
     p.terms = m.L % 64 == 0 ? 1 : 2;
-    p.act = align_up((size_t)m.tokens * m.dff * 2 * p.terms, 256);
-    const size_t fl = budget > p.act ? (budget - p.act) / sizeof(float) : 0;
-    p.gu = dense_split(m, m.L, m.dff, m.d, 2, 1, fl);
-    p.down = dense_split(m, m.L, m.d, m.dff, 1, p.terms, fl);
-    size_t a = p.gu.rows ? (size_t)p.gu.ks * 2 * m.tokens * m.dff : 0;
-    const size_t b = p.down.rows ? (size_t)p.down.ks * p.terms * m.tokens * m.d : 0;
-    if (b > a) a = b;
-    p.parts = align_up(a * sizeof(float), 256);
+    const size_t per_row = (size_t)m.B * m.dff * 2 * p.terms;
+    p.rows = m.L;
+    if (scratch.fixed && per_row * m.L > scratch.bytes) {
+        size_t r = scratch.bytes / per_row;
+        if (r < 1) r = 1;
+        // blocks of equal size, in whole tiles where one fits
+        const size_t n = ((size_t)m.L + r - 1) / r, even = ((size_t)m.L + n - 1) / n;
+        p.rows = (int)(r >= 64 ? (even + 63) / 64 * 64 <= r ? (even + 63) / 64 * 64 : r / 64 * 64 : r);
+    }
+    p.act = align_up(per_row * p.rows, 256);
+    p.floats = scratch.bytes > p.act ? (scratch.bytes - p.act) / 256 * 256 / sizeof(float) : 0;
     return p;
 }
 
 }  // namespace
 
-// `budget`: the partial sums of split contractions are kept within this many bytes (activations included).
-size_t bf16_dense_workspace_bytes(const Dims &m, size_t budget)
+size_t bf16_dense_workspace_bytes(const Dims &m, const DenseScratch &scratch)
 {
-    const DensePlan p = dense_plan(m, budget);
-    return p.act + p.parts;
+    const DensePlan p = dense_plan(m, scratch);
+    const int last = m.L % p.rows;
+    size_t parts = p.parts(m, p.rows);
+    if (last) {
+        const size_t q = p.parts(m, last);
+        if (q > parts) parts = q;
+    }
+    return p.act + align_up(parts * sizeof(float), 256);
 }
 
 // Dense SwiGLU FFN of every sequence with its own materialised merged parameters
 // (m.T == m.L: one parameter set per sequence, any number of rows).
-int bf16_dense_ffn_fwd(const Dims &m, const void *Xv, const void *Wbarv, void *Yv, void *ws, size_t budget,
+int bf16_dense_ffn_fwd(const Dims &m, const void *Xv, const void *Wbarv, void *Yv, void *ws, const DenseScratch &scratch,
                        hipStream_t st)
 {
-    const bf *X = (const bf *)Xv, *Wbar = (const bf *)Wbarv;
-    const DensePlan pl = dense_plan(m, budget);
-    bf *Y = (bf *)Yv, *Act = (bf *)ws;
+    const bf *Wbar = (const bf *)Wbarv;
+    const DensePlan pl = dense_plan(m, scratch);
+    const int nt = pl.terms;
+    bf *Act = (bf *)ws;
     float *parts = (float *)((char *)ws + pl.act);
-    const long TD = (long)m.T * m.d, TF = (long)m.T * m.dff;
-    {
-        Params p = {};
-        p.A[0] = X; p.a_batch[0] = TD; p.lda[0] = m.d;
-        p.B[0] = Wbar; p.b_batch[0] = m.D; p.ldb[0] = m.dff;
-        p.B[1] = Wbar + (size_t)m.S * m.D; p.b_batch[1] = m.D; p.ldb[1] = m.dff;
-        p.M = m.T; p.N = m.dff; p.K = m.d; p.batches = m.S;
-        prof::Range r(st, prof::kGemmGU, gemm_flops(p, 2, 1),
-                      2.0 * ((double)m.S * TD + 2.0 * m.S * m.D + (double)m.S * TF));
-        if (pl.gu.rows) {
-            p.ksplit = pl.gu.ks;
-            p.batches = m.S * pl.gu.ks;
-            const k::EpiPart<2> epi = {parts, pl.gu.ks, m.S, m.T, m.dff};
-            LORY_TRY(k::launch_gu_split(st, p, epi, pl.gu.rows));
-            LORY_TRY(k::launch_sum_act(st, parts, pl.gu.ks, m.S, TF, pl.terms, Act));
-        } else if (pl.terms == 1) {
-            EpiGU epi = {nullptr, nullptr, Act, m.T, m.dff, 0};
-            LORY_TRY(k::launch_gu(st, p, epi));
-        } else {
-            LORY_TRY(k::launch_gu2(st, p, k::EpiAct2{Act, m.T, m.dff}));
+    const long TD = (long)m.L * m.d;
+    for (int r0 = 0; r0 < m.L; r0 += pl.rows) {
+        const int rows = m.L - r0 < pl.rows ? m.L - r0 : pl.rows;
+        const bf *X = (const bf *)Xv + (size_t)r0 * m.d;
+        bf *Y = (bf *)Yv + (size_t)r0 * m.d;
+        const long RD = (long)rows * m.d, RF = (long)rows * m.dff;   // a sequence's part of the block
+        {
+            const DenseSplit sp = pl.gate_up(m, rows);
+            Params p = {};
+            p.A[0] = X; p.a_batch[0] = TD; p.lda[0] = m.d;
+            p.B[0] = Wbar; p.b_batch[0] = m.D; p.ldb[0] = m.dff;
+            p.B[1] = Wbar + (size_t)m.B * m.D; p.b_batch[1] = m.D; p.ldb[1] = m.dff;
+            p.M = rows; p.N = m.dff; p.K = m.d; p.batches = m.B;
+            prof::Range r(st, prof::kGemmGU, gemm_flops(p, 2, 1), 2.0 * m.B * ((double)RD + 2.0 * m.D + (double)RF));
+            if (sp.rows) {
+                p.ksplit = sp.ks;
+                p.batches = m.B * sp.ks;
+                const k::EpiPart<2> epi = {parts, sp.ks, m.B, rows, m.dff};
+                LORY_TRY(k::launch_gu_split(st, p, epi, sp.rows));
+                LORY_TRY(k::launch_sum_act(st, parts, sp.ks, m.B, RF, nt, Act));
+            } else if (nt == 1) {
+                EpiGU epi = {nullptr, nullptr, Act, rows, m.dff, 0};
+                LORY_TRY(k::launch_gu(st, p, epi));
+            } else {
+                LORY_TRY(k::launch_gu2(st, p, k::EpiAct2{Act, rows, m.dff}));
+            }
         }
-    }
-    {
-        // the two terms of an activation are blocks of rows of one matrix, or two sources
-        const int nt = pl.terms;
-        Params p = {};
-        p.A[0] = Act; p.A[1] = Act + TF; p.a_batch[0] = p.a_batch[1] = nt * TF; p.lda[0] = p.lda[1] = m.dff;
-        p.B[0] = p.B[1] = Wbar + (size_t)2 * m.S * m.D; p.b_batch[0] = p.b_batch[1] = m.D; p.ldb[0] = p.ldb[1] = m.d;
-        p.M = m.T; p.N = m.d; p.K = m.dff; p.batches = m.S;
-        prof::Range r(st, prof::kGemmDown, gemm_flops(p, 1, 1),
-                      2.0 * ((double)m.S * TF + (double)m.S * m.D + (double)m.S * TD));
-        EpiStore epi = {Y, TD, m.d};
-        if (pl.down.rows) {
-            p.M = nt * m.T;
-            p.ksplit = pl.down.ks;
-            p.batches = m.S * pl.down.ks;
-            const k::EpiPart<1> part = {parts, pl.down.ks, m.S, nt * m.T, m.d};
-            LORY_TRY(k::launch_down_split(st, p, part, pl.down.rows));
-            LORY_TRY(k::launch_sum_store(st, parts, pl.down.ks, m.S, TD, nt, Y));
-        } else if (nt == 1) {
-            LORY_TRY(k::launch_down(st, p, epi));
-        } else {
-            LORY_TRY(k::launch_down2(st, p, epi));
+        {
+            // the two terms of an activation are blocks of rows of one matrix, or two sources
+            const DenseSplit sp = pl.down(m, rows);
+            Params p = {};
+            p.A[0] = Act; p.A[1] = Act + RF; p.a_batch[0] = p.a_batch[1] = nt * RF; p.lda[0] = p.lda[1] = m.dff;
+            p.B[0] = p.B[1] = Wbar + (size_t)2 * m.B * m.D; p.b_batch[0] = p.b_batch[1] = m.D; p.ldb[0] = p.ldb[1] = m.d;
+            p.M = rows; p.N = m.d; p.K = m.dff; p.batches = m.B;
+            prof::Range r(st, prof::kGemmDown, gemm_flops(p, 1, 1), 2.0 * m.B * ((double)RF + (double)m.D + (double)RD));
+            const EpiStore epi = {Y, TD, m.d};
+            if (sp.rows) {
+                p.M = nt * rows;
+                p.ksplit = sp.ks;
+                p.batches = m.B * sp.ks;
+                const k::EpiPart<1> part = {parts, sp.ks, m.B, nt * rows, m.d};
+                LORY_TRY(k::launch_down_split(st, p, part, sp.rows));
+                LORY_TRY(k::launch_sum_store(st, parts, sp.ks, m.B, RD, nt, Y, TD));
+            } else if (nt == 1) {
+                LORY_TRY(k::launch_down(st, p, epi));
+            } else {
+                LORY_TRY(k::launch_down2(st, p, epi));
+            }
         }
     }
     return LORY_OK;

@@ -266,9 +266,9 @@ int skinny_ffn(const Dims &m, const T *X, const T *Wbar, T *Y, void *ws, hipStre
     return LORY_OK;
 }
 
-// Partial sums of the skinny plan.  For bf16 it is the size that calls of other than a multiple of 64
-// tokens report (the ring GEMM needs less or as much): which calls fit the library-held scratch is part of
-// the interface.
+// The least scratch a call accepts: the partial sums of the skinny passes over up to 8 tokens, or (bf16, multiples
+// of 64 tokens) the activation block.  For bf16 the kernels need not be those, but which calls fit the library-held
+// scratch and which workspaces are large enough is part of the interface, so the sizes stay.
 size_t base_bytes(const Dims &m)
 {
     if (m.dtype == LORY_BF16 && m.L % 64 == 0) return align_up((size_t)m.tokens * m.dff * 2, 256);
@@ -276,11 +276,15 @@ size_t base_bytes(const Dims &m)
     return align_up(sizeof(float) * (pl.part1 + pl.part2), 256);
 }
 
-// Bound on the scratch of the matrix-core path: calls that fit the library-held array keep fitting it.
-size_t gemm_budget(const Dims &m)
+// Scratch of the matrix-core path when the caller lets it choose.  Calls that fit the library-held array stay
+// within it, long ones in blocks of rows: the least scratch holds two rows' activation for every pass of one token
+// already, so there is always a block that fits.  Larger calls take the whole activation at once (every block
+// reads the weights again).
+DenseScratch gemm_scratch(const Dims &m)
 {
     const size_t base = base_bytes(m);
-    return base <= kStaticScratchBytes ? kStaticScratchBytes : (base > kGemmBudget ? base : kGemmBudget);
+    if (base <= kStaticScratchBytes) return {kStaticScratchBytes, true};
+    return {base > kGemmBudget ? base : kGemmBudget, false};
 }
 
 // Scratch of lory_dense_ffn_fwd_static: the partial sums (or the activation block) that
@@ -317,21 +321,24 @@ int dense_ffn_fwd_static(const Dims &m, const void *X, const void *Wbar, void *Y
     if (rc != LORY_OK) return rc;
     // Every value the kernels read from the scratch is written earlier in the same call, so
     // nothing has to be cleared between calls.
-    return dense_ffn_fwd(m, X, Wbar, Y, ws, st);
+    return dense_ffn_fwd(m, X, Wbar, Y, ws, kStaticScratchBytes, st);
 }
+
+size_t dense_min_workspace_bytes(const Dims &m) { return base_bytes(m); }
 
 size_t dense_workspace_bytes(const Dims &m)
 {
     const size_t base = base_bytes(m);
     if (m.dtype == LORY_F32) return base;
-    const size_t n = bf16_dense_workspace_bytes(m, gemm_budget(m));
+    const size_t n = bf16_dense_workspace_bytes(m, gemm_scratch(m));
     return n > base ? n : base;
 }
 
-int dense_ffn_fwd(const Dims &m, const void *X, const void *Wbar, void *Y, void *ws, hipStream_t st)
+int dense_ffn_fwd(const Dims &m, const void *X, const void *Wbar, void *Y, void *ws, size_t ws_bytes, hipStream_t st)
 {
-    if (m.dtype == LORY_BF16) return bf16_dense_ffn_fwd(m, X, Wbar, Y, ws, gemm_budget(m), st);
-    return skinny_ffn<float>(m, (const float *)X, (const float *)Wbar, (float *)Y, ws, st);
+    if (m.dtype == LORY_F32) return skinny_ffn<float>(m, (const float *)X, (const float *)Wbar, (float *)Y, ws, st);
+    if (ws_bytes >= dense_workspace_bytes(m)) return bf16_dense_ffn_fwd(m, X, Wbar, Y, ws, gemm_scratch(m), st);
+    return bf16_dense_ffn_fwd(m, X, Wbar, Y, ws, DenseScratch{base_bytes(m), true}, st);
 }
 
 }  // namespace lory

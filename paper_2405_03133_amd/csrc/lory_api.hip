@@ -173,8 +173,8 @@ int lory_dense_ffn_fwd(const lory_shape *shape, const void *X, const void *Wbar,
     if (!X || !Wbar || !Y || !workspace) return LORY_ERR_NULL;
     if (!aligned16(X) || !aligned16(Wbar) || !aligned16(Y) || !aligned16(workspace)) return LORY_ERR_ALIGN;
     const Dims m = lory::make_dims(*shape);
-    if (workspace_bytes < lory::align_up(lory::dense_workspace_bytes(m), 256)) return LORY_ERR_WORKSPACE;
-    return lory::dense_ffn_fwd(m, X, Wbar, Y, workspace, (hipStream_t)stream);
+    if (workspace_bytes < lory::align_up(lory::dense_min_workspace_bytes(m), 256)) return LORY_ERR_WORKSPACE;
+    return lory::dense_ffn_fwd(m, X, Wbar, Y, workspace, workspace_bytes, (hipStream_t)stream);
 }
 
 int lory_dense_ffn_fwd_static(const lory_shape *shape, const void *X, const void *Wbar, void *Y, void *stream)

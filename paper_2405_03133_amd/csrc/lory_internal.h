@@ -86,16 +86,24 @@ int f32_merge_all(const Dims &m, const float *w, const float *Wg, const float *W
                   float *Wbar, hipStream_t st);
 
 // ---- inference with prompt-only routing (infer.hip)
-size_t dense_workspace_bytes(const Dims &m);
-int dense_ffn_fwd(const Dims &m, const void *X, const void *Wbar, void *Y, void *ws, hipStream_t st);
+size_t dense_workspace_bytes(const Dims &m);       // what lory_workspace_bytes reports
+size_t dense_min_workspace_bytes(const Dims &m);   // the least that a call accepts
+int dense_ffn_fwd(const Dims &m, const void *X, const void *Wbar, void *Y, void *ws, size_t ws_bytes, hipStream_t st);
 size_t dense_static_scratch_limit();
 int dense_ffn_fwd_static(const Dims &m, const void *X, const void *Wbar, void *Y, hipStream_t st);
 
 // ---- bf16 path (ffn_bf16.hip)
 int bf16_merge_all(const Dims &m, const float *w, const void *Wg, const void *Wu, const void *Wd,
                    void *Wbar, hipStream_t st);
-size_t bf16_dense_workspace_bytes(const Dims &m, size_t budget);
-int bf16_dense_ffn_fwd(const Dims &m, const void *X, const void *Wbar, void *Y, void *ws, size_t budget, hipStream_t st);
+// Scratch of the dense FFN.  fixed: no call may use more than `bytes` (rows are walked in blocks that fit); else the
+// activation takes what it needs and `bytes` bounds what split contractions add to it.
+struct DenseScratch {
+    size_t bytes;
+    bool fixed;
+};
+size_t bf16_dense_workspace_bytes(const Dims &m, const DenseScratch &scratch);
+int bf16_dense_ffn_fwd(const Dims &m, const void *X, const void *Wbar, void *Y, void *ws, const DenseScratch &scratch,
+                       hipStream_t st);
 int set_slab_budget(size_t bytes);
 int set_fused_mode(int mode);
 size_t bf16_workspace_bytes(const Dims &m, int pass);

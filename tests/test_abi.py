@@ -81,6 +81,15 @@ def test_route_bwd_validation():
     assert L.lory_route_bwd(None, F, F, F, F, F, F, 0, None) == lb.LORY_ERR_NULL
 
 
+DENSE_LEAST = [
+    ((3, 2001, 512, 1408), 12976128), ((1, 8001, 512, 1408), 4325376), ((1, 50000, 64, 192), 73728),
+    ((1, 6000, 1024, 1408), 8650752), ((4, 6001, 256, 704), 4325376), ((1, 1, 2048, 5632), 6332416),
+    ((2, 100, 512, 1408), 8650752), ((2000, 3, 64, 64), 4608000), ((2, 8, 2048, 5632), 50659328),
+    ((8, 1000, 2048, 5632), 51380224), ((4, 64, 2048, 5632), 4 * 64 * 5632 * 2),
+    ((1, 131072, 64, 64), 131072 * 64 * 2), ((1, 131136, 64, 64), 131136 * 64 * 2),
+]
+
+
 def test_inference_entry_points_validation():
     L = lb.lib()
     F = FAKE
@@ -112,6 +121,13 @@ def test_inference_entry_points_validation():
         args[i] = F + 8
         assert L.lory_dense_ffn_fwd(sp, *args, need, None) == lb.LORY_ERR_ALIGN
     assert L.lory_dense_ffn_fwd(sp, F, F, F, F, need - 1, None) == lb.LORY_ERR_WORKSPACE
+    # the least that bf16 calls take: the activation block (multiples of 64 tokens), or what a pass of up to 8
+    # tokens keeps as partial sums.  Calls whose least fits the library-held 16 MiB are reported within it.
+    for (B, n, d, d_ff), least in DENSE_LEAST:
+        b = shape(dtype=lb.LORY_BF16, B=B, L=n, T=n, d=d, d_ff=d_ff, E=1)
+        assert L.lory_dense_ffn_fwd(ctypes.byref(b), F, F, F, F, least - 1, None) == lb.LORY_ERR_WORKSPACE
+        need = lb.lory_workspace_bytes(b, lb.LORY_PASS_DENSE)
+        assert need >= least and (need <= 16 << 20) == (least <= 16 << 20), (B, n, d, d_ff, need, least)
     # bf16: d and d_ff granularity still applies, the token count does not
     assert lb.lory_workspace_bytes(shape(dtype=lb.LORY_BF16, L=5, T=5, d=64, d_ff=128), lb.LORY_PASS_DENSE) > 0
     assert L.lory_workspace_bytes(ctypes.byref(shape(dtype=lb.LORY_BF16, L=5, T=5, d=72)), lb.LORY_PASS_DENSE,

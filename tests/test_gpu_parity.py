@@ -4,6 +4,8 @@ oracle, element by element on the same seeded inputs.
 Tolerances (relative L2 per output tensor): 1e-5 for the fp32 configuration,
 1e-2 for bf16 operands with fp32 accumulation.
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -586,6 +588,38 @@ def test_dense_block_activation_at_the_end_of_the_range(d, d_ff):
     Y = lb.lory_dense_ffn_fwd(X.bfloat16(), W.bfloat16().reshape(3, 1, d * d_ff).contiguous(), d_ff).double().cpu()
     assert bool(((Y[0, 0] / (d_ff * a * 2.0 ** -100) - 1).abs() < 2.0 ** -8).all()), Y[0, 0, :4]
     assert bool((Y[0, 1] == float("inf")).all()), Y[0, 1, :4]
+
+
+# Scratch that holds a part of the rows at a time: the library-held array under long ragged blocks, and the least
+# workspace that is accepted (several row blocks with a short last one, blocks of fewer than 64 rows, and one block
+# without room for partial sums).  The bytes behind the workspace stay as they were.
+@pytest.mark.parametrize("B,n_tok,d,d_ff,least", [
+    (1, 50000, 64, 192, 73728), (4, 2001, 256, 704, 4325376), (3, 333, 128, 704, 1622016), (600, 100, 64, 64, 7372800),
+    (4, 64, 512, 1408, 720896),
+])
+def test_dense_block_in_little_scratch(B, n_tok, d, d_ff, least):
+    cfg = LoryConfig("dense_scratch", B=B, L=n_tok, T=n_tok, d=d, d_ff=d_ff, E=B, dtype="bf16", seed=63)
+    print(f"[gpu] {cfg}", flush=True)
+    t = make_inputs(cfg, with_dy=False)
+    X = to_dev(t["X"], cfg)
+    Wbar = torch.stack([to_dev(t[k], cfg).reshape(B, d * d_ff) for k in ("Wg", "Wu", "Wd")]).contiguous()
+    ref = orc.ffn_fwd(t["X"], np.eye(B), t["Wg"], t["Wu"], t["Wd"], n_tok)["Y"]
+    shape = lb.make_shape(B, n_tok, n_tok, d, d_ff, 1, X.dtype)
+    need = lb.lory_workspace_bytes(shape, lb.LORY_PASS_DENSE)
+    assert need <= 16 << 20
+    outs = []
+    for size in (need, least):
+        ws = torch.full((size + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+        Y = torch.full_like(X, float("nan"))
+        rc = lb.lib().lory_dense_ffn_fwd(ctypes.byref(shape), X.data_ptr(), Wbar.data_ptr(), Y.data_ptr(), ws.data_ptr(),
+                                         size, torch.cuda.current_stream().cuda_stream)
+        assert rc == lb.LORY_OK, (size, lb.status_string(rc))
+        torch.cuda.synchronize()
+        assert bool((ws[size:] == 0x5A).all())
+        check(f"{size} bytes", host(Y), ref, TOL["bf16"])
+        outs.append(Y)
+    Y = lb.lory_dense_ffn_fwd_static(X, Wbar, d_ff, torch.full_like(X, float("nan")))
+    assert torch.equal(Y, outs[0])
 
 
 def test_prefill_with_saved_merged_parameters_feeds_decode(default_budget):
