@@ -752,3 +752,19 @@ def test_prompt_merge_with_prompts_of_different_lengths(L, lens):
     D = cfg.d * cfg.d_ff
     ref_g = np.einsum("be,en->bn", got_w, t["Wg"].astype(np.float64).reshape(cfg.E, D))
     assert rel_l2(host(Wbar).reshape(3, cfg.B, D)[0], ref_g) <= 4e-3
+
+
+@pytest.mark.parametrize("dtype,classes", [("bf16", "gemm_gate_up + gemm_down"), ("f32", "dense_skinny")])
+def test_bench_decode_mode(dtype, classes, capsys, monkeypatch):
+    """bench.py --mode infer: one JSON line whose roofline names the kernel classes that a decode step launches."""
+    import json
+    import types
+
+    import bench
+
+    cfg = LoryConfig("bench_infer", B=2, L=64, T=64, d=128, d_ff=256, E=4, dtype=dtype, seed=71)
+    monkeypatch.setitem(CONFIGS, cfg.name, cfg)
+    bench.bench_infer(types.SimpleNamespace(config=cfg.name, warmup=1, steps=2))
+    out = json.loads(capsys.readouterr().out.strip().splitlines()[-1])
+    assert out["roofline"]["kernel"] == classes
+    assert out["value"] > 0 and out["roofline"]["achieved"] > 0 and out["roofline"]["avg_launch_us"] > 0
