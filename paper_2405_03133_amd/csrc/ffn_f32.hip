@@ -49,9 +49,11 @@ struct Problem {
 };
 
 constexpr int kMaxProblems = 7;
+constexpr long kMaxGrid = (1L << 24) - 1;
 struct Group {
     Problem p[kMaxProblems];
     int n;
+    int first;                  // of this launch's workgroups, counted through the problems
 };
 
 // Elementwise operands of the epilogues, all with the layout of C.
@@ -96,7 +98,7 @@ __global__ __launch_bounds__(256) void contract_kernel(const Group grp, const El
 {
     constexpr int NSET = MODE == kGateUp ? 2 : 1;
     __shared__ float red[3][NSET][16][64];
-    int bid = blockIdx.x, pi = 0;
+    int bid = grp.first + blockIdx.x, pi = 0;
     while (bid >= grp.p[pi].blocks) bid -= grp.p[pi++].blocks;
     const Problem &p = grp.p[pi];
     const int tile = p.split_waves ? 32 : 64;
@@ -289,7 +291,14 @@ void launch(hipStream_t st, Group &g, const Elementwise &ew = Elementwise())
         p.blocks = (int)(p.split_waves ? small : big);
         blocks += p.blocks;
     }
-    hipLaunchKernelGGL(contract_kernel<MODE>, dim3((unsigned)blocks), dim3(256), 0, st, g, ew);
+    // A grid dimension counts fewer than 2^32 threads, i.e. 2^24 workgroups, which the merge of one segment at
+    // d * d_ff = 3.6e8 passes: further launches take the rest.  (2^31 workgroups of 64 x 64 elements would not fit
+    // the memory.)
+    for (long first = 0; first < blocks; first += kMaxGrid) {
+        g.first = (int)first;
+        const long n = blocks - first < kMaxGrid ? blocks - first : kMaxGrid;
+        hipLaunchKernelGGL(contract_kernel<MODE>, dim3((unsigned)n), dim3(256), 0, st, g, ew);
+    }
 }
 
 // slab_x[s][i] = sum_e w[s][e] stack_x[e][i]  for the given matrices

@@ -151,6 +151,19 @@ def test_route_forms(dtype, d, T, E):
     check("w, prompt", host(w_p), orc.route(t["X"], t["R"], cfg.L)["w"], TOL["f32"])
 
 
+def test_fp32_merge_of_very_large_matrices():
+    """More workgroups than one launch counts.  One expert: its routing weight is 1, the merge a copy."""
+    d, d_ff = 16384, 21888
+    X, R = torch.ones((1, 4, d), device="cuda"), torch.ones((d, 1), device="cuda")
+    W = [torch.empty(s, device="cuda").uniform_() for s in ((1, d, d_ff), (1, d, d_ff), (1, d_ff, d))]
+    Wbar = torch.full((3, 1, d * d_ff), float("nan"), device="cuda")
+    print(f"[gpu] prompt merge d={d} d_ff={d_ff}", flush=True)
+    w, _ = lb.lory_prompt_merge(X, R, *W, Wbar=Wbar)
+    assert w.item() == 1.0
+    for i in range(3):
+        assert torch.equal(Wbar[i].view(-1), W[i].view(-1)), i
+
+
 def test_fp32_given_routing_weights_onehot_and_accumulate():
     cfg = CONFIGS["C1"]
     t = make_inputs(cfg)
