@@ -627,6 +627,11 @@ inline hipError_t launch(const Params &p, const Epi &epi, hipStream_t st)
 // with four waves and three stages than with eight and four (A Wd_bar of 32 segments at d = 1024: 45
 // against 53 us).
 using T256 = Tile<2, 4, 4, 2, 4, 1>;
+// Two operand sets: a wave of T256 would own 32 columns of each and store 64 bytes of a row, half a line; 64 x 64 per
+// wave and set stores whole lines.  Gate/up with G and U saved, us: 64 segments of 256 tokens at d = 2048, d_ff = 5632
+// 852 -> 824; 128 segments at d = 1024, d_ff = 2816 491 -> 467; 8 of 1024 at d = 2048 425 -> 408.  The activation alone
+// (half the stores): 803 -> 799, 443 -> 438, 400 -> 397.
+using T256x2 = Tile<4, 2, 2, 4, 4, 1>;
 using T192 = Tile<2, 2, 3, 4, 4, 1>;
 using T128 = Tile<2, 2, 2, 4, 3, 1>;
 using T64 = Tile<2, 2, 1, 4, 4, 1>;
@@ -649,7 +654,8 @@ inline hipError_t launch_rows(const Params &p, const Epi &e, hipStream_t st)
     const int bns = 256 / NSET;
     const double t256 = 0.90 * rounds_of(p, 256, bns), t192 = 0.72 * rounds_of(p, 192, bns);
     const double t128 = 0.55 * rounds_of(p, 128, bns), t64 = 0.42 * rounds_of(p, 64, bns);
-    if (t256 <= t192 && t256 <= t128 && t256 <= t64) return launch<NSET, NSRC, A_MC, B_NC, T256>(p, e, st);
+    if (t256 <= t192 && t256 <= t128 && t256 <= t64)
+        return launch<NSET, NSRC, A_MC, B_NC, std::conditional_t<NSET == 2, T256x2, T256>>(p, e, st);
     if (t192 <= t128 && t192 <= t64) return launch<NSET, NSRC, A_MC, B_NC, T192>(p, e, st);
     if (t128 <= t64) return launch<NSET, NSRC, A_MC, B_NC, T128>(p, e, st);
     return launch<NSET, NSRC, A_MC, B_NC, T64>(p, e, st);
