@@ -381,12 +381,17 @@ __global__ __launch_bounds__(TL::threads, TL::waves_per_simd) void gemm2_kernel(
     };
 
     // The MI * NB MFMAs of a K slice are issued one per "slot"; the first slots also carry the LDS fragment
-    // reads of the next slice, the later ones this wave's direct loads for the ring, so that those issue in
-    // the shadow of the matrix pipe and the fragments have arrived when the slice ends.  Fragments are
+    // reads of the next slice, and some this wave's direct loads for the ring, so that those issue in
+    // the shadow of the matrix pipe and the fragments have arrived when the slice ends.  Where B streams K-slow rows
+    // and A is K-contiguous (gate/up and down, forward) the loads of eight waves are spread over the slice from its
+    // first slot: gate/up of 64 segments of 256 tokens at d = 2048, d_ff = 5632 792 -> 779 us, down of 128 at d = 1024
+    // 257 -> 242.  Elsewhere they stay in the second half (dX of the first shape, two K-contiguous sources: 749, spread
+    // 762; down of 16 segments of 448 at d = 1280 on four waves: 76, spread 78).  Fragments are
     // double buffered in registers.  The single barrier of a K step sits between its two slices: by then
     // every wave has finished reading step g-1 (its ring slot may be refilled with step g+S-1) and step
     // g+1 has landed for everyone (its first slice can be fetched behind the second slice's MFMAs).
     constexpr int NM = NB * MI;
+    auto load_slot = [](int l, int n) { return (B_NC && !A_MC && NSRC == 1 && TL::NW == 8) ? l * NM / n : NM / 2 + l * (NM / 2) / n; };
     bf16x8 a0[MI], b0[NB], a1[MI], b1[NB];
     wait_vmcnt<(S - 1) * (LA + LB)>();  // steps 1 .. S-1 may still be in flight
     ring_barrier();
@@ -418,7 +423,7 @@ __global__ __launch_bounds__(TL::threads, TL::waves_per_simd) void gemm2_kernel(
             if constexpr (!first) {
 #pragma unroll
                 for (int l = 0; l < LA; ++l)
-                    if (NM / 2 + l * (NM / 2) / LA == sl) issue_A(slotA, l);
+                    if (load_slot(l, LA) == sl) issue_A(slotA, l);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -439,11 +444,11 @@ __global__ __launch_bounds__(TL::threads, TL::waves_per_simd) void gemm2_kernel(
                 if (f * NM / (2 * NF) == sl) load_frag(nxt, 0, f, a0, b0);
 #pragma unroll
             for (int l = 0; l < LB; ++l)
-                if (NM / 2 + l * (NM / 2) / LB == sl) issue_B(cur, l);
+                if (load_slot(l, LB) == sl) issue_B(cur, l);
             if constexpr (last) {
 #pragma unroll
                 for (int l = 0; l < LA; ++l)
-                    if (NM / 2 + l * (NM / 2) / LA == sl) issue_A(cur, l);
+                    if (load_slot(l, LA) == sl) issue_A(cur, l);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
