@@ -364,7 +364,7 @@ DenseSplit dense_split(const Dims &m, int M, int N, int K, int nset, int terms, 
     DenseSplit best = {0, 1};
     double best_t = 1e30;
     for (int rows = 64; rows <= 256; rows += rows) {
-        const double step = rows == 64 ? 0.42 : rows == 128 ? 0.55 : 0.90;
+        const double step = gemm2::step_us(rows);
         const long tiles1 = (long)m.B * ((M + rows - 1) / rows) * ((N + bns - 1) / bns);
         const double t1 = step * (double)((tiles1 + cus - 1) / cus) * (terms * steps + 6);
         if (t1 < best_t) {

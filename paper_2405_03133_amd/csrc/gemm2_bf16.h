@@ -649,21 +649,37 @@ inline double rounds_of(const Params &p, int bm, int bns)
     return (double)((tiles + cu_count() - 1) / cu_count());
 }
 
-// Tile height of a contraction whose rows are the tokens of a segment: the shortest estimated time,
-// i.e. rounds of tiles over the CUs times the measured time of a tile's K step (us, all CUs busy:
-// 0.90, 0.72, 0.55 and 0.42 for 256, 192, 128 and 64 rows).  A taller tile costs less per row, a lower one
-// wastes fewer rows of a segment and fewer CUs of the last round.
+// Time of a tile's K step, us, all CUs busy on slabs of T = 64 .. 1024 rows.
+constexpr double step_us(int rows) { return rows == 256 ? 0.90 : rows == 192 ? 0.72 : rows == 128 ? 0.62 : 0.42; }
+
+// Tile height of a contraction whose rows are the tokens of a segment: the shortest estimated time, rounds of tiles
+// over the CUs times the time of a step.  A taller tile costs less per row, a lower one wastes fewer rows of a segment
+// and fewer CUs of the last round.  128 rows of a 256-row segment read the merged operand twice: 64 segments, K = 4096,
+// N = 1536 take 297 us in two rounds of 256 rows and 317 in three of 128 (dX of the same 527 and 593), 32 segments,
+// K = 2816, N = 1024 94 in half a round of 256 and 67 in one of 128.
+inline int tile_rows(const Params &p, int bns)
+{
+    int best = 256;
+    double t = step_us(256) * rounds_of(p, 256, bns);
+    for (int rows = 192; rows >= 64; rows -= 64) {
+        const double r = step_us(rows) * rounds_of(p, rows, bns);
+        if (r < t) {
+            t = r;
+            best = rows;
+        }
+    }
+    return best;
+}
+
 template <int NSET, int NSRC, bool A_MC, bool B_NC, class Epi>
 inline hipError_t launch_rows(const Params &p, const Epi &e, hipStream_t st)
 {
-    const int bns = 256 / NSET;
-    const double t256 = 0.90 * rounds_of(p, 256, bns), t192 = 0.72 * rounds_of(p, 192, bns);
-    const double t128 = 0.55 * rounds_of(p, 128, bns), t64 = 0.42 * rounds_of(p, 64, bns);
-    if (t256 <= t192 && t256 <= t128 && t256 <= t64)
-        return launch<NSET, NSRC, A_MC, B_NC, std::conditional_t<NSET == 2, T256x2, T256>>(p, e, st);
-    if (t192 <= t128 && t192 <= t64) return launch<NSET, NSRC, A_MC, B_NC, T192>(p, e, st);
-    if (t128 <= t64) return launch<NSET, NSRC, A_MC, B_NC, T128>(p, e, st);
-    return launch<NSET, NSRC, A_MC, B_NC, T64>(p, e, st);
+    switch (tile_rows(p, 256 / NSET)) {
+    case 256: return launch<NSET, NSRC, A_MC, B_NC, std::conditional_t<NSET == 2, T256x2, T256>>(p, e, st);
+    case 192: return launch<NSET, NSRC, A_MC, B_NC, T192>(p, e, st);
+    case 128: return launch<NSET, NSRC, A_MC, B_NC, T128>(p, e, st);
+    default: return launch<NSET, NSRC, A_MC, B_NC, T64>(p, e, st);
+    }
 }
 
 // Tile of a weight gradient (K = tokens of a segment): both heights take the same time per element
