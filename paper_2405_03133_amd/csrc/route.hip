@@ -28,17 +28,16 @@ constexpr int kMaxE = 64;
 // lanes per row of R whatever E is would make it up to four times as long.  hbar [d] and zpart [1024/P][P]
 // are in LDS; all 1024 threads call this; lanes tid < E of the first wavefront return the probability
 // of expert tid, everyone else 0.
-template <typename T>
-__device__ __forceinline__ float router_softmax(const float *hbar, float *zpart, const T *__restrict__ R, int d,
-                                                int E, int tid)
+template <typename T, int LP>
+__device__ __forceinline__ float router_softmax_p(const float *hbar, float *zpart, const T *__restrict__ R, int d,
+                                                  int E, int tid)
 {
-    const int lp = E <= 16 ? 4 : E <= 32 ? 5 : 6;   // log2 P
-    const int groups = kRouteThreads >> lp;
+    constexpr int groups = kRouteThreads >> LP;
     {
-        const int e = tid & ((1 << lp) - 1);
+        const int e = tid & ((1 << LP) - 1);
         float acc = 0.f;
         if (e < E) {
-            int j = tid >> lp;
+            int j = tid >> LP;
             for (; j + 7 * groups < d; j += 8 * groups) {
                 float r[8];
 #pragma unroll
@@ -56,9 +55,8 @@ __device__ __forceinline__ float router_softmax(const float *hbar, float *zpart,
         float z = -INFINITY;
         if (tid < E) {
             z = 0.f;
-            for (int g = 0; g < groups; g += 16)
 #pragma unroll
-                for (int i = 0; i < 16; ++i) z += zpart[((g + i) << lp) + tid];
+            for (int g = 0; g < groups; ++g) z += zpart[(g << LP) + tid];
         }
         float zmax = z;
 #pragma unroll
@@ -70,6 +68,15 @@ __device__ __forceinline__ float router_softmax(const float *hbar, float *zpart,
         prob = p / denom;
     }
     return prob;
+}
+
+template <typename T>
+__device__ __forceinline__ float router_softmax(const float *hbar, float *zpart, const T *__restrict__ R, int d,
+                                                int E, int tid)
+{
+    if (E <= 16) return router_softmax_p<T, 4>(hbar, zpart, R, d, E, tid);
+    if (E <= 32) return router_softmax_p<T, 5>(hbar, zpart, R, d, E, tid);
+    return router_softmax_p<T, 6>(hbar, zpart, R, d, E, tid);
 }
 
 // grid = S workgroups, block = 1024 threads, dynamic LDS =
@@ -130,29 +137,36 @@ __global__ __launch_bounds__(kRouteThreads) void route_kernel(const T *__restric
 #pragma unroll
                     for (int i = 0; i < VEC; ++i) acc[i] += v[u][i];
             }
-            for (; t < rows; t += row_groups) {
-                float v[VEC];
-                if constexpr (VECTOR) {
-                    Vec<T>::load(Xs + (size_t)t * d + c, v);
-                } else {
-                    v[0] = Vec<T>::one(Xs + (size_t)t * d + c);
+            if (t < rows) {  // fewer than eight rows left: one round as well, the last row repeated and not added
+                float v[8][VEC];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int r = t + u * row_groups < rows ? t + u * row_groups : rows - 1;
+                    if constexpr (VECTOR) {
+                        Vec<T>::load(Xs + (size_t)r * d + c, v[u]);
+                    } else {
+                        v[u][0] = Vec<T>::one(Xs + (size_t)r * d + c);
+                    }
                 }
 #pragma unroll
-                for (int i = 0; i < VEC; ++i) acc[i] += v[i];
+                for (int u = 0; u < 8; ++u)
+                    if (t + u * row_groups < rows) {
+#pragma unroll
+                        for (int i = 0; i < VEC; ++i) acc[i] += v[u][i];
+                    }
             }
         }
 #pragma unroll
         for (int i = 0; i < VEC; ++i) part[tid * VEC + i] = acc[i];
         __syncthreads();
-        if (ty == 0 && c < d) {
+        for (int q = tid; q < ct * VEC && c0 + q < d; q += kRouteThreads) {
+            float sum = 0.f;
+            for (int g = 0; g < row_groups; g += 4)
 #pragma unroll
-            for (int i = 0; i < VEC; ++i) {
-                float sum = 0.f;
-                for (int g = 0; g < row_groups; ++g) sum += part[(g * ct + tx) * VEC + i];
-                const float mean = sum * invT;
-                hbar[c + i] = mean;
-                if (hbar_out) hbar_out[(size_t)s * d + c + i] = mean;
-            }
+                for (int i = 0; i < 4; ++i) sum += part[(g + i) * ct * VEC + q];
+            const float mean = sum * invT;
+            hbar[c0 + q] = mean;
+            if (hbar_out) hbar_out[(size_t)s * d + c0 + q] = mean;
         }
         __syncthreads();
     }
