@@ -1,8 +1,8 @@
 // fp32 instantiation of the merged FFN (paper Eq. 1 / Eq. 2, SwiGLU experts)
 // and of its backward, for arbitrary shapes at fp32 accuracy (rel-L2 <= 1e-5).
 //
-// Every stage is a small dense contraction - the merge is w [S,E] x stack [E,n], the scatter
-// w^T [E,S] x slab [S,n], the inner products slab [S,n] x stack^T [n,E], the rest are the layer's token
+// Every stage is a small dense contraction - the merge is w [S,E] x stack [E,n] (with few experts or segments a
+// kernel of its own that streams the stack), the scatter w^T [E,S] x slab [S,n], the inner products slab [S,n] x stack^T [n,E], the rest are the layer's token
 // GEMMs - so one kernel on the fp32 matrix instruction (v_mfma_f32_32x32x2_f32, full fp32 products and
 // sums) runs them all, and independent ones share a launch: the shapes of this configuration are small and
 // a pass is bound by the number of dependent launches (B=2, L=512, T=128, d=64, d_ff=256, E=4: 27 launches
@@ -291,8 +291,8 @@ void launch(hipStream_t st, Group &g, const Elementwise &ew = Elementwise())
         p.blocks = (int)(p.split_waves ? small : big);
         blocks += p.blocks;
     }
-    // A grid dimension counts fewer than 2^32 threads, i.e. 2^24 workgroups, which the merge of one segment at
-    // d * d_ff = 3.6e8 passes: further launches take the rest.  (2^31 workgroups of 64 x 64 elements would not fit
+    // A grid dimension counts fewer than 2^32 threads, i.e. 2^24 workgroups, which the expert gradients of
+    // d * d_ff = 3.6e8 pass: further launches take the rest.  (2^31 workgroups of 64 x 64 elements would not fit
     // the memory.)
     for (long first = 0; first < blocks; first += kMaxGrid) {
         g.first = (int)first;
@@ -301,10 +301,87 @@ void launch(hipStream_t st, Group &g, const Elementwise &ew = Elementwise())
     }
 }
 
+struct MergeArgs {
+    const float *stack[3];
+    float *slab[3];
+};
+
+// Merge of up to SB segments (grid y: blocks of segments, z: matrices): a thread owns VEC consecutive elements, keeps
+// the sums of all SB segments and reads every expert once; the routing weights are uniform.  HBM-bound: one sequence, 4
+// experts of 1024 x 2816 take 26 us (6.8 TB/s), 16 experts 112.  The contraction kernel, a workgroup of one step per 64
+// columns, is bound by the rate at which workgroups start: 398 and 431.
+template <int SB, int VEC>
+__global__ __launch_bounds__(256) void merge_f32_kernel(const float *__restrict__ w, const MergeArgs m, int S, int E, long n)
+{
+    const long i = ((long)blockIdx.x * 256 + threadIdx.x) * VEC;
+    if (i >= n) return;
+    const int s0 = blockIdx.y * SB;
+    const float *src = m.stack[blockIdx.z] + i;
+    float acc[SB][VEC];
+#pragma unroll
+    for (int s = 0; s < SB; ++s)
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) acc[s][j] = 0.f;
+#pragma unroll 4
+    for (int e = 0; e < E; ++e) {
+        float v[VEC];
+        if constexpr (VEC == 4) {
+            const float4 f = *reinterpret_cast<const float4 *>(src + (size_t)e * n);
+            v[0] = f.x; v[1] = f.y; v[2] = f.z; v[3] = f.w;
+        } else {
+            v[0] = src[(size_t)e * n];
+        }
+#pragma unroll
+        for (int s = 0; s < SB; ++s) {
+            const float ws = w[(size_t)(s0 + s < S ? s0 + s : S - 1) * E + e];
+#pragma unroll
+            for (int j = 0; j < VEC; ++j) acc[s][j] = fmaf(ws, v[j], acc[s][j]);
+        }
+    }
+    float *dst = m.slab[blockIdx.z] + (size_t)s0 * n + i;
+#pragma unroll
+    for (int s = 0; s < SB; ++s) {
+        if (s0 + s >= S) continue;
+        if constexpr (VEC == 4)
+            *reinterpret_cast<float4 *>(dst + (size_t)s * n) = make_float4(acc[s][0], acc[s][1], acc[s][2], acc[s][3]);
+        else
+            dst[(size_t)s * n] = acc[s][0];
+    }
+}
+
+template <int SB>
+void launch_merge(hipStream_t st, const float *w, int E, int S, long n, const MergeArgs &m, int count)
+{
+    bool vec = n % 4 == 0;
+    for (int x = 0; x < count; ++x) vec = vec && aligned(m.stack[x], 0, 0) && aligned(m.slab[x], 0, 0);
+    const long per = vec ? 4 : 1;
+    const dim3 grid((unsigned)((n + 256 * per - 1) / (256 * per)), (S + SB - 1) / SB, count);
+    if (vec)
+        hipLaunchKernelGGL((merge_f32_kernel<SB, 4>), grid, dim3(256), 0, st, w, m, S, E, n);
+    else
+        hipLaunchKernelGGL((merge_f32_kernel<SB, 1>), grid, dim3(256), 0, st, w, m, S, E, n);
+}
+
 // slab_x[s][i] = sum_e w[s][e] stack_x[e][i]  for the given matrices
 void merge(hipStream_t st, const float *w, int E, int Sc, long n, const float *const *stacks, float *const *slabs,
            int count)
 {
+    // Many experts for many segments are a contraction: blocks of 16 segments would read the stack again and again (us,
+    // contraction / vectors: 64 segments, 40 experts, 1024 x 2816 1125 / 1457; 32 of 64 x 256 11.8 / 14.8).  Up to 16
+    // experts or 8 segments the vectors win at every size tried (128 segments, 16 experts, 256 x 640 85 / 59; 8 and 40
+    // 41 / 15), but for 10 % at 16 and 32 segments of the smallest matrices (50 x 130: 6.3 / 7.0).
+    if (E <= 16 || Sc <= 8) {
+        MergeArgs m = {};
+        for (int x = 0; x < count; ++x) {
+            m.stack[x] = stacks[x];
+            m.slab[x] = slabs[x];
+        }
+        if (Sc == 1) return launch_merge<1>(st, w, E, Sc, n, m, count);
+        if (Sc == 2) return launch_merge<2>(st, w, E, Sc, n, m, count);
+        if (Sc <= 4) return launch_merge<4>(st, w, E, Sc, n, m, count);
+        if (Sc <= 8) return launch_merge<8>(st, w, E, Sc, n, m, count);
+        return launch_merge<16>(st, w, E, Sc, n, m, count);
+    }
     Group g = {};
     g.n = count;
     for (int x = 0; x < count; ++x)

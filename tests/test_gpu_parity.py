@@ -151,17 +151,51 @@ def test_route_forms(dtype, d, T, E):
     check("w, prompt", host(w_p), orc.route(t["X"], t["R"], cfg.L)["w"], TOL["f32"])
 
 
-def test_fp32_merge_of_very_large_matrices():
-    """More workgroups than one launch counts.  One expert: its routing weight is 1, the merge a copy."""
+# fp32 merges: one to 16 segments per thread with a short last block, rows of matrices that are not 16-byte aligned, and
+# the contraction for many experts and segments.  Sums of at most 40 products in fp32.
+@pytest.mark.parametrize("B,E", [(1, 3), (2, 40), (3, 5), (8, 17), (9, 16), (9, 17), (17, 4), (33, 16), (40, 20)])
+@pytest.mark.parametrize("d,d_ff", [(7, 9), (24, 10), (40, 36)])
+def test_fp32_merge_forms(B, E, d, d_ff):
+    gen = torch.Generator(device="cuda").manual_seed(B + E)
+    X, R = torch.randn((B, 3, d), generator=gen, device="cuda"), torch.randn((d, E), generator=gen, device="cuda")
+    W = [torch.randn(s, generator=gen, device="cuda") for s in ((E, d, d_ff), (E, d, d_ff), (E, d_ff, d))]
+    w, Wbar = lb.lory_prompt_merge(X, R, *W, Wbar=torch.full((3, B, d * d_ff), float("nan"), device="cuda"))
+    for i in range(3):
+        ref = host(w) @ host(W[i]).reshape(E, -1)
+        assert np.abs(host(Wbar[i]) - ref).max() <= 40 * 2.0 ** -24 * np.abs(host(W[i])).max(), i
+
+
+def test_fp32_very_large_matrices():
+    """Matrices whose workgroups exceed what one launch counts: the merge of one expert is a copy, and the expert
+    gradients of one token are outer products."""
     d, d_ff = 16384, 21888
-    X, R = torch.ones((1, 4, d), device="cuda"), torch.ones((d, 1), device="cuda")
-    W = [torch.empty(s, device="cuda").uniform_() for s in ((1, d, d_ff), (1, d, d_ff), (1, d_ff, d))]
-    Wbar = torch.full((3, 1, d * d_ff), float("nan"), device="cuda")
-    print(f"[gpu] prompt merge d={d} d_ff={d_ff}", flush=True)
-    w, _ = lb.lory_prompt_merge(X, R, *W, Wbar=Wbar)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    X, dY = (torch.randn((1, 1, d), generator=gen, device="cuda") for _ in range(2))
+    W = [torch.empty(s, device="cuda").uniform_(-0.01, 0.01, generator=gen) for s in ((1, d, d_ff), (1, d, d_ff), (1, d_ff, d))]
+    print(f"[gpu] d={d} d_ff={d_ff}", flush=True)
+    w, Wbar = lb.lory_prompt_merge(X, torch.ones((d, 1), device="cuda"), *W,
+                                   Wbar=torch.full((3, 1, d * d_ff), float("nan"), device="cuda"))
     assert w.item() == 1.0
     for i in range(3):
         assert torch.equal(Wbar[i].view(-1), W[i].view(-1)), i
+    del Wbar
+    grads = [torch.full(t.shape, float("nan"), device="cuda") for t in W]
+    dX = lb.lory_merged_ffn_bwd(X, w, *W, dY, 1, dWg=grads[0], dWu=grads[1], dWd=grads[2], grad_dtype=torch.float32)[0]
+    x, dy = X[0, 0].double(), dY[0, 0].double()
+
+    def mv(m, v):   # m @ v and m.T @ v without a copy of m in 64 bits
+        return (torch.mv(m[0], v.float()) if m.shape[2] == v.numel() else torch.mv(m[0].t(), v.float())).double()
+
+    g, u, da = mv(W[0], x), mv(W[1], x), mv(W[2], dy)
+    sg = torch.sigmoid(g)
+    dg, du, a = da * u * sg * (1 + g * (1 - sg)), da * g * sg, g * sg * u
+    tol = 1e-4   # sums of 16384 .. 21888 products in fp32 on both sides
+    for got, (col, row) in zip(grads, ((x, dg), (x, du), (a, dy))):
+        err = sum(float((got[0, i:i + 1024].double() - col[i:i + 1024, None] * row).pow(2).sum())
+                  for i in range(0, got.shape[1], 1024)) ** 0.5
+        assert err <= tol * float(col.norm() * row.norm())
+    ref = mv(W[0], dg) + mv(W[1], du)
+    assert float((dX[0, 0].double() - ref).norm()) <= tol * float(ref.norm())
 
 
 def test_fp32_given_routing_weights_onehot_and_accumulate():
