@@ -128,6 +128,7 @@ struct EpiStore {
     }
 };
 
+// The same for two operand sets: C0 from the first, C1 from the second.
 struct EpiStore2 {
     static constexpr int NOUT = 2;
     static constexpr bool SPLIT = false;
@@ -141,6 +142,7 @@ struct EpiStore2 {
     {
         return o == 0 ? pack4(v[0][0], v[0][1], v[0][2], v[0][3]) : pack4(v[1][0], v[1][1], v[1][2], v[1][3]);
     }
+    __device__ __forceinline__ long row_bytes() const { return 2L * ldc; }
     __device__ __forceinline__ uint16_t *ptr(int o, int b, int m, int n) const
     {
         return (o == 0 ? C0 : C1) + (size_t)b * c_batch + (size_t)m * ldc + n;
