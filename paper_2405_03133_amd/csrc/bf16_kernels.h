@@ -16,22 +16,12 @@ using gemm::float_to_bf16_bits;
 
 using gemm::u32x2;
 
-struct NoIn {};
-
 __device__ __forceinline__ u32x2 pack4(float a, float b, float c, float d)
 {
     u32x2 r;
     r.x = gemm::cvt_pk_bf16(a, b);
     r.y = gemm::cvt_pk_bf16(c, d);
     return r;
-}
-
-__device__ __forceinline__ void unpack4(u32x2 p, float (&f)[4])
-{
-    f[0] = __uint_as_float(p.x << 16);
-    f[1] = __uint_as_float(p.x & 0xffff0000u);
-    f[2] = __uint_as_float(p.y << 16);
-    f[3] = __uint_as_float(p.y & 0xffff0000u);
 }
 
 // Gate/up projections of one column block of d_ff: planes A = silu(G) * U, G, U.
@@ -41,12 +31,10 @@ template <bool SAVE, bool ACT>
 struct EpiGUT {
     static constexpr int NOUT = 3;
     static constexpr bool SPLIT = false;
-    typedef NoIn In;
     uint16_t *G, *U, *Act;  // [tokens, d_ff]
     int T, dff, n_off;
-    __device__ __forceinline__ In load(int, int, int) const { return In(); }
     __device__ __forceinline__ bool enabled(int o) const { return o == 0 ? ACT : SAVE; }
-    __device__ __forceinline__ u32x2 pack(int o, int, int, int, const In &, const float (&v)[2][4]) const
+    __device__ __forceinline__ u32x2 pack(int o, const float (&v)[2][4]) const
     {
         if (o == 1) return pack4(v[0][0], v[0][1], v[0][2], v[0][3]);
         if (o == 2) return pack4(v[1][0], v[1][1], v[1][2], v[1][3]);
@@ -89,11 +77,10 @@ __device__ __forceinline__ void act_terms(float g, float u, float &hi, float &lo
 struct EpiAct2 {
     static constexpr int NOUT = 2;
     static constexpr bool SPLIT = false;
-    typedef NoIn In;
     uint16_t *Act;
     int T, dff;
     __device__ __forceinline__ bool enabled(int) const { return true; }
-    __device__ __forceinline__ u32x2 pack(int o, int, int, int, const In &, const float (&v)[2][4]) const
+    __device__ __forceinline__ u32x2 pack(int o, const float (&v)[2][4]) const
     {
         float t[2][4];
 #pragma unroll
@@ -111,13 +98,11 @@ struct EpiAct2 {
 struct EpiStore {
     static constexpr int NOUT = 1;
     static constexpr bool SPLIT = false;
-    typedef NoIn In;
     uint16_t *C;
     long c_batch;
     int ldc;
-    __device__ __forceinline__ In load(int, int, int) const { return In(); }
     __device__ __forceinline__ bool enabled(int) const { return true; }
-    __device__ __forceinline__ u32x2 pack(int, int, int, int, const In &, const float (&v)[1][4]) const
+    __device__ __forceinline__ u32x2 pack(int, const float (&v)[1][4]) const
     {
         return pack4(v[0][0], v[0][1], v[0][2], v[0][3]);
     }
@@ -132,13 +117,11 @@ struct EpiStore {
 struct EpiStore2 {
     static constexpr int NOUT = 2;
     static constexpr bool SPLIT = false;
-    typedef NoIn In;
     uint16_t *C0, *C1;
     long c_batch;
     int ldc;
-    __device__ __forceinline__ In load(int, int, int) const { return In(); }
     __device__ __forceinline__ bool enabled(int) const { return true; }
-    __device__ __forceinline__ u32x2 pack(int o, int, int, int, const In &, const float (&v)[2][4]) const
+    __device__ __forceinline__ u32x2 pack(int o, const float (&v)[2][4]) const
     {
         return o == 0 ? pack4(v[0][0], v[0][1], v[0][2], v[0][3]) : pack4(v[1][0], v[1][1], v[1][2], v[1][3]);
     }
@@ -154,13 +137,12 @@ template <int NSET>
 struct EpiPart {
     static constexpr int NOUT = 1;
     static constexpr bool SPLIT = true;
-    typedef NoIn In;
     float *P;
     int ksplit, batches, M, N;   // batches: items before the split
     __device__ __forceinline__ bool enabled(int) const { return false; }
     __device__ __forceinline__ long row_bytes() const { return 0; }
     __device__ __forceinline__ uint16_t *ptr(int, int, int, int) const { return nullptr; }
-    __device__ __forceinline__ u32x2 pack(int, int, int, int, const In &, const float (&)[NSET][4]) const { return u32x2{0, 0}; }
+    __device__ __forceinline__ u32x2 pack(int, const float (&)[NSET][4]) const { return u32x2{0, 0}; }
     __device__ __forceinline__ float *part(int set, int bs, int m, int n) const
     {
         const int sl = bs % ksplit, b = bs / ksplit;
@@ -168,8 +150,8 @@ struct EpiPart {
     }
 };
 
-// Every wrapper returns a hipError_t.  M, N, K must be multiples of the tile
-// sizes the wrapper picks (64 granularity is always accepted).
+// Every wrapper returns a hipError_t.  Any M (a multiple of 8 where A is stored K-slow), N a multiple of 8,
+// K a multiple of 32 and at least 64.
 hipError_t launch_merge(hipStream_t st, const ms::MergeParams &p);
 hipError_t launch_scatter(hipStream_t st, const ms::ScatterParams &p, int grid);
 hipError_t launch_dw_reduce(hipStream_t st, const float *partials, int slots, int rows, int cols,

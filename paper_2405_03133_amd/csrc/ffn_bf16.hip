@@ -344,8 +344,8 @@ namespace {
 
 // Tile height and K slices of one projection of the dense FFN.
 struct DenseSplit {
-    int rows;    // 0: not split, launch_rows picks the tile
-    int ks;
+    int rows;
+    int ks;      // 0: not split, launch_rows picks the tile (of `rows`)
 };
 
 // Estimated time, us, of a projection whose rows fit one tile (decode steps, short blocks): it streams the weights, so
@@ -381,7 +381,7 @@ DenseSplit dense_split(const Dims &m, int M, int N, int K, int nset, int terms, 
     p.M = M; p.N = N; p.batches = m.B;
     const int whole = gemm2::tile_rows(p, bns);
     const long tiles1 = tiles_of(M, whole);
-    DenseSplit best = {0, 1};
+    DenseSplit best = {whole, 0};
     double best_t = (M <= 128 && whole <= 128) ? stream_us(whole, tiles1, terms * steps, cus)
                                                : rounds_us(whole, tiles1, terms * steps);
     for (int rows = 64; rows <= 128; rows += rows) {
@@ -411,8 +411,8 @@ struct DensePlan {
     size_t parts(const Dims &m, int r) const   // floats that a block of r rows uses
     {
         const DenseSplit g = gate_up(m, r), w = down(m, r);
-        const size_t a = g.rows ? (size_t)g.ks * 2 * m.B * r * m.dff : 0;
-        const size_t b = w.rows ? (size_t)w.ks * terms * m.B * r * m.d : 0;
+        const size_t a = g.ks ? (size_t)g.ks * 2 * m.B * r * m.dff : 0;
+        const size_t b = w.ks ? (size_t)w.ks * terms * m.B * r * m.d : 0;
         return a > b ? a : b;
     }
 };
@@ -451,6 +451,13 @@ size_t bf16_dense_workspace_bytes(const Dims &m, const DenseScratch &scratch)
     return p.act + align_up(parts * sizeof(float), 256);
 }
 
+DenseForm bf16_dense_form(const Dims &m, const DenseScratch &scratch)
+{
+    const DensePlan p = dense_plan(m, scratch);
+    const DenseSplit g = p.gate_up(m, p.rows), d = p.down(m, p.rows);
+    return {p.rows, p.terms, g.rows, g.ks, d.rows, d.ks};
+}
+
 // Dense SwiGLU FFN of every sequence with its own materialised merged parameters
 // (m.T == m.L: one parameter set per sequence, any number of rows).
 int bf16_dense_ffn_fwd(const Dims &m, const void *Xv, const void *Wbarv, void *Yv, void *ws, const DenseScratch &scratch,
@@ -475,7 +482,7 @@ int bf16_dense_ffn_fwd(const Dims &m, const void *Xv, const void *Wbarv, void *Y
             p.B[1] = Wbar + (size_t)m.B * m.D; p.b_batch[1] = m.D; p.ldb[1] = m.dff;
             p.M = rows; p.N = m.dff; p.K = m.d; p.batches = m.B;
             prof::Range r(st, prof::kGemmGU, gemm_flops(p, 2, 1), 2.0 * m.B * ((double)RD + 2.0 * m.D + (double)RF));
-            if (sp.rows) {
+            if (sp.ks) {
                 p.ksplit = sp.ks;
                 p.batches = m.B * sp.ks;
                 const k::EpiPart<2> epi = {parts, sp.ks, m.B, rows, m.dff};
@@ -497,7 +504,7 @@ int bf16_dense_ffn_fwd(const Dims &m, const void *Xv, const void *Wbarv, void *Y
             p.M = rows; p.N = m.d; p.K = m.dff; p.batches = m.B;
             prof::Range r(st, prof::kGemmDown, gemm_flops(p, 1, 1), 2.0 * m.B * ((double)RF + (double)m.D + (double)RD));
             const EpiStore epi = {Y, TD, m.d};
-            if (sp.rows) {
+            if (sp.ks) {
                 p.M = nt * rows;
                 p.ksplit = sp.ks;
                 p.batches = m.B * sp.ks;

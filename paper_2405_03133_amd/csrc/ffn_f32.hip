@@ -285,7 +285,7 @@ void launch(hipStream_t st, Group &g, const Elementwise &ew = Elementwise())
         Problem &p = g.p[i];
         const long big = ((p.N + 63) / 64) * ((p.M + 63) / 64) * p.ksplit * p.batches;
         const long small = ((p.N + 31) / 32) * ((p.M + 31) / 32) * p.ksplit * p.batches;
-        // Fewer tiles than CUs: split the steps of a block over the wavefronts instead (down projection of 8 segments
+        // Fewer than two tiles per CU: split the steps of a block over the wavefronts instead (down projection of 8 segments
         // of 128 tokens, d_ff = 256: 18.6 -> 6.6 us); a contraction of one step has nothing to split.
         p.split_waves = big < 512 && p.K > TK;
         p.blocks = (int)(p.split_waves ? small : big);
@@ -492,7 +492,7 @@ int f32_ffn_bwd(const Dims &m, const float *X, const float *w, const float *Wg, 
             launch<kStore>(st, g);
         }
         // dX = dG Wg_bar^T + dU Wu_bar^T; dWx[e] (+)= sum_s w[s,e] dWx_bar(s); partial sums of
-        // <Wx[e], dWx_bar(s)> over slices of the matrix, at least 8 K steps each
+        // <Wx[e], dWx_bar(s)> over slices of the matrix, 8 K steps or a little less each
         long slices = (m.D + 8 * TK - 1) / (8 * TK);
         const long room = (long)(p.act / ((size_t)3 * sc * m.E));
         if (slices > room) slices = room;

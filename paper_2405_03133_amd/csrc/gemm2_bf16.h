@@ -39,8 +39,8 @@ using gemm::u32x4;
 constexpr int BK = 32;
 
 // A tile shape: WMV x WNV wavefronts, each with MI x NB blocks of 32 x 32 outputs (NB counted through the
-// operand sets), the stages of its ring and how many workgroups share a CU.
-template <int WMV_, int WNV_, int MI_, int NB_, int STAGES, int WGS>
+// operand sets), and the stages of its ring.  One workgroup per CU.
+template <int WMV_, int WNV_, int MI_, int NB_, int STAGES>
 struct Tile {
     static constexpr int WMV = WMV_, WNV = WNV_, MI = MI_, NB = NB_;
     static constexpr int NW = WMV * WNV;
@@ -48,8 +48,7 @@ struct Tile {
     static constexpr int BM = WMV * MI * 32;        // rows
     static constexpr int BN = WNV * NB * 32;        // columns over all operand sets
     static constexpr int stages = STAGES;
-    static constexpr int wgs = WGS;
-    static constexpr int waves_per_simd = NW * WGS / 4;
+    static constexpr int waves_per_simd = NW / 4;
     static constexpr int a_bytes = BM * 64;
     static constexpr int b_bytes = BN * 64;
     static constexpr int stage = a_bytes + b_bytes;
@@ -58,7 +57,7 @@ struct Tile {
     static constexpr int stage_out = 32 * JG * 64;  // bytes per wave
     static constexpr int total = ring + NW * stage_out;
     static_assert(a_bytes % (NW * 1024) == 0 && b_bytes % (NW * 1024) == 0, "every wave fetches whole kilobytes");
-    static_assert(WGS * total <= 160 * 1024, "LDS of a CU");
+    static_assert(total <= 160 * 1024, "LDS of a CU");
 };
 
 __device__ __forceinline__ int fkc(int row)
@@ -137,9 +136,9 @@ __device__ __forceinline__ void ring_barrier()
     asm volatile("" ::: "memory");
 }
 
-// Persistent kernel: the grid is one workgroup per CU (two where the tile's LDS allows); every workgroup walks its own list of
-// tiles, and the K steps of consecutive tiles form one stream through the ring, so the first operands of
-// the next tile are already in flight while the current tile is multiplied and written out.
+// Persistent kernel: the grid is one workgroup per CU; every workgroup walks its own list of tiles, and the K
+// steps of consecutive tiles form one stream through the ring, so the first operands of the next tile are already
+// in flight while the current tile is multiplied and written out.
 template <int NSET, int NSRC, bool A_MC, bool B_NC, class TL, class Epi>
 __global__ __launch_bounds__(TL::threads, TL::waves_per_simd) void gemm2_kernel(const Params p, const Epi epi)
 {
@@ -524,13 +523,12 @@ __global__ __launch_bounds__(TL::threads, TL::waves_per_simd) void gemm2_kernel(
 #pragma unroll
                         for (int rq = 0; rq < 4; ++rq) {
                             const int j = jg + jj;
-                            const int nl = j * 32 + 8 * rq + 4 * h;  // column inside the wave's WN columns
                             float v[NSET][4];
 #pragma unroll
                             for (int s = 0; s < NSET; ++s)
 #pragma unroll
                                 for (int e = 0; e < 4; ++e) v[s][e] = acc[s][i][j][rq * 4 + e];
-                            const u32x2 pk = epi.pack(o, batch, mb + r, n0 + wn0 + nl, typename Epi::In(), v);
+                            const u32x2 pk = epi.pack(o, v);
                             const int c = jj * 4 + rq;
                             *reinterpret_cast<u32x2 *>(stg + r * (CP * 16) + ((c ^ (r & (CP - 1))) << 4) + h * 8) = pk;
                             __builtin_amdgcn_sched_barrier(0);  // one quad at a time: keeps register use flat
@@ -616,9 +614,8 @@ inline hipError_t launch(const Params &p, const Epi &epi, hipStream_t st)
     }
     constexpr int BNS = TL::BN / NSET;
     const long ntiles = (long)p.batches * ((p.M + TL::BM - 1) / TL::BM) * ((p.N + BNS - 1) / BNS);
-    const long slots = (long)cu_count() * TL::wgs;
     long blocks = (ntiles + 7) / 8 * 8;
-    if (blocks > slots) blocks = slots;  // every workgroup walks several tiles
+    if (blocks > cu_count()) blocks = cu_count();  // every workgroup walks several tiles
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(TL::threads), TL::total, st, p, epi);
     return hipGetLastError();
 }
@@ -631,16 +628,16 @@ inline hipError_t launch(const Params &p, const Epi &epi, hipStream_t st)
 // its power limit.  192 rows need four waves (12 KB of A do not divide by eight); 128 rows ran faster
 // with four waves and three stages than with eight and four (A Wd_bar of 32 segments at d = 1024: 45
 // against 53 us).
-using T256 = Tile<2, 4, 4, 2, 4, 1>;
+using T256 = Tile<2, 4, 4, 2, 4>;
 // Two operand sets: a wave of T256 would own 32 columns of each and store 64 bytes of a row, half a line; 64 x 64 per
 // wave and set stores whole lines.  Gate/up with G and U saved, us: 64 segments of 256 tokens at d = 2048, d_ff = 5632
 // 852 -> 824; 128 segments at d = 1024, d_ff = 2816 491 -> 467; 8 of 1024 at d = 2048 425 -> 408.  The activation alone
 // (half the stores): 803 -> 799, 443 -> 438, 400 -> 397.
-using T256x2 = Tile<4, 2, 2, 4, 4, 1>;
-using T192 = Tile<2, 2, 3, 4, 4, 1>;
-using T128 = Tile<2, 2, 2, 4, 3, 1>;
-using T64 = Tile<2, 2, 1, 4, 4, 1>;
-using W128 = Tile<2, 4, 2, 2, 4, 1>;   // 128 rows of a weight gradient
+using T256x2 = Tile<4, 2, 2, 4, 4>;
+using T192 = Tile<2, 2, 3, 4, 4>;
+using T128 = Tile<2, 2, 2, 4, 3>;
+using T64 = Tile<2, 2, 1, 4, 4>;
+using W128 = Tile<2, 4, 2, 2, 4>;   // 128 rows of a weight gradient
 
 // Rounds of tiles over the CUs, in units of the time of one round.
 inline double rounds_of(const Params &p, int bm, int bns)

@@ -326,6 +326,8 @@ int dense_ffn_fwd_static(const Dims &m, const void *X, const void *Wbar, void *Y
 
 size_t dense_min_workspace_bytes(const Dims &m) { return base_bytes(m); }
 
+DenseForm dense_form(const Dims &m) { return bf16_dense_form(m, gemm_scratch(m)); }
+
 size_t dense_workspace_bytes(const Dims &m)
 {
     const size_t base = base_bytes(m);

@@ -102,6 +102,13 @@ struct DenseScratch {
     bool fixed;
 };
 size_t bf16_dense_workspace_bytes(const Dims &m, const DenseScratch &scratch);
+// How a call runs with the workspace that is reported for it: rows of a block, bf16 terms of the activation, and for
+// the two projections the tile height and the K slices (0: not split).
+struct DenseForm {
+    int rows, terms, gu_tile, gu_slices, down_tile, down_slices;
+};
+DenseForm bf16_dense_form(const Dims &m, const DenseScratch &scratch);
+DenseForm dense_form(const Dims &m);
 int bf16_dense_ffn_fwd(const Dims &m, const void *X, const void *Wbar, void *Y, void *ws, const DenseScratch &scratch,
                        hipStream_t st);
 int set_slab_budget(size_t bytes);
