@@ -1,5 +1,5 @@
 // Walks the host-side layer of liblory (argument validation, shape checks, workspace and
-// merged-save sizing with its block planning, tuning knobs, the profiler's bookkeeping) for a
+// merged-save sizing with its block planning, the plans of the dense FFN, tuning knobs, the profiler's bookkeeping) for a
 // build with -fsanitize=address,undefined on the host pass.  No call below reaches a kernel
 // launch: every one returns from validation, or only computes sizes.
 #include <stdint.h>
@@ -7,6 +7,7 @@
 #include <string.h>
 
 #include "lory.h"
+#include "lory_internal.h"
 
 static int failures = 0;
 #define EXPECT(cond)                                                  \
@@ -104,6 +105,24 @@ int main()
     EXPECT(lory_dense_ffn_fwd_static(&inf, fake, NULL, fake, NULL) == LORY_ERR_NULL);
     lory_shape big = shape(2, 8, 8, 2048, 5632, 1, LORY_BF16);
     EXPECT(lory_dense_ffn_fwd_static(&big, fake, fake, fake, NULL) == LORY_ERR_WORKSPACE);
+
+    // how the dense blocks of the GPU tests run (256 CUs): rows of a block, terms of the activation, tile height and
+    // K slices of gate/up and down; every form that the dispatch has is among them
+    static const struct { int B, L, d, dff; lory::DenseForm f; } forms[] = {
+        {1, 1, 320, 832, {1, 2, 64, 0, 64, 6}},         {5, 7, 320, 832, {7, 2, 64, 0, 64, 6}},
+        {1, 65, 1664, 2816, {65, 2, 128, 9, 64, 8}},    {2, 100, 512, 1408, {100, 2, 64, 0, 64, 9}},
+        {3, 200, 64, 64, {200, 2, 64, 0, 64, 0}},       {130, 100, 64, 64, {100, 2, 128, 0, 128, 0}},
+        {150, 129, 64, 128, {129, 2, 192, 0, 192, 0}},  {130, 250, 64, 64, {250, 2, 256, 0, 256, 0}},
+        {40, 63, 192, 1728, {63, 2, 64, 0, 128, 5}},    {16, 130, 320, 1408, {130, 2, 192, 0, 128, 2}},
+        {2, 1, 1088, 2880, {1, 2, 64, 5, 64, 15}},      {40, 128, 192, 1728, {128, 1, 128, 0, 128, 5}},
+        {1, 128, 320, 832, {128, 1, 64, 0, 64, 6}},     {40, 65, 192, 1728, {65, 2, 128, 0, 64, 2}},
+        {1, 50000, 64, 192, {16704, 2, 192, 0, 128, 0}}, {4, 2001, 256, 704, {1024, 2, 128, 0, 64, 0}},
+    };
+    for (size_t i = 0; i < sizeof(forms) / sizeof(forms[0]); ++i) {
+        const lory_shape s = shape(forms[i].B, forms[i].L, forms[i].L, forms[i].d, forms[i].dff, 1, LORY_BF16);
+        const lory::DenseForm f = lory::dense_form(lory::make_dims(s));
+        EXPECT(memcmp(&f, &forms[i].f, sizeof(f)) == 0);
+    }
 
     // profiler bookkeeping without launches
     lory_kernel_stat st[8];

@@ -296,6 +296,18 @@ def test_bf16_ring_gemm_edge_tiles(cfg):
     compare(cfg, got, oracle_layer(cfg, t, got["w_used"]), ALL, TOL["bf16"])
 
 
+@pytest.mark.parametrize("cfg", RING_EDGE_CASES, ids=lambda c: c.name)
+def test_bf16_ring_gemm_edge_tiles_without_saved_planes(cfg):
+    """The gate/up instance that writes the activation alone."""
+    t = make_inputs(cfg, structured=True, with_dy=False)
+    print(f"[gpu] {cfg}", flush=True)
+    w = orc.route(t["X"], t["R"], cfg.T)["w"].astype(np.float32)
+    Y = lb.lory_merged_ffn_fwd(to_dev(t["X"], cfg), torch.from_numpy(w).cuda(), *(to_dev(t[k], cfg) for k in ("Wg", "Wu", "Wd")),
+                               cfg.T)
+    ref = orc.ffn_fwd(t["X"], w.astype(np.float64), t["Wg"], t["Wu"], t["Wd"], cfg.T)["Y"]
+    check(f"{cfg.name} Y", host(Y), ref, TOL["bf16"])
+
+
 def test_bf16_recompute_bf16_grads_and_accumulate(default_budget):
     cfg = BF16_CASES[0][0]
     lb.lory_set_slab_budget(1 << 20)
@@ -587,7 +599,8 @@ def test_prompt_only_routing_inference(cfg, Lp, steps):
 
 
 # One row, the edges of the 64- and 128-row tiles, K slices of different lengths (d / 32 and d_ff / 32 not
-# multiples of the slice count), the smallest widths, and enough sequences that nothing is split.
+# multiples of the slice count), and the smallest widths.  How each case runs (tile heights, K slices) is pinned by
+# tests/host_sanitize/abi_driver.cpp.
 @pytest.mark.parametrize("B,d,d_ff", [(1, 320, 832), (3, 64, 64), (2, 1088, 2880), (40, 192, 1728)])
 @pytest.mark.parametrize("n_tok", [1, 63, 65, 128, 200])
 def test_dense_block_split_contractions(B, d, d_ff, n_tok):
@@ -604,10 +617,11 @@ def test_dense_block_split_contractions(B, d, d_ff, n_tok):
 # Token counts other than multiples of 64 (decode steps, ragged blocks) keep the activation in fp32 precision into the
 # down projection: what separates the output from the exact one is its own rounding to bf16.  The bound is the error of
 # the rounded oracle (1.7e-3) with 3 % for rows whose fp32 sums round the other way; an activation rounded to bf16 is
-# 1.4 times as far off.  The shapes split both, one or none of the projections, over tiles of every height.
+# 1.4 times as far off.  The shapes split both, one or none of the projections, over tiles of every height (pinned by
+# tests/host_sanitize/abi_driver.cpp).
 @pytest.mark.parametrize("B,n_tok,d,d_ff", [
     (1, 1, 320, 832), (5, 7, 320, 832), (1, 65, 1664, 2816), (2, 100, 512, 1408), (3, 200, 64, 64),
-    (130, 100, 64, 64), (150, 129, 64, 128), (130, 250, 64, 64),
+    (130, 100, 64, 64), (150, 129, 64, 128), (130, 250, 64, 64), (40, 63, 192, 1728), (16, 130, 320, 1408),
 ])
 def test_dense_block_rounds_only_its_output(B, n_tok, d, d_ff):
     cfg = LoryConfig("dense_exact", B=B, L=n_tok, T=n_tok, d=d, d_ff=d_ff, E=B, dtype="bf16", seed=62)
