@@ -348,31 +348,31 @@ struct DenseSplit {
     int ks;      // 0: not split, launch_rows picks the tile (of `rows`)
 };
 
-// Estimated time, us, of a projection whose rows fit one tile (decode steps, short blocks): it streams the weights, so
+// Estimated time, us, of a projection of up to 128 rows (decode steps, short blocks): it streams the weights, so
 // a round of tiles over the CUs takes its K steps at the latency of the ring, or at the rate the chip reads memory
 // when enough CUs take part (0.7 us for 16 KB on each of 256: 6 TB/s), and a nearly empty last round costs its steps
-// all the same.  Fitted to 25 forms each of 41 projections (1 .. 16 sequences of 1 .. 128 tokens, d = 256 .. 2560): what
-// it picks is 0.4 us slower than the fastest form on average.  us per call, one round of tiles at most -> this: 12
-// sequences at d = 2560, d_ff = 6144 224 -> 207 (206 on the vector ALUs), 8 at d = 768, d_ff = 2048 24.7 -> 22.5, 2 x 100
-// tokens at d = 2048, d_ff = 5632 56.7 -> 48.8; 4 x 64 tokens there 65.6 -> 69.
+// all the same.  Fitted to 25 forms each of 41 projections (1 .. 16 sequences of 1 .. 128 tokens, d = 256 .. 2560) whose
+// weights are read from memory, as between the layers of a model: what it picks is 0.25 us slower than the fastest
+// form on average.
 double stream_us(int rows, long tiles, int steps, int cus)
 {
-    const double lat = rows == 64 ? 0.30 : 0.52, mem = (rows == 64 ? 0.70 : 0.66) / cus;
-    auto round = [&](long n) { return steps * (mem * n > lat ? mem * n : lat) + 0.8; };
-    return (rows == 64 ? 2.5 : 2.8) + (tiles / cus) * round(cus) + (tiles % cus ? round(tiles % cus) : 0.0);
+    const double lat = rows == 64 ? 0.52 : 0.64, mem = (rows == 64 ? 0.70 : 0.66) / cus;
+    auto round = [&](long n) { return steps * (mem * n > lat ? mem * n : lat) + 1.2; };
+    return (rows == 64 ? 2.5 : 4.0) + (tiles / cus) * round(cus) + (tiles % cus ? round(tiles % cus) : 0.0);
 }
 
 // M rows per sequence, N columns per operand set, nset operand sets, the row operand in `terms` bf16 terms (unsplit: one
 // source each; split: rows of their own, whose sums are added with those of the slices).  A few dozen rows against one
 // weight matrix per sequence leave CUs without a tile or the last round of tiles nearly empty, and the pass is bound by
 // how many CUs stream the weights, so the contraction is cut into slices; what they cost is a launch that adds their
-// fp32 partial sums (4.5 us with the gap before it) and those sums (written once, read once).  Blocks of more rows than
-// a tile are cut until the tiles fill the chip once (estimate: step_us, six steps for the fill of the ring and the
-// epilogue, partial sums at 4 TB/s).  max_floats bounds the partial sums.
+// fp32 partial sums (4.5 us with the gap before it) and those sums (written once, read once: 0.6 us a million where a
+// tile holds all rows, 2 beyond).  Blocks of more rows than a tile are cut until the tiles fill the chip once (beyond
+// 128 rows by step_us, with six steps for the fill of the ring and the epilogue).  max_floats bounds the partial sums.
+// us per call with weights from memory, one round of tiles at most and 3 us for the sums -> this: 12 sequences at
+// d = 2560, d_ff = 6144 224 -> 208 (207 on the vector ALUs), 6 at d = 2048, d_ff = 5632 100 -> 90.
 DenseSplit dense_split(const Dims &m, int M, int N, int K, int nset, int terms, size_t max_floats)
 {
     const int cus = gemm2::cu_count(), bns = 256 / nset, steps = K / gemm2::BK;
-    const bool few = terms * M <= 128;
     auto tiles_of = [&](int r, int rows) { return (long)m.B * ((r + rows - 1) / rows) * ((N + bns - 1) / bns); };
     auto rounds_us = [&](int rows, long tiles, int k) {
         return gemm2::step_us(rows) * ((double)((tiles + cus - 1) / cus) * k + 6);
@@ -386,11 +386,12 @@ DenseSplit dense_split(const Dims &m, int M, int N, int K, int nset, int terms, 
                                                : rounds_us(whole, tiles1, terms * steps);
     for (int rows = 64; rows <= 128; rows += rows) {
         const long tiles = tiles_of(terms * M, rows);
-        for (int ks = 1; ks <= steps / 4 && (few || tiles * ks <= cus); ++ks) {
+        const bool few = terms * M <= 128, one = terms * M <= rows;
+        for (int ks = 1; ks <= steps / 4 && (one || tiles * ks <= cus); ++ks) {
             const double parts = (double)ks * nset * terms * m.B * M * N;
             if (parts > (double)max_floats) break;
             const int k = (steps + ks - 1) / ks;
-            const double t = (few ? stream_us(rows, tiles * ks, k, cus) + parts * 1e-6 : rounds_us(rows, tiles, k) + parts * 2e-6) + 4.5;
+            const double t = (few ? stream_us(rows, tiles * ks, k, cus) : rounds_us(rows, tiles, k)) + parts * (one ? 6e-7 : 2e-6) + 4.5;
             if (t < best_t) {
                 best_t = t;
                 best = {rows, ks};

@@ -110,11 +110,11 @@ int main()
     // K slices of gate/up and down; every form that the dispatch has is among them
     static const struct { int B, L, d, dff; lory::DenseForm f; } forms[] = {
         {1, 1, 320, 832, {1, 2, 64, 0, 64, 6}},         {5, 7, 320, 832, {7, 2, 64, 0, 64, 6}},
-        {1, 65, 1664, 2816, {65, 2, 128, 9, 64, 8}},    {2, 100, 512, 1408, {100, 2, 64, 0, 64, 9}},
+        {1, 65, 1664, 2816, {65, 2, 128, 11, 64, 8}},    {2, 100, 512, 1408, {100, 2, 64, 0, 64, 9}},
         {3, 200, 64, 64, {200, 2, 64, 0, 64, 0}},       {130, 100, 64, 64, {100, 2, 128, 0, 128, 0}},
         {150, 129, 64, 128, {129, 2, 192, 0, 192, 0}},  {130, 250, 64, 64, {250, 2, 256, 0, 256, 0}},
-        {40, 63, 192, 1728, {63, 2, 64, 0, 128, 5}},    {16, 130, 320, 1408, {130, 2, 192, 0, 128, 2}},
-        {2, 1, 1088, 2880, {1, 2, 64, 5, 64, 15}},      {40, 128, 192, 1728, {128, 1, 128, 0, 128, 5}},
+        {40, 63, 192, 1728, {63, 2, 64, 0, 128, 6}},    {16, 130, 320, 1408, {130, 2, 192, 0, 128, 2}},
+        {2, 1, 1088, 2880, {1, 2, 64, 5, 64, 18}},      {40, 128, 192, 1728, {128, 1, 128, 0, 128, 6}},
         {1, 128, 320, 832, {128, 1, 64, 0, 64, 6}},     {40, 65, 192, 1728, {65, 2, 128, 0, 64, 2}},
         {1, 50000, 64, 192, {16704, 2, 192, 0, 128, 0}}, {4, 2001, 256, 704, {1024, 2, 128, 0, 64, 0}},
     };
