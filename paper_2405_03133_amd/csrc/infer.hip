@@ -4,7 +4,7 @@
 // FFN of a sequence is an ordinary dense FFN,
 //   Y_b = (silu(X_b Wg_bar_b) (.) X_b Wu_bar_b) Wd_bar_b .
 // bf16 runs on the ring GEMM for every number of tokens (bf16_dense_ffn_fwd: contractions split over K
-// where the tiles would leave the chip idle).  fp32 goes through the "skinny" kernels below, which are
+// where the tiles would leave the chip idle, rows in blocks where the scratch is small).  fp32 goes through the "skinny" kernels below, which are
 // HBM-bound: every weight is read once per pass of up to 8 tokens.
 //
 // Skinny pass, per matrix product out[t][n] = sum_k x[t][k] W[k][n], W row-major:
