@@ -51,7 +51,8 @@ typedef enum {
     LORY_ERR_SHAPE = 2,     /* a dimension is <= 0, L % T != 0, or a granularity rule is violated */
     LORY_ERR_DTYPE = 3,     /* unknown dtype value */
     LORY_ERR_ALIGN = 4,     /* a pointer is not 16-byte aligned */
-    LORY_ERR_WORKSPACE = 5, /* workspace_bytes is smaller than lory_workspace_bytes() reports */
+    LORY_ERR_WORKSPACE = 5, /* workspace_bytes is smaller than lory_workspace_bytes() reports (than the
+                               least a call takes, where its description names one) */
     LORY_ERR_DEVICE = 6     /* a HIP call or kernel launch failed */
 } lory_status;
 
