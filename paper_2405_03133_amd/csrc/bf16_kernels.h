@@ -9,6 +9,25 @@
 #include "fused_bwd_bf16.h"
 
 namespace lory {
+namespace stream {
+
+// One projection of the streaming dense FFN (dense_stream_bf16.h).
+struct Params {
+    int M, K, N;           // rows per sequence (at most 16); K a multiple of 32, N of 8
+    int ks;                // K slices of the contraction
+    const uint16_t *W[2];  // [batches][K][N]: gate and up, or down
+    long w_batch;
+    const uint16_t *x;     // gate/up: token rows x + b * x_batch + m * K
+    long x_batch;
+    const float *gu;       // down: gate/up sums [gu_ks][batches][2][M][K]
+    int gu_ks;
+    float *part;           // sums [ks][batches][matrices][M][N] (gate/up; down where ks > 1)
+    uint16_t *Y;           // down where ks == 1: Y + b * y_batch + m * N
+    long y_batch;
+};
+
+}  // namespace stream
+
 namespace k {
 
 using gemm::bf16_bits_to_float;
@@ -182,6 +201,15 @@ hipError_t launch_down_split(hipStream_t st, const gemm::Params &p, const EpiPar
 hipError_t launch_sum_act(hipStream_t st, const float *part, int ksplit, long batches, long mn, int terms, uint16_t *Act);
 hipError_t launch_sum_store(hipStream_t st, const float *part, int ksplit, long batches, long mn, int terms, uint16_t *Y,
                             long y_batch);
+// Dense FFN of at most 16 rows per sequence (dense_stream_bf16.h): K slices of its two projections, both 0 where it
+// does not take the call (more rows, or partial sums that `floats` do not hold).
+struct DenseStream {
+    int gu, down;
+};
+DenseStream dense_stream_plan(int B, int M, int d, int dff, size_t floats);
+hipError_t launch_dense_stream_gu(hipStream_t st, const stream::Params &p, int B);
+hipError_t launch_dense_stream_down(hipStream_t st, const stream::Params &p, int B);
+
 hipError_t launch_da(hipStream_t st, const gemm::Params &p, const EpiStore &e);  // dY * Wd_bar^T
 hipError_t launch_swiglu_fwd(hipStream_t st, const uint16_t *G, const uint16_t *U, uint16_t *Act, long rows,
                              int dff, int n0, int nf);

@@ -1,0 +1,220 @@
+// Dense FFN of a few token rows per sequence (decode steps of prompt-only routing, paper Section 3.1):
+// out[t][n] = sum_k x[t][k] W[k][n], W row-major, streamed from memory to the matrix instruction without passing
+// through LDS.  gfx950, bf16 operands, fp32 accumulation.
+//
+// A workgroup owns 128 columns of one matrix of one sequence and a K slice; its wavefronts take the K steps of 32 in
+// turn.  Lane (c, g) of a wavefront loads 8 consecutive columns of the 8 K rows 8 g .. 8 g + 7 of a step (256-byte
+// pieces of a row per 16 lanes: a CU reads 43 GB/s from memory that way and 28 in 128-byte pieces) and transposes them
+// in registers into the operand of v_mfma_f32_16x16x32_bf16, 8 K values of one column; the other operand is up to 16
+// token rows.  The wavefronts' sums meet in LDS and are added in wavefront order, those of the K slices in slice order
+// by whoever reads them (bit-reproducible): the down projection forms its slice of the activation from the gate/up
+// sums while its first weights are in flight, so a call is two launches and, where the down projection is cut, a small
+// third one that adds.
+//
+// Bound by the latency of memory for small matrices and by its read rate for large ones: a CU reads at most 25 .. 45 GB/s,
+// so the K slices are cut until all 256 take part.  us per call, ring GEMM -> this, weights from memory: one sequence,
+// one token, d = 1024, d_ff = 2816 (17 MB) 20.0 -> 13.5 replayed from a graph, 19.5 -> 15.5 launched one by one; 4 at
+// d = 2048, d_ff = 5632 (277 MB) 59.5 -> 52.1, 5.3 TB/s.  Unsplit, with the activation in the epilogue of gate/up, the
+// same kernels took 21.2 for the first: too few CUs read.
+#pragma once
+
+#include "bf16_kernels.h"
+
+namespace lory {
+namespace stream {
+
+using gemm::bf16x8;
+using gemm::u32x4;
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kMaxRows = 16;
+constexpr int kCols = 128;   // columns of a workgroup
+
+template <class F, int... D>
+__device__ __forceinline__ void each_of(F &&f, std::integer_sequence<int, D...>)
+{
+    (f(std::integral_constant<int, D>()), ...);
+}
+
+// DOWN: x is formed from the gate/up sums and leaves as bf16 or, where the contraction is cut, as partial sums; else
+// gate or up (blockIdx.z & 1), partial sums.  NW: wavefronts.  DEPTH: K steps of a wavefront in flight.
+template <bool DOWN, int NW, int DEPTH>
+__global__ __launch_bounds__(NW * 64) void dense_stream_kernel(const Params p)
+{
+    constexpr int TERMS = DOWN ? 2 : 1, SETS = DOWN ? 1 : 2;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    uint16_t *act = reinterpret_cast<uint16_t *>(smem);   // DOWN: [2][M][slice]
+    float *red = reinterpret_cast<float *>(smem);         // afterwards: [NW][M][kCols]
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c = lane & 15, g = lane >> 4;
+    const int sl = blockIdx.y, b = blockIdx.z / SETS, set = blockIdx.z % SETS, batches = gridDim.z / SETS;
+    const int n0 = blockIdx.x * kCols;
+    const int nc = n0 + 8 * c < p.N ? n0 + 8 * c : p.N - 8;   // columns beyond the matrix are not stored
+    const int m = c < p.M ? c : p.M - 1;                      // nor are rows beyond the block
+    const int total = p.K / 32;
+    const int s0 = (int)((long)total * sl / p.ks), steps = (int)((long)total * (sl + 1) / p.ks) - s0;
+    const int len = steps * 32;
+
+    // wave-uniform bases in scalar registers, 32-bit lane offsets
+    const char *W = reinterpret_cast<const char *>(p.W[set] + (size_t)b * p.w_batch + (size_t)s0 * 32 * p.N);
+    const uint32_t offW = 2u * ((uint32_t)(8 * g) * (uint32_t)p.N + (uint32_t)nc);
+    const char *x = nullptr;
+    if constexpr (!DOWN) x = reinterpret_cast<const char *>(p.x + (size_t)b * p.x_batch + s0 * 32);
+    const uint32_t offX = DOWN ? (uint32_t)m * (uint32_t)len + 8u * g : 2u * ((uint32_t)m * (uint32_t)p.K + 8u * g);
+
+    u32x4 wr[DEPTH][8];
+    bf16x8 xr[DEPTH][TERMS];
+    f32x4 acc[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    auto load = [&](auto buf, int step) {
+        const size_t k = (size_t)step * 32;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            wr[buf][i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(W + (k + i) * p.N * 2 + offW));
+        if constexpr (!DOWN) xr[buf][0] = *reinterpret_cast<const bf16x8 *>(x + 2 * k + offX);
+    };
+    auto multiply = [&](auto buf, int step) {
+        if constexpr (DOWN) {
+#pragma unroll
+            for (int t = 0; t < TERMS; ++t)
+                xr[buf][t] = *reinterpret_cast<const bf16x8 *>(act + (size_t)t * p.M * len + offX + step * 32);
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            union {
+                uint32_t w[4];
+                bf16x8 v;
+            } o;   // column j of the lane's piece, K rows 8 g .. 8 g + 7
+#pragma unroll
+            for (int ip = 0; ip < 4; ++ip)
+                o.w[ip] = __builtin_amdgcn_perm(wr[buf][2 * ip + 1][j >> 1], wr[buf][2 * ip][j >> 1],
+                                                (j & 1) ? 0x07060302u : 0x05040100u);
+#pragma unroll
+            for (int t = 0; t < TERMS; ++t)
+                acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xr[buf][t], o.v, acc[j], 0, 0, 0);
+        }
+    };
+    // the activation of the slice: gate/up sums added in slice order, two bf16 terms
+    auto stage_act = [&]() {
+        if constexpr (DOWN) {
+            const int quads = p.M * len / 4;
+            const size_t up = (size_t)p.M * p.K, pitch = (size_t)batches * 2 * up;
+            for (int q = tid; q < quads; q += NW * 64) {
+                const int t = q / (len / 4), k = (q - t * (len / 4)) * 4;
+                const float *src = p.gu + ((size_t)b * 2 * p.M + t) * p.K + s0 * 32 + k;
+                float4 sg = make_float4(0.f, 0.f, 0.f, 0.f), su = sg;
+#pragma unroll 4
+                for (int s = 0; s < p.gu_ks; ++s) {
+                    const float4 a = *reinterpret_cast<const float4 *>(src + s * pitch);
+                    const float4 u = *reinterpret_cast<const float4 *>(src + s * pitch + up);
+                    sg.x += a.x; sg.y += a.y; sg.z += a.z; sg.w += a.w;
+                    su.x += u.x; su.y += u.y; su.z += u.z; su.w += u.w;
+                }
+                float h[4], l[4];
+                k::act_terms(sg.x, su.x, h[0], l[0]);
+                k::act_terms(sg.y, su.y, h[1], l[1]);
+                k::act_terms(sg.z, su.z, h[2], l[2]);
+                k::act_terms(sg.w, su.w, h[3], l[3]);
+                uint16_t *dst = act + (size_t)t * len + k;
+                *reinterpret_cast<gemm::u32x2 *>(dst) = k::pack4(h[0], h[1], h[2], h[3]);
+                *reinterpret_cast<gemm::u32x2 *>(dst + (size_t)p.M * len) = k::pack4(l[0], l[1], l[2], l[3]);
+            }
+            __syncthreads();
+        }
+    };
+
+    const int n = (steps - wave + NW - 1) / NW;   // this wavefront's steps: wave, wave + NW, ..
+    auto nth = [&](int i) { return wave + i * NW; };
+    auto each = [](auto f) { each_of(f, std::make_integer_sequence<int, DEPTH>()); };
+    // The loop's loads are unconditional: behind a conditional load the compiler waits for everything in flight.
+    if (n >= DEPTH) {
+        each([&](auto d) { load(d, nth(d)); });
+        stage_act();
+        int i = 0;
+        for (; i + 2 * DEPTH <= n; i += DEPTH)
+            each([&](auto d) {
+                multiply(d, nth(i + d));
+                load(d, nth(i + DEPTH + d));
+            });
+        const int left = n - i - DEPTH;   // steps that are not in flight yet, fewer than DEPTH
+        each([&](auto d) {
+            multiply(d, nth(i + d));
+            if (d < left) load(d, nth(i + DEPTH + d));
+        });
+        each([&](auto d) {
+            if (d < left) multiply(d, nth(i + DEPTH + d));
+        });
+    } else {
+        each([&](auto d) {
+            if (d < n) load(d, nth(d));
+        });
+        stage_act();
+        each([&](auto d) {
+            if (d < n) multiply(d, nth(d));
+        });
+    }
+
+    // Lane (c, g) holds tokens 4 g .. 4 g + 3 of columns 8 c .. 8 c + 7.
+    if constexpr (DOWN) __syncthreads();   // every wavefront has read its activation
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        if (4 * g + r < p.M) {
+#pragma unroll
+            for (int j = 0; j < 8; j += 4)
+                *reinterpret_cast<float4 *>(red + (wave * p.M + 4 * g + r) * kCols + 8 * c + j) =
+                    make_float4(acc[j][r], acc[j + 1][r], acc[j + 2][r], acc[j + 3][r]);
+        }
+    __syncthreads();
+#pragma unroll 1
+    for (int q = tid; q < p.M * (kCols / 4); q += NW * 64) {
+        const int tok = q / (kCols / 4), col = q % (kCols / 4) * 4;
+        if (n0 + col >= p.N) continue;
+        float v[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const float4 s = *reinterpret_cast<const float4 *>(red + (w * p.M + tok) * kCols + col);
+            v[0] += s.x; v[1] += s.y; v[2] += s.z; v[3] += s.w;
+        }
+        if (!DOWN || p.ks > 1)
+            *reinterpret_cast<float4 *>(p.part + ((((size_t)sl * batches + b) * SETS + set) * p.M + tok) * p.N + n0 + col) =
+                make_float4(v[0], v[1], v[2], v[3]);
+        else
+            *reinterpret_cast<gemm::u32x2 *>(p.Y + (size_t)b * p.y_batch + (size_t)tok * p.N + n0 + col) =
+                k::pack4(v[0], v[1], v[2], v[3]);
+    }
+}
+
+template <bool DOWN, int NW>
+constexpr size_t lds_bytes(int M, int steps, int ks)
+{
+    const size_t red = (size_t)NW * M * kCols * 4, act = DOWN ? (size_t)2 * M * ((steps + ks - 1) / ks) * 64 : 0;
+    return red > act ? red : act;
+}
+
+template <bool DOWN, int NW, int DEPTH>
+inline hipError_t launch(hipStream_t st, const Params &p, int batches)
+{
+    const long z = (long)batches * (DOWN ? 1 : 2);
+    if (p.M < 1 || p.M > kMaxRows || p.ks < 1 || p.ks > 65535 || p.ks > p.K / 32 || z > 65535 || p.K % 32 != 0 || p.N % 8 != 0 ||
+        p.N < 8 || p.K >= (1 << 26) || p.N >= (1 << 26))
+        return hipErrorInvalidValue;
+    const size_t lds = lds_bytes<DOWN, NW>(p.M, p.K / 32, p.ks);
+    if (lds > 160 * 1024) return hipErrorInvalidValue;
+    auto kern = dense_stream_kernel<DOWN, NW, DEPTH>;
+    static bool configured = false;  // per instantiation
+    if (!configured) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           160 * 1024);
+        if (e != hipSuccess) return e;
+        configured = true;
+    }
+    hipLaunchKernelGGL(kern, dim3((unsigned)((p.N + kCols - 1) / kCols), (unsigned)p.ks, (unsigned)z), dim3(NW * 64), lds, st, p);
+    return hipGetLastError();
+}
+
+}  // namespace stream
+}  // namespace lory

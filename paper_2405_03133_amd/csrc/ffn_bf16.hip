@@ -459,6 +459,45 @@ DenseForm bf16_dense_form(const Dims &m, const DenseScratch &scratch)
     return {p.rows, p.terms, g.rows, g.ks, d.rows, d.ks};
 }
 
+namespace {
+
+// Decode steps and blocks of at most 16 rows: two streaming projections, the gate/up sums between them in the scratch.
+int dense_stream(const Dims &m, const k::DenseStream &sp, const bf *X, const bf *Wbar, bf *Y, float *ws, hipStream_t st)
+{
+    float *parts = ws + (size_t)sp.gu * 2 * m.B * m.L * m.dff;
+    stream::Params p = {};
+    p.M = m.L;
+    p.w_batch = m.D;
+    {
+        prof::Range r(st, prof::kGemmGU, 4.0 * m.tokens * m.D, 2.0 * (m.tokens * (double)m.d + 2.0 * m.B * m.D));
+        p.K = m.d; p.N = m.dff; p.ks = sp.gu;
+        p.W[0] = Wbar; p.W[1] = Wbar + (size_t)m.B * m.D;
+        p.x = X; p.x_batch = (long)m.L * m.d;
+        p.part = ws;
+        LORY_TRY(k::launch_dense_stream_gu(st, p, m.B));
+    }
+    prof::Range r(st, prof::kGemmDown, 2.0 * m.tokens * m.D, 2.0 * (m.tokens * (double)m.d + (double)m.B * m.D));
+    p.K = m.dff; p.N = m.d; p.ks = sp.down;
+    p.W[0] = Wbar + (size_t)2 * m.B * m.D;
+    p.gu = ws; p.gu_ks = sp.gu;
+    p.part = parts;
+    p.Y = Y; p.y_batch = (long)m.L * m.d;
+    LORY_TRY(k::launch_dense_stream_down(st, p, m.B));
+    if (sp.down > 1) LORY_TRY(k::launch_sum_store(st, parts, sp.down, m.B, (long)m.L * m.d, 1, Y, (long)m.L * m.d));
+    return LORY_OK;
+}
+
+}  // namespace
+
+bool bf16_dense_stream(const Dims &m, const void *X, const void *Wbar, void *Y, void *ws, size_t ws_bytes, hipStream_t st,
+                       int *rc)
+{
+    const k::DenseStream sp = k::dense_stream_plan(m.B, m.L, m.d, m.dff, ws_bytes / sizeof(float));
+    if (!sp.gu) return false;
+    *rc = dense_stream(m, sp, (const bf *)X, (const bf *)Wbar, (bf *)Y, (float *)ws, st);
+    return true;
+}
+
 // Dense SwiGLU FFN of every sequence with its own materialised merged parameters
 // (m.T == m.L: one parameter set per sequence, any number of rows).
 int bf16_dense_ffn_fwd(const Dims &m, const void *Xv, const void *Wbarv, void *Yv, void *ws, const DenseScratch &scratch,

@@ -3,7 +3,8 @@
 // inference"; Appendix G.1).  After one routing decision per layer the merged
 // FFN of a sequence is an ordinary dense FFN,
 //   Y_b = (silu(X_b Wg_bar_b) (.) X_b Wu_bar_b) Wd_bar_b .
-// bf16 runs on the ring GEMM for every number of tokens (bf16_dense_ffn_fwd: contractions split over K
+// bf16 runs on streaming projections for up to 16 tokens and on the ring GEMM beyond (bf16_dense_ffn_fwd: contractions
+// split over K
 // where the tiles would leave the chip idle, rows in blocks where the scratch is small).  fp32 goes through the "skinny" kernels below, which are
 // HBM-bound: every weight is read once per pass of up to 8 tokens.
 //
@@ -339,6 +340,9 @@ size_t dense_workspace_bytes(const Dims &m)
 int dense_ffn_fwd(const Dims &m, const void *X, const void *Wbar, void *Y, void *ws, size_t ws_bytes, hipStream_t st)
 {
     if (m.dtype == LORY_F32) return skinny_ffn<float>(m, (const float *)X, (const float *)Wbar, (float *)Y, ws, st);
+    // the streaming path keeps to the least workspace, so that a call runs the same way whatever it is given
+    int rc = LORY_OK;
+    if (bf16_dense_stream(m, X, Wbar, Y, ws, base_bytes(m), st, &rc)) return rc;
     if (ws_bytes >= dense_workspace_bytes(m)) return bf16_dense_ffn_fwd(m, X, Wbar, Y, ws, gemm_scratch(m), st);
     return bf16_dense_ffn_fwd(m, X, Wbar, Y, ws, DenseScratch{base_bytes(m), true}, st);
 }

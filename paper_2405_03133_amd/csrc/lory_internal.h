@@ -102,7 +102,8 @@ struct DenseScratch {
     bool fixed;
 };
 size_t bf16_dense_workspace_bytes(const Dims &m, const DenseScratch &scratch);
-// How a call runs with the workspace that is reported for it: rows of a block, bf16 terms of the activation, and for
+// How the ring GEMM runs a call with the workspace that is reported for it (blocks of at most 16 rows stream their
+// weights instead, bf16_dense_stream): rows of a block, bf16 terms of the activation, and for
 // the two projections the tile height and the K slices (0: not split).
 struct DenseForm {
     int rows, terms, gu_tile, gu_slices, down_tile, down_slices;
@@ -111,6 +112,9 @@ DenseForm bf16_dense_form(const Dims &m, const DenseScratch &scratch);
 DenseForm dense_form(const Dims &m);
 int bf16_dense_ffn_fwd(const Dims &m, const void *X, const void *Wbar, void *Y, void *ws, const DenseScratch &scratch,
                        hipStream_t st);
+// Blocks of at most 16 rows, weights streamed; false where they take more rows or more scratch than ws_bytes.
+bool bf16_dense_stream(const Dims &m, const void *X, const void *Wbar, void *Y, void *ws, size_t ws_bytes, hipStream_t st,
+                       int *rc);
 int set_slab_budget(size_t bytes);
 int set_fused_mode(int mode);
 size_t bf16_workspace_bytes(const Dims &m, int pass);

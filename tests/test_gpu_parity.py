@@ -635,6 +635,51 @@ def test_dense_block_rounds_only_its_output(B, n_tok, d, d_ff):
     assert err <= 1.03 * rounded, (err / rounded, rounded / np.linalg.norm(ref))
 
 
+# Streamed weights (up to 16 rows): one row and a full block of rows, half a block of columns, fewer K steps than
+# wavefronts, an activation slice at the limit of LDS (K slices forced), many and few sequences, and the first row count
+# that the ring GEMM takes.  The bound is that of the test above; the least workspace and the library-held scratch give
+# the same bits.
+@pytest.mark.parametrize("B,n_tok,d,d_ff", [
+    (1, 16, 64, 64), (2, 16, 64, 1088), (3, 9, 1088, 192), (1, 2, 2560, 6144), (17, 16, 128, 320), (1, 16, 64, 12352),
+    (300, 1, 64, 192), (2, 17, 320, 832),
+])
+def test_dense_block_of_few_rows(B, n_tok, d, d_ff):
+    cfg = LoryConfig("dense_stream", B=B, L=n_tok, T=n_tok, d=d, d_ff=d_ff, E=B, dtype="bf16", seed=64)
+    print(f"[gpu] {cfg}", flush=True)
+    t = make_inputs(cfg, with_dy=False)
+    X = to_dev(t["X"], cfg)
+    Wbar = torch.stack([to_dev(t[k], cfg).reshape(B, d * d_ff) for k in ("Wg", "Wu", "Wd")]).contiguous()
+    Y = lb.lory_dense_ffn_fwd(X, Wbar, d_ff)
+    ref = orc.ffn_fwd(t["X"], np.eye(B), t["Wg"], t["Wu"], t["Wd"], n_tok)["Y"]
+    rounded = np.linalg.norm(round_to_bf16(ref.astype(np.float32)) - ref)
+    assert np.linalg.norm(host(Y) - ref) <= 1.03 * rounded, (np.linalg.norm(host(Y) - ref) / rounded)
+    shape = lb.make_shape(B, n_tok, n_tok, d, d_ff, 1, X.dtype)
+    assert lb.lory_workspace_bytes(shape, lb.LORY_PASS_DENSE) <= 16 << 20
+    Ys = lb.lory_dense_ffn_fwd_static(X, Wbar, d_ff, torch.full_like(X, float("nan")))
+    assert torch.equal(Y, Ys)
+    if n_tok > 16:
+        return
+    # the least workspace that is accepted, and the bytes behind it
+    lo, hi = 256, lb.lory_workspace_bytes(shape, lb.LORY_PASS_DENSE)
+    ws = torch.full((hi + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+
+    def call(size):
+        Yl = torch.full_like(X, float("nan"))
+        rc = lb.lib().lory_dense_ffn_fwd(ctypes.byref(shape), X.data_ptr(), Wbar.data_ptr(), Yl.data_ptr(), ws.data_ptr(),
+                                         size, torch.cuda.current_stream().cuda_stream)
+        return rc, Yl
+
+    while lo < hi:
+        mid = (lo + hi) // 512 * 256
+        if call(mid)[0] == lb.LORY_OK:
+            hi = mid
+        else:
+            lo = mid + 256
+    ws.fill_(0x5A)
+    rc, Yl = call(lo)
+    assert rc == lb.LORY_OK and torch.equal(Y, Yl) and bool((ws[lo:] == 0x5A).all())
+
+
 @pytest.mark.parametrize("d,d_ff", [(64, 64), (256, 512)], ids=["two sources", "split"])
 def test_dense_block_activation_at_the_end_of_the_range(d, d_ff):
     """An activation above the largest bf16 but finite in fp32 stays finite; an infinite one stays infinite."""
