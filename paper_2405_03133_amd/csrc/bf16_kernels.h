@@ -49,7 +49,7 @@ __device__ __forceinline__ u32x2 pack4(float a, float b, float c, float d)
 template <bool SAVE, bool ACT>
 struct EpiGUT {
     static constexpr int NOUT = 3;
-    static constexpr bool SPLIT = false;
+    static constexpr bool SPLIT = false, TAIL = false;
     uint16_t *G, *U, *Act;  // [tokens, d_ff]
     int T, dff, n_off;
     __device__ __forceinline__ bool enabled(int o) const { return o == 0 ? ACT : SAVE; }
@@ -95,7 +95,7 @@ __device__ __forceinline__ void act_terms(float g, float u, float &hi, float &lo
 // Gate/up projections, activation as two terms: Act[batch][hi rows | lo rows][d_ff].
 struct EpiAct2 {
     static constexpr int NOUT = 2;
-    static constexpr bool SPLIT = false;
+    static constexpr bool SPLIT = false, TAIL = false;
     uint16_t *Act;
     int T, dff;
     __device__ __forceinline__ bool enabled(int) const { return true; }
@@ -116,7 +116,7 @@ struct EpiAct2 {
 // C[batch][m][n] = bf16(v)
 struct EpiStore {
     static constexpr int NOUT = 1;
-    static constexpr bool SPLIT = false;
+    static constexpr bool SPLIT = false, TAIL = true;
     uint16_t *C;
     long c_batch;
     int ldc;
@@ -135,7 +135,7 @@ struct EpiStore {
 // The same for two operand sets: C0 from the first, C1 from the second.
 struct EpiStore2 {
     static constexpr int NOUT = 2;
-    static constexpr bool SPLIT = false;
+    static constexpr bool SPLIT = false, TAIL = false;
     uint16_t *C0, *C1;
     long c_batch;
     int ldc;
@@ -155,7 +155,7 @@ struct EpiStore2 {
 template <int NSET>
 struct EpiPart {
     static constexpr int NOUT = 1;
-    static constexpr bool SPLIT = true;
+    static constexpr bool SPLIT = true, TAIL = false;
     float *P;
     int ksplit, batches, M, N;   // batches: items before the split
     __device__ __forceinline__ bool enabled(int) const { return false; }

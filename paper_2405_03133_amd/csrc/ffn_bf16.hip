@@ -170,6 +170,17 @@ Rect rect(long D, int pitch, int r0, int nr, int c0, int nc)
     return rc;
 }
 
+// Scratch for a cut last round of tiles: what lies unused between two places of the workspace while the GEMM runs.
+// Only where the transient slab holds the whole matrix, and the same scratch whether the merged parameters are saved or
+// not: the sums of the two modes are then added in the same order.
+void set_tail(Params &p, bool whole, void *from, void *to)
+{
+    if (!whole) return;
+    const size_t a = align_up((size_t)from, 256), b = (size_t)to;
+    p.tail = b > a ? (float *)a : nullptr;
+    p.tail_floats = b > a ? (b - a) / sizeof(float) : 0;
+}
+
 double gemm_flops(const Params &p, int nset, int nsrc)
 {
     return 2.0 * p.batches * p.M * p.N * p.K * nset * nsrc;
@@ -261,6 +272,7 @@ int bf16_ffn_fwd(const Dims &m, const void *Xv, const float *w, const void *Wgv,
                  const void *Wdv, void *Yv, void *Gv, void *Uv, void *Wbarv, void *ws, hipStream_t st)
 {
     Plan pl = make_plan(m);
+    const bool whole_d = pl.jf_fwd == m.d;
     bf *Wbar = (bf *)Wbarv;  // [Wg_bar | Wu_bar | Wd_bar], each [S][rows][cols]; doubles as the slab
     if (Wbar) {
         pl.nf_fwd = m.dff;
@@ -312,6 +324,7 @@ int bf16_ffn_fwd(const Dims &m, const void *Xv, const float *w, const void *Wgv,
             p.A[0] = Act; p.a_batch[0] = TF; p.lda[0] = m.dff;
             p.B[0] = sd; p.b_batch[0] = (long)m.dff * jf; p.ldb[0] = jf;
             p.M = m.T; p.N = jf; p.K = m.dff; p.batches = S;
+            set_tail(p, whole_d, slab + (size_t)S * m.dff * jf, (char *)slab + pl.slab_fwd);
             EpiStore epi = {Y + (size_t)s0 * TD + j0, TD, m.d};
             prof::Range r(st, prof::kGemmDown, gemm_flops(p, 1, 1),
                           2.0 * ((double)S * TF + (double)S * m.dff * jf + (double)S * m.T * jf));
@@ -409,6 +422,13 @@ struct DensePlan {
     size_t floats;       // bound on the partial sums of split contractions
     DenseSplit gate_up(const Dims &m, int r) const { return dense_split(m, r, m.dff, m.d, 2, 1, floats); }
     DenseSplit down(const Dims &m, int r) const { return dense_split(m, r, m.d, m.dff, 1, terms, floats); }
+    // The down projection where it is not split as a whole: its last round of tiles may be.
+    Params down_params(const Dims &m, int r) const
+    {
+        Params p = {};
+        p.M = r; p.N = m.d; p.K = m.dff; p.batches = m.B;
+        return p;
+    }
     size_t parts(const Dims &m, int r) const   // floats that a block of r rows uses
     {
         const DenseSplit g = gate_up(m, r), w = down(m, r);
@@ -450,6 +470,17 @@ size_t bf16_dense_workspace_bytes(const Dims &m, const DenseScratch &scratch)
         if (q > parts) parts = q;
     }
     return p.act + align_up(parts * sizeof(float), 256);
+}
+
+// Scratch of a cut last round of the down projection, for calls that are not held to a fixed scratch.
+size_t bf16_dense_tail_bytes(const Dims &m, const DenseScratch &scratch)
+{
+    const DensePlan p = dense_plan(m, scratch);
+    if (scratch.fixed || p.down(m, m.L).ks) return 0;
+    Params q = p.down_params(m, m.L);
+    q.tail = (float *)1;
+    q.tail_floats = (size_t)-1;
+    return p.act + gemm2::tail_floats(q, gemm2::tile_form(q, 256, p.terms), 256) * sizeof(float);
 }
 
 DenseForm bf16_dense_form(const Dims &m, const DenseScratch &scratch)
@@ -500,8 +531,8 @@ bool bf16_dense_stream(const Dims &m, const void *X, const void *Wbar, void *Y, 
 
 // Dense SwiGLU FFN of every sequence with its own materialised merged parameters
 // (m.T == m.L: one parameter set per sequence, any number of rows).
-int bf16_dense_ffn_fwd(const Dims &m, const void *Xv, const void *Wbarv, void *Yv, void *ws, const DenseScratch &scratch,
-                       hipStream_t st)
+int bf16_dense_ffn_fwd(const Dims &m, const void *Xv, const void *Wbarv, void *Yv, void *ws, size_t ws_bytes,
+                       const DenseScratch &scratch, hipStream_t st)
 {
     const bf *Wbar = (const bf *)Wbarv;
     const DensePlan pl = dense_plan(m, scratch);
@@ -538,10 +569,13 @@ int bf16_dense_ffn_fwd(const Dims &m, const void *Xv, const void *Wbarv, void *Y
         {
             // the two terms of an activation are blocks of rows of one matrix, or two sources
             const DenseSplit sp = pl.down(m, rows);
-            Params p = {};
+            Params p = pl.down_params(m, rows);
             p.A[0] = Act; p.A[1] = Act + RF; p.a_batch[0] = p.a_batch[1] = nt * RF; p.lda[0] = p.lda[1] = m.dff;
             p.B[0] = p.B[1] = Wbar + (size_t)2 * m.B * m.D; p.b_batch[0] = p.b_batch[1] = m.D; p.ldb[0] = p.ldb[1] = m.d;
-            p.M = rows; p.N = m.d; p.K = m.dff; p.batches = m.B;
+            if (!scratch.fixed && ws_bytes > pl.act) {
+                p.tail = parts;
+                p.tail_floats = (ws_bytes - pl.act) / sizeof(float);
+            }
             prof::Range r(st, prof::kGemmDown, gemm_flops(p, 1, 1), 2.0 * m.B * ((double)RF + (double)m.D + (double)RD));
             const EpiStore epi = {Y, TD, m.d};
             if (sp.ks) {
@@ -678,6 +712,7 @@ int bf16_ffn_bwd(const Dims &m, const void *Xv, const float *w, const void *Wgv,
                 p.b_batch[0] = Wbar ? m.D : (long)nf * m.d;
                 p.ldb[0] = m.d;
                 p.M = m.T; p.N = nf; p.K = m.d; p.batches = S;
+                set_tail(p, nf == m.dff, s_gd, (char *)slab + pl.slab_bwd);   // the gradient slabs are written later
                 EpiStore epi = {dG + n0, TF, m.dff};  // dA parks in the dG buffer
                 {
                     prof::Range r(st, prof::kGemmDA, gemm_flops(p, 1, 1),
@@ -758,6 +793,7 @@ int bf16_ffn_bwd(const Dims &m, const void *Xv, const float *w, const void *Wgv,
             p.b_batch[0] = p.b_batch[1] = Wbar ? m.D : (long)kf * m.dff;
             p.ldb[0] = p.ldb[1] = m.dff;
             p.M = m.T; p.N = kf; p.K = m.dff; p.batches = S;
+            set_tail(p, kf == m.d, slab + 2 * blk, (char *)slab + pl.slab_bwd);
             EpiStore epi = {dX + (size_t)s0 * TD + k0, TD, m.d};
             prof::Range r(st, prof::kGemmDX, gemm_flops(p, 1, 2),
                           2.0 * (2.0 * S * TF + 2.0 * S * kf * m.dff + (double)S * m.T * kf));

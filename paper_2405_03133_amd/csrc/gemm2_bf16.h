@@ -118,6 +118,14 @@ __device__ __forceinline__ void dma16s(const char *base, uint32_t off, uint32_t 
                  : "memory", "m0");
 }
 
+// A wave-uniform pointer, for the compiler to see as one.
+__device__ __forceinline__ const char *uniform(const char *p)
+{
+    const uint64_t v = (uint64_t)p;
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return (const char *)(((uint64_t)hi << 32) | lo);
+}
+
 template <int N>
 __device__ __forceinline__ void wait_vmcnt()
 {
@@ -139,10 +147,14 @@ __device__ __forceinline__ void ring_barrier()
 // Persistent kernel: the grid is one workgroup per CU; every workgroup walks its own list of tiles, and the K
 // steps of consecutive tiles form one stream through the ring, so the first operands of the next tile are already
 // in flight while the current tile is multiplied and written out.
-template <int NSET, int NSRC, bool A_MC, bool B_NC, class TL, class Epi>
+//
+// TAIL: the tiles that do not fill a round of workgroups are cut into p.pieces K slices, one for each
+// workgroup after its whole tiles; their fp32 sums go to p.tail and tail_kernel adds them and runs the epilogue.
+template <int NSET, int NSRC, bool A_MC, bool B_NC, bool TAIL, class TL, class Epi>
 __global__ __launch_bounds__(TL::threads, TL::waves_per_simd) void gemm2_kernel(const Params p, const Epi epi)
 {
     static_assert(NSET == 1 || NSRC == 1, "either two operand sets or two sources");
+    static_assert(!TAIL || !Epi::SPLIT, "all tiles or those of the last round are cut");
     constexpr int MI = TL::MI, NB = TL::NB;
     constexpr int BM = TL::BM;
     constexpr int BNS = TL::BN / NSET;    // columns per operand set
@@ -168,12 +180,15 @@ __global__ __launch_bounds__(TL::threads, TL::waves_per_simd) void gemm2_kernel(
     const int tiles_n = (p.N + BNS - 1) / BNS;
     const int tiles_m = (p.M + BM - 1) / BM;
     const int ntiles = p.batches * tiles_m * tiles_n;
-    const int per_xcd = (ntiles + 7) >> 3;
+    const int whole = TAIL ? ntiles / (int)gridDim.x * (int)gridDim.x : ntiles;   // tiles that are not cut
+    const int per_xcd = (whole + 7) >> 3;
     const int wg_per_xcd = gridDim.x >> 3;
     const int xcd = blockIdx.x & 7, qx = blockIdx.x >> 3;
-    int xcd_tiles = ntiles - xcd * per_xcd;  // tiles in this XCD's range
+    int xcd_tiles = whole - xcd * per_xcd;  // tiles in this XCD's range
     if (xcd_tiles > per_xcd) xcd_tiles = per_xcd;
-    const int my_tiles = (xcd_tiles > qx) ? (xcd_tiles - qx + wg_per_xcd - 1) / wg_per_xcd : 0;
+    const int my_whole = (xcd_tiles > qx) ? (xcd_tiles - qx + wg_per_xcd - 1) / wg_per_xcd : 0;
+    const int piece = xcd * wg_per_xcd + qx;   // this workgroup's K slice of the cut tiles, slices of a tile adjacent
+    const int my_tiles = my_whole + ((TAIL && piece < (ntiles - whole) * p.pieces) ? 1 : 0);
     if (my_tiles == 0) return;
 
     const int ktiles = p.K / BK;
@@ -184,12 +199,27 @@ __global__ __launch_bounds__(TL::threads, TL::waves_per_simd) void gemm2_kernel(
 
     auto tile_coords = [&](int i, int &batch, int &m0, int &n0) {
         int id = xcd * per_xcd + qx + i * wg_per_xcd;
+        if (TAIL && i == my_whole) id = whole + piece / p.pieces;
         const int nt = id % tiles_n;
         id /= tiles_n;
         const int mt = id % tiles_m;
         batch = id / tiles_m;
         m0 = mt * BM;
         n0 = nt * BNS;
+    };
+
+    // the K steps of the cut tile, counted through the sources
+    auto piece_begin = [&](int sl) { return __builtin_amdgcn_readfirstlane((int)((uint32_t)(ktiles * NSRC) * (uint32_t)sl / (uint32_t)p.pieces)); };
+    // the cut tile's first K step: of source 1, or counted in source 0; steps in that source and, after it, in source 1
+    struct Entry {
+        int k0, left, left1;
+        bool second;
+    };
+    auto enter_piece = [&]() -> Entry {
+        const int sl = piece % p.pieces, k0 = piece_begin(sl), k1 = piece_begin(sl + 1);
+        if (NSRC == 2 && k0 >= ktiles) return {k0 - ktiles, k1 - k0, 0, true};
+        if (NSRC == 2 && k1 > ktiles) return {k0, ktiles - k0, k1 - ktiles, false};
+        return {k0, k1 - k0, 0, false};
     };
 
     // ---- the two load streams.  A and B of a K step are fetched at different times, so each stream keeps
@@ -201,6 +231,7 @@ __global__ __launch_bounds__(TL::threads, TL::waves_per_simd) void gemm2_kernel(
     // divisions, spent more scalar instructions on them than the step has MFMA issue slots).
     const char *ptrA, *ptrB;
     int leftA, leftB, srcA = 0, srcB = 0, iA = 0, iB = 0;
+    int left1A = ktiles, left1B = ktiles;   // K steps in the second source
     long bA = 0, bB = 0;     // byte offset of the current tile inside a source (second source: same offset)
     uint32_t offA[LA], offB[LB];
     const long kA = 2 * (A_MC ? (long)BK * p.lda[0] : (long)BK);
@@ -237,6 +268,15 @@ __global__ __launch_bounds__(TL::threads, TL::waves_per_simd) void gemm2_kernel(
                    2 * ((long)(batch / p.ksplit) * p.a_batch[0] + (A_MC ? (long)m0 : (long)m0 * p.lda[0]));
             leftA = slice_begin(sl + 1) - k0;
         }
+        if constexpr (TAIL)
+            if (i == my_whole) {
+                const Entry e = enter_piece();
+                if (NSRC == 2 && e.second) ptrA = reinterpret_cast<const char *>(p.A[NSRC - 1]) + bA;
+                ptrA += kA * e.k0;
+                leftA = e.left;
+                left1A = e.left1;
+                if (NSRC == 2 && e.left1 == 0) srcA = 1;   // nothing left in the second source
+            }
     };
     auto enter_B = [&](int i) {
         int batch, m0, n0;
@@ -269,6 +309,15 @@ __global__ __launch_bounds__(TL::threads, TL::waves_per_simd) void gemm2_kernel(
                    2 * ((long)(batch / p.ksplit) * (s ? p.b_batch[1] : p.b_batch[0]) + in_b);
             leftB = slice_begin(sl + 1) - k0;
         }
+        if constexpr (TAIL)
+            if (i == my_whole) {
+                const Entry e = enter_piece();
+                if (NSRC == 2 && e.second) ptrB = reinterpret_cast<const char *>(p.B[NSRC - 1]) + bB;
+                ptrB += kB * e.k0;
+                leftB = e.left;
+                left1B = e.left1;
+                if (NSRC == 2 && e.left1 == 0) srcB = 1;   // nothing left in the second source
+            }
     };
     // One K step further.  Past the end of the stream the last K step is fetched again, into slots nobody
     // reads, so that the wait counts below always hold.
@@ -278,7 +327,7 @@ __global__ __launch_bounds__(TL::threads, TL::waves_per_simd) void gemm2_kernel(
             if (NSRC == 2 && srcA == 0) {
                 srcA = 1;
                 ptrA = reinterpret_cast<const char *>(p.A[1]) + bA;
-                leftA = ktiles;
+                leftA = left1A;
             } else if (iA + 1 < my_tiles) {
                 enter_A(++iA);
             } else {
@@ -293,7 +342,7 @@ __global__ __launch_bounds__(TL::threads, TL::waves_per_simd) void gemm2_kernel(
             if (NSRC == 2 && srcB == 0) {
                 srcB = 1;
                 ptrB = reinterpret_cast<const char *>(p.B[1]) + bB;
-                leftB = ktiles;
+                leftB = left1B;
             } else if (iB + 1 < my_tiles) {
                 enter_B(++iB);
             } else {
@@ -304,8 +353,8 @@ __global__ __launch_bounds__(TL::threads, TL::waves_per_simd) void gemm2_kernel(
     };
     const uint32_t ldsA = lds0 + wave * (LA * 1024);
     const uint32_t ldsB = lds0 + TL::a_bytes + wave * (LB * 1024);
-    auto issue_A = [&](uint32_t slot, int i) { dma16s(ptrA, offA[i], ldsA + slot + i * 1024); };
-    auto issue_B = [&](uint32_t slot, int j) { dma16s(ptrB, offB[j], ldsB + slot + j * 1024); };
+    auto issue_A = [&](uint32_t slot, int i) { dma16s(TAIL ? uniform(ptrA) : ptrA, offA[i], ldsA + slot + i * 1024); };
+    auto issue_B = [&](uint32_t slot, int j) { dma16s(TAIL ? uniform(ptrB) : ptrB, offB[j], ldsB + slot + j * 1024); };
     auto next_slot = [&](uint32_t s) -> uint32_t { return s + TL::stage == TL::ring ? 0u : s + TL::stage; };
 
     f32x16 acc[NSET][MI][NI];
@@ -567,10 +616,34 @@ __global__ __launch_bounds__(TL::threads, TL::waves_per_simd) void gemm2_kernel(
         tile_coords(tile_i, batch, m0, n0);
         int total = ktiles * NSRC;
         if constexpr (Epi::SPLIT) total = slice_begin(batch % p.ksplit + 1) - slice_begin(batch % p.ksplit);
+        if (TAIL && tile_i == my_whole) total = piece_begin(piece % p.pieces + 1) - piece_begin(piece % p.pieces);
         // the first S-1 K steps of a tile run while the previous tile's stores drain
         step(T(), F(), extra);
         for (int t = 1; t < total - 1; ++t) step(F(), F(), t < S - 1 ? extra : 0);
         step(F(), T(), total - 1 < S - 1 ? extra : 0);
+        if constexpr (TAIL)
+            if (tile_i == my_whole) {
+                // accumulators as they lie, 1 KB per store; rows and columns beyond the matrix are never read
+                asm volatile("; piece" ::: "memory");
+                int el = lane;
+                asm volatile("" : "+v"(el));
+                char *dst = reinterpret_cast<char *>(p.tail) + ((size_t)piece * TL::NW + wave) * (MI * NB * 4 * 1024);
+#pragma unroll
+                for (int i = 0; i < MI; ++i)
+#pragma unroll
+                    for (int j = 0; j < NI; ++j)
+#pragma unroll
+                        for (int s = 0; s < NSET; ++s)
+#pragma unroll
+                            for (int rq = 0; rq < 4; ++rq) {
+                                *reinterpret_cast<float4 *>(dst + (uint32_t)el * 16u) =
+                                    make_float4(acc[s][i][j][rq * 4 + 0], acc[s][i][j][rq * 4 + 1],
+                                                acc[s][i][j][rq * 4 + 2], acc[s][i][j][rq * 4 + 3]);
+                                dst += 1024;
+                                __builtin_amdgcn_sched_barrier(0);
+                            }
+                break;   // a workgroup's last tile
+            }
         if (m0 + BM <= p.M && n0 + BNS <= p.N) {
             epilogue(T(), batch, m0, n0);
             extra = nst;
@@ -580,6 +653,76 @@ __global__ __launch_bounds__(TL::threads, TL::waves_per_simd) void gemm2_kernel(
         }
     }
     wait_vmcnt<0>();  // no direct load may still be writing LDS when the workgroup retires
+}
+
+// Adds the K slices of the cut tiles in slice order and runs the epilogue on the sums.  A wavefront takes 32 rows x 64
+// columns (of every set) of a wavefront of the GEMM; they leave through LDS as whole lines, like an interior tile's.
+// Bound by reading the sums back (256 KB a slice, 256-row tile), which sit in the memory-side cache.
+template <int NSET, class TL, class Epi>
+__global__ __launch_bounds__(256) void tail_kernel(const Params p, const Epi epi, int whole, int jobs)
+{
+    constexpr int MI = TL::MI, NI = TL::NB / NSET, BNS = TL::BN / NSET, JG = 2;
+    static_assert(NI % JG == 0, "blocks of 64 columns");
+    constexpr int CP = JG * 4, RPI = 64 / CP;
+    __shared__ __attribute__((aligned(16))) char stage[4][32 * CP * 16];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    int job = blockIdx.x * 4 + wv;
+    if (job >= jobs) return;
+    const int jg = job % (NI / JG) * JG;
+    job /= NI / JG;
+    const int i = job % MI;
+    job /= MI;
+    const int wave = job % TL::NW, t = job / TL::NW;
+    const int tiles_n = (p.N + BNS - 1) / BNS, tiles_m = (p.M + TL::BM - 1) / TL::BM;
+    int id = whole + t;
+    const int n0 = id % tiles_n * BNS + wave % TL::WNV * (NI * 32) + jg * 32;
+    id /= tiles_n;
+    const int m0 = id % tiles_m * TL::BM + wave / TL::WNV * (MI * 32) + i * 32, batch = id / tiles_m;
+
+    constexpr int Q = JG * NSET * 4;   // quads of a lane
+    float4 v[Q];
+    const size_t pitch = (size_t)TL::NW * (MI * TL::NB * 4 * 64);
+    const float4 *src = reinterpret_cast<const float4 *>(p.tail) + (size_t)t * p.pieces * pitch +
+                        (size_t)wave * (MI * TL::NB * 4 * 64) + (i * NI + jg) * (NSET * 4 * 64) + lane;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) v[q] = src[q * 64];
+#pragma unroll 2
+    for (int s = 1; s < p.pieces; ++s) {
+        src += pitch;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const float4 a = src[q * 64];
+            v[q].x += a.x; v[q].y += a.y; v[q].z += a.z; v[q].w += a.w;
+        }
+    }
+    const int r = lane & 31, h = lane >> 5, srow = lane / CP, sc = lane % CP;
+    char *stg = stage[wv];
+#pragma unroll
+    for (int o = 0; o < Epi::NOUT; ++o) {
+        if (!epi.enabled(o)) continue;
+#pragma unroll
+        for (int jj = 0; jj < JG; ++jj)
+#pragma unroll
+            for (int rq = 0; rq < 4; ++rq) {
+                float x[NSET][4];
+#pragma unroll
+                for (int s = 0; s < NSET; ++s) {
+                    const float4 a = v[(jj * NSET + s) * 4 + rq];
+                    x[s][0] = a.x; x[s][1] = a.y; x[s][2] = a.z; x[s][3] = a.w;
+                }
+                const u32x2 pk = epi.pack(o, x);
+                *reinterpret_cast<u32x2 *>(stg + r * (CP * 16) + (((jj * 4 + rq) ^ (r & (CP - 1))) << 4) + h * 8) = pk;
+            }
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int it = 0; it < 32 / RPI; ++it) {
+            const int row = it * RPI + srow;
+            const u32x4 val = *reinterpret_cast<const u32x4 *>(stg + row * (CP * 16) + ((sc ^ (row & (CP - 1))) << 4));
+            if (m0 + row < p.M && n0 + sc * 8 < p.N)
+                *reinterpret_cast<u32x4 *>(epi.ptr(o, batch, m0 + row, n0 + sc * 8)) = val;
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
 }
 
 inline int cu_count()
@@ -597,14 +740,15 @@ inline int cu_count()
 
 inline int persistent_grid() { return cu_count(); }
 
-template <int NSET, int NSRC, bool A_MC, bool B_NC, class TL, class Epi>
+template <int NSET, int NSRC, bool A_MC, bool B_NC, class TL, class Epi, bool TAIL = false>
 inline hipError_t launch(const Params &p, const Epi &epi, hipStream_t st)
 {
     if (p.K % BK != 0 || p.K < 2 * BK || p.N % 8 != 0 || p.M < 1 || p.N < 8 || (A_MC && p.M % 8 != 0)) return hipErrorInvalidValue;
     if (NSRC == 2 && (p.lda[0] != p.lda[1] || p.ldb[0] != p.ldb[1])) return hipErrorInvalidValue;
     if (NSET == 2 && p.ldb[0] != p.ldb[1]) return hipErrorInvalidValue;
     if (Epi::SPLIT && (p.ksplit < 1 || p.ksplit > 1024 || p.K > (1 << 24) || p.batches % p.ksplit != 0 || p.K / BK < 2 * p.ksplit)) return hipErrorInvalidValue;
-    auto kern = gemm2_kernel<NSET, NSRC, A_MC, B_NC, TL, Epi>;
+    const int cus = cu_count();
+    auto kern = gemm2_kernel<NSET, NSRC, A_MC, B_NC, TAIL, TL, Epi>;
     static bool configured = false;  // per instantiation
     if (!configured) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
@@ -615,8 +759,20 @@ inline hipError_t launch(const Params &p, const Epi &epi, hipStream_t st)
     constexpr int BNS = TL::BN / NSET;
     const long ntiles = (long)p.batches * ((p.M + TL::BM - 1) / TL::BM) * ((p.N + BNS - 1) / BNS);
     long blocks = (ntiles + 7) / 8 * 8;
-    if (blocks > cu_count()) blocks = cu_count();  // every workgroup walks several tiles
+    if (blocks > cus) blocks = cus;  // every workgroup walks several tiles
+    if (TAIL) {
+        if (p.pieces < 1 || !p.tail || ntiles % cus == 0 || ntiles % cus * p.pieces > cus || p.K / BK * NSRC < 2 * p.pieces ||
+            p.tail_floats < (size_t)(ntiles % cus) * p.pieces * TL::BM * TL::BN || p.K > (1 << 24) || ntiles >= (1L << 31))
+            return hipErrorInvalidValue;
+        blocks = cus;
+    }
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(TL::threads), TL::total, st, p, epi);
+    if constexpr (TAIL) {
+        const long cut = ntiles % cus;
+        const int jobs = (int)(cut * TL::NW * TL::MI * (TL::NB / NSET / 2));
+        hipLaunchKernelGGL((tail_kernel<NSET, TL, Epi>), dim3((unsigned)((jobs + 3) / 4)), dim3(256), 0, st, p, epi,
+                           (int)(ntiles - cut), jobs);
+    }
     return hipGetLastError();
 }
 
@@ -654,29 +810,78 @@ constexpr double step_us(int rows) { return rows == 256 ? 0.90 : rows == 192 ? 0
 // and fewer CUs of the last round.  128 rows of a 256-row segment read the merged operand twice: 64 segments, K = 4096,
 // N = 1536 take 297 us in two rounds of 256 rows and 317 in three of 128 (dX of the same 527 and 593), 32 segments,
 // K = 2816, N = 1024 94 in half a round of 256 and 67 in one of 128.
-inline int tile_rows(const Params &p, int bns)
+struct Form {
+    int rows;
+    int pieces;   // K slices of a tile of the last round, 0 where it is not cut
+};
+
+// With scratch for its partial sums (p.tail) a last round that leaves CUs without a tile may be cut over K, one slice for
+// each CU: it costs its share of the steps, the sums a CU writes (45 KB a us) and a launch that adds them (4.5 us and
+// the rate of the memory-side cache).
+inline Form tile_form(const Params &p, int bns, int nsrc)
 {
-    int best = 256;
-    double t = step_us(256) * rounds_of(p, 256, bns);
-    for (int rows = 192; rows >= 64; rows -= 64) {
-        const double r = step_us(rows) * rounds_of(p, rows, bns);
-        if (r < t) {
-            t = r;
-            best = rows;
+    const int cus = cu_count(), steps = p.K / BK * nsrc;
+    Form best = {256, 0};
+    double best_t = 0;
+    for (int rows = 256; rows >= 64; rows -= 64) {
+        const double us = step_us(rows);
+        const double t = us * steps * rounds_of(p, rows, bns);
+        if (rows == 256 || t < best_t) {
+            best = {rows, 0};
+            best_t = t;
+        }
+        const long tiles = (long)p.batches * ((p.M + rows - 1) / rows) * ((p.N + bns - 1) / bns), cut = tiles % cus;
+        if (!p.tail || cut == 0) continue;
+        const double kb = rows * 256 * 4 / 1000.0;
+        for (int n = 2; cut * n <= cus && 4 * n <= steps && (size_t)(cut * n) * rows * 256 <= p.tail_floats; ++n) {
+            const double c = us * (steps * (double)(tiles / cus) + (steps + n - 1) / n + 2) + kb / 45.0 + 4.5 + cut * n * kb / 4000.0;
+            if (c < 0.97 * best_t) {
+                best = {rows, n};
+                best_t = c;
+            }
         }
     }
     return best;
 }
 
-template <int NSET, int NSRC, bool A_MC, bool B_NC, class Epi>
-inline hipError_t launch_rows(const Params &p, const Epi &e, hipStream_t st)
+inline size_t tail_floats(const Params &p, const Form &f, int bns)
 {
-    switch (tile_rows(p, 256 / NSET)) {
-    case 256: return launch<NSET, NSRC, A_MC, B_NC, std::conditional_t<NSET == 2, T256x2, T256>>(p, e, st);
-    case 192: return launch<NSET, NSRC, A_MC, B_NC, T192>(p, e, st);
-    case 128: return launch<NSET, NSRC, A_MC, B_NC, T128>(p, e, st);
-    default: return launch<NSET, NSRC, A_MC, B_NC, T64>(p, e, st);
+    const long tiles = (long)p.batches * ((p.M + f.rows - 1) / f.rows) * ((p.N + bns - 1) / bns);
+    return (size_t)(tiles % cu_count()) * f.pieces * f.rows * 256;
+}
+
+inline int tile_rows(const Params &p, int bns)
+{
+    Params q = p;
+    q.K = BK;   // the rounds alone decide
+    q.tail = nullptr;
+    return tile_form(q, bns, 1).rows;
+}
+
+template <int NSET, int NSRC, bool A_MC, bool B_NC, class Epi, bool TAIL>
+inline hipError_t launch_tile(int rows, const Params &p, const Epi &e, hipStream_t st)
+{
+    switch (rows) {
+    case 256: return launch<NSET, NSRC, A_MC, B_NC, std::conditional_t<NSET == 2, T256x2, T256>, Epi, TAIL>(p, e, st);
+    case 192: return launch<NSET, NSRC, A_MC, B_NC, T192, Epi, TAIL>(p, e, st);
+    case 128: return launch<NSET, NSRC, A_MC, B_NC, T128, Epi, TAIL>(p, e, st);
+    default: return launch<NSET, NSRC, A_MC, B_NC, T64, Epi, TAIL>(p, e, st);
     }
+}
+
+template <int NSET, int NSRC, bool A_MC, bool B_NC, class Epi>
+inline hipError_t launch_rows(const Params &p0, const Epi &e, hipStream_t st)
+{
+    const Form f = tile_form(p0, 256 / NSET, NSRC);
+    // an instance of its own for the cut round: its code costs every launch 1 .. 2 us
+    if constexpr (Epi::TAIL) {
+        if (f.pieces) {
+            Params p = p0;
+            p.pieces = f.pieces;
+            return launch_tile<NSET, NSRC, A_MC, B_NC, Epi, true>(f.rows, p, e, st);
+        }
+    }
+    return launch_tile<NSET, NSRC, A_MC, B_NC, Epi, false>(f.rows, p0, e, st);
 }
 
 // Tile of a weight gradient (K = tokens of a segment): both heights take the same time per element

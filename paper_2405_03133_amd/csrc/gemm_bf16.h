@@ -25,6 +25,9 @@ struct Params {
     int M, N, K;           // per batch item; K per source
     int batches;           // split contraction: ksplit entries per batch item
     int ksplit;            // K slices per batch item (split epilogues only)
+    float *tail;           // scratch for the partial sums of a last round of tiles that is cut over K, or NULL
+    size_t tail_floats;
+    int pieces;            // set by the launch: K slices of a tile of that round (0: none is cut)
 };
 
 __device__ __forceinline__ float bf16_bits_to_float(uint16_t b)

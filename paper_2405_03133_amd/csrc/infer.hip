@@ -329,12 +329,19 @@ size_t dense_min_workspace_bytes(const Dims &m) { return base_bytes(m); }
 
 DenseForm dense_form(const Dims &m) { return bf16_dense_form(m, gemm_scratch(m)); }
 
-size_t dense_workspace_bytes(const Dims &m)
+// What the ring GEMM needs to take all rows at once (or in the blocks of a fixed scratch).
+static size_t dense_whole_bytes(const Dims &m)
 {
     const size_t base = base_bytes(m);
-    if (m.dtype == LORY_F32) return base;
     const size_t n = bf16_dense_workspace_bytes(m, gemm_scratch(m));
     return n > base ? n : base;
+}
+
+size_t dense_workspace_bytes(const Dims &m)
+{
+    if (m.dtype == LORY_F32) return base_bytes(m);
+    const size_t n = dense_whole_bytes(m), tail = align_up(bf16_dense_tail_bytes(m, gemm_scratch(m)), 256);
+    return n > tail ? n : tail;
 }
 
 int dense_ffn_fwd(const Dims &m, const void *X, const void *Wbar, void *Y, void *ws, size_t ws_bytes, hipStream_t st)
@@ -343,8 +350,8 @@ int dense_ffn_fwd(const Dims &m, const void *X, const void *Wbar, void *Y, void 
     // the streaming path keeps to the least workspace, so that a call runs the same way whatever it is given
     int rc = LORY_OK;
     if (bf16_dense_stream(m, X, Wbar, Y, ws, base_bytes(m), st, &rc)) return rc;
-    if (ws_bytes >= dense_workspace_bytes(m)) return bf16_dense_ffn_fwd(m, X, Wbar, Y, ws, gemm_scratch(m), st);
-    return bf16_dense_ffn_fwd(m, X, Wbar, Y, ws, DenseScratch{base_bytes(m), true}, st);
+    if (ws_bytes >= dense_whole_bytes(m)) return bf16_dense_ffn_fwd(m, X, Wbar, Y, ws, ws_bytes, gemm_scratch(m), st);
+    return bf16_dense_ffn_fwd(m, X, Wbar, Y, ws, ws_bytes, DenseScratch{base_bytes(m), true}, st);
 }
 
 }  // namespace lory

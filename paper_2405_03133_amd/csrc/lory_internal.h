@@ -110,8 +110,9 @@ struct DenseForm {
 };
 DenseForm bf16_dense_form(const Dims &m, const DenseScratch &scratch);
 DenseForm dense_form(const Dims &m);
-int bf16_dense_ffn_fwd(const Dims &m, const void *X, const void *Wbar, void *Y, void *ws, const DenseScratch &scratch,
-                       hipStream_t st);
+size_t bf16_dense_tail_bytes(const Dims &m, const DenseScratch &scratch);   // workspace for a cut last round, or 0
+int bf16_dense_ffn_fwd(const Dims &m, const void *X, const void *Wbar, void *Y, void *ws, size_t ws_bytes,
+                       const DenseScratch &scratch, hipStream_t st);
 // Blocks of at most 16 rows, weights streamed; false where they take more rows or more scratch than ws_bytes.
 bool bf16_dense_stream(const Dims &m, const void *X, const void *Wbar, void *Y, void *ws, size_t ws_bytes, hipStream_t st,
                        int *rc);

@@ -308,6 +308,48 @@ def test_bf16_ring_gemm_edge_tiles_without_saved_planes(cfg):
     check(f"{cfg.name} Y", host(Y), ref, TOL["bf16"])
 
 
+# A last round of tiles cut over K, with every tile height: no whole round before it or one, edge tiles, K slices that
+# begin in the first or second source of dX or span both, and slices of different lengths.
+TAIL_CASES = [
+    LoryConfig("tail_T320", B=2, L=960, T=320, d=320, d_ff=4160, E=3, dtype="bf16", seed=101),
+    LoryConfig("tail_T64", B=3, L=256, T=64, d=128, d_ff=4096, E=17, dtype="bf16", seed=102),
+    LoryConfig("tail_T192", B=1, L=2688, T=192, d=320, d_ff=4032, E=3, dtype="bf16", seed=103),
+    LoryConfig("tail_wide", B=2, L=1024, T=256, d=2880, d_ff=192, E=3, dtype="bf16", seed=104),
+]
+
+
+@pytest.mark.parametrize("cfg", TAIL_CASES, ids=lambda c: c.name)
+def test_bf16_ring_gemm_cut_last_round(cfg):
+    t = make_inputs(cfg, structured=True)
+    got = run_layer(cfg, t)
+    compare(cfg, got, oracle_layer(cfg, t, got["w_used"]), ALL, TOL["bf16"])
+    saved = run_layer(cfg, t, merged_save=True)
+    for key in ALL:
+        assert np.array_equal(got[key], saved[key]), key
+
+
+def test_dense_block_cut_last_round():
+    cfg = LoryConfig("dense_tail", B=2, L=2048, T=2048, d=768, d_ff=4160, E=2, dtype="bf16", seed=105)
+    print(f"[gpu] {cfg}", flush=True)
+    t = make_inputs(cfg, with_dy=False)
+    Wbar = torch.stack([to_dev(t[k], cfg).reshape(2, -1) for k in ("Wg", "Wu", "Wd")]).contiguous()
+    X = to_dev(t["X"], cfg)
+    shape = lb.make_shape(2, cfg.L, cfg.L, cfg.d, cfg.d_ff, 1, X.dtype)
+    need = lb.lory_workspace_bytes(shape, lb.LORY_PASS_DENSE)
+    assert need > cfg.tokens * cfg.d_ff * 2
+    ref = orc.ffn_fwd(t["X"], np.eye(2), t["Wg"], t["Wu"], t["Wd"], cfg.L)["Y"]
+    # with the reported workspace, and with one that holds the activation alone
+    for size in (need, cfg.tokens * cfg.d_ff * 2):
+        ws = torch.full((size + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+        Y = torch.full_like(X, float("nan"))
+        rc = lb.lib().lory_dense_ffn_fwd(ctypes.byref(shape), X.data_ptr(), Wbar.data_ptr(), Y.data_ptr(), ws.data_ptr(),
+                                         size, torch.cuda.current_stream().cuda_stream)
+        assert rc == lb.LORY_OK, lb.status_string(rc)
+        torch.cuda.synchronize()
+        assert bool((ws[size:] == 0x5A).all())
+        check(f"{size} bytes", host(Y), ref, TOL["bf16"])
+
+
 def test_bf16_recompute_bf16_grads_and_accumulate(default_budget):
     cfg = BF16_CASES[0][0]
     lb.lory_set_slab_budget(1 << 20)
