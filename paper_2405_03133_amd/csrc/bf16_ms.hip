@@ -67,15 +67,29 @@ hipError_t launch_merge(hipStream_t st, const ms::MergeParams &p)
     const int MB = (p.S + 31) / 32;
     const size_t lds = (size_t)MB * KS * 2 * 64 * 16;
     if (lds > 64 * 1024) return hipErrorInvalidValue;
+    // One workgroup fits a CU.  Each pays about 3 us for its start (routing-weight operands, first loads), several in
+    // turn even out what the CUs get done: short launches take one round of workgroups, long ones four.  us per forward
+    // pass with its three merges in 256 / 512 / 1024 workgroups, by what a merge reads + writes, MB: 37 + 18 (32 experts
+    // 768 x 768, 16 segments) 74.5 / 81.4 / 89.3, 184 + 92 231 / 237 / 251, 92 + 184 297 / 308 / 320, 184 + 184
+    // 346 / 342 / 353, 46 + 369 546 / 519 / 505, 184 + 369 623 / 608 / 608, 369 + 738 1152 / 1138 / 1131; three prompts
+    // of 16 experts, 369 + 69, 281 / 282 / 295.
+    const double n = 2e-6 * p.rc.nr * p.rc.nc, mb = n * (p.E + p.S);
+    const int most = mb < 280 || (mb < 450 && p.E >= 4 * p.S) ? gemm2::cu_count() : mb < 380 ? 2 * gemm2::cu_count() : kMsGrid;
     int grid = (units_of(p.rc) + 3) / 4;
-    if (grid > kMsGrid) grid = kMsGrid;
+    if (grid > most) grid = most;
+#define LORY_MERGE(K)                                                                              \
+    if (p.seg_map)                                                                                 \
+        hipLaunchKernelGGL((ms::merge_kernel<K, true>), dim3(grid), dim3(256), lds, st, p);        \
+    else                                                                                           \
+        hipLaunchKernelGGL((ms::merge_kernel<K, false>), dim3(grid), dim3(256), lds, st, p)
     switch (KS) {
-    case 1: hipLaunchKernelGGL(ms::merge_kernel<1>, dim3(grid), dim3(256), lds, st, p); break;
-    case 2: hipLaunchKernelGGL(ms::merge_kernel<2>, dim3(grid), dim3(256), lds, st, p); break;
-    case 3: hipLaunchKernelGGL(ms::merge_kernel<3>, dim3(grid), dim3(256), lds, st, p); break;
-    case 4: hipLaunchKernelGGL(ms::merge_kernel<4>, dim3(grid), dim3(256), lds, st, p); break;
+    case 1: LORY_MERGE(1); break;
+    case 2: LORY_MERGE(2); break;
+    case 3: LORY_MERGE(3); break;
+    case 4: LORY_MERGE(4); break;
     default: return hipErrorInvalidValue;
     }
+#undef LORY_MERGE
     return hipGetLastError();
 }
 

@@ -170,6 +170,16 @@ Rect rect(long D, int pitch, int r0, int nr, int c0, int nc)
     return rc;
 }
 
+// The map of segments that share their merged values (MergeParams::seg_map), in memory that lies unused between two
+// places while the slab is written and read; NULL where there is too little.
+constexpr size_t kMapElems = ms::kMapSegments * sizeof(int32_t) / sizeof(bf) + 128;   // with the rounding to 256 bytes
+
+int32_t *map_place(int S, void *from, void *to)
+{
+    const size_t a = align_up((size_t)from, 256);
+    return S > 1 && S <= ms::kMapSegments && a + ms::kMapSegments * sizeof(int32_t) <= (size_t)to ? (int32_t *)a : nullptr;
+}
+
 // Scratch for a cut last round of tiles: what lies unused between two places of the workspace while the GEMM runs.
 // Only where the transient slab holds the whole matrix, and the same scratch whether the merged parameters are saved or
 // not: the sums of the two modes are then added in the same order.
@@ -186,7 +196,8 @@ double gemm_flops(const Params &p, int nset, int nsrc)
     return 2.0 * p.batches * p.M * p.N * p.K * nset * nsrc;
 }
 
-hipError_t merge(hipStream_t st, const float *w, int S, int E, const bf *stack, const Rect &rc, bf *slab)
+hipError_t merge(hipStream_t st, const float *w, int S, int E, const bf *stack, const Rect &rc, bf *slab,
+                 int32_t *seg_map = nullptr)
 {
     const double n = (double)rc.nr * rc.nc;
     prof::Range r(st, prof::kMerge, 2.0 * S * E * n, 2.0 * n * (E + S));
@@ -198,22 +209,25 @@ hipError_t merge(hipStream_t st, const float *w, int S, int E, const bf *stack, 
     p.rc = rc;
     p.slab = slab;
     p.seg_stride = (long)rc.nr * rc.nc;
+    p.seg_map = seg_map;
     return k::launch_merge(st, p);
 }
 
 // Gate/up projections of one d_ff column block for a chunk of segments.
 hipError_t gate_up_block(hipStream_t st, const Dims &m, int S, const bf *X, const float *w, const bf *Wg,
-                         const bf *Wu, int n0, int nf, bf *slab, bf *G, bf *U, bf *Act, bf *slab_up = nullptr)
+                         const bf *Wu, int n0, int nf, bf *slab, bf *G, bf *U, bf *Act, bf *slab_up = nullptr,
+                         int32_t *seg_map = nullptr)
 {
     bf *sg = slab, *su = slab_up ? slab_up : slab + (size_t)S * m.d * nf;
     const Rect rc = rect(m.D, m.dff, 0, m.d, n0, nf);
     hipError_t e;
-    if ((e = merge(st, w, S, m.E, Wg, rc, sg)) != hipSuccess) return e;
-    if ((e = merge(st, w, S, m.E, Wu, rc, su)) != hipSuccess) return e;
+    if ((e = merge(st, w, S, m.E, Wg, rc, sg, seg_map)) != hipSuccess) return e;
+    if ((e = merge(st, w, S, m.E, Wu, rc, su, seg_map)) != hipSuccess) return e;
     Params p = {};
     p.A[0] = X; p.a_batch[0] = (long)m.T * m.d; p.lda[0] = m.d;
     p.B[0] = sg; p.b_batch[0] = (long)m.d * nf; p.ldb[0] = nf;
     p.B[1] = su; p.b_batch[1] = (long)m.d * nf; p.ldb[1] = nf;
+    p.b_map = seg_map;
     p.M = m.T; p.N = nf; p.K = m.d; p.batches = S;
     // With G and U saved anyway, the activation A = silu(G) * U is cheaper as a streaming pass
     // over them than as a third output plane of the GEMM epilogue; without saved G, U it is
@@ -306,6 +320,10 @@ int bf16_ffn_fwd(const Dims &m, const void *Xv, const float *w, const void *Wgv,
         const bf *Xc = X + (size_t)s0 * TD;
         bf *Gc = G ? G + (size_t)s0 * TF : nullptr;
         bf *Uc = U ? U + (size_t)s0 * TF : nullptr;
+        // Y is written by the down projection alone: until then it holds the map (unless it is X as well)
+        const char *y0 = (const char *)(Y + (size_t)s0 * TD), *y1 = y0 + sizeof(bf) * S * TD;
+        const char *x0 = (const char *)X, *x1 = x0 + sizeof(bf) * m.tokens * m.d;
+        int32_t *map_gu = (y1 <= x0 || x1 <= y0) ? map_place(S, (void *)y0, (void *)y1) : nullptr;
         // gate / up projections + SwiGLU, one d_ff column block at a time
         for (int n0 = 0; n0 < m.dff; n0 += pl.nf_fwd) {
             const int nf = (m.dff - n0 < pl.nf_fwd) ? (m.dff - n0) : pl.nf_fwd;
@@ -313,18 +331,21 @@ int bf16_ffn_fwd(const Dims &m, const void *Xv, const float *w, const void *Wgv,
                 LORY_TRY(gate_up_block(st, m, S, Xc, wc, Wg, Wu, n0, nf, Wbar, Gc, Uc, Act,
                                        Wbar + (size_t)m.S * m.D));
             else
-                LORY_TRY(gate_up_block(st, m, S, Xc, wc, Wg, Wu, n0, nf, slab, Gc, Uc, Act));
+                LORY_TRY(gate_up_block(st, m, S, Xc, wc, Wg, Wu, n0, nf, slab, Gc, Uc, Act, nullptr, map_gu));
         }
         // down projection, one block of output columns at a time
         for (int j0 = 0; j0 < m.d; j0 += pl.jf_fwd) {
             const int jf = (m.d - j0 < pl.jf_fwd) ? (m.d - j0) : pl.jf_fwd;
             bf *sd = Wbar ? Wbar + (size_t)2 * m.S * m.D : slab;
-            LORY_TRY(merge(st, wc, S, m.E, Wd, rect(m.D, m.d, 0, m.dff, j0, jf), sd));
+            bf *past = slab + (size_t)S * m.dff * jf;
+            int32_t *map = Wbar ? nullptr : map_place(S, past, (char *)slab + pl.slab_fwd);
+            LORY_TRY(merge(st, wc, S, m.E, Wd, rect(m.D, m.d, 0, m.dff, j0, jf), sd, map));
             Params p = {};
+            p.b_map = map;
             p.A[0] = Act; p.a_batch[0] = TF; p.lda[0] = m.dff;
             p.B[0] = sd; p.b_batch[0] = (long)m.dff * jf; p.ldb[0] = jf;
             p.M = m.T; p.N = jf; p.K = m.dff; p.batches = S;
-            set_tail(p, whole_d, slab + (size_t)S * m.dff * jf, (char *)slab + pl.slab_fwd);
+            set_tail(p, whole_d, past + kMapElems, (char *)slab + pl.slab_fwd);
             EpiStore epi = {Y + (size_t)s0 * TD + j0, TD, m.d};
             prof::Range r(st, prof::kGemmDown, gemm_flops(p, 1, 1),
                           2.0 * ((double)S * TF + (double)S * m.dff * jf + (double)S * m.T * jf));
@@ -704,15 +725,17 @@ int bf16_ffn_bwd(const Dims &m, const void *Xv, const float *w, const void *Wgv,
             const Rect cols_f = rect(m.D, m.dff, 0, m.d, n0, nf);    // columns n0.. of Wg/Wu [d, d_ff]
 
             // dA = dY Wd_bar^T for these d_ff columns, then the SwiGLU backward pass: dG, dU, A
-            if (!Wbar && !fused) LORY_TRY(merge(st, wc, S, m.E, Wd, rows_d, s_md));
+            int32_t *map = Wbar ? nullptr : map_place(S, s_gd, (char *)slab + pl.slab_bwd);   // the gradient slabs are written later
+            if (!Wbar && !fused) LORY_TRY(merge(st, wc, S, m.E, Wd, rows_d, s_md, map));
             if (!fused) {
                 Params p = {};
+                p.b_map = map;
                 p.A[0] = dYc; p.a_batch[0] = TD; p.lda[0] = m.d;
                 p.B[0] = Wbar ? Wbar_d + (size_t)n0 * m.d : s_md;
                 p.b_batch[0] = Wbar ? m.D : (long)nf * m.d;
                 p.ldb[0] = m.d;
                 p.M = m.T; p.N = nf; p.K = m.d; p.batches = S;
-                set_tail(p, nf == m.dff, s_gd, (char *)slab + pl.slab_bwd);   // the gradient slabs are written later
+                set_tail(p, nf == m.dff, s_gd + kMapElems, (char *)slab + pl.slab_bwd);
                 EpiStore epi = {dG + n0, TF, m.dff};  // dA parks in the dG buffer
                 {
                     prof::Range r(st, prof::kGemmDA, gemm_flops(p, 1, 1),
@@ -781,11 +804,13 @@ int bf16_ffn_bwd(const Dims &m, const void *Xv, const float *w, const void *Wgv,
             const size_t blk = (size_t)S * kf * m.dff;
             bf *s_g = slab, *s_u = slab + blk;
             const Rect rows = rect(m.D, m.dff, k0, kf, 0, m.dff);
+            int32_t *map = Wbar ? nullptr : map_place(S, slab + 2 * blk, (char *)slab + pl.slab_bwd);
             if (!Wbar) {
-                LORY_TRY(merge(st, wc, S, m.E, Wg, rows, s_g));
-                LORY_TRY(merge(st, wc, S, m.E, Wu, rows, s_u));
+                LORY_TRY(merge(st, wc, S, m.E, Wg, rows, s_g, map));
+                LORY_TRY(merge(st, wc, S, m.E, Wu, rows, s_u, map));
             }
             Params p = {};
+            p.b_map = map;
             p.A[0] = dG; p.a_batch[0] = TF; p.lda[0] = m.dff;
             p.A[1] = dU; p.a_batch[1] = TF; p.lda[1] = m.dff;
             p.B[0] = Wbar ? Wbar_g + (size_t)k0 * m.dff : s_g;
@@ -793,7 +818,7 @@ int bf16_ffn_bwd(const Dims &m, const void *Xv, const float *w, const void *Wgv,
             p.b_batch[0] = p.b_batch[1] = Wbar ? m.D : (long)kf * m.dff;
             p.ldb[0] = p.ldb[1] = m.dff;
             p.M = m.T; p.N = kf; p.K = m.dff; p.batches = S;
-            set_tail(p, kf == m.d, slab + 2 * blk, (char *)slab + pl.slab_bwd);
+            set_tail(p, kf == m.d, slab + 2 * blk + kMapElems, (char *)slab + pl.slab_bwd);
             EpiStore epi = {dX + (size_t)s0 * TD + k0, TD, m.d};
             prof::Range r(st, prof::kGemmDX, gemm_flops(p, 1, 2),
                           2.0 * (2.0 * S * TF + 2.0 * S * kf * m.dff + (double)S * m.T * kf));

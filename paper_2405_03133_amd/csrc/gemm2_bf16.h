@@ -297,6 +297,11 @@ __global__ __launch_bounds__(TL::threads, TL::waves_per_simd) void gemm2_kernel(
                 offB[q] = 2u * ((uint32_t)rr * (uint32_t)p.ldb[0] + 8u * c);
             }
         }
+        if constexpr (!Epi::SPLIT) {
+            // a scalar load: a vector load would count among the ring's
+            typedef const __attribute__((address_space(4))) int32_t *const_ptr;
+            if (p.b_map) batch = ((const_ptr)p.b_map)[batch];
+        }
         const long in_b = B_NC ? (long)n0 : (long)n0 * p.ldb[0];
         const int s = (NSET == 2) ? bset : 0;
         ptrB = reinterpret_cast<const char *>(s ? p.B[1] : p.B[0]) + 2 * ((long)batch * (s ? p.b_batch[1] : p.b_batch[0]) + in_b);

@@ -22,6 +22,7 @@ struct Params {
     const uint16_t *B[2];  // per operand set (NSET == 2) or per source (NSRC == 2)
     long b_batch[2];
     int ldb[2];
+    const int32_t *b_map;  // batch item whose B operand an item reads, or NULL: its own
     int M, N, K;           // per batch item; K per source
     int batches;           // split contraction: ksplit entries per batch item
     int ksplit;            // K slices per batch item (split epilogues only)

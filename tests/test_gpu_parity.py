@@ -308,6 +308,44 @@ def test_bf16_ring_gemm_edge_tiles_without_saved_planes(cfg):
     check(f"{cfg.name} Y", host(Y), ref, TOL["bf16"])
 
 
+# Segments with equal routing rows share their merged values: runs that start, end and cross at the 32- and 64-segment
+# words, one run over everything, rows equal but not adjacent, and none.  The saved mode stores every segment, so its bits
+# are the reference for the sharing mode's.
+@pytest.mark.parametrize("cfg", [
+    LoryConfig("shared_S150", B=5, L=3840, T=128, d=64, d_ff=128, E=5, dtype="bf16", seed=111),
+    LoryConfig("shared_E33", B=2, L=4096, T=128, d=64, d_ff=64, E=33, dtype="bf16", seed=112),
+], ids=lambda c: c.name)
+@pytest.mark.parametrize("runs", ["words", "all", "alternating", "none"])
+def test_bf16_equal_routing_rows(cfg, runs):
+    t = make_inputs(cfg, structured=True)
+    w = make_routing_weights(cfg, "peaked")
+    if runs == "words":
+        for a, b in ((0, 2), (31, 33), (40, 64), (64, 66), (100, cfg.S)):
+            w[a:min(b, cfg.S)] = w[a if a < cfg.S else 0]
+    elif runs == "all":
+        w[:] = w[0]
+    elif runs == "alternating":
+        w[0::2], w[1::2] = w[0], w[1]
+    w = np.ascontiguousarray(w, dtype=np.float32)
+    for save in (True, False):   # the second recomputes G and U in the backward
+        got, saved = (run_layer(cfg, t, w_override=w, save=save, merged_save=m) for m in (False, True))
+        for key in ("Y", "dX", "dWg", "dWu", "dWd", "dw"):
+            assert np.array_equal(got[key], saved[key]), key
+
+
+def test_bf16_forward_in_place():
+    """Y may be X: the down projection writes it after everything that reads X."""
+    cfg = LoryConfig("in_place", B=2, L=512, T=128, d=128, d_ff=192, E=4, dtype="bf16", seed=113)
+    t = make_inputs(cfg, structured=True, with_dy=False)
+    X, Wg, Wu, Wd = (to_dev(t[k], cfg) for k in ("X", "Wg", "Wu", "Wd"))
+    w = lb.lory_route(X, to_dev(t["R"], cfg), cfg.T, d_ff=cfg.d_ff)
+    Y = lb.lory_merged_ffn_fwd(X, w, Wg, Wu, Wd, cfg.T)
+    Z = X.clone()
+    lb.lory_merged_ffn_fwd(Z, w, Wg, Wu, Wd, cfg.T, Y=Z)
+    torch.cuda.synchronize()
+    assert torch.equal(Y, Z)
+
+
 # A last round of tiles cut over K, with every tile height: no whole round before it or one, edge tiles, K slices that
 # begin in the first or second source of dX or span both, and slices of different lengths.
 TAIL_CASES = [
