@@ -1,4 +1,4 @@
-// Dense FFN of at most 16 token rows per sequence: plan and launches of the streaming projections.
+// Dense FFN of few token rows per sequence: plans and launches of the streaming projections.
 #include "dense_stream_bf16.h"
 
 namespace lory {
@@ -53,9 +53,22 @@ DenseStream dense_stream_plan(int B, int M, int d, int dff, size_t floats)
     return p;
 }
 
+int dense_stream_gu_slices(int B, int M, int d, int dff, size_t floats)
+{
+    if (M <= stream::kMaxRows || M > stream::kMaxGuRows || B > 32767 || d >= (1 << 26) || dff >= (1 << 26)) return 0;
+    const long cols = (dff + stream::kCols - 1) / stream::kCols;
+    const size_t fg = (size_t)2 * B * M * dff;
+    if (floats < fg) return 0;
+    // every sum is written once and read once
+    return slices(2 * B * cols, d / 32, kGuWaves, 1.2, 8.0 * fg / 12e6, 0.0, 1, floats / fg);
+}
+
 hipError_t launch_dense_stream_gu(hipStream_t st, const stream::Params &p, int B)
 {
-    return stream::launch<false, kGuWaves, 2>(st, p, B);
+    if (p.M <= 16) return stream::launch<false, kGuWaves, 2>(st, p, B);
+    if (p.M <= 32) return stream::launch<false, kGuWaves, 2, 2>(st, p, B);
+    if (p.M <= 48) return stream::launch<false, kGuWaves, 2, 3>(st, p, B);
+    return stream::launch<false, kGuWaves, 2, 4>(st, p, B);
 }
 
 hipError_t launch_dense_stream_down(hipStream_t st, const stream::Params &p, int B)

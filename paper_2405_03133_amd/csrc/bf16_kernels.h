@@ -13,7 +13,7 @@ namespace stream {
 
 // One projection of the streaming dense FFN (dense_stream_bf16.h).
 struct Params {
-    int M, K, N;           // rows per sequence (at most 16); K a multiple of 32, N of 8
+    int M, K, N;           // rows per sequence; K a multiple of 32, N of 8
     int ks;                // K slices of the contraction
     const uint16_t *W[2];  // [batches][K][N]: gate and up, or down
     long w_batch;
@@ -207,6 +207,8 @@ struct DenseStream {
     int gu, down;
 };
 DenseStream dense_stream_plan(int B, int M, int d, int dff, size_t floats);
+// Its gate/up projections alone, for 17 .. 64 rows: K slices, 0 where it does not take them.
+int dense_stream_gu_slices(int B, int M, int d, int dff, size_t floats);
 hipError_t launch_dense_stream_gu(hipStream_t st, const stream::Params &p, int B);
 hipError_t launch_dense_stream_down(hipStream_t st, const stream::Params &p, int B);
 

@@ -16,6 +16,15 @@
 // one token, d = 1024, d_ff = 2816 (17 MB) 20.0 -> 13.5 replayed from a graph, 19.5 -> 15.5 launched one by one; 4 at
 // d = 2048, d_ff = 5632 (277 MB) 59.5 -> 52.1, 5.3 TB/s.  Unsplit, with the activation in the epilogue of gate/up, the
 // same kernels took 21.2 for the first: too few CUs read.
+//
+// Gate/up alone also for 17 .. 63 rows, 2 .. 4 row blocks per wavefront against the same weights; their sums leave for the
+// launch that forms the activation, and the down projection stays on the ring GEMM (the activation of that many rows in
+// two terms does not fit in LDS beside its sums, and every column block would form it again).  The weights
+// skip LDS, and a barrier per K step with it.  us per call, ring GEMM -> this: 2 x 40 rows at
+// d = 2048, d_ff = 5632 52.1 -> 46.4, 2 x 50 at 1536, 4096 39.5 -> 36.9, 3 x 45 at 768, 2048 27.8 -> 25.5, 24 at 1024,
+// 2816 21.7 -> 20.8, 18 .. 33 at 2048, 5632 unchanged.  64 rows are slower (32.5 -> 34.4 at 2048, 5632), two workgroups
+// sharing the rows of more are as well (2 x 100 63 -> 74: the weights pass through the CUs twice), and the accumulators
+// of 96 rows spill.
 #pragma once
 
 #include "bf16_kernels.h"
@@ -28,6 +37,7 @@ using gemm::u32x4;
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kMaxRows = 16;
+constexpr int kMaxGuRows = 63;   // of gate/up alone
 constexpr int kCols = 128;   // columns of a workgroup
 
 template <class F, int... D>
@@ -38,10 +48,13 @@ __device__ __forceinline__ void each_of(F &&f, std::integer_sequence<int, D...>)
 
 // DOWN: x is formed from the gate/up sums and leaves as bf16 or, where the contraction is cut, as partial sums; else
 // gate or up (blockIdx.z & 1), partial sums.  NW: wavefronts.  DEPTH: K steps of a wavefront in flight.
-template <bool DOWN, int NW, int DEPTH>
+// MT: blocks of 16 rows.
+template <bool DOWN, int NW, int DEPTH, int MT>
 __global__ __launch_bounds__(NW * 64) void dense_stream_kernel(const Params p)
 {
+    static_assert(!DOWN || MT == 1, "the activation of a slice of many rows does not fit in LDS");
     constexpr int TERMS = DOWN ? 2 : 1, SETS = DOWN ? 1 : 2;
+    constexpr int XF = DOWN ? TERMS : MT;   // row fragments of a step
     extern __shared__ __attribute__((aligned(16))) char smem[];
     uint16_t *act = reinterpret_cast<uint16_t *>(smem);   // DOWN: [2][M][slice]
     float *red = reinterpret_cast<float *>(smem);         // afterwards: [NW][M][kCols]
@@ -52,7 +65,7 @@ __global__ __launch_bounds__(NW * 64) void dense_stream_kernel(const Params p)
     const int sl = blockIdx.y, b = blockIdx.z / SETS, set = blockIdx.z % SETS, batches = gridDim.z / SETS;
     const int n0 = blockIdx.x * kCols;
     const int nc = n0 + 8 * c < p.N ? n0 + 8 * c : p.N - 8;   // columns beyond the matrix are not stored
-    const int m = c < p.M ? c : p.M - 1;                      // nor are rows beyond the block
+    auto row = [&](int t) { return 16 * t + c < p.M ? 16 * t + c : p.M - 1; };   // nor are rows beyond the block
     const int total = p.K / 32;
     const int s0 = (int)((long)total * sl / p.ks), steps = (int)((long)total * (sl + 1) / p.ks) - s0;
     const int len = steps * 32;
@@ -62,26 +75,34 @@ __global__ __launch_bounds__(NW * 64) void dense_stream_kernel(const Params p)
     const uint32_t offW = 2u * ((uint32_t)(8 * g) * (uint32_t)p.N + (uint32_t)nc);
     const char *x = nullptr;
     if constexpr (!DOWN) x = reinterpret_cast<const char *>(p.x + (size_t)b * p.x_batch + s0 * 32);
-    const uint32_t offX = DOWN ? (uint32_t)m * (uint32_t)len + 8u * g : 2u * ((uint32_t)m * (uint32_t)p.K + 8u * g);
+    uint32_t offX[MT];
+#pragma unroll
+    for (int t = 0; t < MT; ++t)
+        offX[t] = DOWN ? (uint32_t)row(t) * (uint32_t)len + 8u * g : 2u * ((uint32_t)row(t) * (uint32_t)p.K + 8u * g);
 
     u32x4 wr[DEPTH][8];
-    bf16x8 xr[DEPTH][TERMS];
-    f32x4 acc[8];
+    bf16x8 xr[DEPTH][XF];
+    f32x4 acc[MT][8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) acc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < MT; ++t)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     auto load = [&](auto buf, int step) {
         const size_t k = (size_t)step * 32;
 #pragma unroll
         for (int i = 0; i < 8; ++i)
             wr[buf][i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(W + (k + i) * p.N * 2 + offW));
-        if constexpr (!DOWN) xr[buf][0] = *reinterpret_cast<const bf16x8 *>(x + 2 * k + offX);
+        if constexpr (!DOWN) {
+#pragma unroll
+            for (int t = 0; t < MT; ++t) xr[buf][t] = *reinterpret_cast<const bf16x8 *>(x + 2 * k + offX[t]);
+        }
     };
     auto multiply = [&](auto buf, int step) {
         if constexpr (DOWN) {
 #pragma unroll
             for (int t = 0; t < TERMS; ++t)
-                xr[buf][t] = *reinterpret_cast<const bf16x8 *>(act + (size_t)t * p.M * len + offX + step * 32);
+                xr[buf][t] = *reinterpret_cast<const bf16x8 *>(act + (size_t)t * p.M * len + offX[0] + step * 32);
         }
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
@@ -94,8 +115,11 @@ __global__ __launch_bounds__(NW * 64) void dense_stream_kernel(const Params p)
                 o.w[ip] = __builtin_amdgcn_perm(wr[buf][2 * ip + 1][j >> 1], wr[buf][2 * ip][j >> 1],
                                                 (j & 1) ? 0x07060302u : 0x05040100u);
 #pragma unroll
-            for (int t = 0; t < TERMS; ++t)
-                acc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xr[buf][t], o.v, acc[j], 0, 0, 0);
+            for (int t = 0; t < XF; ++t) {
+                f32x4 &a = acc[DOWN ? 0 : t][j];
+                a = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xr[buf][t], o.v, a, 0, 0, 0);
+            }
+            if constexpr (MT > 1) __builtin_amdgcn_sched_barrier(0);   // one column at a time: keeps register use flat
         }
     };
     // the activation of the slice: gate/up sums added in slice order, two bf16 terms
@@ -131,7 +155,22 @@ __global__ __launch_bounds__(NW * 64) void dense_stream_kernel(const Params p)
     auto nth = [&](int i) { return wave + i * NW; };
     auto each = [](auto f) { each_of(f, std::make_integer_sequence<int, DEPTH>()); };
     // The loop's loads are unconditional: behind a conditional load the compiler waits for everything in flight.
-    if (n >= DEPTH) {
+    if constexpr (MT > 1) {
+        // One copy of the loop, or the accumulators move between registers at its ends.  Past the slice its last step is
+        // loaded again, for nobody.
+        auto at = [&](int i) { return nth(i) < steps ? nth(i) : steps - 1; };
+        each([&](auto d) { load(d, at(d)); });
+        int i = 0;
+#pragma unroll 1
+        for (; i + DEPTH <= n; i += DEPTH)
+            each([&](auto d) {
+                multiply(d, 0);
+                load(d, at(i + DEPTH + d));
+            });
+        each([&](auto d) {
+            if (i + d < n) multiply(d, 0);
+        });
+    } else if (n >= DEPTH) {
         each([&](auto d) { load(d, nth(d)); });
         stage_act();
         int i = 0;
@@ -158,15 +197,20 @@ __global__ __launch_bounds__(NW * 64) void dense_stream_kernel(const Params p)
         });
     }
 
-    // Lane (c, g) holds tokens 4 g .. 4 g + 3 of columns 8 c .. 8 c + 7.
+    // Lane (c, g) holds tokens 4 g .. 4 g + 3 of a row block, columns 8 c .. 8 c + 7.
     if constexpr (DOWN) __syncthreads();   // every wavefront has read its activation
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-        if (4 * g + r < p.M) {
+    for (int t = 0; t < MT; ++t)
 #pragma unroll
-            for (int j = 0; j < 8; j += 4)
-                *reinterpret_cast<float4 *>(red + (wave * p.M + 4 * g + r) * kCols + 8 * c + j) =
-                    make_float4(acc[j][r], acc[j + 1][r], acc[j + 2][r], acc[j + 3][r]);
+        for (int r = 0; r < 4; ++r) {
+            const int tok = 16 * t + 4 * g + r;
+            if (tok < p.M) {
+#pragma unroll
+                for (int j = 0; j < 8; j += 4)
+                    *reinterpret_cast<float4 *>(red + (wave * p.M + tok) * kCols + 8 * c + j) =
+                        make_float4(acc[t][j][r], acc[t][j + 1][r], acc[t][j + 2][r], acc[t][j + 3][r]);
+            }
+            if constexpr (MT > 1) __builtin_amdgcn_sched_barrier(0);
         }
     __syncthreads();
 #pragma unroll 1
@@ -195,16 +239,16 @@ constexpr size_t lds_bytes(int M, int steps, int ks)
     return red > act ? red : act;
 }
 
-template <bool DOWN, int NW, int DEPTH>
+template <bool DOWN, int NW, int DEPTH, int MT = 1>
 inline hipError_t launch(hipStream_t st, const Params &p, int batches)
 {
     const long z = (long)batches * (DOWN ? 1 : 2);
-    if (p.M < 1 || p.M > kMaxRows || p.ks < 1 || p.ks > 65535 || p.ks > p.K / 32 || z > 65535 || p.K % 32 != 0 || p.N % 8 != 0 ||
+    if (p.M < 1 || p.M > 16 * MT || p.ks < 1 || p.ks > 65535 || p.ks > p.K / 32 || z > 65535 || p.K % 32 != 0 || p.N % 8 != 0 ||
         p.N < 8 || p.K >= (1 << 26) || p.N >= (1 << 26))
         return hipErrorInvalidValue;
     const size_t lds = lds_bytes<DOWN, NW>(p.M, p.K / 32, p.ks);
     if (lds > 160 * 1024) return hipErrorInvalidValue;
-    auto kern = dense_stream_kernel<DOWN, NW, DEPTH>;
+    auto kern = dense_stream_kernel<DOWN, NW, DEPTH, MT>;
     static bool configured = false;  // per instantiation
     if (!configured) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,

@@ -457,6 +457,13 @@ struct DensePlan {
         const size_t b = w.ks ? (size_t)w.ks * terms * m.B * r * m.d : 0;
         return a > b ? a : b;
     }
+    // K slices of the streaming gate/up projections, 0: the ring GEMM.  Where the latter is not cut it forms the activation
+    // in its epilogue, which neither the sums through memory nor the launch that reads them can match: 4 sequences of 64
+    // rows at d = 2048, d_ff = 5632 73 us a call, streamed 82.  The sums stay within the ring GEMM's.
+    int stream_gu(const Dims &m, int r) const
+    {
+        return gate_up(m, r).ks ? k::dense_stream_gu_slices(m.B, r, m.d, m.dff, parts(m, r)) : 0;
+    }
 };
 
 DensePlan dense_plan(const Dims &m, const DenseScratch &scratch)
@@ -574,7 +581,15 @@ int bf16_dense_ffn_fwd(const Dims &m, const void *Xv, const void *Wbarv, void *Y
             p.B[1] = Wbar + (size_t)m.B * m.D; p.b_batch[1] = m.D; p.ldb[1] = m.dff;
             p.M = rows; p.N = m.dff; p.K = m.d; p.batches = m.B;
             prof::Range r(st, prof::kGemmGU, gemm_flops(p, 2, 1), 2.0 * m.B * ((double)RD + 2.0 * m.D + (double)RF));
-            if (sp.ks) {
+            if (const int ks = pl.stream_gu(m, rows)) {
+                stream::Params q = {};
+                q.M = rows; q.K = m.d; q.N = m.dff; q.ks = ks;
+                q.W[0] = p.B[0]; q.W[1] = p.B[1]; q.w_batch = m.D;
+                q.x = X; q.x_batch = TD;
+                q.part = parts;
+                LORY_TRY(k::launch_dense_stream_gu(st, q, m.B));
+                LORY_TRY(k::launch_sum_act(st, parts, ks, m.B, RF, nt, Act));
+            } else if (sp.ks) {
                 p.ksplit = sp.ks;
                 p.batches = m.B * sp.ks;
                 const k::EpiPart<2> epi = {parts, sp.ks, m.B, rows, m.dff};

@@ -722,6 +722,10 @@ def test_dense_block_rounds_only_its_output(B, n_tok, d, d_ff):
 @pytest.mark.parametrize("B,n_tok,d,d_ff", [
     (1, 16, 64, 64), (2, 16, 64, 1088), (3, 9, 1088, 192), (1, 2, 2560, 6144), (17, 16, 128, 320), (1, 16, 64, 12352),
     (300, 1, 64, 192), (2, 17, 320, 832),
+    # gate/up alone streamed: each number of row blocks, full and with one row; one K step per wavefront and uneven
+    # slices, half a block of columns, several sequences
+    (1, 17, 1024, 1088), (1, 32, 1024, 1408), (2, 33, 704, 832), (3, 48, 1344, 320), (1, 49, 2048, 128),
+    (2, 63, 1024, 832), (1, 24, 2560, 64),
 ])
 def test_dense_block_of_few_rows(B, n_tok, d, d_ff):
     cfg = LoryConfig("dense_stream", B=B, L=n_tok, T=n_tok, d=d, d_ff=d_ff, E=B, dtype="bf16", seed=64)
