@@ -103,7 +103,7 @@ struct DenseScratch {
 };
 size_t bf16_dense_workspace_bytes(const Dims &m, const DenseScratch &scratch);
 // How the ring GEMM runs a call with the workspace that is reported for it (blocks of at most 16 rows stream their
-// weights instead, bf16_dense_stream): rows of a block, bf16 terms of the activation, and for
+// weights instead, bf16_dense_stream, and up to 63 rows gate/up's where they would be cut): rows of a block, bf16 terms of the activation, and for
 // the two projections the tile height and the K slices (0: not split).
 struct DenseForm {
     int rows, terms, gu_tile, gu_slices, down_tile, down_slices;
