@@ -131,13 +131,25 @@ __global__ __launch_bounds__(NW * 64) void dense_stream_kernel(const Params p)
                 const int t = q / (len / 4), k = (q - t * (len / 4)) * 4;
                 const float *src = p.gu + ((size_t)b * 2 * p.M + t) * p.K + s0 * 32 + k;
                 float4 sg = make_float4(0.f, 0.f, 0.f, 0.f), su = sg;
-#pragma unroll 4
-                for (int s = 0; s < p.gu_ks; ++s) {
-                    const float4 a = *reinterpret_cast<const float4 *>(src + s * pitch);
-                    const float4 u = *reinterpret_cast<const float4 *>(src + s * pitch + up);
-                    sg.x += a.x; sg.y += a.y; sg.z += a.z; sg.w += a.w;
-                    su.x += u.x; su.y += u.y; su.z += u.z; su.w += u.w;
-                }
+                // eight loads in flight: left to itself the compiler waits for each pair beside the weights' registers
+                auto add = [&](auto count, int s) {
+                    float4 a[count], u[count];
+#pragma unroll
+                    for (int i = 0; i < count; ++i) {
+                        a[i] = *reinterpret_cast<const float4 *>(src + (s + i) * pitch);
+                        u[i] = *reinterpret_cast<const float4 *>(src + (s + i) * pitch + up);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int i = 0; i < count; ++i) {
+                        sg.x += a[i].x; sg.y += a[i].y; sg.z += a[i].z; sg.w += a[i].w;
+                        su.x += u[i].x; su.y += u[i].y; su.z += u[i].z; su.w += u[i].w;
+                    }
+                };
+                int s = 0;
+                for (; s + 4 <= p.gu_ks; s += 4) add(std::integral_constant<int, 4>(), s);
+                if (p.gu_ks & 2) add(std::integral_constant<int, 2>(), s);
+                if (p.gu_ks & 1) add(std::integral_constant<int, 1>(), p.gu_ks - 1);
                 float h[4], l[4];
                 k::act_terms(sg.x, su.x, h[0], l[0]);
                 k::act_terms(sg.y, su.y, h[1], l[1]);
@@ -170,31 +182,48 @@ __global__ __launch_bounds__(NW * 64) void dense_stream_kernel(const Params p)
         each([&](auto d) {
             if (i + d < n) multiply(d, 0);
         });
-    } else if (n >= DEPTH) {
-        each([&](auto d) { load(d, nth(d)); });
-        stage_act();
-        int i = 0;
-        for (; i + 2 * DEPTH <= n; i += DEPTH)
+    } else {
+        auto fill_full = [&]() { each([&](auto d) { load(d, nth(d)); }); };
+        auto run_full = [&]() {
+            int i = 0;
+            for (; i + 2 * DEPTH <= n; i += DEPTH)
+                each([&](auto d) {
+                    multiply(d, nth(i + d));
+                    load(d, nth(i + DEPTH + d));
+                });
+            const int left = n - i - DEPTH;   // steps that are not in flight yet, fewer than DEPTH
             each([&](auto d) {
                 multiply(d, nth(i + d));
-                load(d, nth(i + DEPTH + d));
+                if (d < left) load(d, nth(i + DEPTH + d));
             });
-        const int left = n - i - DEPTH;   // steps that are not in flight yet, fewer than DEPTH
-        each([&](auto d) {
-            multiply(d, nth(i + d));
-            if (d < left) load(d, nth(i + DEPTH + d));
-        });
-        each([&](auto d) {
-            if (d < left) multiply(d, nth(i + DEPTH + d));
-        });
-    } else {
-        each([&](auto d) {
-            if (d < n) load(d, nth(d));
-        });
-        stage_act();
-        each([&](auto d) {
-            if (d < n) multiply(d, nth(d));
-        });
+            each([&](auto d) {
+                if (d < left) multiply(d, nth(i + DEPTH + d));
+            });
+        };
+        auto fill_few = [&]() {
+            each([&](auto d) {
+                if (d < n) load(d, nth(d));
+            });
+        };
+        auto run_few = [&]() {
+            each([&](auto d) {
+                if (d < n) multiply(d, nth(d));
+            });
+        };
+        const bool full = n >= DEPTH;   // not the same for every wavefront of a workgroup
+        if constexpr (DOWN) {
+            if (full) fill_full();
+            else fill_few();
+            stage_act();   // holds a barrier: outside the arms, where every wavefront passes
+            if (full) run_full();
+            else run_few();
+        } else if (full) {
+            fill_full();
+            run_full();
+        } else {
+            fill_few();
+            run_few();
+        }
     }
 
     // Lane (c, g) holds tokens 4 g .. 4 g + 3 of a row block, columns 8 c .. 8 c + 7.

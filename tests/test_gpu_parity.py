@@ -722,6 +722,8 @@ def test_dense_block_rounds_only_its_output(B, n_tok, d, d_ff):
 @pytest.mark.parametrize("B,n_tok,d,d_ff", [
     (1, 16, 64, 64), (2, 16, 64, 1088), (3, 9, 1088, 192), (1, 2, 2560, 6144), (17, 16, 128, 320), (1, 16, 64, 12352),
     (300, 1, 64, 192), (2, 17, 320, 832),
+    # wavefronts of a down projection with two K steps beside wavefronts with one (10 and 14 steps)
+    (1, 3, 64, 320), (2, 16, 64, 448),
     # gate/up alone streamed: each number of row blocks, full and with one row; one K step per wavefront and uneven
     # slices, half a block of columns, several sequences
     (1, 17, 1024, 1088), (1, 32, 1024, 1408), (2, 33, 704, 832), (3, 48, 1344, 320), (1, 49, 2048, 128),
