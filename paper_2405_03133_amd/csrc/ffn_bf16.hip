@@ -376,6 +376,8 @@ int bf16_merge_all(const Dims &m, const float *w, const void *Wgv, const void *W
 
 namespace {
 
+void *const kNoWorkspace = (void *)256;   // stands for one where a call is planned and not launched
+
 // Tile height and K slices of one projection of the dense FFN.
 struct DenseSplit {
     int rows;
@@ -418,7 +420,7 @@ DenseSplit dense_split(const Dims &m, int M, int N, int K, int nset, int terms, 
     DenseSplit best = {whole, 0};
     double best_t = (M <= 128 && whole <= 128) ? stream_us(whole, tiles1, terms * steps, cus)
                                                : rounds_us(whole, tiles1, terms * steps);
-    for (int rows = 64; rows <= 128; rows += rows) {
+    for (int rows = 64; rows <= 128 && K <= gemm2::kMaxCutK; rows += rows) {
         const long tiles = tiles_of(terms * M, rows);
         const bool few = terms * M <= 128, one = terms * M <= rows;
         for (int ks = 1; ks <= steps / 4 && (one || tiles * ks <= cus); ++ks) {
@@ -441,13 +443,19 @@ struct DensePlan {
     int rows;
     size_t act;          // bytes of a block's activation
     size_t floats;       // bound on the partial sums of split contractions
+    bool fixed;          // the scratch is
     DenseSplit gate_up(const Dims &m, int r) const { return dense_split(m, r, m.dff, m.d, 2, 1, floats); }
     DenseSplit down(const Dims &m, int r) const { return dense_split(m, r, m.d, m.dff, 1, terms, floats); }
-    // The down projection where it is not split as a whole: its last round of tiles may be.
-    Params down_params(const Dims &m, int r) const
+    // The down projection where it is not split as a whole: its last round of tiles may be, unless the call is held to a
+    // fixed scratch.
+    Params down_params(const Dims &m, int r, void *ws, size_t ws_bytes) const
     {
         Params p = {};
         p.M = r; p.N = m.d; p.K = m.dff; p.batches = m.B;
+        if (!fixed && ws_bytes > act) {
+            p.tail = (float *)((char *)ws + act);
+            p.tail_floats = (ws_bytes - act) / sizeof(float);
+        }
         return p;
     }
     size_t parts(const Dims &m, int r) const   // floats that a block of r rows uses
@@ -469,6 +477,7 @@ struct DensePlan {
 DensePlan dense_plan(const Dims &m, const DenseScratch &scratch)
 {
     DensePlan p;
+    p.fixed = scratch.fixed;
     // Blocks of 64 k tokens (prefill) round the activation to bf16 like the training forward; every other
     // number of tokens, decode steps among them, keeps it in fp32 precision.
     p.terms = m.L % 64 == 0 ? 1 : 2;
@@ -504,18 +513,18 @@ size_t bf16_dense_workspace_bytes(const Dims &m, const DenseScratch &scratch)
 size_t bf16_dense_tail_bytes(const Dims &m, const DenseScratch &scratch)
 {
     const DensePlan p = dense_plan(m, scratch);
-    if (scratch.fixed || p.down(m, m.L).ks) return 0;
-    Params q = p.down_params(m, m.L);
-    q.tail = (float *)1;
-    q.tail_floats = (size_t)-1;
+    if (p.down(m, m.L).ks) return 0;
+    const Params q = p.down_params(m, m.L, kNoWorkspace, (size_t)1 << 60);
     return p.act + gemm2::tail_floats(q, gemm2::tile_form(q, 256, p.terms), 256) * sizeof(float);
 }
 
-DenseForm bf16_dense_form(const Dims &m, const DenseScratch &scratch)
+DenseForm bf16_dense_form(const Dims &m, const DenseScratch &scratch, size_t ws_bytes)
 {
     const DensePlan p = dense_plan(m, scratch);
     const DenseSplit g = p.gate_up(m, p.rows), d = p.down(m, p.rows);
-    return {p.rows, p.terms, g.rows, g.ks, d.rows, d.ks};
+    if (d.ks) return {p.rows, p.terms, g.rows, g.ks, d.rows, d.ks, 0};
+    const gemm2::Form f = gemm2::tile_form(p.down_params(m, p.rows, kNoWorkspace, ws_bytes), 256, p.terms);
+    return {p.rows, p.terms, g.rows, g.ks, f.rows, 0, f.pieces};
 }
 
 namespace {
@@ -605,13 +614,9 @@ int bf16_dense_ffn_fwd(const Dims &m, const void *Xv, const void *Wbarv, void *Y
         {
             // the two terms of an activation are blocks of rows of one matrix, or two sources
             const DenseSplit sp = pl.down(m, rows);
-            Params p = pl.down_params(m, rows);
+            Params p = pl.down_params(m, rows, ws, ws_bytes);
             p.A[0] = Act; p.A[1] = Act + RF; p.a_batch[0] = p.a_batch[1] = nt * RF; p.lda[0] = p.lda[1] = m.dff;
             p.B[0] = p.B[1] = Wbar + (size_t)2 * m.B * m.D; p.b_batch[0] = p.b_batch[1] = m.D; p.ldb[0] = p.ldb[1] = m.d;
-            if (!scratch.fixed && ws_bytes > pl.act) {
-                p.tail = parts;
-                p.tail_floats = (ws_bytes - pl.act) / sizeof(float);
-            }
             prof::Range r(st, prof::kGemmDown, gemm_flops(p, 1, 1), 2.0 * m.B * ((double)RF + (double)m.D + (double)RD));
             const EpiStore epi = {Y, TD, m.d};
             if (sp.ks) {

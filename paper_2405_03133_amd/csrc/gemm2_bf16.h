@@ -37,6 +37,7 @@ using gemm::u32x2;
 using gemm::u32x4;
 
 constexpr int BK = 32;
+constexpr int kMaxCutK = 1 << 24;   // a contraction cut over K finds its slices in 32-bit arithmetic
 
 // A tile shape: WMV x WNV wavefronts, each with MI x NB blocks of 32 x 32 outputs (NB counted through the
 // operand sets), and the stages of its ring.  One workgroup per CU.
@@ -751,7 +752,7 @@ inline hipError_t launch(const Params &p, const Epi &epi, hipStream_t st)
     if (p.K % BK != 0 || p.K < 2 * BK || p.N % 8 != 0 || p.M < 1 || p.N < 8 || (A_MC && p.M % 8 != 0)) return hipErrorInvalidValue;
     if (NSRC == 2 && (p.lda[0] != p.lda[1] || p.ldb[0] != p.ldb[1])) return hipErrorInvalidValue;
     if (NSET == 2 && p.ldb[0] != p.ldb[1]) return hipErrorInvalidValue;
-    if (Epi::SPLIT && (p.ksplit < 1 || p.ksplit > 1024 || p.K > (1 << 24) || p.batches % p.ksplit != 0 || p.K / BK < 2 * p.ksplit)) return hipErrorInvalidValue;
+    if (Epi::SPLIT && (p.ksplit < 1 || p.ksplit > 1024 || p.K > kMaxCutK || p.batches % p.ksplit != 0 || p.K / BK < 2 * p.ksplit)) return hipErrorInvalidValue;
     const int cus = cu_count();
     auto kern = gemm2_kernel<NSET, NSRC, A_MC, B_NC, TAIL, TL, Epi>;
     static bool configured = false;  // per instantiation
@@ -767,7 +768,7 @@ inline hipError_t launch(const Params &p, const Epi &epi, hipStream_t st)
     if (blocks > cus) blocks = cus;  // every workgroup walks several tiles
     if (TAIL) {
         if (p.pieces < 1 || !p.tail || ntiles % cus == 0 || ntiles % cus * p.pieces > cus || p.K / BK * NSRC < 2 * p.pieces ||
-            p.tail_floats < (size_t)(ntiles % cus) * p.pieces * TL::BM * TL::BN || p.K > (1 << 24) || ntiles >= (1L << 31))
+            p.tail_floats < (size_t)(ntiles % cus) * p.pieces * TL::BM * TL::BN || p.K > kMaxCutK || ntiles >= (1L << 31))
             return hipErrorInvalidValue;
         blocks = cus;
     }
@@ -820,10 +821,18 @@ struct Form {
     int pieces;   // K slices of a tile of the last round, 0 where it is not cut
 };
 
+inline size_t tail_floats(const Params &p, const Form &f, int bns)
+{
+    const long tiles = (long)p.batches * ((p.M + f.rows - 1) / f.rows) * ((p.N + bns - 1) / bns);
+    return (size_t)(tiles % cu_count()) * f.pieces * f.rows * 256;
+}
+
 // With scratch for its partial sums (p.tail) a last round that leaves CUs without a tile may be cut over K, one slice for
 // each CU: it costs its share of the steps, the sums a CU writes (45 KB a us) and a launch that adds them (4.5 us and
-// the rate of the memory-side cache).
-inline Form tile_form(const Params &p, int bns, int nsrc)
+// the rate of the memory-side cache).  A form has to promise 3 % more than the best one before it, in the order of falling
+// tile heights and rising slices: the promise of more slices is kept in part only (the cheapest estimate of all instead:
+// 5 x 1655 rows at d = 384, d_ff = 1728 88 -> 96 us, 4 x 704 at 1472, 3200 121 -> 124, 4 x 1024 at 2048, 5632 268 -> 272).
+inline Form plan_form(const Params &p, int bns, int nsrc, size_t floats)
 {
     const int cus = cu_count(), steps = p.K / BK * nsrc;
     Form best = {256, 0};
@@ -836,9 +845,9 @@ inline Form tile_form(const Params &p, int bns, int nsrc)
             best_t = t;
         }
         const long tiles = (long)p.batches * ((p.M + rows - 1) / rows) * ((p.N + bns - 1) / bns), cut = tiles % cus;
-        if (!p.tail || cut == 0) continue;
+        if (!p.tail || cut == 0 || p.K > kMaxCutK || tiles >= (1L << 31)) continue;
         const double kb = rows * 256 * 4 / 1000.0;
-        for (int n = 2; cut * n <= cus && 4 * n <= steps && (size_t)(cut * n) * rows * 256 <= p.tail_floats; ++n) {
+        for (int n = 2; cut * n <= cus && 4 * n <= steps && (size_t)(cut * n) * rows * 256 <= floats; ++n) {
             const double c = us * (steps * (double)(tiles / cus) + (steps + n - 1) / n + 2) + kb / 45.0 + 4.5 + cut * n * kb / 4000.0;
             if (c < 0.97 * best_t) {
                 best = {rows, n};
@@ -849,10 +858,12 @@ inline Form tile_form(const Params &p, int bns, int nsrc)
     return best;
 }
 
-inline size_t tail_floats(const Params &p, const Form &f, int bns)
+// The form of unlimited scratch where the scratch holds it, so that a caller who sizes its scratch from that form gets it
+// and more scratch changes nothing; else one that fits.
+inline Form tile_form(const Params &p, int bns, int nsrc)
 {
-    const long tiles = (long)p.batches * ((p.M + f.rows - 1) / f.rows) * ((p.N + bns - 1) / bns);
-    return (size_t)(tiles % cu_count()) * f.pieces * f.rows * 256;
+    const Form f = plan_form(p, bns, nsrc, (size_t)-1);
+    return f.pieces && tail_floats(p, f, bns) > p.tail_floats ? plan_form(p, bns, nsrc, p.tail_floats) : f;
 }
 
 inline int tile_rows(const Params &p, int bns)

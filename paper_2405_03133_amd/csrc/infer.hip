@@ -327,7 +327,7 @@ int dense_ffn_fwd_static(const Dims &m, const void *X, const void *Wbar, void *Y
 
 size_t dense_min_workspace_bytes(const Dims &m) { return base_bytes(m); }
 
-DenseForm dense_form(const Dims &m) { return bf16_dense_form(m, gemm_scratch(m)); }
+DenseForm dense_form(const Dims &m, size_t ws_bytes) { return bf16_dense_form(m, gemm_scratch(m), ws_bytes); }
 
 // What the ring GEMM needs to take all rows at once (or in the blocks of a fixed scratch).
 static size_t dense_whole_bytes(const Dims &m)

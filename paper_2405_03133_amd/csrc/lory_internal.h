@@ -102,14 +102,15 @@ struct DenseScratch {
     bool fixed;
 };
 size_t bf16_dense_workspace_bytes(const Dims &m, const DenseScratch &scratch);
-// How the ring GEMM runs a call with the workspace that is reported for it (blocks of at most 16 rows stream their
-// weights instead, bf16_dense_stream, and up to 63 rows gate/up's where they would be cut): rows of a block, bf16 terms of the activation, and for
-// the two projections the tile height and the K slices (0: not split).
+// How the ring GEMM runs a call with the workspace that is reported for it, or more (blocks of at most 16 rows stream their
+// weights instead, bf16_dense_stream, and up to 63 rows gate/up's where they would be cut): rows of a block, bf16 terms of
+// the activation, for the two projections the tile height and the K slices (0: not split), and the K slices of the
+// down projection's last round of tiles (0: not cut).
 struct DenseForm {
-    int rows, terms, gu_tile, gu_slices, down_tile, down_slices;
+    int rows, terms, gu_tile, gu_slices, down_tile, down_slices, down_pieces;
 };
-DenseForm bf16_dense_form(const Dims &m, const DenseScratch &scratch);
-DenseForm dense_form(const Dims &m);
+DenseForm bf16_dense_form(const Dims &m, const DenseScratch &scratch, size_t ws_bytes);
+DenseForm dense_form(const Dims &m, size_t ws_bytes);
 size_t bf16_dense_tail_bytes(const Dims &m, const DenseScratch &scratch);   // workspace for a cut last round, or 0
 int bf16_dense_ffn_fwd(const Dims &m, const void *X, const void *Wbar, void *Y, void *ws, size_t ws_bytes,
                        const DenseScratch &scratch, hipStream_t st);

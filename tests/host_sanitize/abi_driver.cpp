@@ -107,21 +107,43 @@ int main()
     EXPECT(lory_dense_ffn_fwd_static(&big, fake, fake, fake, NULL) == LORY_ERR_WORKSPACE);
 
     // how the dense blocks of the GPU tests run (256 CUs): rows of a block, terms of the activation, tile height and
-    // K slices of gate/up and down; every form that the dispatch has is among them
+    // K slices of gate/up and down, K slices of down's last round of tiles; every form that the dispatch has is among them
     static const struct { int B, L, d, dff; lory::DenseForm f; } forms[] = {
-        {1, 1, 320, 832, {1, 2, 64, 0, 64, 6}},         {5, 7, 320, 832, {7, 2, 64, 0, 64, 6}},
-        {1, 65, 1664, 2816, {65, 2, 128, 11, 64, 8}},    {2, 100, 512, 1408, {100, 2, 64, 0, 64, 9}},
-        {3, 200, 64, 64, {200, 2, 64, 0, 64, 0}},       {130, 100, 64, 64, {100, 2, 128, 0, 128, 0}},
-        {150, 129, 64, 128, {129, 2, 192, 0, 192, 0}},  {130, 250, 64, 64, {250, 2, 256, 0, 256, 0}},
-        {40, 63, 192, 1728, {63, 2, 64, 0, 128, 6}},    {16, 130, 320, 1408, {130, 2, 192, 0, 128, 2}},
-        {2, 1, 1088, 2880, {1, 2, 64, 5, 64, 18}},      {40, 128, 192, 1728, {128, 1, 128, 0, 128, 6}},
-        {1, 128, 320, 832, {128, 1, 64, 0, 64, 6}},     {40, 65, 192, 1728, {65, 2, 128, 0, 64, 2}},
-        {1, 50000, 64, 192, {16704, 2, 192, 0, 128, 0}}, {4, 2001, 256, 704, {1024, 2, 128, 0, 64, 0}},
+        {1, 1, 320, 832, {1, 2, 64, 0, 64, 6, 0}},         {5, 7, 320, 832, {7, 2, 64, 0, 64, 6, 0}},
+        {1, 65, 1664, 2816, {65, 2, 128, 11, 64, 8, 0}},    {2, 100, 512, 1408, {100, 2, 64, 0, 64, 9, 0}},
+        {3, 200, 64, 64, {200, 2, 64, 0, 64, 0, 0}},       {130, 100, 64, 64, {100, 2, 128, 0, 128, 0, 0}},
+        {150, 129, 64, 128, {129, 2, 192, 0, 192, 0, 0}},  {130, 250, 64, 64, {250, 2, 256, 0, 256, 0, 0}},
+        {40, 63, 192, 1728, {63, 2, 64, 0, 128, 6, 0}},    {16, 130, 320, 1408, {130, 2, 192, 0, 128, 2, 0}},
+        {2, 1, 1088, 2880, {1, 2, 64, 5, 64, 18, 0}},      {40, 128, 192, 1728, {128, 1, 128, 0, 128, 6, 0}},
+        {1, 128, 320, 832, {128, 1, 64, 0, 64, 6, 0}},     {40, 65, 192, 1728, {65, 2, 128, 0, 64, 2, 0}},
+        {1, 50000, 64, 192, {16704, 2, 192, 0, 128, 0, 0}}, {4, 2001, 256, 704, {1024, 2, 128, 0, 64, 0, 0}},
+        // a last round of tiles that is cut (test_dense_block_cut_last_round)
+        {2, 2048, 768, 4160, {2048, 1, 192, 0, 256, 0, 5}},
+        // contractions too long for the arithmetic of a slice stay whole
+        {1, 64, 64, (1 << 24) + 64, {64, 1, 64, 0, 64, 0, 0}}, {1, 40, 64, (1 << 24) + 64, {40, 2, 64, 0, 64, 0, 0}},
     };
     for (size_t i = 0; i < sizeof(forms) / sizeof(forms[0]); ++i) {
         const lory_shape s = shape(forms[i].B, forms[i].L, forms[i].L, forms[i].d, forms[i].dff, 1, LORY_BF16);
-        const lory::DenseForm f = lory::dense_form(lory::make_dims(s));
+        EXPECT(lory_workspace_bytes(&s, LORY_PASS_DENSE, &out) == LORY_OK);
+        const lory::DenseForm f = lory::dense_form(lory::make_dims(s), out);
+        if (memcmp(&f, &forms[i].f, sizeof(f)) != 0)
+            printf("form %d x %d, %d, %d: {%d, %d, %d, %d, %d, %d, %d}\n", s.B, s.L, s.d, s.d_ff, f.rows, f.terms, f.gu_tile,
+                   f.gu_slices, f.down_tile, f.down_slices, f.down_pieces);
         EXPECT(memcmp(&f, &forms[i].f, sizeof(f)) == 0);
+    }
+    // the reported workspace is what the planned form needs, and a larger one changes nothing
+    unsigned rng = 12345;
+    auto rnd = [&](int n) { rng = rng * 1664525u + 1013904223u; return (int)((rng >> 8) % (unsigned)n); };
+    for (int i = 0; i < 20000; ++i) {
+        lory_shape s = shape(1 + rnd(12), 1 + rnd(2048), 0, 64 * (1 + rnd(40)), 64 * (1 + rnd(96)), 1, LORY_BF16);
+        s.T = s.L;
+        EXPECT(lory_workspace_bytes(&s, LORY_PASS_DENSE, &out) == LORY_OK);
+        const lory::DenseForm f = lory::dense_form(lory::make_dims(s), out);
+        const lory::DenseForm g = lory::dense_form(lory::make_dims(s), (size_t)1 << 40);
+        if (memcmp(&f, &g, sizeof(f)) != 0)
+            printf("form %d x %d, %d, %d: down %d / %d, with more scratch %d / %d\n", s.B, s.L, s.d, s.d_ff, f.down_tile,
+                   f.down_pieces, g.down_tile, g.down_pieces);
+        EXPECT(memcmp(&f, &g, sizeof(f)) == 0);
     }
 
     // profiler bookkeeping without launches
