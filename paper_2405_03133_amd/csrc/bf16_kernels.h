@@ -2,6 +2,7 @@
 // translation unit of its own so that they compile in parallel.
 #pragma once
 
+#include "lory_internal.h"
 #include "gemm_bf16.h"
 #include "gemm2_bf16.h"
 #include "merge_scatter_bf16.h"
@@ -203,12 +204,10 @@ hipError_t launch_sum_store(hipStream_t st, const float *part, int ksplit, long 
                             long y_batch);
 // Dense FFN of at most 16 rows per sequence (dense_stream_bf16.h): K slices of its two projections, both 0 where it
 // does not take the call (more rows, or partial sums that `floats` do not hold).
-struct DenseStream {
-    int gu, down;
-};
 DenseStream dense_stream_plan(int B, int M, int d, int dff, size_t floats);
-// Its gate/up projections alone, for 17 .. 64 rows: K slices, 0 where it does not take them.
-int dense_stream_gu_slices(int B, int M, int d, int dff, size_t floats);
+// Its gate/up projections alone, for 17 .. 63 rows: K slices, 0 where it does not take them or the ring GEMM, in its
+// estimated time, is not slower.
+int dense_stream_gu_slices(int B, int M, int d, int dff, size_t floats, double ring_us);
 hipError_t launch_dense_stream_gu(hipStream_t st, const stream::Params &p, int B);
 hipError_t launch_dense_stream_down(hipStream_t st, const stream::Params &p, int B);
 

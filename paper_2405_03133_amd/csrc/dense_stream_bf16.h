@@ -22,7 +22,7 @@
 // two terms does not fit in LDS beside its sums, and every column block would form it again).  The weights
 // skip LDS, and a barrier per K step with it.  us per call, ring GEMM -> this: 2 x 40 rows at
 // d = 2048, d_ff = 5632 52.1 -> 46.4, 2 x 50 at 1536, 4096 39.5 -> 36.9, 3 x 45 at 768, 2048 27.8 -> 25.5, 24 at 1024,
-// 2816 21.7 -> 20.8, 18 .. 33 at 2048, 5632 unchanged.  64 rows are slower (32.5 -> 34.4 at 2048, 5632), two workgroups
+// 2816 21.7 -> 20.8, 18 .. 33 at 2048, 5632 unchanged; where it is not faster the ring GEMM runs (dense_stream_gu_slices).  64 rows are slower (32.5 -> 34.4 at 2048, 5632), two workgroups
 // sharing the rows of more are as well (2 x 100 63 -> 74: the weights pass through the CUs twice), and the accumulators
 // of 96 rows spill.
 #pragma once

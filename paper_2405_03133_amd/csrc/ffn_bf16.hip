@@ -382,6 +382,7 @@ void *const kNoWorkspace = (void *)256;   // stands for one where a call is plan
 struct DenseSplit {
     int rows;
     int ks;      // 0: not split, launch_rows picks the tile (of `rows`)
+    double us;   // estimated time
 };
 
 // Estimated time, us, of a projection of up to 128 rows (decode steps, short blocks): it streams the weights, so
@@ -417,9 +418,8 @@ DenseSplit dense_split(const Dims &m, int M, int N, int K, int nset, int terms, 
     p.M = M; p.N = N; p.batches = m.B;
     const int whole = gemm2::tile_rows(p, bns);
     const long tiles1 = tiles_of(M, whole);
-    DenseSplit best = {whole, 0};
-    double best_t = (M <= 128 && whole <= 128) ? stream_us(whole, tiles1, terms * steps, cus)
-                                               : rounds_us(whole, tiles1, terms * steps);
+    DenseSplit best = {whole, 0, (M <= 128 && whole <= 128) ? stream_us(whole, tiles1, terms * steps, cus)
+                                                            : rounds_us(whole, tiles1, terms * steps)};
     for (int rows = 64; rows <= 128 && K <= gemm2::kMaxCutK; rows += rows) {
         const long tiles = tiles_of(terms * M, rows);
         const bool few = terms * M <= 128, one = terms * M <= rows;
@@ -428,10 +428,7 @@ DenseSplit dense_split(const Dims &m, int M, int N, int K, int nset, int terms, 
             if (parts > (double)max_floats) break;
             const int k = (steps + ks - 1) / ks;
             const double t = (few ? stream_us(rows, tiles * ks, k, cus) : rounds_us(rows, tiles, k)) + parts * (one ? 6e-7 : 2e-6) + 4.5;
-            if (t < best_t) {
-                best_t = t;
-                best = {rows, ks};
-            }
+            if (t < best.us) best = {rows, ks, t};
         }
     }
     return best;
@@ -470,7 +467,8 @@ struct DensePlan {
     // rows at d = 2048, d_ff = 5632 73 us a call, streamed 82.  The sums stay within the ring GEMM's.
     int stream_gu(const Dims &m, int r) const
     {
-        return gate_up(m, r).ks ? k::dense_stream_gu_slices(m.B, r, m.d, m.dff, parts(m, r)) : 0;
+        const DenseSplit g = gate_up(m, r);
+        return g.ks ? k::dense_stream_gu_slices(m.B, r, m.d, m.dff, parts(m, r), g.us) : 0;
     }
 };
 
@@ -518,21 +516,44 @@ size_t bf16_dense_tail_bytes(const Dims &m, const DenseScratch &scratch)
     return p.act + gemm2::tail_floats(q, gemm2::tile_form(q, 256, p.terms), 256) * sizeof(float);
 }
 
-DenseForm bf16_dense_form(const Dims &m, const DenseScratch &scratch, size_t ws_bytes)
+DenseForm bf16_dense_form(const Dims &m, const DenseScratch &scratch, size_t ws_bytes, const DenseStream &sp)
 {
     const DensePlan p = dense_plan(m, scratch);
+    if (sp.gu) return {m.L, 2, 0, 0, 0, 0, 0, sp};
     const DenseSplit g = p.gate_up(m, p.rows), d = p.down(m, p.rows);
-    if (d.ks) return {p.rows, p.terms, g.rows, g.ks, d.rows, d.ks, 0};
-    const gemm2::Form f = gemm2::tile_form(p.down_params(m, p.rows, kNoWorkspace, ws_bytes), 256, p.terms);
-    return {p.rows, p.terms, g.rows, g.ks, f.rows, 0, f.pieces};
+    const int ks = p.stream_gu(m, p.rows);
+    DenseForm f = {p.rows, p.terms, ks ? 0 : g.rows, ks ? 0 : g.ks, d.rows, d.ks, 0, {ks, 0}};
+    if (!d.ks) {
+        const gemm2::Form t = gemm2::tile_form(p.down_params(m, p.rows, kNoWorkspace, ws_bytes), 256, p.terms);
+        f.down_tile = t.rows;
+        f.down_pieces = t.pieces;
+    }
+    return f;
 }
 
-namespace {
+// Every block of up to 12 rows streams.  So do 13 .. 16, unless the ring GEMM would form the activation in the epilogue of
+// an uncut gate/up whose last round of tiles uses half the CUs or more, and has the K steps to pay for its fill.  us, streamed and
+// ring GEMM, 16 rows: 4 sequences at d = 1216, d_ff = 4992 (156 tiles) 41.1 and 37.4, 8 at 1536, 4096 (256) 70.8 and 65.8,
+// 3 at 2048, 5632 (132) 56.1 and 54.7; 8 at 768, 6144 (384 tiles, 24 steps) 54.3 and 57.6, 8 at 768, 2048 (128) 25.1 and 28.1.
+// The 20 such calls measured take 0.88 .. 0.997 of the ring GEMM's time with 8 rows and 0.92 .. 1.08, 1.00 on average,
+// with 12.
+DenseStream bf16_dense_stream_plan(const Dims &m, size_t ws_bytes, const DenseScratch &scratch)
+{
+    if (m.L > 12 && m.L <= 16 && m.d >= 1024) {
+        const DensePlan p = dense_plan(m, scratch);
+        const DenseSplit g = p.gate_up(m, p.rows);
+        const long cus = gemm2::cu_count(), tiles = (long)m.B * ((p.rows + g.rows - 1) / g.rows) * ((m.dff + 127) / 128);
+        if (!g.ks && 2 * tiles >= (tiles + cus - 1) / cus * cus) return {0, 0};
+    }
+    return k::dense_stream_plan(m.B, m.L, m.d, m.dff, ws_bytes / sizeof(float));
+}
 
 // Decode steps and blocks of at most 16 rows: two streaming projections, the gate/up sums between them in the scratch.
-int dense_stream(const Dims &m, const k::DenseStream &sp, const bf *X, const bf *Wbar, bf *Y, float *ws, hipStream_t st)
+int bf16_dense_stream(const Dims &m, const DenseStream &sp, const void *X, const void *Wbarv, void *Yv, void *scratch, hipStream_t st)
 {
-    float *parts = ws + (size_t)sp.gu * 2 * m.B * m.L * m.dff;
+    const bf *Wbar = (const bf *)Wbarv;
+    bf *Y = (bf *)Yv;
+    float *ws = (float *)scratch, *parts = ws + (size_t)sp.gu * 2 * m.B * m.L * m.dff;
     stream::Params p = {};
     p.M = m.L;
     p.w_batch = m.D;
@@ -540,7 +561,7 @@ int dense_stream(const Dims &m, const k::DenseStream &sp, const bf *X, const bf 
         prof::Range r(st, prof::kGemmGU, 4.0 * m.tokens * m.D, 2.0 * (m.tokens * (double)m.d + 2.0 * m.B * m.D));
         p.K = m.d; p.N = m.dff; p.ks = sp.gu;
         p.W[0] = Wbar; p.W[1] = Wbar + (size_t)m.B * m.D;
-        p.x = X; p.x_batch = (long)m.L * m.d;
+        p.x = (const bf *)X; p.x_batch = (long)m.L * m.d;
         p.part = ws;
         LORY_TRY(k::launch_dense_stream_gu(st, p, m.B));
     }
@@ -553,17 +574,6 @@ int dense_stream(const Dims &m, const k::DenseStream &sp, const bf *X, const bf 
     LORY_TRY(k::launch_dense_stream_down(st, p, m.B));
     if (sp.down > 1) LORY_TRY(k::launch_sum_store(st, parts, sp.down, m.B, (long)m.L * m.d, 1, Y, (long)m.L * m.d));
     return LORY_OK;
-}
-
-}  // namespace
-
-bool bf16_dense_stream(const Dims &m, const void *X, const void *Wbar, void *Y, void *ws, size_t ws_bytes, hipStream_t st,
-                       int *rc)
-{
-    const k::DenseStream sp = k::dense_stream_plan(m.B, m.L, m.d, m.dff, ws_bytes / sizeof(float));
-    if (!sp.gu) return false;
-    *rc = dense_stream(m, sp, (const bf *)X, (const bf *)Wbar, (bf *)Y, (float *)ws, st);
-    return true;
 }
 
 // Dense SwiGLU FFN of every sequence with its own materialised merged parameters

@@ -327,7 +327,10 @@ int dense_ffn_fwd_static(const Dims &m, const void *X, const void *Wbar, void *Y
 
 size_t dense_min_workspace_bytes(const Dims &m) { return base_bytes(m); }
 
-DenseForm dense_form(const Dims &m, size_t ws_bytes) { return bf16_dense_form(m, gemm_scratch(m), ws_bytes); }
+// The streaming path keeps to the least workspace, so that a call runs the same way whatever it is given.
+static DenseStream stream_plan(const Dims &m) { return bf16_dense_stream_plan(m, base_bytes(m), gemm_scratch(m)); }
+
+DenseForm dense_form(const Dims &m, size_t ws_bytes) { return bf16_dense_form(m, gemm_scratch(m), ws_bytes, stream_plan(m)); }
 
 // What the ring GEMM needs to take all rows at once (or in the blocks of a fixed scratch).
 static size_t dense_whole_bytes(const Dims &m)
@@ -347,9 +350,8 @@ size_t dense_workspace_bytes(const Dims &m)
 int dense_ffn_fwd(const Dims &m, const void *X, const void *Wbar, void *Y, void *ws, size_t ws_bytes, hipStream_t st)
 {
     if (m.dtype == LORY_F32) return skinny_ffn<float>(m, (const float *)X, (const float *)Wbar, (float *)Y, ws, st);
-    // the streaming path keeps to the least workspace, so that a call runs the same way whatever it is given
-    int rc = LORY_OK;
-    if (bf16_dense_stream(m, X, Wbar, Y, ws, base_bytes(m), st, &rc)) return rc;
+    const DenseStream sp = stream_plan(m);
+    if (sp.gu) return bf16_dense_stream(m, sp, X, Wbar, Y, ws, st);
     if (ws_bytes >= dense_whole_bytes(m)) return bf16_dense_ffn_fwd(m, X, Wbar, Y, ws, ws_bytes, gemm_scratch(m), st);
     return bf16_dense_ffn_fwd(m, X, Wbar, Y, ws, ws_bytes, DenseScratch{base_bytes(m), true}, st);
 }

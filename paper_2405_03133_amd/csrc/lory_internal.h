@@ -102,21 +102,26 @@ struct DenseScratch {
     bool fixed;
 };
 size_t bf16_dense_workspace_bytes(const Dims &m, const DenseScratch &scratch);
-// How the ring GEMM runs a call with the workspace that is reported for it, or more (blocks of at most 16 rows stream their
-// weights instead, bf16_dense_stream, and up to 63 rows gate/up's where they would be cut): rows of a block, bf16 terms of
-// the activation, for the two projections the tile height and the K slices (0: not split), and the K slices of the
-// down projection's last round of tiles (0: not cut).
+// Streaming projections of the dense FFN: K slices of gate/up and of down, 0 where the ring GEMM takes it.
+struct DenseStream {
+    int gu, down;
+};
+// How a call runs with the workspace that is reported for it, or more: rows of a block, bf16 terms of the activation, for
+// the two projections on the ring GEMM the tile height and the K slices (0: not split), the K slices of the
+// down projection's last round of tiles (0: not cut), and what streams its weights instead.
 struct DenseForm {
     int rows, terms, gu_tile, gu_slices, down_tile, down_slices, down_pieces;
+    DenseStream stream;
 };
-DenseForm bf16_dense_form(const Dims &m, const DenseScratch &scratch, size_t ws_bytes);
+DenseForm bf16_dense_form(const Dims &m, const DenseScratch &scratch, size_t ws_bytes, const DenseStream &sp);
 DenseForm dense_form(const Dims &m, size_t ws_bytes);
 size_t bf16_dense_tail_bytes(const Dims &m, const DenseScratch &scratch);   // workspace for a cut last round, or 0
 int bf16_dense_ffn_fwd(const Dims &m, const void *X, const void *Wbar, void *Y, void *ws, size_t ws_bytes,
                        const DenseScratch &scratch, hipStream_t st);
-// Blocks of at most 16 rows, weights streamed; false where they take more rows or more scratch than ws_bytes.
-bool bf16_dense_stream(const Dims &m, const void *X, const void *Wbar, void *Y, void *ws, size_t ws_bytes, hipStream_t st,
-                       int *rc);
+// Blocks of at most 16 rows with both projections streamed: the plan for a workspace (0, 0: the ring GEMM takes the
+// call, with `scratch`), and the call.
+DenseStream bf16_dense_stream_plan(const Dims &m, size_t ws_bytes, const DenseScratch &scratch);
+int bf16_dense_stream(const Dims &m, const DenseStream &sp, const void *X, const void *Wbar, void *Y, void *ws, hipStream_t st);
 int set_slab_budget(size_t bytes);
 int set_fused_mode(int mode);
 size_t bf16_workspace_bytes(const Dims &m, int pass);

@@ -107,28 +107,60 @@ int main()
     EXPECT(lory_dense_ffn_fwd_static(&big, fake, fake, fake, NULL) == LORY_ERR_WORKSPACE);
 
     // how the dense blocks of the GPU tests run (256 CUs): rows of a block, terms of the activation, tile height and
-    // K slices of gate/up and down, K slices of down's last round of tiles; every form that the dispatch has is among them
+    // K slices of gate/up and down on the ring GEMM, K slices of down's last round of tiles, K slices of the projections
+    // that stream their weights; every form that the dispatch has is among them
     static const struct { int B, L, d, dff; lory::DenseForm f; } forms[] = {
-        {1, 1, 320, 832, {1, 2, 64, 0, 64, 6, 0}},         {5, 7, 320, 832, {7, 2, 64, 0, 64, 6, 0}},
-        {1, 65, 1664, 2816, {65, 2, 128, 11, 64, 8, 0}},    {2, 100, 512, 1408, {100, 2, 64, 0, 64, 9, 0}},
-        {3, 200, 64, 64, {200, 2, 64, 0, 64, 0, 0}},       {130, 100, 64, 64, {100, 2, 128, 0, 128, 0, 0}},
-        {150, 129, 64, 128, {129, 2, 192, 0, 192, 0, 0}},  {130, 250, 64, 64, {250, 2, 256, 0, 256, 0, 0}},
-        {40, 63, 192, 1728, {63, 2, 64, 0, 128, 6, 0}},    {16, 130, 320, 1408, {130, 2, 192, 0, 128, 2, 0}},
-        {2, 1, 1088, 2880, {1, 2, 64, 5, 64, 18, 0}},      {40, 128, 192, 1728, {128, 1, 128, 0, 128, 6, 0}},
-        {1, 128, 320, 832, {128, 1, 64, 0, 64, 6, 0}},     {40, 65, 192, 1728, {65, 2, 128, 0, 64, 2, 0}},
-        {1, 50000, 64, 192, {16704, 2, 192, 0, 128, 0, 0}}, {4, 2001, 256, 704, {1024, 2, 128, 0, 64, 0, 0}},
-        // a last round of tiles that is cut (test_dense_block_cut_last_round)
-        {2, 2048, 768, 4160, {2048, 1, 192, 0, 256, 0, 5}},
+        // the ring GEMM
+        {1, 65, 1664, 2816, {65, 2, 128, 11, 64, 8, 0, {0, 0}}},
+        {2, 100, 512, 1408, {100, 2, 64, 0, 64, 9, 0, {0, 0}}},
+        {3, 200, 64, 64, {200, 2, 64, 0, 64, 0, 0, {0, 0}}},
+        {130, 100, 64, 64, {100, 2, 128, 0, 128, 0, 0, {0, 0}}},
+        {150, 129, 64, 128, {129, 2, 192, 0, 192, 0, 0, {0, 0}}},
+        {130, 250, 64, 64, {250, 2, 256, 0, 256, 0, 0, {0, 0}}},
+        {40, 63, 192, 1728, {63, 2, 64, 0, 128, 6, 0, {0, 0}}},
+        {16, 130, 320, 1408, {130, 2, 192, 0, 128, 2, 0, {0, 0}}},
+        {40, 128, 192, 1728, {128, 1, 128, 0, 128, 6, 0, {0, 0}}},
+        {1, 128, 320, 832, {128, 1, 64, 0, 64, 6, 0, {0, 0}}},
+        {40, 65, 192, 1728, {65, 2, 128, 0, 64, 2, 0, {0, 0}}},
+        {1, 50000, 64, 192, {16704, 2, 192, 0, 128, 0, 0, {0, 0}}},
+        {4, 2001, 256, 704, {1024, 2, 128, 0, 64, 0, 0, {0, 0}}},
+        {2, 17, 320, 832, {17, 2, 64, 0, 64, 6, 0, {0, 0}}},
+        {4, 14, 1024, 4160, {14, 2, 64, 0, 64, 13, 0, {0, 0}}},
+        {6, 40, 1024, 1408, {40, 2, 64, 3, 128, 9, 0, {0, 0}}},
+        // a last round of tiles that is cut
+        {2, 2048, 768, 4160, {2048, 1, 192, 0, 256, 0, 5, {0, 0}}},
         // contractions too long for the arithmetic of a slice stay whole
-        {1, 64, 64, (1 << 24) + 64, {64, 1, 64, 0, 64, 0, 0}}, {1, 40, 64, (1 << 24) + 64, {40, 2, 64, 0, 64, 0, 0}},
+        {1, 64, 64, (1 << 24) + 64, {64, 1, 64, 0, 64, 0, 0, {0, 0}}},
+        {1, 40, 64, (1 << 24) + 64, {40, 2, 64, 0, 64, 0, 0, {0, 0}}},
+        // weights streamed: both projections
+        {1, 1, 320, 832, {1, 2, 0, 0, 0, 0, 0, {4, 24}}},
+        {5, 7, 320, 832, {7, 2, 0, 0, 0, 0, 0, {3, 4}}},
+        {2, 1, 1088, 2880, {1, 2, 0, 0, 0, 0, 0, {2, 12}}},
+        {1, 16, 64, 64, {16, 2, 0, 0, 0, 0, 0, {2, 1}}},
+        {2, 16, 64, 1088, {16, 2, 0, 0, 0, 0, 0, {2, 12}}},
+        {3, 9, 1088, 192, {9, 2, 0, 0, 0, 0, 0, {8, 1}}},
+        {1, 2, 2560, 6144, {2, 2, 0, 0, 0, 0, 0, {2, 12}}},
+        {17, 16, 128, 320, {16, 2, 0, 0, 0, 0, 0, {2, 3}}},
+        {1, 16, 64, 12352, {16, 2, 0, 0, 0, 0, 0, {1, 32}}},
+        {300, 1, 64, 192, {1, 2, 0, 0, 0, 0, 0, {1, 1}}},
+        {1, 3, 64, 320, {3, 2, 0, 0, 0, 0, 0, {2, 1}}},
+        {40, 2, 64, 448, {2, 2, 0, 0, 0, 0, 0, {1, 1}}},
+        // gate/up alone
+        {1, 17, 1024, 1088, {17, 2, 0, 0, 64, 7, 0, {4, 0}}},
+        {1, 32, 1024, 1408, {32, 2, 0, 0, 64, 11, 0, {4, 0}}},
+        {2, 33, 704, 832, {33, 2, 0, 0, 64, 6, 0, {3, 0}}},
+        {3, 48, 1344, 320, {48, 2, 0, 0, 64, 2, 0, {6, 0}}},
+        {1, 49, 2048, 128, {49, 2, 0, 0, 64, 0, 0, {16, 0}}},
+        {2, 63, 1024, 832, {63, 2, 0, 0, 128, 6, 0, {4, 0}}},
+        {1, 24, 2560, 64, {24, 2, 0, 0, 64, 0, 0, {16, 0}}},
     };
     for (size_t i = 0; i < sizeof(forms) / sizeof(forms[0]); ++i) {
         const lory_shape s = shape(forms[i].B, forms[i].L, forms[i].L, forms[i].d, forms[i].dff, 1, LORY_BF16);
         EXPECT(lory_workspace_bytes(&s, LORY_PASS_DENSE, &out) == LORY_OK);
         const lory::DenseForm f = lory::dense_form(lory::make_dims(s), out);
         if (memcmp(&f, &forms[i].f, sizeof(f)) != 0)
-            printf("form %d x %d, %d, %d: {%d, %d, %d, %d, %d, %d, %d}\n", s.B, s.L, s.d, s.d_ff, f.rows, f.terms, f.gu_tile,
-                   f.gu_slices, f.down_tile, f.down_slices, f.down_pieces);
+            printf("{%d, %d, %d, %d, {%d, %d, %d, %d, %d, %d, %d, {%d, %d}}},\n", s.B, s.L, s.d, s.d_ff, f.rows, f.terms, f.gu_tile,
+                   f.gu_slices, f.down_tile, f.down_slices, f.down_pieces, f.stream.gu, f.stream.down);
         EXPECT(memcmp(&f, &forms[i].f, sizeof(f)) == 0);
     }
     // the reported workspace is what the planned form needs, and a larger one changes nothing

@@ -702,6 +702,8 @@ def test_dense_block_split_contractions(B, d, d_ff, n_tok):
 @pytest.mark.parametrize("B,n_tok,d,d_ff", [
     (1, 1, 320, 832), (5, 7, 320, 832), (1, 65, 1664, 2816), (2, 100, 512, 1408), (3, 200, 64, 64),
     (130, 100, 64, 64), (150, 129, 64, 128), (130, 250, 64, 64), (40, 63, 192, 1728), (16, 130, 320, 1408),
+    # few rows that the ring GEMM takes: gate/up whole, and cut in 64-row tiles
+    (4, 14, 1024, 4160), (6, 40, 1024, 1408),
 ])
 def test_dense_block_rounds_only_its_output(B, n_tok, d, d_ff):
     cfg = LoryConfig("dense_exact", B=B, L=n_tok, T=n_tok, d=d, d_ff=d_ff, E=B, dtype="bf16", seed=62)
@@ -723,7 +725,7 @@ def test_dense_block_rounds_only_its_output(B, n_tok, d, d_ff):
     (1, 16, 64, 64), (2, 16, 64, 1088), (3, 9, 1088, 192), (1, 2, 2560, 6144), (17, 16, 128, 320), (1, 16, 64, 12352),
     (300, 1, 64, 192), (2, 17, 320, 832),
     # wavefronts of a down projection with two K steps beside wavefronts with one (10 and 14 steps)
-    (1, 3, 64, 320), (2, 16, 64, 448),
+    (1, 3, 64, 320), (40, 2, 64, 448),
     # gate/up alone streamed: each number of row blocks, full and with one row; one K step per wavefront and uneven
     # slices, half a block of columns, several sequences
     (1, 17, 1024, 1088), (1, 32, 1024, 1408), (2, 33, 704, 832), (3, 48, 1344, 320), (1, 49, 2048, 128),
