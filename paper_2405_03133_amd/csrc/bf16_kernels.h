@@ -172,6 +172,7 @@ struct EpiPart {
 
 // Every wrapper returns a hipError_t.  Any M (a multiple of 8 where A is stored K-slow), N a multiple of 8,
 // K a multiple of 32 and at least 64.
+int merge_rounds(int E, int S, long elems, bool transient);   // rounds of workgroups that launch_merge starts
 hipError_t launch_merge(hipStream_t st, const ms::MergeParams &p);
 hipError_t launch_scatter(hipStream_t st, const ms::ScatterParams &p, int grid);
 hipError_t launch_dw_reduce(hipStream_t st, const float *partials, int slots, int rows, int cols,

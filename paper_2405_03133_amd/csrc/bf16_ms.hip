@@ -61,20 +61,29 @@ void scatter_partial_dims(int S, int E, int *rows, int *cols)
     *cols = ((E + 31) / 32) * 32;
 }
 
+// Rounds of workgroups of a merge of `elems` parameters (one workgroup fits a CU).  Each round pays for a start
+// (routing-weight operands, first loads: 3 us), several even out what the CUs get done.  What is uneven are the stores: beside the
+// E streams that it reads, a wavefront writes S, and up to about ten more than a quarter of its reads a single round is the fastest
+// at every size.  Beyond, the gain grows with the bytes of those stores, twice as fast into merged parameters
+// that are kept as into the slab that the GEMM behind the merge reads (`transient`), part of which the memory-side cache holds.
+// The lines are fitted to 803 prompt merges (S = 1 .. 64, 4 .. 32 experts, 768 x 768 .. 2560 x 6144) and 393 forward passes
+// (S = 4 .. 128) in one, two and four rounds: 0.2 % slower than the fastest on average, 6 and 3 % at most (moved by 15 %
+// either way the average stays); one round everywhere 1.1 and 0.7 %, 18 and 7 %, four 11 and 7 %, 41 and 24 %.
+// us in one / two / four rounds: 3 prompts, 16 experts, 2048 x 5632 281 / 282 / 295; 64 sequences, 12 experts, 1024 x 2816
+// 291 / 275 / 250.
+int merge_rounds(int E, int S, long elems, bool transient)
+{
+    const double mb = 2e-6 * elems * (S - 10 - 0.25 * E) * (transient ? 0.5 : 1.0);
+    return mb < 75 ? 1 : mb < 190 ? 2 : 4;
+}
+
 hipError_t launch_merge(hipStream_t st, const ms::MergeParams &p)
 {
     const int KS = (p.E + 15) / 16;
     const int MB = (p.S + 31) / 32;
     const size_t lds = (size_t)MB * KS * 2 * 64 * 16;
     if (lds > 64 * 1024) return hipErrorInvalidValue;
-    // One workgroup fits a CU.  Each pays about 3 us for its start (routing-weight operands, first loads), several in
-    // turn even out what the CUs get done: short launches take one round of workgroups, long ones four.  us per forward
-    // pass with its three merges in 256 / 512 / 1024 workgroups, by what a merge reads + writes, MB: 37 + 18 (32 experts
-    // 768 x 768, 16 segments) 74.5 / 81.4 / 89.3, 184 + 92 231 / 237 / 251, 92 + 184 297 / 308 / 320, 184 + 184
-    // 346 / 342 / 353, 46 + 369 546 / 519 / 505, 184 + 369 623 / 608 / 608, 369 + 738 1152 / 1138 / 1131; three prompts
-    // of 16 experts, 369 + 69, 281 / 282 / 295.
-    const double n = 2e-6 * p.rc.nr * p.rc.nc, mb = n * (p.E + p.S);
-    const int most = mb < 280 || (mb < 450 && p.E >= 4 * p.S) ? gemm2::cu_count() : mb < 380 ? 2 * gemm2::cu_count() : kMsGrid;
+    const int most = merge_rounds(p.E, p.S, (long)p.rc.nr * p.rc.nc, p.seg_map != nullptr) * gemm2::cu_count();
     int grid = (units_of(p.rc) + 3) / 4;
     if (grid > most) grid = most;
 #define LORY_MERGE(K)                                                                              \

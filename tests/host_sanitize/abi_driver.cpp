@@ -7,6 +7,7 @@
 #include <string.h>
 
 #include "lory.h"
+#include "bf16_kernels.h"
 #include "lory_internal.h"
 
 static int failures = 0;
@@ -177,6 +178,22 @@ int main()
                    f.down_pieces, g.down_tile, g.down_pieces);
         EXPECT(memcmp(&f, &g, sizeof(f)) == 0);
     }
+
+    // rounds of workgroups of a merge: a few prompts take one whatever the size, and one more sequence, expert or 64
+    // columns changes the rounds by one step at most
+    for (int d = 768; d <= 2560; d += 256)
+        for (int f = 704; f <= 6144; f += 64)
+            for (int e = 4; e <= 64; ++e)
+                for (int s = 1; s <= 12; ++s) EXPECT(lory::k::merge_rounds(e, s, (long)d * f, false) == 1 || s > 10 + e / 4);
+    for (int t = 0; t < 2; ++t)
+        for (int f = 704; f <= 6144; f += 64)
+            for (int e = 4; e <= 32; ++e)
+                for (int s = 1; s <= 128; ++s) {
+                    const int r = lory::k::merge_rounds(e, s, 2048L * f, t);
+                    const int n[3] = {lory::k::merge_rounds(e, s + 1, 2048L * f, t), lory::k::merge_rounds(e + 1, s, 2048L * f, t),
+                                      lory::k::merge_rounds(e, s, 2048L * (f + 64), t)};
+                    for (int i = 0; i < 3; ++i) EXPECT(n[i] <= 2 * r && r <= 2 * n[i]);
+                }
 
     // profiler bookkeeping without launches
     lory_kernel_stat st[8];
