@@ -115,13 +115,14 @@ int lory_set_fused_merge(int mode);
  * caller's stream (the measurement model is the paper's Appendix B: GEMM work
  * 6*tokens*d*d_ff per pass direction, merge-class work 6*E*d*d_ff per segment
  * and pass).  lory_profile_enable(1) makes every later launch record a pair
- * of events tagged with that launch's algorithmic FLOPs and bytes;
+ * of events tagged with that launch's algorithmic FLOPs and bytes (merged
+ * values that segments with equal routing weights share are counted once);
  * lory_profile_read waits for the recorded events, sums them per class into
  * out[0..*n_out) (at most max_out entries; classes without launches are
  * skipped) and clears the records.  Host-side state is process-global and not
- * thread-safe.  The event objects (4096, i.e. 2048 timed launches between two
- * reads; further launches go untimed) are created by lory_profile_enable(1),
- * never inside a launch, and reused.
+ * thread-safe.  The event objects (6144, for 2048 timed launches between two
+ * reads; further launches go untimed) and 8 KiB of pinned host memory are
+ * created by lory_profile_enable(1), never inside a launch, and reused.
  */
 typedef struct {
     char name[32];   /* kernel class, e.g. "gemm_gate_up", "merge", "scatter_dots" */

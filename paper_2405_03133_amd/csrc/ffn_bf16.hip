@@ -200,7 +200,6 @@ hipError_t merge(hipStream_t st, const float *w, int S, int E, const bf *stack, 
                  int32_t *seg_map = nullptr)
 {
     const double n = (double)rc.nr * rc.nc;
-    prof::Range r(st, prof::kMerge, 2.0 * S * E * n, 2.0 * n * (E + S));
     MergeParams p;
     p.w = w;
     p.S = S;
@@ -210,7 +209,15 @@ hipError_t merge(hipStream_t st, const float *w, int S, int E, const bf *stack, 
     p.slab = slab;
     p.seg_stride = (long)rc.nr * rc.nc;
     p.seg_map = seg_map;
-    return k::launch_merge(st, p);
+    int rec;
+    {
+        prof::Range r(st, prof::kMerge, 2.0 * S * E * n, 2.0 * n * (E + S));
+        rec = r.index();
+        const hipError_t e = k::launch_merge(st, p);
+        if (e != hipSuccess) return e;
+    }
+    prof::shared_segments(st, rec, seg_map, S, 2.0 * n);
+    return hipSuccess;
 }
 
 // Gate/up projections of one d_ff column block for a chunk of segments.
@@ -235,11 +242,14 @@ hipError_t gate_up_block(hipStream_t st, const Dims &m, int S, const bf *X, cons
     const bool split = (G != nullptr && Act != nullptr);
     EpiGU epi = {G, U, split ? nullptr : Act, m.T, m.dff, n0};
     const double out_elems = (double)S * m.T * nf * ((G ? 2 : 0) + ((Act && !split) ? 1 : 0));
+    int rec;
     {
         prof::Range r(st, prof::kGemmGU, gemm_flops(p, 2, 1),
                       2.0 * ((double)S * m.T * m.d + 2.0 * S * m.d * nf + out_elems));
+        rec = r.index();
         if ((e = k::launch_gu(st, p, epi)) != hipSuccess) return e;
     }
+    prof::shared_segments(st, rec, seg_map, S, 4.0 * m.d * nf);
     if (split) {
         prof::Range r(st, prof::kSwigluFwd, 4.0 * S * m.T * nf, 2.0 * 3.0 * S * m.T * nf);
         return k::launch_swiglu_fwd(st, G, U, Act, (long)S * m.T, m.dff, n0, nf);
@@ -347,9 +357,14 @@ int bf16_ffn_fwd(const Dims &m, const void *Xv, const float *w, const void *Wgv,
             p.M = m.T; p.N = jf; p.K = m.dff; p.batches = S;
             set_tail(p, whole_d, past + kMapElems, (char *)slab + pl.slab_fwd);
             EpiStore epi = {Y + (size_t)s0 * TD + j0, TD, m.d};
-            prof::Range r(st, prof::kGemmDown, gemm_flops(p, 1, 1),
-                          2.0 * ((double)S * TF + (double)S * m.dff * jf + (double)S * m.T * jf));
-            LORY_TRY(k::launch_down(st, p, epi));
+            int rec;
+            {
+                prof::Range r(st, prof::kGemmDown, gemm_flops(p, 1, 1),
+                              2.0 * ((double)S * TF + (double)S * m.dff * jf + (double)S * m.T * jf));
+                rec = r.index();
+                LORY_TRY(k::launch_down(st, p, epi));
+            }
+            prof::shared_segments(st, rec, map, S, 2.0 * m.dff * jf);
         }
     }
     return LORY_OK;
@@ -767,11 +782,14 @@ int bf16_ffn_bwd(const Dims &m, const void *Xv, const float *w, const void *Wgv,
                 p.M = m.T; p.N = nf; p.K = m.d; p.batches = S;
                 set_tail(p, nf == m.dff, s_gd + kMapElems, (char *)slab + pl.slab_bwd);
                 EpiStore epi = {dG + n0, TF, m.dff};  // dA parks in the dG buffer
+                int rec;
                 {
                     prof::Range r(st, prof::kGemmDA, gemm_flops(p, 1, 1),
                                   2.0 * ((double)S * TD + (double)S * nf * m.d + (double)S * m.T * nf));
+                    rec = r.index();
                     LORY_TRY(k::launch_da(st, p, epi));
                 }
+                prof::shared_segments(st, rec, map, S, 2.0 * nf * m.d);
                 prof::Range r2(st, prof::kSwigluBwd, 12.0 * S * m.T * nf, 2.0 * 6.0 * S * m.T * nf);
                 LORY_TRY(k::launch_swiglu_bwd(st, Gc, Uc, dG, dU, Act, (long)S * m.T, m.dff, n0, nf));
             }
@@ -850,9 +868,14 @@ int bf16_ffn_bwd(const Dims &m, const void *Xv, const float *w, const void *Wgv,
             p.M = m.T; p.N = kf; p.K = m.dff; p.batches = S;
             set_tail(p, kf == m.d, slab + 2 * blk + kMapElems, (char *)slab + pl.slab_bwd);
             EpiStore epi = {dX + (size_t)s0 * TD + k0, TD, m.d};
-            prof::Range r(st, prof::kGemmDX, gemm_flops(p, 1, 2),
-                          2.0 * (2.0 * S * TF + 2.0 * S * kf * m.dff + (double)S * m.T * kf));
-            LORY_TRY(k::launch_dx(st, p, epi));
+            int rec;
+            {
+                prof::Range r(st, prof::kGemmDX, gemm_flops(p, 1, 2),
+                              2.0 * (2.0 * S * TF + 2.0 * S * kf * m.dff + (double)S * m.T * kf));
+                rec = r.index();
+                LORY_TRY(k::launch_dx(st, p, epi));
+            }
+            prof::shared_segments(st, rec, map, S, 4.0 * kf * m.dff);
         }
 
         if (!fused_dw) {

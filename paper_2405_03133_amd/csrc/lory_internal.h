@@ -55,10 +55,14 @@ public:
     ~Range();
     Range(const Range &) = delete;
     Range &operator=(const Range &) = delete;
+    int index() const { return idx_; }   // of the record, -1: none
 private:
     hipStream_t st_;
     int idx_;
 };
+// After the launches of record `idx`: they moved only the merged values of the segments that `map` names (device memory,
+// S entries, map[s] == s where s has values of its own), so seg_bytes are not counted for each of the others.
+void shared_segments(hipStream_t st, int idx, const int32_t *map, int S, double seg_bytes);
 }  // namespace prof
 
 // ---- routing (route.hip)

@@ -333,6 +333,34 @@ def test_bf16_equal_routing_rows(cfg, runs):
             assert np.array_equal(got[key], saved[key]), key
 
 
+def test_profile_counts_shared_merges_once():
+    """Bytes of the merges and of the GEMMs behind them: merged values of segments with equal routing rows are
+    written and read once; saved merged parameters are written for every segment."""
+    cfg = LoryConfig("profile_shared", B=3, L=1280, T=128, d=128, d_ff=192, E=4, dtype="bf16", seed=114)
+    t = make_inputs(cfg, structured=True)
+    w = make_routing_weights(cfg, "peaked")
+    w[7:12], w[29] = w[7], w[28]     # five segments of one row, and the last pair
+    S, D, tok = cfg.S, cfg.d * cfg.d_ff, cfg.tokens
+    kept = 1 + sum(not np.array_equal(w[s], w[s - 1]) for s in range(1, S))
+    assert kept <= S - 5
+    for merged_save, n in ((False, kept), (True, S)):
+        lb.lory_profile_enable(True)
+        try:
+            lb.lory_profile_read()
+            run_layer(cfg, t, w_override=w, merged_save=merged_save)
+            stats = {s["name"]: s for s in lb.lory_profile_read()}
+        finally:
+            lb.lory_profile_enable(False)
+        merges = 3 if merged_save else 6
+        assert stats["merge"]["launches"] == merges
+        assert stats["merge"]["bytes"] == 2.0 * D * (cfg.E + n) * merges
+        acts = 2.0 * tok * (cfg.d + cfg.d_ff)
+        assert stats["gemm_gate_up"]["bytes"] == acts + 2.0 * tok * cfg.d_ff + 4.0 * n * D   # G and U are saved
+        assert stats["gemm_down"]["bytes"] == acts + 2.0 * n * D
+        assert stats["gemm_dA"]["bytes"] == acts + 2.0 * n * D
+        assert stats["gemm_dX"]["bytes"] == acts + 2.0 * tok * cfg.d_ff + 4.0 * n * D
+
+
 def test_bf16_forward_in_place():
     """Y may be X: the down projection writes it after everything that reads X."""
     cfg = LoryConfig("in_place", B=2, L=512, T=128, d=128, d_ff=192, E=4, dtype="bf16", seed=113)
