@@ -191,6 +191,31 @@ void set_tail(Params &p, bool whole, void *from, void *to)
     p.tail_floats = b > a ? (b - a) / sizeof(float) : 0;
 }
 
+// Sizes and scratch of the token GEMMs whose last round of tiles may be cut, for S segments with the slab at `slab`.
+Params down_gemm(const Dims &m, const Plan &pl, bool whole, int S, int jf, bf *slab)
+{
+    Params p = {};
+    p.M = m.T; p.N = jf; p.K = m.dff; p.batches = S;
+    set_tail(p, whole, slab + (size_t)S * m.dff * jf + kMapElems, (char *)slab + pl.slab_fwd);
+    return p;
+}
+
+Params da_gemm(const Dims &m, const Plan &pl, int S, int nf, bf *slab)
+{
+    Params p = {};
+    p.M = m.T; p.N = nf; p.K = m.d; p.batches = S;
+    set_tail(p, nf == m.dff, slab + (size_t)S * m.d * nf + kMapElems, (char *)slab + pl.slab_bwd);
+    return p;
+}
+
+Params dx_gemm(const Dims &m, const Plan &pl, int S, int kf, bf *slab)
+{
+    Params p = {};
+    p.M = m.T; p.N = kf; p.K = m.dff; p.batches = S;
+    set_tail(p, kf == m.d, slab + (size_t)2 * S * m.dff * kf + kMapElems, (char *)slab + pl.slab_bwd);
+    return p;
+}
+
 double gemm_flops(const Params &p, int nset, int nsrc)
 {
     return 2.0 * p.batches * p.M * p.N * p.K * nset * nsrc;
@@ -292,6 +317,19 @@ size_t bf16_workspace_bytes(const Dims &m, int pass)
     return 5 * p.act + p.slab_bwd + p.partials;
 }
 
+LayerForm bf16_layer_form(const Dims &m)
+{
+    const Plan pl = make_plan(m);
+    bf *slab = (bf *)256;   // nothing is launched
+    const int S = pl.Sc, jf = pl.jf_fwd, nf = pl.nf_bwd, kf = pl.kf_bwd;
+    auto form = [](const Params &p, int nsrc) -> TileForm {
+        const gemm2::Form f = gemm2::tile_form(p, 256, nsrc);
+        const long tiles = (long)p.batches * ((p.M + f.rows - 1) / f.rows) * ((p.N + 255) / 256);
+        return {f.rows, f.pieces, (int)(tiles / gemm2::cu_count())};
+    };
+    return {form(down_gemm(m, pl, jf == m.d, S, jf, slab), 1), form(da_gemm(m, pl, S, nf, slab), 1), form(dx_gemm(m, pl, S, kf, slab), 2)};
+}
+
 int bf16_ffn_fwd(const Dims &m, const void *Xv, const float *w, const void *Wgv, const void *Wuv,
                  const void *Wdv, void *Yv, void *Gv, void *Uv, void *Wbarv, void *ws, hipStream_t st)
 {
@@ -350,12 +388,10 @@ int bf16_ffn_fwd(const Dims &m, const void *Xv, const float *w, const void *Wgv,
             bf *past = slab + (size_t)S * m.dff * jf;
             int32_t *map = Wbar ? nullptr : map_place(S, past, (char *)slab + pl.slab_fwd);
             LORY_TRY(merge(st, wc, S, m.E, Wd, rect(m.D, m.d, 0, m.dff, j0, jf), sd, map));
-            Params p = {};
+            Params p = down_gemm(m, pl, whole_d, S, jf, slab);
             p.b_map = map;
             p.A[0] = Act; p.a_batch[0] = TF; p.lda[0] = m.dff;
             p.B[0] = sd; p.b_batch[0] = (long)m.dff * jf; p.ldb[0] = jf;
-            p.M = m.T; p.N = jf; p.K = m.dff; p.batches = S;
-            set_tail(p, whole_d, past + kMapElems, (char *)slab + pl.slab_fwd);
             EpiStore epi = {Y + (size_t)s0 * TD + j0, TD, m.d};
             int rec;
             {
@@ -773,14 +809,12 @@ int bf16_ffn_bwd(const Dims &m, const void *Xv, const float *w, const void *Wgv,
             int32_t *map = Wbar ? nullptr : map_place(S, s_gd, (char *)slab + pl.slab_bwd);   // the gradient slabs are written later
             if (!Wbar && !fused) LORY_TRY(merge(st, wc, S, m.E, Wd, rows_d, s_md, map));
             if (!fused) {
-                Params p = {};
+                Params p = da_gemm(m, pl, S, nf, slab);
                 p.b_map = map;
                 p.A[0] = dYc; p.a_batch[0] = TD; p.lda[0] = m.d;
                 p.B[0] = Wbar ? Wbar_d + (size_t)n0 * m.d : s_md;
                 p.b_batch[0] = Wbar ? m.D : (long)nf * m.d;
                 p.ldb[0] = m.d;
-                p.M = m.T; p.N = nf; p.K = m.d; p.batches = S;
-                set_tail(p, nf == m.dff, s_gd + kMapElems, (char *)slab + pl.slab_bwd);
                 EpiStore epi = {dG + n0, TF, m.dff};  // dA parks in the dG buffer
                 int rec;
                 {
@@ -857,7 +891,7 @@ int bf16_ffn_bwd(const Dims &m, const void *Xv, const float *w, const void *Wgv,
                 LORY_TRY(merge(st, wc, S, m.E, Wg, rows, s_g, map));
                 LORY_TRY(merge(st, wc, S, m.E, Wu, rows, s_u, map));
             }
-            Params p = {};
+            Params p = dx_gemm(m, pl, S, kf, slab);
             p.b_map = map;
             p.A[0] = dG; p.a_batch[0] = TF; p.lda[0] = m.dff;
             p.A[1] = dU; p.a_batch[1] = TF; p.lda[1] = m.dff;
@@ -865,8 +899,6 @@ int bf16_ffn_bwd(const Dims &m, const void *Xv, const float *w, const void *Wgv,
             p.B[1] = Wbar ? Wbar_u + (size_t)k0 * m.dff : s_u;
             p.b_batch[0] = p.b_batch[1] = Wbar ? m.D : (long)kf * m.dff;
             p.ldb[0] = p.ldb[1] = m.dff;
-            p.M = m.T; p.N = kf; p.K = m.dff; p.batches = S;
-            set_tail(p, kf == m.d, slab + 2 * blk + kMapElems, (char *)slab + pl.slab_bwd);
             EpiStore epi = {dX + (size_t)s0 * TD + k0, TD, m.d};
             int rec;
             {

@@ -126,6 +126,15 @@ int bf16_dense_ffn_fwd(const Dims &m, const void *X, const void *Wbar, void *Y, 
 // call, with `scratch`), and the call.
 DenseStream bf16_dense_stream_plan(const Dims &m, size_t ws_bytes, const DenseScratch &scratch);
 int bf16_dense_stream(const Dims &m, const DenseStream &sp, const void *X, const void *Wbar, void *Y, void *ws, hipStream_t st);
+// How the slab pipeline runs the token GEMMs of the first chunk and block that may cut their last round of tiles: tile
+// height, K slices of that round (0: not cut), whole rounds before it.
+struct TileForm {
+    int rows, pieces, rounds;
+};
+struct LayerForm {
+    TileForm down, da, dx;
+};
+LayerForm bf16_layer_form(const Dims &m);
 int set_slab_budget(size_t bytes);
 int set_fused_mode(int mode);
 size_t bf16_workspace_bytes(const Dims &m, int pass);

@@ -130,6 +130,11 @@ int main()
         {6, 40, 1024, 1408, {40, 2, 64, 3, 128, 9, 0, {0, 0}}},
         // a last round of tiles that is cut
         {2, 2048, 768, 4160, {2048, 1, 192, 0, 256, 0, 5, {0, 0}}},
+        {65, 128, 1024, 1024, {128, 1, 128, 0, 128, 0, 7, {0, 0}}},
+        {65, 192, 1024, 1024, {192, 1, 192, 0, 192, 0, 7, {0, 0}}},
+        {65, 256, 1024, 1024, {256, 1, 256, 0, 256, 0, 7, {0, 0}}},
+        {66, 100, 1024, 1408, {100, 2, 128, 0, 128, 0, 9, {0, 0}}},
+        {66, 180, 1024, 1024, {180, 2, 192, 0, 192, 0, 6, {0, 0}}},
         // contractions too long for the arithmetic of a slice stay whole
         {1, 64, 64, (1 << 24) + 64, {64, 1, 64, 0, 64, 0, 0, {0, 0}}},
         {1, 40, 64, (1 << 24) + 64, {40, 2, 64, 0, 64, 0, 0, {0, 0}}},
@@ -163,6 +168,25 @@ int main()
             printf("{%d, %d, %d, %d, {%d, %d, %d, %d, %d, %d, %d, {%d, %d}}},\n", s.B, s.L, s.d, s.d_ff, f.rows, f.terms, f.gu_tile,
                    f.gu_slices, f.down_tile, f.down_slices, f.down_pieces, f.stream.gu, f.stream.down);
         EXPECT(memcmp(&f, &forms[i].f, sizeof(f)) == 0);
+    }
+    // the same for the token GEMMs of the training steps in test_bf16_ring_gemm_cut_last_round: down, dA and dX
+    static const struct { int B, L, T, d, dff, E; lory::LayerForm f; } layers[] = {
+        {2, 960, 320, 320, 4160, 3, {{64, 4, 0}, {192, 0, 0}, {64, 4, 0}}},
+        {3, 256, 64, 128, 4096, 17, {{64, 12, 0}, {64, 0, 0}, {64, 16, 0}}},
+        {1, 2688, 192, 320, 4032, 3, {{64, 3, 0}, {192, 0, 0}, {192, 9, 0}}},
+        {2, 1024, 256, 2880, 192, 3, {{128, 0, 0}, {64, 6, 0}, {128, 0, 0}}},
+        {1, 4160, 64, 1024, 1536, 17, {{64, 10, 1}, {64, 0, 1}, {64, 16, 1}}},
+        {5, 1664, 128, 1024, 384, 3, {{128, 0, 1}, {128, 0, 0}, {128, 6, 1}}},
+        {5, 2496, 192, 1024, 384, 3, {{192, 0, 1}, {192, 0, 0}, {192, 6, 1}}},
+    };
+    for (size_t i = 0; i < sizeof(layers) / sizeof(layers[0]); ++i) {
+        const lory_shape s = shape(layers[i].B, layers[i].L, layers[i].T, layers[i].d, layers[i].dff, layers[i].E, LORY_BF16);
+        const lory::LayerForm f = lory::bf16_layer_form(lory::make_dims(s));
+        if (memcmp(&f, &layers[i].f, sizeof(f)) != 0)
+            printf("{%d, %d, %d, %d, %d, %d, {{%d, %d, %d}, {%d, %d, %d}, {%d, %d, %d}}},\n", s.B, s.L, s.T, s.d, s.d_ff, s.E,
+                   f.down.rows, f.down.pieces, f.down.rounds, f.da.rows, f.da.pieces, f.da.rounds, f.dx.rows, f.dx.pieces,
+                   f.dx.rounds);
+        EXPECT(memcmp(&f, &layers[i].f, sizeof(f)) == 0);
     }
     // the reported workspace is what the planned form needs, and a larger one changes nothing
     unsigned rng = 12345;

@@ -374,13 +374,18 @@ def test_bf16_forward_in_place():
     assert torch.equal(Y, Z)
 
 
-# A last round of tiles cut over K, with every tile height: no whole round before it or one, edge tiles, K slices that
-# begin in the first or second source of dX or span both, and slices of different lengths.
+# A last round of tiles cut over K: with and without whole rounds before it, edge tiles, K slices that begin in the first or
+# second source of dX or span both, and slices of different lengths.  tests/host_sanitize/abi_driver.cpp pins the tile heights,
+# the slices and the whole rounds of each contraction.
 TAIL_CASES = [
     LoryConfig("tail_T320", B=2, L=960, T=320, d=320, d_ff=4160, E=3, dtype="bf16", seed=101),
     LoryConfig("tail_T64", B=3, L=256, T=64, d=128, d_ff=4096, E=17, dtype="bf16", seed=102),
     LoryConfig("tail_T192", B=1, L=2688, T=192, d=320, d_ff=4032, E=3, dtype="bf16", seed=103),
     LoryConfig("tail_wide", B=2, L=1024, T=256, d=2880, d_ff=192, E=3, dtype="bf16", seed=104),
+    # one whole round and four tiles
+    LoryConfig("tail_whole_T64", B=1, L=4160, T=64, d=1024, d_ff=1536, E=17, dtype="bf16", seed=115),
+    LoryConfig("tail_whole_T128", B=5, L=1664, T=128, d=1024, d_ff=384, E=3, dtype="bf16", seed=116),
+    LoryConfig("tail_whole_T192", B=5, L=2496, T=192, d=1024, d_ff=384, E=3, dtype="bf16", seed=117),
 ]
 
 
@@ -414,6 +419,40 @@ def test_dense_block_cut_last_round():
         torch.cuda.synchronize()
         assert bool((ws[size:] == 0x5A).all())
         check(f"{size} bytes", host(Y), ref, TOL["bf16"])
+
+
+# One whole round before four to eight tiles of 128, 192 and 256 rows, with one source and with the two terms of a ragged
+# block's activation.  The reference is the product in fp32 on the same operands.
+@pytest.mark.parametrize("B,n_tok,d,d_ff", [
+    (65, 128, 1024, 1024), (65, 192, 1024, 1024), (65, 256, 1024, 1024), (66, 100, 1024, 1408), (66, 180, 1024, 1024),
+])
+def test_dense_block_cut_round_after_a_whole_one(B, n_tok, d, d_ff):
+    print(f"[gpu] dense_tail {B} {n_tok} {d} {d_ff}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(105)
+    X = torch.randn((B, n_tok, d), generator=gen, device="cuda").bfloat16()
+    Wbar = torch.stack([torch.randn((B, d * d_ff), generator=gen, device="cuda").mul_(0.02).bfloat16() for _ in range(3)])
+    ref = []
+    for b in range(B):
+        wg, wu, wd = (Wbar[i, b].float().reshape((d, d_ff) if i < 2 else (d_ff, d)) for i in range(3))
+        x = X[b].float()
+        ref.append((torch.nn.functional.silu(x @ wg) * (x @ wu)) @ wd)
+    ref = host(torch.stack(ref))
+    shape = lb.make_shape(B, n_tok, n_tok, d, d_ff, 1, X.dtype)
+    need, act = lb.lory_workspace_bytes(shape, lb.LORY_PASS_DENSE), B * n_tok * d_ff * (2 if n_tok % 64 == 0 else 4)
+    assert need > act
+    got = {}
+    # with the reported workspace, with more, and (where calls take so little) with one that holds the activation alone
+    for size in (need, need + (8 << 20)) + ((act,) if n_tok % 64 == 0 else ()):
+        ws = torch.full((size + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+        Y = torch.full_like(X, float("nan"))
+        rc = lb.lib().lory_dense_ffn_fwd(ctypes.byref(shape), X.data_ptr(), Wbar.data_ptr(), Y.data_ptr(), ws.data_ptr(),
+                                         size, torch.cuda.current_stream().cuda_stream)
+        assert rc == lb.LORY_OK, lb.status_string(rc)
+        torch.cuda.synchronize()
+        assert bool((ws[size:] == 0x5A).all())
+        got[size] = Y
+        check(f"{size} bytes", host(Y), ref, TOL["bf16"])
+    assert torch.equal(got[need], got[need + (8 << 20)])
 
 
 def test_bf16_recompute_bf16_grads_and_accumulate(default_budget):
