@@ -81,6 +81,9 @@ const char *lory_version(void);
  * CUs) measured faster than blocks sized for the 256 MB memory-side cache; the
  * LORY_SLAB_MB environment variable sets the initial value.  Changes what
  * lory_workspace_bytes reports, so set it before sizing a workspace.
+ * Results are reproducible under one budget; another may add the same products
+ * in another order: where the slab holds whole matrices, a last round of tiles
+ * of the down, dA and dX products that leaves CUs idle is cut over K.
  * Returns LORY_ERR_SHAPE for values below 64 KiB.
  */
 int lory_set_slab_budget(size_t bytes);
@@ -226,8 +229,10 @@ int lory_prompt_merge(const lory_shape *shape, const void *X_prompt, const int32
  * shape: L = tokens per sequence in this call (1 for a decode step), T = L.
  * in:  X [B, L, d] (dtype); Wbar as lory_prompt_merge wrote it
  * out: Y [B, L, d] (dtype)
- * LORY_BF16 runs on the batched matrix-core GEMMs (contractions split over K when
- * few tokens would leave the chip idle).  The activation between the projections
+ * LORY_BF16 streams the weights past LDS for up to 16 tokens, and those of the
+ * gate and up projections for up to 63, where that is the faster way, and runs
+ * on the batched matrix-core GEMMs otherwise (contractions split over K when few
+ * tokens would leave the chip idle).  The activation between the projections
  * is rounded to bf16 when L is a multiple of 64 and keeps fp32 precision (two bf16
  * terms) for every other L.  LORY_F32 runs HBM-bound kernels that read each weight
  * once per 8 tokens.
@@ -235,7 +240,8 @@ int lory_prompt_merge(const lory_shape *shape, const void *X_prompt, const int32
  * take less, down to B L d_ff elements when L is a multiple of 64 and to the
  * partial sums of one pass of up to 8 tokens otherwise: contractions are then
  * split less and rows walked in blocks, which is slower and adds the same
- * products in another order.
+ * products in another order (calls that stream both projections run the same way
+ * in the least workspace).  More than is reported changes nothing.
  */
 int lory_dense_ffn_fwd(const lory_shape *shape, const void *X, const void *Wbar, void *Y,
                        void *workspace, size_t workspace_bytes, void *stream);

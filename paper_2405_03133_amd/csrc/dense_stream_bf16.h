@@ -13,8 +13,8 @@
 //
 // Bound by the latency of memory for small matrices and by its read rate for large ones: a CU reads at most 25 .. 45 GB/s,
 // so the K slices are cut until all 256 take part.  us per call, ring GEMM -> this, weights from memory: one sequence,
-// one token, d = 1024, d_ff = 2816 (17 MB) 20.0 -> 13.5 replayed from a graph, 19.5 -> 15.5 launched one by one; 4 at
-// d = 2048, d_ff = 5632 (277 MB) 59.5 -> 52.1, 5.3 TB/s.  Unsplit, with the activation in the epilogue of gate/up, the
+// one token, d = 1024, d_ff = 2816 (17 MB) 19.6 -> 15.1 launched from Python, 13.2 from C; 4 at d = 2048, d_ff = 5632
+// (277 MB) 59.6 -> 51.4, 5.4 TB/s.  Unsplit, with the activation in the epilogue of gate/up, the
 // same kernels took 21.2 for the first: too few CUs read.
 //
 // Gate/up alone also for 17 .. 63 rows, 2 .. 4 row blocks per wavefront against the same weights; their sums leave for the
@@ -22,9 +22,9 @@
 // two terms does not fit in LDS beside its sums, and every column block would form it again).  The weights
 // skip LDS, and a barrier per K step with it.  us per call, ring GEMM -> this: 2 x 40 rows at
 // d = 2048, d_ff = 5632 52.1 -> 46.4, 2 x 50 at 1536, 4096 39.5 -> 36.9, 3 x 45 at 768, 2048 27.8 -> 25.5, 24 at 1024,
-// 2816 21.7 -> 20.8, 18 .. 33 at 2048, 5632 unchanged; where it is not faster the ring GEMM runs (dense_stream_gu_slices).  64 rows are slower (32.5 -> 34.4 at 2048, 5632), two workgroups
-// sharing the rows of more are as well (2 x 100 63 -> 74: the weights pass through the CUs twice), and the accumulators
-// of 96 rows spill.
+// 2816 21.7 -> 20.8, 18 .. 33 at 2048, 5632 unchanged; where its estimate is not lower the ring GEMM runs
+// (dense_stream_gu_slices).  64 rows are slower (32.5 -> 34.4 at 2048, 5632), two workgroups sharing the rows of more are
+// as well (2 x 100 63 -> 74: the weights pass through the CUs twice), and the accumulators of 96 rows spill.
 #pragma once
 
 #include "bf16_kernels.h"

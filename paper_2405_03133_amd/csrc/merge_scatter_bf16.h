@@ -132,7 +132,8 @@ __global__ __launch_bounds__(256) void merge_kernel(const MergeParams p)
     // Segments whose routing row repeats that of the segment before (the first two of every sequence route on the same
     // mean; a caller's rows may be equal over longer runs) share its merged values: bit s of keep[] is set where s is
     // the first of its run.  Compared as bits, so that the shared values are the ones it would have formed.  A merge
-    // writes, and its GEMM reads, 1/16 less at 16 segments per sequence (training step, 64 segments at d = 2048, 32
+    // writes 1/16 less at 16 segments per sequence, and the down and dX GEMMs behind it read that much less (gate/up has
+    // the tiles of the two segments too far apart for L2) (training step, 64 segments at d = 2048, 32
     // experts 8583 -> 8452 us; forward of 128 segments at d = 1024, 8 experts 1079 -> 1045) for 1 us at its start.
     __shared__ uint64_t keep[kMapSegments / 64];
     if constexpr (MAP) {
