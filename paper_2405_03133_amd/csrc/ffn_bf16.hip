@@ -582,19 +582,22 @@ DenseForm bf16_dense_form(const Dims &m, const DenseScratch &scratch, size_t ws_
     return f;
 }
 
-// Every block of up to 12 rows streams.  So do 13 .. 16, unless the ring GEMM would form the activation in the epilogue of
-// an uncut gate/up whose last round of tiles uses half the CUs or more, and has the K steps to pay for its fill.  us, streamed and
-// ring GEMM, 16 rows: 4 sequences at d = 1216, d_ff = 4992 (156 tiles) 41.1 and 37.4, 8 at 1536, 4096 (256) 70.8 and 65.8,
-// 3 at 2048, 5632 (132) 56.1 and 54.7; 8 at 768, 6144 (384 tiles, 24 steps) 54.3 and 57.6, 8 at 768, 2048 (128) 25.1 and 28.1.
-// The 20 such calls measured take 0.88 .. 0.997 of the ring GEMM's time with 8 rows and 0.92 .. 1.08, 1.00 on average,
-// with 12.
+// Every block of up to 10 rows streams.  So do 11 .. 16, unless the ring GEMM would form the activation in the epilogue of
+// an uncut gate/up whose last round of tiles uses half the CUs or more, and has the K steps or the rounds to pay for its
+// fill: from 13 rows on at d = 1024 and wider, from 11 on with a second round there or a third below.  us, streamed and ring
+// GEMM.  16 rows: 4 sequences at d = 1216, d_ff = 4992 (156 tiles) 41.1 and 37.4, 8 at 1536, 4096 (256) 70.8 and 65.8,
+// 3 at 2048, 5632 (132) 56.1 and 54.7, 48 at 768, 2048 (768) 109 and 100; 8 at 768, 6144 (384) 54.3 and 57.6, 8 at 768, 2048
+// (128) 25.1 and 28.1.  12 rows: 10 at 1216, 4992 (390) 81.3 and 75.9, 48 there (1872) 333 and 310, 20 at 1024, 2816 (440)
+// 74.6 and 72.0; in one round 1.00 of the ring GEMM's time on average, 0.92 .. 1.04.  8 rows: 0.88 .. 1.02, 0.96 on average.
 DenseStream bf16_dense_stream_plan(const Dims &m, size_t ws_bytes, const DenseScratch &scratch)
 {
-    if (m.L > 12 && m.L <= 16 && m.d >= 1024) {
+    if (m.L > 10 && m.L <= 16) {
         const DensePlan p = dense_plan(m, scratch);
         const DenseSplit g = p.gate_up(m, p.rows);
         const long cus = gemm2::cu_count(), tiles = (long)m.B * ((p.rows + g.rows - 1) / g.rows) * ((m.dff + 127) / 128);
-        if (!g.ks && 2 * tiles >= (tiles + cus - 1) / cus * cus) return {0, 0};
+        const long rounds = (tiles + cus - 1) / cus;
+        const bool pays = m.d >= 1024 ? m.L > 12 || rounds >= 2 : rounds >= 3;
+        if (!g.ks && pays && 2 * tiles >= rounds * cus) return {0, 0};
     }
     return k::dense_stream_plan(m.B, m.L, m.d, m.dff, ws_bytes / sizeof(float));
 }

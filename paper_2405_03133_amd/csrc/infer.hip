@@ -3,7 +3,7 @@
 // inference"; Appendix G.1).  After one routing decision per layer the merged
 // FFN of a sequence is an ordinary dense FFN,
 //   Y_b = (silu(X_b Wg_bar_b) (.) X_b Wu_bar_b) Wd_bar_b .
-// bf16 streams the weights of both projections for up to 12 tokens, and to 16 where that is faster (bf16_dense_stream); those
+// bf16 streams the weights of both projections for up to 10 tokens, and to 16 where that is faster (bf16_dense_stream); those
 // of gate/up alone for 17 to 63 where the ring GEMM would cut them and is slower; everything else runs on the ring GEMM
 // (bf16_dense_ffn_fwd: contractions split over K where the tiles would leave the chip idle, rows in blocks where the scratch
 // is small).  fp32 goes through the "skinny" kernels below, which are HBM-bound: every weight is read once per pass of up

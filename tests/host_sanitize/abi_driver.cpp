@@ -127,6 +127,7 @@ int main()
         {4, 2001, 256, 704, {1024, 2, 128, 0, 64, 0, 0, {0, 0}}},
         {2, 17, 320, 832, {17, 2, 64, 0, 64, 6, 0, {0, 0}}},
         {4, 14, 1024, 4160, {14, 2, 64, 0, 64, 13, 0, {0, 0}}},
+        {130, 11, 64, 704, {11, 2, 64, 0, 64, 3, 0, {0, 0}}},
         {6, 40, 1024, 1408, {40, 2, 64, 3, 128, 9, 0, {0, 0}}},
         // a last round of tiles that is cut
         {2, 2048, 768, 4160, {2048, 1, 192, 0, 256, 0, 5, {0, 0}}},

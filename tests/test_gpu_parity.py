@@ -770,7 +770,7 @@ def test_dense_block_split_contractions(B, d, d_ff, n_tok):
     (1, 1, 320, 832), (5, 7, 320, 832), (1, 65, 1664, 2816), (2, 100, 512, 1408), (3, 200, 64, 64),
     (130, 100, 64, 64), (150, 129, 64, 128), (130, 250, 64, 64), (40, 63, 192, 1728), (16, 130, 320, 1408),
     # few rows that the ring GEMM takes: gate/up whole, and cut in 64-row tiles
-    (4, 14, 1024, 4160), (6, 40, 1024, 1408),
+    (4, 14, 1024, 4160), (130, 11, 64, 704), (6, 40, 1024, 1408),
 ])
 def test_dense_block_rounds_only_its_output(B, n_tok, d, d_ff):
     cfg = LoryConfig("dense_exact", B=B, L=n_tok, T=n_tok, d=d, d_ff=d_ff, E=B, dtype="bf16", seed=62)
