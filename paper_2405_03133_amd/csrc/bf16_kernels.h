@@ -183,6 +183,8 @@ void scatter_partial_dims(int S, int E, int *rows, int *cols);
 // merge inside the GEMM (fused_bf16.h): C = sum over nsrc sources of A_q * Wbar_q(segment of the row)
 bool fused_fits(const fmg::Params &p);
 hipError_t launch_fused(hipStream_t st, const fmg::Params &p, int nsrc, bool w_nc);
+// two products of A[0] with N-contiguous stacks: C = A[0] Wbar_0, C2 = A[0] Wbar_1
+hipError_t launch_fused_pair(hipStream_t st, const fmg::Params &p);
 
 // expert gradients and routing-weight inner products with the per-segment weight gradients kept on
 // chip (fused_bwd_bf16.h); the partial-sum buffer holds fused_dw_slots(p) x S x 16 floats

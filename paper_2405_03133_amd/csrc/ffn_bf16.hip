@@ -90,7 +90,7 @@ bool use_fused(const Dims &m)
     const fmg::Params b = fused_params(m, nullptr, nullptr, m.dff, nullptr, nullptr, m.d, nullptr, m.d, m.dff,
                                        nullptr, m.d);
     if (!k::fused_fits(a) || !k::fused_fits(b)) return false;
-    return mode >= 2 || (m.T <= 64 && m.E <= 16);
+    return mode >= 2 || (m.T <= 64 && m.E <= 16 && m.tokens % fmg::kRows8 == 0);
 }
 
 // Whether the backward keeps the per-segment weight gradients on chip as well (fsg_kernel), for
@@ -104,6 +104,17 @@ hipError_t fused_gemm(hipStream_t st, const Dims &m, int cls, const fmg::Params 
     prof::Range r(st, cls, nsrc * (2.0 * p.tokens * D + 4.0 * m.S * m.E * D),
                   2.0 * (nsrc * ((double)m.E * D + (double)p.tokens * p.K) + (double)p.tokens * p.N));
     return k::launch_fused(st, p, nsrc, w_nc);
+}
+
+// Gate and up projections of all tokens, merged on chip.
+hipError_t fused_gate_up(hipStream_t st, const Dims &m, const bf *X, const bf *Wg, const bf *Wu, const float *w, bf *G, bf *U)
+{
+    fmg::Params p = fused_params(m, X, nullptr, m.d, Wg, Wu, m.dff, w, m.dff, m.d, G, m.dff);
+    p.C2 = U;
+    const double D = (double)m.D;
+    prof::Range r(st, prof::kFusedGU, 2.0 * (2.0 * m.tokens * D + 4.0 * m.S * m.E * D),
+                  2.0 * (2.0 * m.E * D + (double)m.tokens * m.d + 2.0 * m.tokens * m.dff));
+    return k::launch_fused_pair(st, p);
 }
 
 // Largest multiple of `gran` that is <= limit and <= full, at least gran.
@@ -349,10 +360,7 @@ int bf16_ffn_fwd(const Dims &m, const void *Xv, const float *w, const void *Wgv,
     if (!Wbar && m.S <= pl.Sc && use_fused(m)) {
         // merged parameters never leave the chip: three fused contractions and one SwiGLU pass
         bf *Gf = G ? G : slab, *Uf = U ? U : (bf *)((char *)slab + pl.act);
-        LORY_TRY(fused_gemm(st, m, prof::kFusedGU,
-                            fused_params(m, X, nullptr, m.d, Wg, nullptr, m.dff, w, m.dff, m.d, Gf, m.dff), 1, true));
-        LORY_TRY(fused_gemm(st, m, prof::kFusedGU,
-                            fused_params(m, X, nullptr, m.d, Wu, nullptr, m.dff, w, m.dff, m.d, Uf, m.dff), 1, true));
+        LORY_TRY(fused_gate_up(st, m, X, Wg, Wu, w, Gf, Uf));
         {
             prof::Range r(st, prof::kSwigluFwd, 4.0 * m.tokens * m.dff, 2.0 * 3.0 * m.tokens * m.dff);
             LORY_TRY(k::launch_swiglu_fwd(st, Gf, Uf, Act, m.tokens, m.dff, 0, m.dff));
@@ -752,10 +760,7 @@ int bf16_ffn_bwd(const Dims &m, const void *Xv, const float *w, const void *Wgv,
             Gc = G + (size_t)s0 * TF;
             Uc = U + (size_t)s0 * TF;
         } else if (fused) {
-            LORY_TRY(fused_gemm(st, m, prof::kFusedGU,
-                                fused_params(m, X, nullptr, m.d, Wg, nullptr, m.dff, w, m.dff, m.d, Gr, m.dff), 1, true));
-            LORY_TRY(fused_gemm(st, m, prof::kFusedGU,
-                                fused_params(m, X, nullptr, m.d, Wu, nullptr, m.dff, w, m.dff, m.d, Ur, m.dff), 1, true));
+            LORY_TRY(fused_gate_up(st, m, X, Wg, Wu, w, Gr, Ur));
             Gc = Gr;
             Uc = Ur;
         } else {

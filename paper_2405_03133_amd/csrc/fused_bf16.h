@@ -56,6 +56,7 @@ struct Params {
     int N, K;               // output columns (multiple of 64); contraction length per source (multiple of 32)
     uint16_t *C;            // [tokens][ldc]
     int ldc;
+    uint16_t *C2;           // second product of the same token operand, A[0] Wbar_1 (launch_fused_pair)
 };
 
 // KG: the merged tiles are formed per K step (32 wide) instead of per slice (16 wide).
@@ -442,82 +443,101 @@ struct Smem8 {
     static constexpr int total = a_bytes + 2 * m_bytes;
 };
 
-template <int TSEG, int NSRC, bool W_NC>
+constexpr int kRows8 = 512;   // token rows of a task
+
+// PAIR: two contractions of one token operand in a launch, C[i] = A Wbar_i (gate and up): their tasks together fill the
+// rounds of workgroups better than one after the other.
+//
+// Bound by the chain of a K step (expert chunks from L2, transposes, merge, LDS, barrier, multiply) and by how fast the CU
+// takes in the chunks: 96 KB in 1.8 us.  The chunks come through buffer loads, one scalar base for a K step and 32-bit lane
+// offsets that never change, so that a wave's eight loads issue back to back; with 64-bit lane addresses formed between them
+// the loads of the eight waves interleave and the same kernel took 844 us instead of 690 (8192 tokens, K = 2048, N = 5632, 16
+// experts, T = 64; with the loop free of conditionals, in which the compiler overlaps the two products, 672).
+// K-contiguous stacks (their rows are read in 64-byte pieces) are faster with the next tile merged before the current one
+// is multiplied: 726 -> 685 us for dA, 1578 -> 1465 for dX; K-slow ones slower (690 -> 760).
+template <int TSEG, int NSRC, bool W_NC, bool PAIR>
 __global__ __launch_bounds__(512, 1) void fmg8_kernel(const Params p)
 {
+    static_assert(!PAIR || NSRC == 1, "one token operand");
     using SM = Smem8<TSEG>;
-    constexpr int WROWS = 64, R = 512, MI = 2, NI = 2, NLD = 4;
+    constexpr int WROWS = 64, R = kRows8, MI = 2, NI = 2, NLD = 4;
     constexpr int SC = R / TSEG;
     constexpr int SEGB = SM::seg_bytes;
     static_assert(SC >= 1 && SC <= 8, "two units share the 16 rows of one merge MFMA");
+    static_assert(TSEG % WROWS == 0, "a wave's rows belong to one segment");
 
     extern __shared__ __attribute__((aligned(16))) char smem[];
     typedef __attribute__((address_space(3))) s16x4 *lds_tr_ptr;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
-    const int wave = tid >> 6;
-    const uint32_t wave_u = __builtin_amdgcn_readfirstlane(wave);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
     char *a_ring = smem + wave * 2 * SM::a_stage;
-    const uint32_t a_ring_u = lds0 + wave_u * 2 * SM::a_stage;
+    const uint32_t a_ring_u = lds0 + wave * 2 * SM::a_stage;
     char *m_buf = smem + SM::a_bytes;
 
     const int c16 = lane & 15, kg = lane >> 4;
     const int ksteps = p.K / BK;
     const int G = ksteps * NSRC;
+    const int S = p.tokens / TSEG;
 
-    const int nrc = p.tokens / R, ncb = p.N / BN;
-    const int rcg = (nrc + 7) >> 3, cbg = (ncb + 3) >> 2;
-    const int nsuper = rcg * cbg;
-    const int xcd = blockIdx.x & 7, q0 = blockIdx.x >> 3, wg_per_xcd = gridDim.x >> 3;
+    // Tasks of an XCD are consecutive: 8 row chunks (the last group may have fewer) by 4 column blocks run on its 32 CUs
+    // at a time and share token and expert tiles in its L2.
+    const int nrc = (p.tokens + R - 1) / R, ncb = p.N / BN;
+    const int one = nrc * ncb, ntasks = PAIR ? 2 * one : one;
+    const int per_xcd = (ntasks + 7) >> 3;
+    const int xcd = blockIdx.x & 7, wg_per_xcd = gridDim.x >> 3;
+    const int t_end = (xcd + 1) * per_xcd < ntasks ? (xcd + 1) * per_xcd : ntasks;
 
-    // same dealing of tasks as the four-wave kernel: 8 row chunks x 4 column blocks per XCD at a time
-    for (int sup = xcd; sup < nsuper; sup += 8) {
-        for (int q = q0; q < 32; q += wg_per_xcd) {
-            const int rc = (sup % rcg) * 8 + (q & 7);
-            const int cb = (sup / rcg) * 4 + (q >> 3);
-            if (rc >= nrc || cb >= ncb) continue;   // uniform over the workgroup
+    for (int t = xcd * per_xcd + (int)(blockIdx.x >> 3); t < t_end; t += wg_per_xcd) {
+        const int mat = PAIR && t >= one;
+        const int tt = t - mat * one;
+        const int rg = tt / (8 * ncb), left = tt - rg * 8 * ncb;
+        const int nr = nrc - 8 * rg < 8 ? nrc - 8 * rg : 8;
+        const int cb = left / nr, rc = 8 * rg + left % nr;
 
-            const int row0 = rc * R + wave * WROWS;
-            const int seg0 = (rc * R) / TSEG;
-            const int sl = (wave * WROWS) / TSEG;    // segment (within the task) of this wave's rows
-            const int n0 = cb * BN;
+        const int row0 = rc * R + wave * WROWS;
+        const int seg0 = (rc * R) / TSEG;
+        const int sl = (wave * WROWS) / TSEG;    // segment (within the task) of this wave's rows
+        const int n0 = cb * BN;
+        // rows beyond the tokens (the last row chunk): the last rows are read and nothing is stored
+        const int row_ld = row0 < p.tokens ? row0 : p.tokens - WROWS;
 
-            // block-diagonal routing-weight operand: rows 0..7 = segments against K 0..15 = experts
-            // (first unit), rows 8..15 = the same segments against K 16..31 = experts (second unit)
-            Frag whi, wlo;
-            {
-                float v[8];
+        // block-diagonal routing-weight operand: rows 0..7 = segments against K 0..15 = experts
+        // (first unit), rows 8..15 = the same segments against K 16..31 = experts (second unit)
+        Frag whi, wlo;
+        {
+            float v[8];
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const int kk = 8 * kg + i;
-                    const int seg = c16 & 7, e = kk & 15;
-                    const bool ok = (c16 >> 3) == (kk >> 4);
-                    v[i] = (ok && seg < SC && e < p.E) ? p.w[(size_t)(seg0 + seg) * p.E + e] : 0.f;
-                }
-                ms::split_hi_lo(v, whi, wlo);
+            for (int i = 0; i < 8; ++i) {
+                const int kk = 8 * kg + i;
+                const int seg = c16 & 7, e = kk & 15;
+                const bool ok = (c16 >> 3) == (kk >> 4);
+                v[i] = (ok && seg < SC && seg0 + seg < S && e < p.E) ? p.w[(size_t)(seg0 + seg) * p.E + e] : 0.f;
             }
+            ms::split_hi_lo(v, whi, wlo);
+        }
 
-            const int arow = lane >> 2;
-            const int aslot = (lane & 3) ^ gemm2::fkc(arow);
-            long a_off[NSRC];
+        const int arow = lane >> 2;
+        const int aslot = (lane & 3) ^ gemm2::fkc(arow);
+        const uint32_t a_lane = 2u * ((uint32_t)arow * (uint32_t)p.lda[0] + (aslot << 3));   // the sources share lda
+        const uint32_t a_step = 32u * (uint32_t)p.lda[0];
+        auto issue_a = [&](int g) {
+            const int src = (NSRC == 2) ? (g / ksteps) : 0;
+            const int ks = (NSRC == 2) ? (g % ksteps) : g;
+            const char *a = reinterpret_cast<const char *>(p.A[src] + (size_t)row_ld * p.lda[0] + ks * BK);
+            const uint32_t dst = a_ring_u + (g & 1) * SM::a_stage;
 #pragma unroll
-            for (int s = 0; s < NSRC; ++s) a_off[s] = (long)(row0 + arow) * p.lda[s] + (aslot << 3);
-            auto issue_a = [&](int g) {
-                const int src = (NSRC == 2) ? (g / ksteps) : 0;
-                const int ks = (NSRC == 2) ? (g % ksteps) : g;
-                const uint16_t *a = p.A[src] + a_off[src] + ks * BK;
-                const long step = (long)16 * p.lda[src];
-                const uint32_t dst = a_ring_u + (g & 1) * SM::a_stage;
-#pragma unroll
-                for (int i = 0; i < NLD; ++i) gemm2::dma16(a + i * step, dst + i * 1024);
-            };
+            for (int i = 0; i < NLD; ++i) gemm2::dma16s(a, a_lane + i * a_step, dst + i * 1024);
+        };
 
-            // expert chunks of a K step: lane (c16, kg) loads its chunk of unit kg >> 1 from experts
-            // 8 (kg & 1) .. + 7.   W_NC: units = K rows 4 wave + 2 u + {0, 1}, chunk = 8 columns.
-            // else: units = columns 8 wave + 4 u + {0..3}, chunk = 8 K values (64 bytes per column).
-            // (byte offsets from the K step's first element, 32 bits: the stack is smaller than 2 GiB)
+        // expert chunks of a K step: lane (c16, kg) loads its chunk of unit kg >> 1 from experts
+        // 8 (kg & 1) .. + 7.   W_NC: units = K rows 4 wave + 2 u + {0, 1}, chunk = 8 columns.
+        // else: units = columns 8 wave + 4 u + {0..3}, chunk = 8 K values (64 bytes per column).
+        // (byte offsets from the K step's first element, 32 bits: the stack is smaller than 2 GiB)
+        uint32_t w_off[8];
+        {
             uint32_t w_lane;
             if constexpr (W_NC)
                 w_lane = (uint32_t)(4 * wave + 2 * (kg >> 1) + (c16 >> 3)) * (uint32_t)p.ldw + n0 + 8 * (c16 & 7);
@@ -526,170 +546,195 @@ __global__ __launch_bounds__(512, 1) void fmg8_kernel(const Params p)
             const int e_first = 8 * (kg & 1);
             const uint32_t stride_b = (uint32_t)p.expert_stride * 2u;
             w_lane = w_lane * 2u + (uint32_t)(e_first < p.E ? e_first : 0) * stride_b;
-            Frag EX[8];
-            auto load_ex = [&](int g) {
-                const int src = (NSRC == 2) ? (g / ksteps) : 0;
-                const int ks = (NSRC == 2) ? (g % ksteps) : g;
-                const char *wk = reinterpret_cast<const char *>(p.W[src]) +
-                                 (W_NC ? (size_t)ks * BK * p.ldw : (size_t)ks * BK) * 2;   // wave-uniform
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const uint32_t off = w_lane + ((e_first + i < p.E) ? (uint32_t)i * stride_b : 0u);   // beyond E: weight 0
-                    EX[i].u = *reinterpret_cast<const uint4 *>(wk + off);
+            for (int i = 0; i < 8; ++i) w_off[i] = w_lane + ((e_first + i < p.E) ? (uint32_t)i * stride_b : 0u);   // beyond E: weight 0
+        }
+        Frag EX[8];
+        auto load_ex = [&](int g) {
+            const int src = (NSRC == 2) ? (g / ksteps) : mat;
+            const int ks = (NSRC == 2) ? (g % ksteps) : g;
+            const uint16_t *wk = p.W[src] + (W_NC ? (size_t)ks * BK * p.ldw : (size_t)ks * BK);
+            // every offset lies inside the stack: the range is that of the offsets
+            const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(wk), 0, 0x7fffffff, 0x00027000);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, w_off[i], 0, 0);
+                EX[i].u = make_uint4(v.x, v.y, v.z, v.w);
+            }
+        };
+        auto produce = [&](int g) {
+            char *mb = m_buf + (g & 1) * SM::m_bytes;
+            Frag P[8];
+            ms::transpose8x8(EX, P);
+            const int uo = kg >> 1, sbase = 4 * (kg & 1);   // rows 4 kg + r: unit, segment
+            int off;
+            if constexpr (W_NC) {
+                const int kl = 4 * wave + 2 * uo + (c16 >> 3);
+                const int g32 = ((c16 & 7) >> 1) ^ (uo << 1);
+                off = kl * 128 + (g32 << 5) + ((c16 & 1) << 4);
+            } else {
+                const int nl = 8 * wave + 4 * uo + (c16 >> 2);
+                off = nl * 64 + (((c16 & 3) ^ ((nl >> 2) & 3)) << 4);
+            }
+            // two halves of the 8 elements of a chunk, to keep fewer merge accumulators alive
+#pragma unroll
+            for (int hf = 0; hf < 2; ++hf) {
+                f32x4 macc[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    macc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    macc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(whi.v, P[4 * hf + j].v, macc[j], 0, 0, 0);
+                    macc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wlo.v, P[4 * hf + j].v, macc[j], 0, 0, 0);
                 }
-            };
-            auto produce = [&](int g) {
-                char *mb = m_buf + (g & 1) * SM::m_bytes;
-                Frag P[8];
-                ms::transpose8x8(EX, P);
-                const int uo = kg >> 1, sbase = 4 * (kg & 1);   // rows 4 kg + r: unit, segment
-                int off;
-                if constexpr (W_NC) {
-                    const int kl = 4 * wave + 2 * uo + (c16 >> 3);
-                    const int g32 = ((c16 & 7) >> 1) ^ (uo << 1);
-                    off = kl * 128 + (g32 << 5) + ((c16 & 1) << 4);
-                } else {
-                    const int nl = 8 * wave + 4 * uo + (c16 >> 2);
-                    off = nl * 64 + (((c16 & 3) ^ ((nl >> 2) & 3)) << 4);
-                }
-                // two halves of the 8 elements of a chunk, to keep fewer merge accumulators alive
 #pragma unroll
-                for (int hf = 0; hf < 2; ++hf) {
-                    f32x4 macc[4];
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        macc[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-                        macc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(whi.v, P[4 * hf + j].v, macc[j], 0, 0, 0);
-                        macc[j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wlo.v, P[4 * hf + j].v, macc[j], 0, 0, 0);
+                for (int r = 0; r < 4; ++r) {
+                    const int seg = sbase + r;
+                    if (seg < SC) {
+                        uint2 o;
+                        o.x = ms::pack_bf16(macc[0][r], macc[1][r]);
+                        o.y = ms::pack_bf16(macc[2][r], macc[3][r]);
+                        *reinterpret_cast<uint2 *>(mb + seg * SEGB + off + 8 * hf) = o;
                     }
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int seg = sbase + r;
-                        if (seg < SC) {
-                            uint2 o;
-                            o.x = ms::pack_bf16(macc[0][r], macc[1][r]);
-                            o.y = ms::pack_bf16(macc[2][r], macc[3][r]);
-                            *reinterpret_cast<uint2 *>(mb + seg * SEGB + off + 8 * hf) = o;
-                        }
-                    }
                 }
-            };
-            auto frag_b = [&](const char *mb, int jn, int h) -> bf16x8 {
-                if constexpr (W_NC) {
-                    const int g16 = lane >> 4, r = lane & 15;
-                    const int coloff = (jn * 32 + 16 * (g16 & 1) + 4 * (r & 3)) * 2;
-                    const int krow = 16 * h + 8 * (g16 >> 1) + (r >> 2);
-                    const int g32 = (coloff >> 5) ^ (((krow >> 1) & 1) << 1);
-                    const char *q = mb + sl * SEGB + krow * 128 + (g32 << 5) + (coloff & 31);
-                    union {
-                        s16x4 hh[2];
-                        bf16x8 v;
-                    } u;
-                    u.hh[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_tr_ptr)(q));
-                    u.hh[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_tr_ptr)(q + 4 * 128));
-                    return u.v;
-                } else {
-                    const int n = jn * 32 + (lane & 31);
-                    const int c = (2 * h + (lane >> 5)) ^ ((n >> 2) & 3);
-                    return *reinterpret_cast<const bf16x8 *>(mb + sl * SEGB + n * 64 + (c << 4));
-                }
-            };
+            }
+        };
+        auto frag_b = [&](const char *mb, int jn, int h) -> bf16x8 {
+            if constexpr (W_NC) {
+                const int g16 = lane >> 4, r = lane & 15;
+                const int coloff = (jn * 32 + 16 * (g16 & 1) + 4 * (r & 3)) * 2;
+                const int krow = 16 * h + 8 * (g16 >> 1) + (r >> 2);
+                const int g32 = (coloff >> 5) ^ (((krow >> 1) & 1) << 1);
+                const char *q = mb + sl * SEGB + krow * 128 + (g32 << 5) + (coloff & 31);
+                union {
+                    s16x4 hh[2];
+                    bf16x8 v;
+                } u;
+                u.hh[0] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_tr_ptr)(q));
+                u.hh[1] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_tr_ptr)(q + 4 * 128));
+                return u.v;
+            } else {
+                const int n = jn * 32 + (lane & 31);
+                const int c = (2 * h + (lane >> 5)) ^ ((n >> 2) & 3);
+                return *reinterpret_cast<const bf16x8 *>(mb + sl * SEGB + n * 64 + (c << 4));
+            }
+        };
 
-            f32x16 acc[MI][NI];
+        f32x16 acc[MI][NI];
 #pragma unroll
-            for (int i = 0; i < MI; ++i)
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NI; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+        auto multiply = [&](int g, int h) {
+            const char *as = a_ring + (g & 1) * SM::a_stage;
+            const char *mb = m_buf + (g & 1) * SM::m_bytes;
+            bf16x8 bfr[NI];
+#pragma unroll
+            for (int j = 0; j < NI; ++j) bfr[j] = frag_b(mb, j, h);
+#pragma unroll
+            for (int i = 0; i < MI; ++i) {
+                const bf16x8 af = gemm2::frag_kc(as, i * 32, h, lane);
 #pragma unroll
                 for (int j = 0; j < NI; ++j)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af, acc[i][j], 0, 0, 0);
+            }
+        };
 
-            auto multiply = [&](int g, int h) {
-                const char *as = a_ring + (g & 1) * SM::a_stage;
-                const char *mb = m_buf + (g & 1) * SM::m_bytes;
-                bf16x8 bfr[NI];
-#pragma unroll
-                for (int j = 0; j < NI; ++j) bfr[j] = frag_b(mb, j, h);
-#pragma unroll
-                for (int i = 0; i < MI; ++i) {
-                    const bf16x8 af = gemm2::frag_kc(as, i * 32, h, lane);
-#pragma unroll
-                    for (int j = 0; j < NI; ++j)
-                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[j], af, acc[i][j], 0, 0, 0);
-                }
-            };
-
-            // Token tiles two K steps ahead, issued right before the expert loads of the same K step,
-            // whose data is consumed (by produce) before the tile is read: the compiler's wait in
-            // front of that consumption covers the tile (loads retire in order).  (Expert chunks two
-            // K steps ahead and a third ring stage measured the same: the kernel is bound by the bytes
-            // entering the CU, not by their latency.)
-            issue_a(0);
-            issue_a(1);
-            load_ex(0);
-            gemm2::wait_vmcnt<0>();
-            produce(0);
-            load_ex(1);
-            for (int g = 0; g < G; ++g) {   // G is even and at least 2
-                gemm2::ring_barrier();   // merged tile g complete for every wave; tile g - 1 no longer read
+        // K step g: one barrier (merged tile g complete for every wave, tile g - 1 no longer read), then tile g is
+        // multiplied and tile g + 1 merged.  Token tiles run two K steps ahead.  The compiler's wait counts do not
+        // know the direct loads that bring them, so each tile is issued before expert chunks that are consumed before it
+        // is read, and loads retire in order.
+        issue_a(0);
+        issue_a(1);
+        load_ex(0);
+        gemm2::wait_vmcnt<0>();
+        produce(0);
+        load_ex(1);
+        if constexpr (W_NC) {
+            // tokens of step g + 2 before chunks of step g + 2, which step g + 1 consumes
+            auto iter = [&](int g, auto ahead) {
+                gemm2::ring_barrier();
                 multiply(g, 0);
                 multiply(g, 1);
-                if (g + 1 < G) produce(g + 1);
-                if (g + 2 < G) {
+                if constexpr (ahead >= 1) produce(g + 1);
+                if constexpr (ahead >= 2) {
                     __builtin_amdgcn_s_waitcnt(0xC07F);   // this wave's reads of ring slot g & 1 have returned
                     issue_a(g + 2);
                     load_ex(g + 2);
                 }
-            }
-
-            // epilogue through the wave's own ring memory, as in the four-wave kernel
-            {
-                char *stg = a_ring;
-                const int r31 = lane & 31, h2 = lane >> 5;
-#pragma unroll
-                for (int i = 0; i < MI; ++i) {
-#pragma unroll
-                    for (int j = 0; j < NI; ++j)
-#pragma unroll
-                        for (int rq = 0; rq < 4; ++rq) {
-                            const int nl = j * 32 + 8 * rq + 4 * h2;
-                            u32x2 pk;
-                            pk.x = gemm::cvt_pk_bf16(acc[i][j][rq * 4 + 0], acc[i][j][rq * 4 + 1]);
-                            pk.y = gemm::cvt_pk_bf16(acc[i][j][rq * 4 + 2], acc[i][j][rq * 4 + 3]);
-                            const int c = nl >> 3;
-                            *reinterpret_cast<u32x2 *>(stg + r31 * 128 + ((c ^ (r31 & 7)) << 4) + h2 * 8) = pk;
-                        }
-                    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-                    for (int it = 0; it < 4; ++it) {
-                        const int idx = it * 64 + lane;
-                        const int row = idx >> 3, c = idx & 7;
-                        const u32x4 val = *reinterpret_cast<const u32x4 *>(stg + row * 128 + ((c ^ (row & 7)) << 4));
-                        __builtin_nontemporal_store(
-                            val, reinterpret_cast<u32x4 *>(p.C + (size_t)(row0 + i * 32 + row) * p.ldc + n0 + c * 8));
-                    }
-                    __builtin_amdgcn_wave_barrier();
+            };
+            int g = 0;
+            for (; g + 2 < G; ++g) iter(g, std::integral_constant<int, 2>());   // G is even and at least 2
+            iter(g, std::integral_constant<int, 1>());
+            iter(g + 1, std::integral_constant<int, 0>());
+        } else {
+            // tokens of step g + 2 before chunks of step g + 3, which step g + 2 consumes before it multiplies
+            for (int g = 0; g < G; ++g) {
+                gemm2::ring_barrier();
+                if (g + 1 < G) produce(g + 1);
+                if (g + 2 < G) load_ex(g + 2);
+                multiply(g, 0);
+                multiply(g, 1);
+                if (g + 2 < G) {
+                    __builtin_amdgcn_s_waitcnt(0xC07F);   // this wave's reads of ring slot g & 1 have returned
+                    issue_a(g + 2);
+                } else {
+                    gemm2::wait_vmcnt<0>();   // no chunks follow: the tokens of the last step are waited for here
                 }
             }
-            __builtin_amdgcn_s_waitcnt(0xC07F);
         }
+
+        // epilogue through the wave's own ring memory, as in the four-wave kernel
+        if (row0 < p.tokens) {
+            uint16_t *C = mat ? p.C2 : p.C;
+            char *stg = a_ring;
+            const int r31 = lane & 31, h2 = lane >> 5;
+#pragma unroll
+            for (int i = 0; i < MI; ++i) {
+#pragma unroll
+                for (int j = 0; j < NI; ++j)
+#pragma unroll
+                    for (int rq = 0; rq < 4; ++rq) {
+                        const int nl = j * 32 + 8 * rq + 4 * h2;
+                        u32x2 pk;
+                        pk.x = gemm::cvt_pk_bf16(acc[i][j][rq * 4 + 0], acc[i][j][rq * 4 + 1]);
+                        pk.y = gemm::cvt_pk_bf16(acc[i][j][rq * 4 + 2], acc[i][j][rq * 4 + 3]);
+                        const int c = nl >> 3;
+                        *reinterpret_cast<u32x2 *>(stg + r31 * 128 + ((c ^ (r31 & 7)) << 4) + h2 * 8) = pk;
+                    }
+                __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                for (int it = 0; it < 4; ++it) {
+                    const int idx = it * 64 + lane;
+                    const int row = idx >> 3, c = idx & 7;
+                    const u32x4 val = *reinterpret_cast<const u32x4 *>(stg + row * 128 + ((c ^ (row & 7)) << 4));
+                    __builtin_nontemporal_store(
+                        val, reinterpret_cast<u32x4 *>(C + (size_t)(row0 + i * 32 + row) * p.ldc + n0 + c * 8));
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+        }
+        __builtin_amdgcn_s_waitcnt(0xC07F);
     }
     gemm2::wait_vmcnt<0>();
 }
 
-// whole tasks and an even number of K steps, as for the four-wave kernel
+// an even number of K steps (a task's last merged tile then sits in buffer 1, which the next task's prologue leaves alone)
 template <int TSEG>
 inline bool fits8(const Params &p)
 {
-    return p.T == TSEG && p.tokens % 512 == 0 && p.N % BN == 0 && p.K % (2 * BK) == 0 && p.E <= 16 && p.E >= 1 &&
-           (size_t)p.E * (size_t)p.expert_stride * 2 < ((size_t)1 << 31);
+    return p.T == TSEG && p.tokens >= 64 && p.tokens % TSEG == 0 && p.N % BN == 0 && p.K % (2 * BK) == 0 && p.E <= 16 && p.E >= 1 &&
+           p.lda[0] == p.lda[1] && (size_t)p.E * (size_t)p.expert_stride * 2 < ((size_t)1 << 31);
 }
 
-template <int TSEG, int NSRC, bool W_NC>
+template <int TSEG, int NSRC, bool W_NC, bool PAIR>
 inline hipError_t launch8(const Params &p, hipStream_t st)
 {
     using SM = Smem8<TSEG>;
     static_assert(SM::total <= 160 * 1024, "LDS of one CU");
-    auto kern = fmg8_kernel<TSEG, NSRC, W_NC>;
+    auto kern = fmg8_kernel<TSEG, NSRC, W_NC, PAIR>;
     static bool configured = false;  // per instantiation
     if (!configured) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
@@ -697,7 +742,8 @@ inline hipError_t launch8(const Params &p, hipStream_t st)
         if (e != hipSuccess) return e;
         configured = true;
     }
-    const long tasks = (long)(p.tokens / 512) * (p.N / BN);
+    const long tasks = (long)((p.tokens + kRows8 - 1) / kRows8) * (p.N / BN) * (PAIR ? 2 : 1);
+    if (tasks >= (1L << 30)) return hipErrorInvalidValue;
     long blocks = (tasks + 7) / 8 * 8;
     if (blocks > gemm2::persistent_grid()) blocks = gemm2::persistent_grid();
     hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(512), SM::total, st, p);
