@@ -174,6 +174,8 @@ struct EpiPart {
 // K a multiple of 32 and at least 64.
 int merge_rounds(int E, int S, long elems, bool transient);   // rounds of workgroups that launch_merge starts
 hipError_t launch_merge(hipStream_t st, const ms::MergeParams &p);
+bool merge_is_few(int S, int E);          // whether launch_merge_few takes the merge of S segments
+hipError_t launch_merge_few(hipStream_t st, const ms::MergeFewParams &p, int matrices);
 hipError_t launch_scatter(hipStream_t st, const ms::ScatterParams &p, int grid);
 hipError_t launch_dw_reduce(hipStream_t st, const float *partials, int slots, int rows, int cols,
                             float *dw, int S, int E);

@@ -102,6 +102,37 @@ hipError_t launch_merge(hipStream_t st, const ms::MergeParams &p)
     return hipGetLastError();
 }
 
+// The vector ALUs take a merge that they finish before the memory does: (S + 1) E multiply-adds an element (one block of up
+// to 16 segments, which reads the stack once) against 2 (S + E) bytes.  Of few experts two blocks still pay: the
+// matrix-core kernel has no more in flight than their chunks.  us, matrix cores and this, 110 prompt merges of 5 .. 48
+// sequences: 2048 x 6144, 14 experts, 8 segments 319 and 282; 2560 x 6144, 3 and 8 311 and 157; 768 x 5632, 24 and 13 187
+// and 188; 2560 x 1536, 2 and 36 198 and 152; 1024 x 6144, 12 and 27 285 and 386; 2048 x 6144, 3 and 40 611 and 704.
+bool merge_is_few(int S, int E) { return (S <= 16 && (S + 1) * E <= 320) || (S <= 32 && E <= 4); }
+
+hipError_t launch_merge_few(hipStream_t st, const ms::MergeFewParams &p, int matrices)
+{
+    if (p.S < 1 || p.S > ms::kFewSegments || matrices < 1 || matrices > 3) return hipErrorInvalidValue;
+    const int blocks = (p.S + 15) / 16, sb = (p.S + blocks - 1) / blocks;
+    const dim3 grid((unsigned)((p.rc.nr * p.rc.nc / 8 + 255) / 256), (unsigned)matrices, (unsigned)blocks);
+#define LORY_FEW(N)                                                                                  \
+    if (p.seg_map)                                                                                   \
+        hipLaunchKernelGGL((ms::merge_few_kernel<N, true>), grid, dim3(256), 0, st, p);              \
+    else                                                                                             \
+        hipLaunchKernelGGL((ms::merge_few_kernel<N, false>), grid, dim3(256), 0, st, p)
+    switch (sb) {
+    case 1: LORY_FEW(1); break;
+    case 2: LORY_FEW(2); break;
+    case 3: LORY_FEW(3); break;
+    case 4: LORY_FEW(4); break;
+    case 5: case 6: LORY_FEW(6); break;
+    case 7: case 8: LORY_FEW(8); break;
+    case 9: case 10: case 11: case 12: LORY_FEW(12); break;
+    default: LORY_FEW(16); break;
+    }
+#undef LORY_FEW
+    return hipGetLastError();
+}
+
 hipError_t launch_scatter(hipStream_t st, const ms::ScatterParams &p, int grid)
 {
     const int KB = (p.S + 15) / 16;

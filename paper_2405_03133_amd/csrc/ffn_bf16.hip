@@ -232,28 +232,53 @@ double gemm_flops(const Params &p, int nset, int nsrc)
     return 2.0 * p.batches * p.M * p.N * p.K * nset * nsrc;
 }
 
+// Merges of `count` matrices with the same rectangle, each into a slab of its own; of more than one only where few
+// segments are merged (k::merge_is_few).
+hipError_t merge(hipStream_t st, const float *w, int S, int E, const bf *const *stack, int count, const Rect &rc, bf *const *slab,
+                 int32_t *seg_map)
+{
+    const double n = (double)rc.nr * rc.nc;
+    int rec;
+    {
+        prof::Range r(st, prof::kMerge, 2.0 * S * E * n * count, 2.0 * n * (E + S) * count);
+        rec = r.index();
+        hipError_t e;
+        if (k::merge_is_few(S, E)) {
+            ms::MergeFewParams p = {};
+            p.w = w;
+            p.S = S;
+            p.E = E;
+            for (int x = 0; x < count; ++x) {
+                p.stack[x] = stack[x];
+                p.slab[x] = slab[x];
+            }
+            p.rc = rc;
+            p.seg_stride = (long)rc.nr * rc.nc;
+            p.seg_map = seg_map;
+            e = k::launch_merge_few(st, p, count);
+        } else {
+            if (count != 1) return hipErrorInvalidValue;
+            MergeParams p;
+            p.w = w;
+            p.S = S;
+            p.E = E;
+            p.stack = stack[0];
+            p.rc = rc;
+            p.slab = slab[0];
+            p.seg_stride = (long)rc.nr * rc.nc;
+            p.seg_map = seg_map;
+            e = k::launch_merge(st, p);
+        }
+        if (e != hipSuccess) return e;
+    }
+    prof::shared_segments(st, rec, seg_map, S, 2.0 * n * count);
+    return hipSuccess;
+}
+
 hipError_t merge(hipStream_t st, const float *w, int S, int E, const bf *stack, const Rect &rc, bf *slab,
                  int32_t *seg_map = nullptr)
 {
-    const double n = (double)rc.nr * rc.nc;
-    MergeParams p;
-    p.w = w;
-    p.S = S;
-    p.E = E;
-    p.stack = stack;
-    p.rc = rc;
-    p.slab = slab;
-    p.seg_stride = (long)rc.nr * rc.nc;
-    p.seg_map = seg_map;
-    int rec;
-    {
-        prof::Range r(st, prof::kMerge, 2.0 * S * E * n, 2.0 * n * (E + S));
-        rec = r.index();
-        const hipError_t e = k::launch_merge(st, p);
-        if (e != hipSuccess) return e;
-    }
-    prof::shared_segments(st, rec, seg_map, S, 2.0 * n);
-    return hipSuccess;
+    return merge(st, w, S, E, &stack, 1, rc, &slab, seg_map);
 }
 
 // Gate/up projections of one d_ff column block for a chunk of segments.
@@ -421,14 +446,17 @@ int bf16_merge_all(const Dims &m, const float *w, const void *Wgv, const void *W
 {
     const Plan pl = make_plan(m);
     const bf *stacks[3] = {(const bf *)Wgv, (const bf *)Wuv, (const bf *)Wdv};
-    const Rect rcs[3] = {rect(m.D, m.dff, 0, m.d, 0, m.dff), rect(m.D, m.dff, 0, m.d, 0, m.dff),
-                         rect(m.D, m.d, 0, m.dff, 0, m.d)};
+    const Rect all = rect(m.D, (int)m.D, 0, 1, 0, (int)m.D);   // whole matrices lie in one piece
     bf *out = (bf *)Wbarv;
     for (int s0 = 0; s0 < m.S; s0 += pl.Sc) {
         const int S = (m.S - s0 < pl.Sc) ? (m.S - s0) : pl.Sc;
-        for (int x = 0; x < 3; ++x)
-            LORY_TRY(merge(st, w + (size_t)s0 * m.E, S, m.E, stacks[x], rcs[x],
-                           out + ((size_t)x * m.S + s0) * m.D));
+        bf *slabs[3] = {out + (size_t)s0 * m.D, out + ((size_t)m.S + s0) * m.D, out + ((size_t)2 * m.S + s0) * m.D};
+        const float *ws = w + (size_t)s0 * m.E;
+        if (k::merge_is_few(S, m.E)) {
+            LORY_TRY(merge(st, ws, S, m.E, stacks, 3, all, slabs, nullptr));
+            continue;
+        }
+        for (int x = 0; x < 3; ++x) LORY_TRY(merge(st, ws, S, m.E, stacks[x], all, slabs[x]));
     }
     return LORY_OK;
 }

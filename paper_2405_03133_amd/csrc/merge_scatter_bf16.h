@@ -21,6 +21,7 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 #include "gemm_bf16.h"
 
@@ -250,6 +251,100 @@ __global__ __launch_bounds__(256) void merge_kernel(const MergeParams p)
                 }
             }
         }
+    }
+}
+
+// Merge of few segments on the vector ALUs: a thread owns one 16-byte chunk of the rectangle, keeps the fp32 sums of up
+// to SB segments and reads the chunk of every expert once, eight experts in flight; the routing weights are uniform and
+// come through scalar registers.  HBM-bound.  The matrix-core kernel above has one wavefront per SIMD and one unit in
+// flight behind the current one, which is enough where it stores dozens of segments for a unit, but not where a unit is
+// little more than its reads.  us of three merges, matrix cores -> this: 3 segments, 16 experts of 2048 x 5632 (one
+// launch) 263 -> 230; 3 and 6 of 1792 x 6144 220 -> 90 (6.5 TB/s); 1 and 1 of 1024 x 6144 131 -> 23.  The chunks are
+// loaded as non-temporal, they are read once (7 of 2048 x 5632, 32 experts: 517 -> 477); non-temporal stores took 487.
+struct MergeFewParams {
+    const float *w;            // [S, E]
+    int S, E;
+    const uint16_t *stack[3];  // grid y: matrices with the same rectangle
+    Rect rc;
+    uint16_t *slab[3];         // [S][nr*nc]
+    long seg_stride;
+    int32_t *seg_map;          // as MergeParams::seg_map
+};
+
+constexpr int kFewSegments = 64;
+
+template <int SB, bool MAP>
+__global__ __launch_bounds__(256) void merge_few_kernel(const MergeFewParams p)
+{
+    // grid z: blocks of SB segments
+    const int s0 = blockIdx.z * SB, mine = p.S - s0 < SB ? p.S - s0 : SB;
+    // bit s: segment s0 + s is stored (the first of a run of equal routing rows, compared as bits)
+    uint32_t stored = (1u << mine) - 1u;
+    if constexpr (MAP) {
+        __shared__ uint64_t keep;
+        if (threadIdx.x < 64) {
+            const int s = threadIdx.x;
+            bool first = s < p.S;
+            if (s > 0 && s < p.S) {
+                const uint32_t *a = reinterpret_cast<const uint32_t *>(p.w) + (size_t)s * p.E, *b = a - p.E;
+                uint32_t diff = 0;
+                for (int e = 0; e < p.E; ++e) diff |= a[e] ^ b[e];
+                first = diff != 0;
+            }
+            const uint64_t m = __builtin_amdgcn_ballot_w64(first);
+            if (s == 0) keep = m;
+            if (blockIdx.x + blockIdx.y + blockIdx.z == 0 && s < p.S) p.seg_map[s] = 63 - __builtin_clzll(m & (~0ull >> (63 - s)));
+        }
+        __syncthreads();
+        stored &= __builtin_amdgcn_readfirstlane((uint32_t)(keep >> s0));
+        if (stored == 0) return;
+    }
+
+    const int q = blockIdx.x * 256 + threadIdx.x;
+    if (q >= ((p.rc.nr * p.rc.nc) >> 3)) return;
+    const uint16_t *src = p.stack[blockIdx.y] + rect_offset(p.rc, q);
+    uint16_t *dst = p.slab[blockIdx.y] + (size_t)s0 * p.seg_stride + (size_t)q * 8;
+
+    float acc[SB][8];
+#pragma unroll
+    for (int s = 0; s < SB; ++s)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[s][j] = 0.f;
+    auto add = [&](auto count, int e0) {
+        uint4 v[count];
+#pragma unroll
+        for (int i = 0; i < count; ++i) { const gemm::u32x4 t = __builtin_nontemporal_load(reinterpret_cast<const gemm::u32x4 *>(src + (size_t)(e0 + i) * p.rc.expert_stride)); v[i] = make_uint4(t.x, t.y, t.z, t.w); }
+#pragma unroll
+        for (int i = 0; i < count; ++i) {
+            float x[8];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t u = j == 0 ? v[i].x : j == 1 ? v[i].y : j == 2 ? v[i].z : v[i].w;
+                x[2 * j] = __uint_as_float(u << 16);
+                x[2 * j + 1] = __uint_as_float(u & 0xffff0000u);
+            }
+#pragma unroll
+            for (int s = 0; s < SB; ++s) {
+                const float ws = p.w[(size_t)(s0 + (s < mine ? s : 0)) * p.E + e0 + i];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) acc[s][j] = fmaf(ws, x[j], acc[s][j]);
+            }
+        }
+    };
+    int e = 0;
+    for (; e + 8 <= p.E; e += 8) add(std::integral_constant<int, 8>(), e);
+    if (p.E & 4) add(std::integral_constant<int, 4>(), e);
+    if (p.E & 2) add(std::integral_constant<int, 2>(), e + (p.E & 4));
+    if (p.E & 1) add(std::integral_constant<int, 1>(), p.E - 1);
+#pragma unroll
+    for (int s = 0; s < SB; ++s) {
+        if (!(stored >> s & 1)) continue;
+        uint4 o;
+        o.x = pack_bf16(acc[s][0], acc[s][1]);
+        o.y = pack_bf16(acc[s][2], acc[s][3]);
+        o.z = pack_bf16(acc[s][4], acc[s][5]);
+        o.w = pack_bf16(acc[s][6], acc[s][7]);
+        *reinterpret_cast<uint4 *>(dst + (size_t)s * p.seg_stride) = o;
     }
 }
 

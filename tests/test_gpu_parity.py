@@ -314,6 +314,9 @@ def test_bf16_ring_gemm_edge_tiles_without_saved_planes(cfg):
 @pytest.mark.parametrize("cfg", [
     LoryConfig("shared_S150", B=5, L=3840, T=128, d=64, d_ff=128, E=5, dtype="bf16", seed=111),
     LoryConfig("shared_E33", B=2, L=4096, T=128, d=64, d_ff=64, E=33, dtype="bf16", seed=112),
+    # few segments: one block of sums, and two
+    LoryConfig("shared_S15", B=3, L=640, T=128, d=64, d_ff=192, E=7, dtype="bf16", seed=123),
+    LoryConfig("shared_S30", B=5, L=768, T=128, d=64, d_ff=192, E=4, dtype="bf16", seed=124),
 ], ids=lambda c: c.name)
 @pytest.mark.parametrize("runs", ["words", "all", "alternating", "none"])
 def test_bf16_equal_routing_rows(cfg, runs):
@@ -331,6 +334,26 @@ def test_bf16_equal_routing_rows(cfg, runs):
         got, saved = (run_layer(cfg, t, w_override=w, save=save, merged_save=m) for m in (False, True))
         for key in ("Y", "dX", "dWg", "dWu", "dWd", "dw"):
             assert np.array_equal(got[key], saved[key]), key
+
+
+# Every number of sums that a thread keeps, one and two blocks of them, the remainders of the experts in groups of eight, and
+# a last workgroup that the chunks do not fill; the last two are beyond the line and merged on the matrix cores.
+@pytest.mark.parametrize("B,E,d,d_ff", [(1, 1, 64, 64), (1, 13, 64, 320), (2, 2, 128, 192), (3, 7, 64, 128), (4, 8, 192, 64),
+                                        (6, 9, 64, 192), (7, 16, 64, 64), (8, 33, 64, 128), (11, 26, 64, 64), (12, 5, 64, 192),
+                                        (16, 18, 64, 128), (17, 4, 64, 64), (32, 3, 64, 192), (33, 3, 64, 64), (16, 19, 64, 64)])
+def test_bf16_merge_of_few_segments(B, E, d, d_ff):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1000 * B + E)
+    rand = lambda *s: torch.randn(s, generator=g, device="cuda").bfloat16()
+    X, R, W = rand(B, 64, d), rand(d, E), [rand(E, d, d_ff), rand(E, d, d_ff), rand(E, d_ff, d)]
+    print(f"[gpu] few segments B={B} E={E}", flush=True)
+    w, Wbar = lb.lory_prompt_merge(X, R, *W, Wbar=torch.full((3, B, d * d_ff), float("nan"), device="cuda", dtype=torch.bfloat16))
+    w64 = host(w).astype(np.float64)
+    for x in range(3):
+        st = host(W[x]).astype(np.float64).reshape(E, -1)
+        ref, mag = w64 @ st, np.abs(w64) @ np.abs(st)
+        # one rounding to bf16, and sums in 32 bits of weights that the matrix cores take as hi + lo (2^-17)
+        assert np.all(np.abs(host(Wbar[x]) - ref) <= 2.0 ** -8 * np.abs(ref) + 2.0 ** -15 * mag), x
 
 
 def test_profile_counts_shared_merges_once():
