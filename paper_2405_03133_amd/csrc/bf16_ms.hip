@@ -102,24 +102,27 @@ hipError_t launch_merge(hipStream_t st, const ms::MergeParams &p)
     return hipGetLastError();
 }
 
-// The vector ALUs take a merge that they finish before the memory does: (S + 1) E multiply-adds an element (one block of up
-// to 16 segments, which reads the stack once) against 2 (S + E) bytes.  Of few experts two blocks still pay: the
-// matrix-core kernel has no more in flight than their chunks.  us, matrix cores and this, 110 prompt merges of 5 .. 48
-// sequences: 2048 x 6144, 14 experts, 8 segments 319 and 282; 2560 x 6144, 3 and 8 311 and 157; 768 x 5632, 24 and 13 187
-// and 188; 2560 x 1536, 2 and 36 198 and 152; 1024 x 6144, 12 and 27 285 and 386; 2048 x 6144, 3 and 40 611 and 704.
-bool merge_is_few(int S, int E) { return (S <= 16 && (S + 1) * E <= 320) || (S <= 32 && E <= 4); }
+// The vector ALUs take a merge that they finish before the memory does: (S + 1) E multiply-adds an element against
+// 2 (S + E) bytes.  Beyond 8 segments only of few experts, where the matrix-core kernel has no more in flight than their
+// chunks: it writes more segments as fast.  us of the three merges of a layer, matrix cores and this.  Prompts: 14 experts of
+// 2048 x 6144, 8 segments 319 and 282; 3 experts of 2560 x 6144, 8 311 and 157; 5 of 1536 x 2816, 16 119 and 93.  Training
+// (the GEMM reads the slab next): 32 of 2048 x 5632, 4 segments 490 and 439; 8 of 1024 x 2816, 12 87 and 80; 6 of
+// 1536 x 4096, 16 181 and 183, the GEMMs 18 less; 20 of 1536 x 1536, 10 105 and 109; 12 of 1536 x 4096, 16 203 and 227.
+bool merge_is_few(int S, int E)
+{
+    return S <= 8 ? (S + 1) * E <= 320 : S <= 12 ? E <= 8 : S <= 16 && E <= 6;
+}
 
 hipError_t launch_merge_few(hipStream_t st, const ms::MergeFewParams &p, int matrices)
 {
     if (p.S < 1 || p.S > ms::kFewSegments || matrices < 1 || matrices > 3) return hipErrorInvalidValue;
-    const int blocks = (p.S + 15) / 16, sb = (p.S + blocks - 1) / blocks;
-    const dim3 grid((unsigned)((p.rc.nr * p.rc.nc / 8 + 255) / 256), (unsigned)matrices, (unsigned)blocks);
+    const dim3 grid((unsigned)((p.rc.nr * p.rc.nc / 8 + 255) / 256), (unsigned)matrices);
 #define LORY_FEW(N)                                                                                  \
     if (p.seg_map)                                                                                   \
         hipLaunchKernelGGL((ms::merge_few_kernel<N, true>), grid, dim3(256), 0, st, p);              \
     else                                                                                             \
         hipLaunchKernelGGL((ms::merge_few_kernel<N, false>), grid, dim3(256), 0, st, p)
-    switch (sb) {
+    switch (p.S) {
     case 1: LORY_FEW(1); break;
     case 2: LORY_FEW(2); break;
     case 3: LORY_FEW(3); break;

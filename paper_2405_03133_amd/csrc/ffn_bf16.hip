@@ -47,10 +47,8 @@ size_t slab_budget_bytes()
     return g_slab_budget;
 }
 
-// Which shapes run their token contractions with the merge inside the GEMM (fused_bf16.h) instead
-// of the slab pipeline: 0 never, 1 where it measured faster (segments of at most 64 tokens with at
-// most 16 experts: the slab pipeline then moves four times the merged parameters of T = 256 through
-// HBM for a quarter of the rows each), 2 wherever the shape fits the kernel, 3 like 2 and with the
+// Which token contractions run with the merge inside the GEMM (fused_bf16.h) instead of the slab pipeline: 0 none, 1 those
+// that are estimated to be faster (fused_pays), 2 all wherever the shape fits the kernel, 3 like 2 and with the
 // backward's per-segment weight gradients kept on chip as well (fsg_kernel; measured slower than the
 // slab pipeline at every shape tried, so no other mode uses it).
 int g_fused_mode = -1;  // -1 = not initialised yet
@@ -80,17 +78,46 @@ fmg::Params fused_params(const Dims &m, const bf *A0, const bf *A1, int lda, con
     return p;
 }
 
-bool use_fused(const Dims &m)
+// The contractions of the layer that are merged inside the GEMM.
+struct Fused {
+    bool gate_up, down, da, dx;
+};
+
+// Whether the merge inside the GEMM is estimated to be faster for a contraction of `mats` expert matrices (two operand sets
+// or two sources) with N output columns and K per source: on the eight-wave kernel (segments of 64 tokens), against the
+// merges into the slab and the GEMM that reads it.  us: rounds of tasks over the CUs times their K steps, whose expert
+// chunks grow with E; the merges' and the GEMM's bytes.  Fitted to both forms of 700 layers (2 .. 256 segments, 2 .. 16
+// experts, d = 768 .. 2560, d_ff = 704 .. 6144): the estimates are off by 11 and 8 % (rms), what is chosen takes 0.3 % more
+// than the faster form on average (always the slab 25 .. 64 %, fused for all token counts that are multiples of 512, the
+// rule before, 25 .. 60 %), 26 % at most.  us of slab and fused: gate/up of 82 segments, 7 experts of 1792 x 4160 1280 and 650;
+// dX of 3 segments, 14 of 1792 x 5632 230 and 650.  One expert always takes the slab: its segments share their merged values.
+bool fused_pays(const Dims &m, int N, int K, int mats, int nsrc)
 {
+    if (m.E < 2) return false;
+    const long cus = gemm2::cu_count(), tasks = (m.tokens + fmg::kRows8 - 1) / fmg::kRows8 * (N / fmg::BN) * (mats / nsrc);
+    const long rounds = ((tasks + 7) / 8 + cus / 8 - 1) / (cus / 8);
+    const double alone = m.tokens <= fmg::kRows8 ? 1.12 : 1.0;   // one row chunk shares its expert chunks with none
+    const double fused = 10.0 + alone * (double)rounds * nsrc * (K / fmg::BK) * (1.11 + 0.052 * m.E);
+    const double slab = 13.4 + mats * (7.1 + 2e-6 * m.D * (0.403 * m.S + 0.150 * m.E));
+    return fused < 0.95 * slab;
+}
+
+Fused use_fused(const Dims &m)
+{
+    const Fused none = {false, false, false, false}, all = {true, true, true, true};
     const int mode = fused_mode();
-    if (mode == 0 || m.tokens > 0x7fffffffL) return false;
+    if (mode == 0 || m.tokens > 0x7fffffffL) return none;
     // every contraction of the layer has N and K in {d, d_ff}
     const fmg::Params a = fused_params(m, nullptr, nullptr, m.d, nullptr, nullptr, m.dff, nullptr, m.dff, m.d,
                                        nullptr, m.dff);
     const fmg::Params b = fused_params(m, nullptr, nullptr, m.dff, nullptr, nullptr, m.d, nullptr, m.d, m.dff,
                                        nullptr, m.d);
-    if (!k::fused_fits(a) || !k::fused_fits(b)) return false;
-    return mode >= 2 || (m.T <= 64 && m.E <= 16 && m.tokens % fmg::kRows8 == 0);
+    if (!k::fused_fits(a) || !k::fused_fits(b)) return none;
+    if (mode >= 2) return all;
+    // longer segments, and stacks of 2 GiB and more, would run on the four-wave kernel
+    if (!fmg::fits8<64>(a) || !fmg::fits8<64>(b)) return none;
+    return {fused_pays(m, m.dff, m.d, 2, 1), fused_pays(m, m.d, m.dff, 1, 1), fused_pays(m, m.dff, m.d, 1, 1),
+            fused_pays(m, m.d, m.dff, 2, 2)};
 }
 
 // Whether the backward keeps the per-segment weight gradients on chip as well (fsg_kernel), for
@@ -346,7 +373,7 @@ size_t bf16_workspace_bytes(const Dims &m, int pass)
     const Plan p = make_plan(m);
     if (pass == LORY_PASS_FWD) {
         // fused path: G and U of all tokens when the caller does not keep them
-        const size_t gu = use_fused(m) ? 2 * p.act : 0;
+        const size_t gu = use_fused(m).gate_up ? 2 * p.act : 0;
         return p.act + (p.slab_fwd > gu ? p.slab_fwd : gu);
     }
     // dG, dU, Act, recomputed G and U, slabs, router-weight partial sums
@@ -382,17 +409,15 @@ int bf16_ffn_fwd(const Dims &m, const void *Xv, const float *w, const void *Wgv,
     bf *slab = (bf *)((char *)ws + pl.act);
     const long TD = (long)m.T * m.d, TF = (long)m.T * m.dff;
 
-    if (!Wbar && m.S <= pl.Sc && use_fused(m)) {
-        // merged parameters never leave the chip: three fused contractions and one SwiGLU pass
+    const Fused fused = Wbar || m.S > pl.Sc ? Fused{} : use_fused(m);
+    if (fused.gate_up) {
+        // merged parameters never leave the chip: fused contractions and one SwiGLU pass
         bf *Gf = G ? G : slab, *Uf = U ? U : (bf *)((char *)slab + pl.act);
         LORY_TRY(fused_gate_up(st, m, X, Wg, Wu, w, Gf, Uf));
         {
             prof::Range r(st, prof::kSwigluFwd, 4.0 * m.tokens * m.dff, 2.0 * 3.0 * m.tokens * m.dff);
             LORY_TRY(k::launch_swiglu_fwd(st, Gf, Uf, Act, m.tokens, m.dff, 0, m.dff));
         }
-        LORY_TRY(fused_gemm(st, m, prof::kFusedDown,
-                            fused_params(m, Act, nullptr, m.dff, Wd, nullptr, m.d, w, m.d, m.dff, Y, m.d), 1, true));
-        return LORY_OK;
     }
 
     for (int s0 = 0; s0 < m.S; s0 += pl.Sc) {
@@ -406,13 +431,18 @@ int bf16_ffn_fwd(const Dims &m, const void *Xv, const float *w, const void *Wgv,
         const char *x0 = (const char *)X, *x1 = x0 + sizeof(bf) * m.tokens * m.d;
         int32_t *map_gu = (y1 <= x0 || x1 <= y0) ? map_place(S, (void *)y0, (void *)y1) : nullptr;
         // gate / up projections + SwiGLU, one d_ff column block at a time
-        for (int n0 = 0; n0 < m.dff; n0 += pl.nf_fwd) {
+        for (int n0 = 0; !fused.gate_up && n0 < m.dff; n0 += pl.nf_fwd) {
             const int nf = (m.dff - n0 < pl.nf_fwd) ? (m.dff - n0) : pl.nf_fwd;
             if (Wbar)
                 LORY_TRY(gate_up_block(st, m, S, Xc, wc, Wg, Wu, n0, nf, Wbar, Gc, Uc, Act,
                                        Wbar + (size_t)m.S * m.D));
             else
                 LORY_TRY(gate_up_block(st, m, S, Xc, wc, Wg, Wu, n0, nf, slab, Gc, Uc, Act, nullptr, map_gu));
+        }
+        if (fused.down) {
+            LORY_TRY(fused_gemm(st, m, prof::kFusedDown,
+                                fused_params(m, Act, nullptr, m.dff, Wd, nullptr, m.d, w, m.d, m.dff, Y, m.d), 1, true));
+            continue;
         }
         // down projection, one block of output columns at a time
         for (int j0 = 0; j0 < m.d; j0 += pl.jf_fwd) {
@@ -759,7 +789,7 @@ int bf16_ffn_bwd(const Dims &m, const void *Xv, const float *w, const void *Wgv,
     const int grad_f32 = (grad_dtype == LORY_F32) ? 1 : 0;
     // token contractions with the merge inside the GEMM (no re-merged slabs); the per-segment weight
     // gradients still pass through the slab
-    const bool fused = !Wbar && m.S <= pl.Sc && use_fused(m);
+    const Fused fused = Wbar || m.S > pl.Sc ? Fused{} : use_fused(m);
     // ... unless the expert-gradient kernel that keeps them on chip takes the shape (bf16 gradients
     // that overwrite; at most 16 experts)
     auto dw_params = [&](const bf *A, int lda, const bf *B, int ldb, const bf *W, void *dW, int M, int N) {
@@ -771,7 +801,7 @@ int bf16_ffn_bwd(const Dims &m, const void *Xv, const float *w, const void *Wgv,
         q.w = w; q.E = m.E; q.T = m.T; q.S = m.S; q.M = M; q.N = N;
         return q;
     };
-    const bool fused_dw = fused && use_fused_dw() && !grad_f32 && !accumulate &&
+    const bool fused_dw = fused.da && use_fused_dw() && !grad_f32 && !accumulate &&
                           k::fused_dw_fits(dw_params(nullptr, m.dff, nullptr, m.d, nullptr, nullptr, m.dff, m.d)) &&
                           k::fused_dw_fits(dw_params(nullptr, m.d, nullptr, m.dff, nullptr, nullptr, m.d, m.dff));
 
@@ -787,7 +817,7 @@ int bf16_ffn_bwd(const Dims &m, const void *Xv, const float *w, const void *Wgv,
         if (G && U) {
             Gc = G + (size_t)s0 * TF;
             Uc = U + (size_t)s0 * TF;
-        } else if (fused) {
+        } else if (fused.gate_up) {
             LORY_TRY(fused_gate_up(st, m, X, Wg, Wu, w, Gr, Ur));
             Gc = Gr;
             Uc = Ur;
@@ -803,7 +833,7 @@ int bf16_ffn_bwd(const Dims &m, const void *Xv, const float *w, const void *Wgv,
             Uc = Ur;
         }
 
-        if (fused) {
+        if (fused.da) {
             // dA = dY Wd_bar^T for all of d_ff at once (Wd[e] is [d_ff][d]: K contiguous), then the
             // SwiGLU backward pass: dG, dU, A
             LORY_TRY(fused_gemm(st, m, prof::kFusedDA,
@@ -843,8 +873,8 @@ int bf16_ffn_bwd(const Dims &m, const void *Xv, const float *w, const void *Wgv,
 
             // dA = dY Wd_bar^T for these d_ff columns, then the SwiGLU backward pass: dG, dU, A
             int32_t *map = Wbar ? nullptr : map_place(S, s_gd, (char *)slab + pl.slab_bwd);   // the gradient slabs are written later
-            if (!Wbar && !fused) LORY_TRY(merge(st, wc, S, m.E, Wd, rows_d, s_md, map));
-            if (!fused) {
+            if (!Wbar && !fused.da) LORY_TRY(merge(st, wc, S, m.E, Wd, rows_d, s_md, map));
+            if (!fused.da) {
                 Params p = da_gemm(m, pl, S, nf, slab);
                 p.b_map = map;
                 p.A[0] = dYc; p.a_batch[0] = TD; p.lda[0] = m.d;
@@ -911,13 +941,13 @@ int bf16_ffn_bwd(const Dims &m, const void *Xv, const float *w, const void *Wgv,
             }
         }
 
-        if (fused) {
+        if (fused.dx) {
             // dX = dG Wg_bar^T + dU Wu_bar^T: two sources, Wg[e] / Wu[e] are [d][d_ff] (K contiguous)
             LORY_TRY(fused_gemm(st, m, prof::kFusedDX,
                                 fused_params(m, dG, dU, m.dff, Wg, Wu, m.dff, w, m.d, m.dff, dX, m.d), 2, false));
         }
         // ---- dX = dG Wg_bar^T + dU Wu_bar^T, one block of d columns at a time
-        for (int k0 = 0; !fused && k0 < m.d; k0 += pl.kf_bwd) {
+        for (int k0 = 0; !fused.dx && k0 < m.d; k0 += pl.kf_bwd) {
             const int kf = (m.d - k0 < pl.kf_bwd) ? (m.d - k0) : pl.kf_bwd;
             const size_t blk = (size_t)S * kf * m.dff;
             bf *s_g = slab, *s_u = slab + blk;

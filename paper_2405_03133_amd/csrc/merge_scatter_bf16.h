@@ -271,39 +271,29 @@ struct MergeFewParams {
     int32_t *seg_map;          // as MergeParams::seg_map
 };
 
-constexpr int kFewSegments = 64;
+constexpr int kFewSegments = 16;
 
 template <int SB, bool MAP>
 __global__ __launch_bounds__(256) void merge_few_kernel(const MergeFewParams p)
 {
-    // grid z: blocks of SB segments
-    const int s0 = blockIdx.z * SB, mine = p.S - s0 < SB ? p.S - s0 : SB;
-    // bit s: segment s0 + s is stored (the first of a run of equal routing rows, compared as bits)
-    uint32_t stored = (1u << mine) - 1u;
+    // MAP: bit s of a wavefront's word: segment s differs from the one before in an expert that is the wavefront's share, or
+    // is the first.  Rows are compared as bits; the words are read after the sums, so that nothing waits for them.
+    __shared__ uint32_t differs[4];
     if constexpr (MAP) {
-        __shared__ uint64_t keep;
-        if (threadIdx.x < 64) {
-            const int s = threadIdx.x;
-            bool first = s < p.S;
-            if (s > 0 && s < p.S) {
-                const uint32_t *a = reinterpret_cast<const uint32_t *>(p.w) + (size_t)s * p.E, *b = a - p.E;
-                uint32_t diff = 0;
-                for (int e = 0; e < p.E; ++e) diff |= a[e] ^ b[e];
-                first = diff != 0;
-            }
-            const uint64_t m = __builtin_amdgcn_ballot_w64(first);
-            if (s == 0) keep = m;
-            if (blockIdx.x + blockIdx.y + blockIdx.z == 0 && s < p.S) p.seg_map[s] = 63 - __builtin_clzll(m & (~0ull >> (63 - s)));
+        const int s = threadIdx.x & 63, wv = threadIdx.x >> 6;
+        uint32_t diff = s == 0;
+        if (s > 0 && s < p.S) {
+            const uint32_t *a = reinterpret_cast<const uint32_t *>(p.w) + (size_t)s * p.E, *b = a - p.E;
+#pragma unroll 8
+            for (int e = wv; e < p.E; e += 4) diff |= a[e] ^ b[e];
         }
-        __syncthreads();
-        stored &= __builtin_amdgcn_readfirstlane((uint32_t)(keep >> s0));
-        if (stored == 0) return;
+        const uint32_t m = (uint32_t)__builtin_amdgcn_ballot_w64(diff != 0);
+        if (s == 0) differs[wv] = m;
     }
 
-    const int q = blockIdx.x * 256 + threadIdx.x;
-    if (q >= ((p.rc.nr * p.rc.nc) >> 3)) return;
-    const uint16_t *src = p.stack[blockIdx.y] + rect_offset(p.rc, q);
-    uint16_t *dst = p.slab[blockIdx.y] + (size_t)s0 * p.seg_stride + (size_t)q * 8;
+    const int Q = (p.rc.nr * p.rc.nc) >> 3, q = blockIdx.x * 256 + threadIdx.x;
+    const uint16_t *src = p.stack[blockIdx.y] + rect_offset(p.rc, q < Q ? q : Q - 1);
+    uint16_t *dst = p.slab[blockIdx.y] + (size_t)q * 8;
 
     float acc[SB][8];
 #pragma unroll
@@ -325,7 +315,7 @@ __global__ __launch_bounds__(256) void merge_few_kernel(const MergeFewParams p)
             }
 #pragma unroll
             for (int s = 0; s < SB; ++s) {
-                const float ws = p.w[(size_t)(s0 + (s < mine ? s : 0)) * p.E + e0 + i];
+                const float ws = p.w[(size_t)(s < p.S ? s : 0) * p.E + e0 + i];
 #pragma unroll
                 for (int j = 0; j < 8; ++j) acc[s][j] = fmaf(ws, x[j], acc[s][j]);
             }
@@ -336,6 +326,14 @@ __global__ __launch_bounds__(256) void merge_few_kernel(const MergeFewParams p)
     if (p.E & 4) add(std::integral_constant<int, 4>(), e);
     if (p.E & 2) add(std::integral_constant<int, 2>(), e + (p.E & 4));
     if (p.E & 1) add(std::integral_constant<int, 1>(), p.E - 1);
+    uint32_t stored = (1u << p.S) - 1u;   // bit s: segment s is the first of its run
+    if constexpr (MAP) {
+        __syncthreads();
+        stored = __builtin_amdgcn_readfirstlane(differs[0] | differs[1] | differs[2] | differs[3]);
+        const int s = threadIdx.x;
+        if (blockIdx.x + blockIdx.y == 0 && s < p.S) p.seg_map[s] = 31 - __builtin_clz(stored & (~0u >> (31 - s)));
+    }
+    if (q >= Q) return;
 #pragma unroll
     for (int s = 0; s < SB; ++s) {
         if (!(stored >> s & 1)) continue;

@@ -314,9 +314,9 @@ def test_bf16_ring_gemm_edge_tiles_without_saved_planes(cfg):
 @pytest.mark.parametrize("cfg", [
     LoryConfig("shared_S150", B=5, L=3840, T=128, d=64, d_ff=128, E=5, dtype="bf16", seed=111),
     LoryConfig("shared_E33", B=2, L=4096, T=128, d=64, d_ff=64, E=33, dtype="bf16", seed=112),
-    # few segments: one block of sums, and two
-    LoryConfig("shared_S15", B=3, L=640, T=128, d=64, d_ff=192, E=7, dtype="bf16", seed=123),
-    LoryConfig("shared_S30", B=5, L=768, T=128, d=64, d_ff=192, E=4, dtype="bf16", seed=124),
+    # few segments: merged on the vector ALUs
+    LoryConfig("shared_S15", B=3, L=640, T=128, d=64, d_ff=192, E=5, dtype="bf16", seed=123),
+    LoryConfig("shared_S8", B=2, L=512, T=128, d=64, d_ff=192, E=33, dtype="bf16", seed=124),
 ], ids=lambda c: c.name)
 @pytest.mark.parametrize("runs", ["words", "all", "alternating", "none"])
 def test_bf16_equal_routing_rows(cfg, runs):
@@ -336,11 +336,12 @@ def test_bf16_equal_routing_rows(cfg, runs):
             assert np.array_equal(got[key], saved[key]), key
 
 
-# Every number of sums that a thread keeps, one and two blocks of them, the remainders of the experts in groups of eight, and
-# a last workgroup that the chunks do not fill; the last two are beyond the line and merged on the matrix cores.
+# Every number of sums that a thread keeps, the remainders of the experts in groups of eight, and a last workgroup that the
+# chunks do not fill; the last three are beyond the line and merged on the matrix cores.
 @pytest.mark.parametrize("B,E,d,d_ff", [(1, 1, 64, 64), (1, 13, 64, 320), (2, 2, 128, 192), (3, 7, 64, 128), (4, 8, 192, 64),
-                                        (6, 9, 64, 192), (7, 16, 64, 64), (8, 33, 64, 128), (11, 26, 64, 64), (12, 5, 64, 192),
-                                        (16, 18, 64, 128), (17, 4, 64, 64), (32, 3, 64, 192), (33, 3, 64, 64), (16, 19, 64, 64)])
+                                        (5, 11, 64, 64), (6, 9, 64, 192), (7, 16, 64, 64), (8, 33, 64, 128), (11, 6, 64, 64),
+                                        (12, 8, 64, 192), (14, 3, 64, 128), (16, 6, 64, 64), (9, 9, 64, 64), (13, 7, 64, 192),
+                                        (17, 3, 64, 64)])
 def test_bf16_merge_of_few_segments(B, E, d, d_ff):
     g = torch.Generator(device="cuda")
     g.manual_seed(1000 * B + E)
@@ -581,6 +582,27 @@ def test_bf16_fused_merge_gemm(cfg, save, fused_everywhere, default_budget):
     again = run_layer(cfg, t, save=save, grad_dtype=torch.bfloat16)
     for key in names:
         assert np.array_equal(got[key], again[key]), key
+
+
+# Each contraction is merged inside the GEMM or through the slab on its own: long contractions of few segments go through the
+# slab, short ones do not.
+@pytest.mark.parametrize("d,d_ff,fused,slab", [(64, 704, ("fused_gate_up", "fused_dA"), ("gemm_down", "gemm_dX")),
+                                               (704, 64, ("fused_down", "fused_dX"), ("gemm_gate_up", "gemm_dA"))])
+@pytest.mark.parametrize("save", [True, False], ids=["saved_GU", "recompute_GU"])
+def test_bf16_contractions_choose_for_themselves(d, d_ff, fused, slab, save, default_budget):
+    cfg = LoryConfig(f"mixed_{d}", B=3, L=192, T=64, d=d, d_ff=d_ff, E=6, dtype="bf16", seed=125)
+    t = make_inputs(cfg, structured=True)
+    print(f"[gpu] {cfg}", flush=True)
+    lb.lory_profile_enable(True)
+    try:
+        lb.lory_profile_read()
+        got = run_layer(cfg, t, save=save, grad_dtype=torch.bfloat16)
+        classes = {s["name"] for s in lb.lory_profile_read()}
+    finally:
+        lb.lory_profile_enable(False)
+    assert classes.issuperset(fused + slab)
+    ref = oracle_layer(cfg, t, got["w_used"])
+    compare(cfg, got, ref, ALL if save else ("Y", "dX", "dWg", "dWu", "dWd", "dw"), TOL["bf16"])
 
 
 @pytest.fixture
