@@ -95,11 +95,11 @@ int lory_set_slab_budget(size_t bytes);
  * the forward or in the backward's re-merge) instead of the slab pipeline.
  *   0  never
  *   1  where it is estimated to be faster (default), for each of the layer's
- *      token contractions by itself: T = 64, 2 <= E <= 16, an expert stack below
- *      2 GiB.  The fused kernel is bound by the L2 -> CU path at about the
+ *      token contractions by itself: T = 64 or 128, 2 <= E <= 16, an expert stack
+ *      below 2 GiB.  The fused kernel is bound by the L2 -> CU path at about the
  *      same rate for every segment length, while the slab pipeline's HBM
  *      traffic grows with the number of segments
- *   2  wherever the shape fits the kernel: T = 64 with E <= 16, else T in
+ *   2  wherever the shape fits the kernel: T in {64, 128} with E <= 16, else T in
  *      {64, 128, 256}, E <= 32, B*L a multiple of 1024 (512 for T <= 128); no
  *      Wbar_save given
  *   3  as 2, and the backward also keeps the per-segment weight gradients on

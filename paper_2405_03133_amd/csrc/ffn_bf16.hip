@@ -84,22 +84,27 @@ struct Fused {
 };
 
 // Whether the merge inside the GEMM is estimated to be faster for a contraction of `mats` expert matrices (two operand sets
-// or two sources) with N output columns and K per source: on the eight-wave kernel (segments of 64 tokens), against the
-// merges into the slab and the GEMM that reads it.  us: rounds of tasks over the CUs times their K steps, whose expert
-// chunks grow with E; the merges' and the GEMM's bytes.  Fitted to both forms of 700 layers (2 .. 256 segments, 2 .. 16
-// experts, d = 768 .. 2560, d_ff = 704 .. 6144): the estimates are off by 11 and 8 % (rms), what is chosen takes 0.3 % more
-// than the faster form on average (always the slab 25 .. 64 %, fused for all token counts that are multiples of 512, the
-// rule before, 25 .. 60 %), 26 % at most.  us of slab and fused: gate/up of 82 segments, 7 experts of 1792 x 4160 1280 and 650;
-// dX of 3 segments, 14 of 1792 x 5632 230 and 650.  One expert always takes the slab: its segments share their merged values.
+// or two sources) with N output columns and K per source: on the eight-wave kernel (segments of 64 or 128 tokens), against
+// the merges into the slab and the GEMM that reads it.  us: rounds of tasks over the CUs times their K steps, whose expert
+// chunks grow with E; the merges' and the GEMM's bytes.  Fitted to both forms of 700 layers of 64-token segments (2 .. 256
+// segments, 2 .. 16 experts, d = 768 .. 2560, d_ff = 704 .. 6144): off by 11 and 8 % (rms), and what is chosen takes 0.4 %
+// more than the faster form on average, where always the slab takes 24 .. 62 %.  400 layers of 128-token segments fit as
+// well; there the forms are closer (the slab takes 3 .. 11 % more), and 0.92 keeps the gain: 0.935 of the slab for
+// gate/up, 0.965 for dA, 0.99 for down and dX, 1.14 at worst.  us of slab and fused: gate/up of 82 segments of 64, 7 experts
+// of 1792 x 4160 1280 and 650; dX of 3 segments, 14 of 1792 x 5632 230 and 650.  One expert always takes the slab: its
+// segments share their merged values.
+// Layers of fewer parameters than measured stay on the slab with 128-token segments, where the two forms are close.
+constexpr long kFusedLeastD = 500000;
+
 bool fused_pays(const Dims &m, int N, int K, int mats, int nsrc)
 {
-    if (m.E < 2) return false;
+    if (m.E < 2 || (m.T > 64 && m.D < kFusedLeastD)) return false;
     const long cus = gemm2::cu_count(), tasks = (m.tokens + fmg::kRows8 - 1) / fmg::kRows8 * (N / fmg::BN) * (mats / nsrc);
     const long rounds = ((tasks + 7) / 8 + cus / 8 - 1) / (cus / 8);
     const double alone = m.tokens <= fmg::kRows8 ? 1.12 : 1.0;   // one row chunk shares its expert chunks with none
     const double fused = 10.0 + alone * (double)rounds * nsrc * (K / fmg::BK) * (1.11 + 0.052 * m.E);
     const double slab = 13.4 + mats * (7.1 + 2e-6 * m.D * (0.403 * m.S + 0.150 * m.E));
-    return fused < 0.95 * slab;
+    return fused < 0.92 * slab;
 }
 
 Fused use_fused(const Dims &m)
@@ -114,8 +119,8 @@ Fused use_fused(const Dims &m)
                                        nullptr, m.d);
     if (!k::fused_fits(a) || !k::fused_fits(b)) return none;
     if (mode >= 2) return all;
-    // longer segments, and stacks of 2 GiB and more, would run on the four-wave kernel
-    if (!fmg::fits8<64>(a) || !fmg::fits8<64>(b)) return none;
+    // longer segments, more experts and stacks of 2 GiB and more would run on the four-wave kernel
+    if (!(fmg::fits8<64>(a) && fmg::fits8<64>(b)) && !(fmg::fits8<128>(a) && fmg::fits8<128>(b))) return none;
     return {fused_pays(m, m.dff, m.d, 2, 1), fused_pays(m, m.d, m.dff, 1, 1), fused_pays(m, m.dff, m.d, 1, 1),
             fused_pays(m, m.d, m.dff, 2, 2)};
 }

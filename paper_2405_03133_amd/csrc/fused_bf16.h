@@ -725,7 +725,7 @@ __global__ __launch_bounds__(512, 1) void fmg8_kernel(const Params p)
 template <int TSEG>
 inline bool fits8(const Params &p)
 {
-    return p.T == TSEG && p.tokens >= 64 && p.tokens % TSEG == 0 && p.N % BN == 0 && p.K % (2 * BK) == 0 && p.E <= 16 && p.E >= 1 &&
+    return p.T == TSEG && p.tokens >= TSEG && p.tokens % TSEG == 0 && p.N % BN == 0 && p.K % (2 * BK) == 0 && p.E <= 16 && p.E >= 1 &&
            p.lda[0] == p.lda[1] && (size_t)p.E * (size_t)p.expert_stride * 2 < ((size_t)1 << 31);
 }
 

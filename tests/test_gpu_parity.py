@@ -555,6 +555,7 @@ FUSED_CASES = [
     # one beyond the eight chunks that share an XCD's L2, with more gate/up tasks than workgroups
     LoryConfig("fused_T64_one_segment", B=1, L=64, T=64, d=64, d_ff=64, E=3, dtype="bf16", seed=120),
     LoryConfig("fused_T64_rows_over", B=3, L=192, T=64, d=192, d_ff=320, E=13, dtype="bf16", seed=121),
+    LoryConfig("fused_T128_rows_over", B=5, L=256, T=128, d=192, d_ff=320, E=11, dtype="bf16", seed=126),
     LoryConfig("fused_T64_many", B=5, L=832, T=64, d=256, d_ff=1536, E=9, dtype="bf16", seed=122),
     LoryConfig("fused_one_expert", B=1, L=1024, T=256, d=64, d_ff=64, E=1, dtype="bf16", seed=95),
     # more tasks than one round of workgroups per XCD block, several K steps per source
