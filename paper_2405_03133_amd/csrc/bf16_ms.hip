@@ -6,7 +6,7 @@ namespace k {
 
 namespace {
 // dw[s][e] = sum over slots of partials[slot][s][e].  One workgroup per segment row: thread
-// (e, g) adds slots g, g+16, ... along four interleaved chains (fixed order), then the 16 group
+// (e, g) adds slots g, g+16, ... along four interleaved chains (fixed order), sixteen loads in flight, then the 16 group
 // sums are added in order.
 __global__ __launch_bounds__(1024) void dw_reduce_kernel(const float *__restrict__ partials, int slots,
                                                          int rows, int cols, float *__restrict__ dw,
@@ -20,6 +20,18 @@ __global__ __launch_bounds__(1024) void dw_reduce_kernel(const float *__restrict
         const float *src = partials + (size_t)s * cols + e;
         const size_t pitch = (size_t)rows * cols;
         int k = g;
+        for (; k + 240 < slots; k += 256) {
+            float v[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) v[i] = src[(size_t)(k + 16 * i) * pitch];
+#pragma unroll
+            for (int i = 0; i < 16; i += 4) {
+                a0 += v[i];
+                a1 += v[i + 1];
+                a2 += v[i + 2];
+                a3 += v[i + 3];
+            }
+        }
         for (; k + 48 < slots; k += 64) {
             a0 += src[(size_t)k * pitch];
             a1 += src[(size_t)(k + 16) * pitch];

@@ -11,9 +11,10 @@
 // e[b,j] is read back from the forward's output as w[b,j+1]; the last segment's
 // e is never needed because its dz is zero.
 //
-// Two kernels, both with fixed summation orders (bit-reproducible):
-//   route_bwd_dx_kernel: HBM-bound read-modify-write of dX, grid (segments, row blocks)
-//   route_bwd_dr_kernel: tiny [d, S] x [S, E] product, one workgroup per 16 rows of R
+// One launch of two kinds of workgroups, both with fixed summation orders (bit-reproducible): the tiny [d, S] x [S, E] product
+// dR, a workgroup per four rows of R, and beside it the HBM-bound read-modify-write of dX, a workgroup per segment and
+// block of rows.  64 segments of 256 tokens at d = 2048, 32 experts: 38 us (two launches, the rows loaded after the
+// gradient of the mean: 42 + 12).
 #include "lory_internal.h"
 
 #include <hip/hip_bf16.h>
@@ -23,9 +24,9 @@ namespace lory {
 namespace {
 
 constexpr int kDxThreads = 256;
-constexpr int kDrThreads = 1024;  // 64 experts x 16 rows of R
-constexpr int kDrRows = 16;
-constexpr int kDrChunk = 64;      // segments whose dz sit in LDS at a time
+constexpr int kDrRows = kDxThreads / 64;   // rows of R of a workgroup: one for each wavefront, lane = expert
+constexpr int kDrChunk = 64;               // segments whose dz sit in LDS at a time
+constexpr int kDxRows = 8;                 // rows of dX that a thread has in flight
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t v) { return __uint_as_float((uint32_t)v << 16); }
 
@@ -89,29 +90,33 @@ __device__ __forceinline__ float softmax_jacobian_row(const float *__restrict__ 
     return e * (de - inner);
 }
 
-// grid = (S, row blocks); block = 256 threads; LDS = 64 floats.
 // Adds dhbar[s, :] / T to rows [rb * rows_per, ...) of segment s of dX.
 template <typename T>
-__global__ __launch_bounds__(kDxThreads) void route_bwd_dx_kernel(const T *__restrict__ R,
-                                                                  const float *__restrict__ w,
-                                                                  const float *__restrict__ dw,
-                                                                  T *__restrict__ dX, int Tseg, int d,
-                                                                  int E, int N, int rows_per)
+__device__ __forceinline__ void route_bwd_dx(const T *__restrict__ R, const float *__restrict__ w, const float *__restrict__ dw,
+                                             T *__restrict__ dX, int Tseg, int d, int E, int N, int rows_per, int s, int rb,
+                                             float *dz)
 {
     constexpr int VEC = 16 / (int)sizeof(T);  // elements per 16-byte access
-    __shared__ float dz[64];
-    const int s = blockIdx.x;
     if (s % N == N - 1) return;  // nothing routes on the last segment of a sequence
     const int tid = threadIdx.x;
-    if (tid < 64) dz[tid] = softmax_jacobian_row(w, dw, s, E, tid);
-    __syncthreads();
-
-    const int t0 = blockIdx.y * rows_per;
+    const int t0 = rb * rows_per;
     const int t1 = (t0 + rows_per < Tseg) ? (t0 + rows_per) : Tseg;
     const float invT = 1.0f / (float)Tseg;
     T *Xs = dX + (size_t)s * Tseg * d;
+    const bool vec = d % VEC == 0;
 
-    if (d % VEC == 0) {
+    // the first rows are on their way while the gradient of the mean is formed
+    uint4 q[kDxRows];
+    auto load_rows = [&](int c, int t) {
+#pragma unroll
+        for (int u = 0; u < kDxRows; ++u)
+            if (t + u < t1) q[u] = *reinterpret_cast<const uint4 *>(Xs + (size_t)(t + u) * d + c);
+    };
+    if (vec && tid * VEC < d) load_rows(tid * VEC, t0);
+    if (tid < 64) dz[tid] = softmax_jacobian_row(w, dw, s, E, tid);
+    __syncthreads();
+
+    if (vec) {
         for (int c = tid * VEC; c < d; c += kDxThreads * VEC) {
             float dh[VEC];
 #pragma unroll
@@ -134,17 +139,15 @@ __global__ __launch_bounds__(kDxThreads) void route_bwd_dx_kernel(const T *__res
                     return make_uint4(r[0], r[1], r[2], r[3]);
                 }
             };
-            int t = t0;
-            for (; t + 4 <= t1; t += 4) {  // four rows in flight
-                uint4 q[4];
+            if (c != tid * VEC) load_rows(c, t0);
+            for (int t = t0; t < t1; t += kDxRows) {
+                uint4 v[kDxRows];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) q[u] = *reinterpret_cast<const uint4 *>(Xs + (size_t)(t + u) * d + c);
+                for (int u = 0; u < kDxRows; ++u) v[u] = q[u];
+                if (t + kDxRows < t1) load_rows(c, t + kDxRows);
 #pragma unroll
-                for (int u = 0; u < 4; ++u) *reinterpret_cast<uint4 *>(Xs + (size_t)(t + u) * d + c) = update(q[u]);
-            }
-            for (; t < t1; ++t) {
-                T *p = Xs + (size_t)t * d + c;
-                *reinterpret_cast<uint4 *>(p) = update(*reinterpret_cast<const uint4 *>(p));
+                for (int u = 0; u < kDxRows; ++u)
+                    if (t + u < t1) *reinterpret_cast<uint4 *>(Xs + (size_t)(t + u) * d + c) = update(v[u]);
             }
         }
     } else {
@@ -163,34 +166,29 @@ __global__ __launch_bounds__(kDxThreads) void route_bwd_dx_kernel(const T *__res
     }
 }
 
-// grid = ceil(d / 16); block = 1024 threads: thread (expert = tid % 64, row = tid / 64).
-// dR[c, e] (+)= sum over s in ascending order of hbar[s, c] * dz[s, e].
-__global__ __launch_bounds__(kDrThreads) void route_bwd_dr_kernel(const float *__restrict__ hbar,
-                                                                  const float *__restrict__ w,
-                                                                  const float *__restrict__ dw,
-                                                                  float *__restrict__ dR, int S, int d, int E,
-                                                                  int N, int accumulate)
+// dR[c, e] (+)= sum over s in ascending order of hbar[s, c] * dz[s, e], c = kDrRows * block + wavefront, e = lane.
+__device__ __forceinline__ void route_bwd_dr(const float *__restrict__ hbar, const float *__restrict__ w,
+                                             const float *__restrict__ dw, float *__restrict__ dR, int S, int d, int E, int N,
+                                             int accumulate, int block, float (*dz)[64])
 {
-    __shared__ float dz[kDrChunk][64];
     const int tid = threadIdx.x;
     const int e = tid & 63, wave = tid >> 6;
-    const int c = blockIdx.x * kDrRows + wave;
+    const int c = block * kDrRows + wave;
     float acc = 0.f;
     for (int s0 = 0; s0 < S; s0 += kDrChunk) {
-        // 16 wavefronts, 4 segments each
+        // lane sl holds the mean of segment s0 + sl in this wavefront's column
+        const float h = (c < d && s0 + e < S) ? hbar[(size_t)(s0 + e) * d + c] : 0.f;
 #pragma unroll
-        for (int i = 0; i < kDrChunk / 16; ++i) {
-            const int sl = wave * (kDrChunk / 16) + i;
+        for (int i = 0; i < kDrChunk / kDrRows; ++i) {
+            const int sl = wave * (kDrChunk / kDrRows) + i;
             const int s = s0 + sl;
             float v = 0.f;
             if (s < S && (s % N) != N - 1) v = softmax_jacobian_row(w, dw, s, E, e);
             dz[sl][e] = v;
         }
         __syncthreads();
-        if (c < d) {
-            const int n = (S - s0 < kDrChunk) ? (S - s0) : kDrChunk;
-            for (int sl = 0; sl < n; ++sl) acc += hbar[(size_t)(s0 + sl) * d + c] * dz[sl][e];
-        }
+        const int n = (S - s0 < kDrChunk) ? (S - s0) : kDrChunk;
+        for (int sl = 0; sl < n; ++sl) acc += __shfl(h, sl, 64) * dz[sl][e];
         __syncthreads();
     }
     if (c < d && e < E) {
@@ -199,21 +197,38 @@ __global__ __launch_bounds__(kDrThreads) void route_bwd_dr_kernel(const float *_
     }
 }
 
+// Workgroups 0 .. dr_blocks - 1: dR (they start first: a chain of loads, few bytes); the others: dX, segment by segment for
+// each block of rows.
+template <typename T>
+__global__ __launch_bounds__(kDxThreads) void route_bwd_dx_kernel(const T *__restrict__ R, const float *__restrict__ w,
+                                                               const float *__restrict__ hbar, const float *__restrict__ dw,
+                                                               T *__restrict__ dX, float *__restrict__ dR, int S, int Tseg, int d,
+                                                               int E, int N, int rows_per, int accumulate, int dr_blocks)
+{
+    __shared__ float dz[kDrChunk][64];
+    const int id = blockIdx.x;
+    if (id < dr_blocks)
+        route_bwd_dr(hbar, w, dw, dR, S, d, E, N, accumulate, id, dz);
+    else
+        route_bwd_dx(R, w, dw, dX, Tseg, d, E, N, rows_per, (id - dr_blocks) % S, (id - dr_blocks) / S, dz[0]);
+}
+
 template <typename T>
 int launch_route_bwd(const Dims &m, const void *R, const float *w, const float *hbar, const float *dw,
                      void *dX, float *dR, int accumulate, hipStream_t st)
 {
-    // enough row blocks to give every CU a few workgroups, at least 8 rows each
-    int rb = (1024 + m.S - 1) / m.S;
+    // Row blocks of at least 8 rows.  Each reads all of R in 16-byte pieces of its rows, so a large router takes one workgroup
+    // for each CU, a small one four (us of the launch with 1024, 512 and 256 workgroups: 64 segments of 256 tokens, 32
+    // experts, d = 2048 50, 48, 38; the fp32 configuration, d = 64 and 4 experts, 5.2, 6.2, 5.6).
+    const int blocks = (long)m.d * m.E >= 8192 ? 256 : 1024;
+    int rb = (blocks + m.S - 1) / m.S;
     if (rb > m.T / 8) rb = m.T / 8;
     if (rb < 1) rb = 1;
     const int rows_per = (m.T + rb - 1) / rb;
     rb = (m.T + rows_per - 1) / rows_per;
-    hipLaunchKernelGGL((route_bwd_dx_kernel<T>), dim3(m.S, rb), dim3(kDxThreads), 0, st, (const T *)R, w, dw,
-                       (T *)dX, m.T, m.d, m.E, m.N, rows_per);
-    if (hipGetLastError() != hipSuccess) return LORY_ERR_DEVICE;
-    hipLaunchKernelGGL(route_bwd_dr_kernel, dim3((m.d + kDrRows - 1) / kDrRows), dim3(kDrThreads), 0, st, hbar,
-                       w, dw, dR, m.S, m.d, m.E, m.N, accumulate);
+    const int dr_blocks = (m.d + kDrRows - 1) / kDrRows;
+    hipLaunchKernelGGL((route_bwd_dx_kernel<T>), dim3(dr_blocks + m.S * rb), dim3(kDxThreads), 0, st, (const T *)R, w, hbar, dw,
+                       (T *)dX, dR, m.S, m.T, m.d, m.E, m.N, rows_per, accumulate, dr_blocks);
     return launch_status();
 }
 
