@@ -83,6 +83,21 @@ __global__ __launch_bounds__(256) void swiglu_fwd_kernel(const uint16_t *__restr
     }
 }
 
+// The same from fp32 G and U, contiguous: nothing is rounded before the activation itself.  HBM-bound, 10 bytes an element.
+__global__ __launch_bounds__(256) void swiglu_fwd_f32_kernel(const float4 *__restrict__ G, const float4 *__restrict__ U,
+                                                             uint4 *__restrict__ Act, long total)
+{
+    for (long idx = (long)blockIdx.x * blockDim.x + threadIdx.x; idx < total; idx += (long)gridDim.x * blockDim.x) {
+        const float4 g0 = G[2 * idx], g1 = G[2 * idx + 1], u0 = U[2 * idx], u1 = U[2 * idx + 1];
+        const float g[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
+        const float u[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
+        float oa[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) oa[i] = g[i] * __builtin_amdgcn_rcpf(1.0f + __expf(-g[i])) * u[i];
+        Act[idx] = pack8(oa);
+    }
+}
+
 // Sums of fp32 partial products over the K slices of a split contraction, in slice order, of NP planes `plane`
 // apart; four consecutive elements per thread.  HBM-bound (the parts of a small call sit in the memory-side cache).
 template <int NP>
@@ -188,6 +203,17 @@ hipError_t launch_swiglu_fwd(hipStream_t st, const uint16_t *G, const uint16_t *
     long blocks = (total + 255) / 256;
     if (blocks > 256 * 16) blocks = 256 * 16;
     hipLaunchKernelGGL(swiglu_fwd_kernel, dim3((unsigned)blocks), dim3(256), 0, st, G, U, Act, rows, dff, n0, nf);
+    return hipGetLastError();
+}
+
+hipError_t launch_swiglu_fwd_f32(hipStream_t st, const float *G, const float *U, uint16_t *Act, long elements)
+{
+    const long total = elements / 8;
+    long blocks = (total + 255) / 256;
+    if (blocks > 256 * 16) blocks = 256 * 16;
+    hipLaunchKernelGGL(swiglu_fwd_f32_kernel, dim3((unsigned)blocks), dim3(256), 0, st,
+                       reinterpret_cast<const float4 *>(G), reinterpret_cast<const float4 *>(U),
+                       reinterpret_cast<uint4 *>(Act), total);
     return hipGetLastError();
 }
 

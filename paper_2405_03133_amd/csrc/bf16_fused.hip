@@ -27,6 +27,13 @@ bool fused_fits(const fmg::Params &p)
     return fmg::fits8<64>(p) || fmg::fits8<128>(p) || fmg::fits<256, 1>(p) || fmg::fits<256, 2>(p) || fmg::fits<128, 1>(p) || fmg::fits<128, 2>(p);
 }
 
+hipError_t launch_fused_pair_f32(hipStream_t st, const fmg::Params &p)
+{
+    if (fmg::fits8<64>(p)) return fmg::launch8<64, 1, true, true, true>(p, st);
+    if (fmg::fits8<128>(p)) return fmg::launch8<128, 1, true, true, true>(p, st);
+    return hipErrorInvalidValue;
+}
+
 hipError_t launch_fused_pair(hipStream_t st, const fmg::Params &p)
 {
     if (fmg::fits8<64>(p)) return fmg::launch8<64, 1, true, true>(p, st);

@@ -187,6 +187,8 @@ bool fused_fits(const fmg::Params &p);
 hipError_t launch_fused(hipStream_t st, const fmg::Params &p, int nsrc, bool w_nc);
 // two products of A[0] with N-contiguous stacks: C = A[0] Wbar_0, C2 = A[0] Wbar_1
 hipError_t launch_fused_pair(hipStream_t st, const fmg::Params &p);
+// the same with fp32 C and C2, on the eight-wave kernel only
+hipError_t launch_fused_pair_f32(hipStream_t st, const fmg::Params &p);
 
 // expert gradients and routing-weight inner products with the per-segment weight gradients kept on
 // chip (fused_bwd_bf16.h); the partial-sum buffer holds fused_dw_slots(p) x S x 16 floats
@@ -217,6 +219,7 @@ hipError_t launch_dense_stream_gu(hipStream_t st, const stream::Params &p, int B
 hipError_t launch_dense_stream_down(hipStream_t st, const stream::Params &p, int B);
 
 hipError_t launch_da(hipStream_t st, const gemm::Params &p, const EpiStore &e);  // dY * Wd_bar^T
+hipError_t launch_swiglu_fwd_f32(hipStream_t st, const float *G, const float *U, uint16_t *Act, long elements);
 hipError_t launch_swiglu_fwd(hipStream_t st, const uint16_t *G, const uint16_t *U, uint16_t *Act, long rows,
                              int dff, int n0, int nf);
 hipError_t launch_swiglu_bwd(hipStream_t st, const uint16_t *G, const uint16_t *U, uint16_t *dG_dA,

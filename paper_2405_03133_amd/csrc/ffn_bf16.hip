@@ -138,15 +138,16 @@ hipError_t fused_gemm(hipStream_t st, const Dims &m, int cls, const fmg::Params 
     return k::launch_fused(st, p, nsrc, w_nc);
 }
 
-// Gate and up projections of all tokens, merged on chip.
-hipError_t fused_gate_up(hipStream_t st, const Dims &m, const bf *X, const bf *Wg, const bf *Wu, const float *w, bf *G, bf *U)
+// Gate and up projections of all tokens, merged on chip; in fp32 (G and U are then of that type) or rounded.
+hipError_t fused_gate_up(hipStream_t st, const Dims &m, const bf *X, const bf *Wg, const bf *Wu, const float *w, bf *G, bf *U,
+                         bool f32)
 {
     fmg::Params p = fused_params(m, X, nullptr, m.d, Wg, Wu, m.dff, w, m.dff, m.d, G, m.dff);
     p.C2 = U;
     const double D = (double)m.D;
     prof::Range r(st, prof::kFusedGU, 2.0 * (2.0 * m.tokens * D + 4.0 * m.S * m.E * D),
-                  2.0 * (2.0 * m.E * D + (double)m.tokens * m.d + 2.0 * m.tokens * m.dff));
-    return k::launch_fused_pair(st, p);
+                  2.0 * (2.0 * m.E * D + (double)m.tokens * m.d + (f32 ? 4.0 : 2.0) * m.tokens * m.dff));
+    return f32 ? k::launch_fused_pair_f32(st, p) : k::launch_fused_pair(st, p);
 }
 
 // Largest multiple of `gran` that is <= limit and <= full, at least gran.
@@ -373,12 +374,27 @@ size_t bf16_merged_save_bytes(const Dims &m)
     return (size_t)3 * m.S * m.D * 2;
 }
 
+// How the fused gate and up projections leave G and U in the workspace of a forward pass whose caller does not keep them:
+// in fp32 where that fits the slab, so that the activation rounds once as in the slab pipeline's epilogue; otherwise rounded,
+// for 64-token segments in whole row chunks, which report two planes at every slab budget.  Other calls take the slab:
+// they ask for no more workspace than it.  Error of Y against 64 bits, 1e-3, 11 segments of 64, 8 experts of 512 x 1408: slab
+// 3.714, fp32 planes 3.713, rounded planes 4.46.  Their bytes cost 1.8 % of a forward pass on average (50 layers, T = 64 and
+// 128; 10 % at most, 192 segments of 64, 16 experts of 960 x 1792), which takes 0.85 of the slab's time on average all the same.
+enum class Planes { kNone, kF32, kBf16 };
+
+Planes gate_up_planes(const Dims &m, const Plan &p, bool explicitly)
+{
+    const bool eight_waves = m.E <= 16 && (m.T == 64 || m.T == 128) && m.D * m.E < (1L << 30);
+    if (eight_waves && 4 * p.act <= p.slab_fwd) return Planes::kF32;
+    return explicitly || (m.T <= 64 && m.tokens % fmg::kRows8 == 0) ? Planes::kBf16 : Planes::kNone;
+}
+
 size_t bf16_workspace_bytes(const Dims &m, int pass)
 {
     const Plan p = make_plan(m);
     if (pass == LORY_PASS_FWD) {
         // fused path: G and U of all tokens when the caller does not keep them
-        const size_t gu = use_fused(m).gate_up ? 2 * p.act : 0;
+        const size_t gu = use_fused(m).gate_up && gate_up_planes(m, p, fused_mode() > 1) == Planes::kBf16 ? 2 * p.act : 0;
         return p.act + (p.slab_fwd > gu ? p.slab_fwd : gu);
     }
     // dG, dU, Act, recomputed G and U, slabs, router-weight partial sums
@@ -414,13 +430,21 @@ int bf16_ffn_fwd(const Dims &m, const void *Xv, const float *w, const void *Wgv,
     bf *slab = (bf *)((char *)ws + pl.act);
     const long TD = (long)m.T * m.d, TF = (long)m.T * m.dff;
 
-    const Fused fused = Wbar || m.S > pl.Sc ? Fused{} : use_fused(m);
+    Fused fused = Wbar || m.S > pl.Sc ? Fused{} : use_fused(m);
+    const Planes planes = G && U ? Planes::kBf16 : gate_up_planes(m, pl, fused_mode() > 1);
+    if (planes == Planes::kNone) fused.gate_up = false;
     if (fused.gate_up) {
         // merged parameters never leave the chip: fused contractions and one SwiGLU pass
-        bf *Gf = G ? G : slab, *Uf = U ? U : (bf *)((char *)slab + pl.act);
-        LORY_TRY(fused_gate_up(st, m, X, Wg, Wu, w, Gf, Uf));
-        {
-            prof::Range r(st, prof::kSwigluFwd, 4.0 * m.tokens * m.dff, 2.0 * 3.0 * m.tokens * m.dff);
+        const double elements = (double)m.tokens * m.dff;
+        if (planes == Planes::kF32) {
+            float *Gf = (float *)slab, *Uf = (float *)((char *)slab + 2 * pl.act);
+            LORY_TRY(fused_gate_up(st, m, X, Wg, Wu, w, (bf *)Gf, (bf *)Uf, true));
+            prof::Range r(st, prof::kSwigluFwd, 4.0 * elements, 10.0 * elements);
+            LORY_TRY(k::launch_swiglu_fwd_f32(st, Gf, Uf, Act, m.tokens * m.dff));
+        } else {
+            bf *Gf = G ? G : slab, *Uf = U ? U : (bf *)((char *)slab + pl.act);
+            LORY_TRY(fused_gate_up(st, m, X, Wg, Wu, w, Gf, Uf, false));
+            prof::Range r(st, prof::kSwigluFwd, 4.0 * elements, 2.0 * 3.0 * elements);
             LORY_TRY(k::launch_swiglu_fwd(st, Gf, Uf, Act, m.tokens, m.dff, 0, m.dff));
         }
     }
@@ -823,7 +847,7 @@ int bf16_ffn_bwd(const Dims &m, const void *Xv, const float *w, const void *Wgv,
             Gc = G + (size_t)s0 * TF;
             Uc = U + (size_t)s0 * TF;
         } else if (fused.gate_up) {
-            LORY_TRY(fused_gate_up(st, m, X, Wg, Wu, w, Gr, Ur));
+            LORY_TRY(fused_gate_up(st, m, X, Wg, Wu, w, Gr, Ur, false));
             Gc = Gr;
             Uc = Ur;
         } else {

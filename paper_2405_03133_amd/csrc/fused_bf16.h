@@ -455,7 +455,9 @@ constexpr int kRows8 = 512;   // token rows of a task
 // experts, T = 64; with the loop free of conditionals, in which the compiler overlaps the two products, 672).
 // K-contiguous stacks (their rows are read in 64-byte pieces) are faster with the next tile merged before the current one
 // is multiplied: 726 -> 685 us for dA, 1578 -> 1465 for dX; K-slow ones slower (690 -> 760).
-template <int TSEG, int NSRC, bool W_NC, bool PAIR>
+//
+// F32: C and C2 are fp32, for an activation that is formed from them before anything is rounded.
+template <int TSEG, int NSRC, bool W_NC, bool PAIR, bool F32>
 __global__ __launch_bounds__(512, 1) void fmg8_kernel(const Params p)
 {
     static_assert(!PAIR || NSRC == 1, "one token operand");
@@ -693,6 +695,26 @@ __global__ __launch_bounds__(512, 1) void fmg8_kernel(const Params p)
             const int r31 = lane & 31, h2 = lane >> 5;
 #pragma unroll
             for (int i = 0; i < MI; ++i) {
+                if constexpr (F32) {   // 32 rows of 256 bytes: both stages of the ring
+#pragma unroll
+                    for (int j = 0; j < NI; ++j)
+#pragma unroll
+                        for (int rq = 0; rq < 4; ++rq) {
+                            const int c = (j * 32 + 8 * rq + 4 * h2) >> 2;
+                            const f32x4 v = {acc[i][j][rq * 4 + 0], acc[i][j][rq * 4 + 1], acc[i][j][rq * 4 + 2], acc[i][j][rq * 4 + 3]};
+                            *reinterpret_cast<f32x4 *>(stg + r31 * 256 + ((c ^ (r31 & 15)) << 4)) = v;
+                        }
+                    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+                    for (int it = 0; it < 8; ++it) {
+                        const int idx = it * 64 + lane;
+                        const int row = idx >> 4, c = idx & 15;
+                        const f32x4 val = *reinterpret_cast<const f32x4 *>(stg + row * 256 + ((c ^ (row & 15)) << 4));
+                        *reinterpret_cast<f32x4 *>(reinterpret_cast<float *>(C) + (size_t)(row0 + i * 32 + row) * p.ldc + n0 + c * 4) = val;
+                    }
+                    __builtin_amdgcn_wave_barrier();
+                    continue;
+                }
 #pragma unroll
                 for (int j = 0; j < NI; ++j)
 #pragma unroll
@@ -729,12 +751,12 @@ inline bool fits8(const Params &p)
            p.lda[0] == p.lda[1] && (size_t)p.E * (size_t)p.expert_stride * 2 < ((size_t)1 << 31);
 }
 
-template <int TSEG, int NSRC, bool W_NC, bool PAIR>
+template <int TSEG, int NSRC, bool W_NC, bool PAIR, bool F32 = false>
 inline hipError_t launch8(const Params &p, hipStream_t st)
 {
     using SM = Smem8<TSEG>;
     static_assert(SM::total <= 160 * 1024, "LDS of one CU");
-    auto kern = fmg8_kernel<TSEG, NSRC, W_NC, PAIR>;
+    auto kern = fmg8_kernel<TSEG, NSRC, W_NC, PAIR, F32>;
     static bool configured = false;  // per instantiation
     if (!configured) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),

@@ -134,6 +134,23 @@ def test_inference_entry_points_validation():
                                   ctypes.byref(out)) == lb.LORY_ERR_SHAPE
 
 
+@pytest.mark.parametrize("T,L,d,d_ff,E", [(64, 192, 1216, 5632, 8), (64, 64, 1472, 5504, 16), (128, 384, 384, 4800, 8),
+                                          (128, 1024, 1152, 3520, 2), (128, 1024, 1600, 5120, 4)])
+def test_lowered_budget_bounds_the_forward_workspace(T, L, d, d_ff, E):
+    """Merging inside the GEMM where it is faster asks for no more workspace than the slab pipeline."""
+    s = shape(dtype=lb.LORY_BF16, B=1, L=L, T=T, d=d, d_ff=d_ff, E=E)
+    try:
+        for budget in (1 << 20, 16 << 20, 6144 << 20):
+            lb.lory_set_slab_budget(budget)
+            lb.lory_set_fused_merge(0)
+            slab = lb.lory_workspace_bytes(s, lb.LORY_PASS_FWD)
+            lb.lory_set_fused_merge(1)
+            assert lb.lory_workspace_bytes(s, lb.LORY_PASS_FWD) <= slab
+    finally:
+        lb.lory_set_fused_merge(1)
+        lb.lory_set_slab_budget(6144 << 20)
+
+
 @pytest.mark.parametrize("dtype", [lb.LORY_F32, lb.LORY_BF16])
 def test_workspace_query_and_ffn_validation(dtype):
     L = lb.lib()

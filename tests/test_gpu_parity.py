@@ -606,6 +606,45 @@ def test_bf16_contractions_choose_for_themselves(d, d_ff, fused, slab, save, def
     compare(cfg, got, ref, ALL if save else ("Y", "dX", "dWg", "dWu", "dWd", "dw"), TOL["bf16"])
 
 
+# A lowered budget holds less than G and U of all tokens: a forward pass that does not keep them takes the slab, block by block.
+@pytest.mark.parametrize("save", [True, False], ids=["saved_GU", "recompute_GU"])
+def test_bf16_contractions_within_a_lowered_budget(save, default_budget):
+    cfg = LoryConfig("mixed_budget", B=3, L=192, T=64, d=64, d_ff=704, E=6, dtype="bf16", seed=125)
+    t = make_inputs(cfg, structured=True)
+    print(f"[gpu] {cfg}", flush=True)
+    lb.lory_set_slab_budget(1 << 20)
+    lb.lory_profile_enable(True)
+    try:
+        lb.lory_profile_read()
+        got = run_layer(cfg, t, save=save, grad_dtype=torch.bfloat16)
+        classes = {s["name"] for s in lb.lory_profile_read()}
+    finally:
+        lb.lory_profile_enable(False)
+    assert ("gemm_gate_up" in classes) == (not save) and classes.issuperset(("fused_gate_up", "fused_dA"))
+    ref = oracle_layer(cfg, t, got["w_used"])
+    compare(cfg, got, ref, ALL if save else ("Y", "dX", "dWg", "dWu", "dWd", "dw"), TOL["bf16"])
+
+
+# Without saved G and U the activation is formed from fp32 and rounded once, as through the slab.  Tensor-wide relative
+# rounding errors, 1.65e-3 each: weights of gate and up, activation, weights of down, output.  G and U rounded before would
+# add two more of that size (SwiGLU's slopes are near 1): 1.2 times the error; 1.03 allows for the scatter of its parts.
+@pytest.mark.parametrize("T", [64, 128])
+def test_bf16_fused_activation_rounds_once(T, default_budget):
+    cfg = LoryConfig(f"once_T{T}", B=3, L=3 * T, T=T, d=320, d_ff=704, E=6, dtype="bf16", seed=126)
+    t = make_inputs(cfg, structured=True)
+    ref, err = None, {}
+    try:
+        for mode in (0, 2):
+            lb.lory_set_fused_merge(mode)
+            got = run_layer(cfg, t, save=False, grad_dtype=torch.bfloat16)
+            ref = ref or oracle_layer(cfg, t, got["w_used"])
+            err[mode] = rel_l2(got["Y"], ref["Y"])
+    finally:
+        lb.lory_set_fused_merge(1)
+    print(f"slab {err[0]:.4e}, merged inside the GEMM {err[2]:.4e}", flush=True)
+    assert err[2] <= 1.03 * err[0]
+
+
 @pytest.fixture
 def fused_with_gradients():
     lb.lory_set_fused_merge(3)
