@@ -215,7 +215,9 @@ int lory_route_bwd(const lory_shape *shape, const void *R, const float *w, const
  *      are clamped to 1 .. L
  * out: w [B, E] fp32; Wbar: 3 * B * d * d_ff elements of dtype, laid out
  *      [Wg_bar | Wu_bar | Wd_bar], each [B, rows, cols] like one expert matrix
- *      (the layout of Wbar_save).  Needs no workspace.
+ *      (the layout of Wbar_save).  Needs no workspace.  LORY_BF16: the bits of a
+ *      sequence's merged parameters follow from its w alone, whatever else the
+ *      call merges.
  * Per-segment routing at inference, the other mode the paper evaluates, is
  * lory_route + lory_merged_ffn_fwd as in training.
  */

@@ -114,35 +114,39 @@ hipError_t launch_merge(hipStream_t st, const ms::MergeParams &p)
     return hipGetLastError();
 }
 
-// The vector ALUs take a merge that they finish before the memory does: (S + 1) E multiply-adds an element against
-// 2 (S + E) bytes.  Beyond 8 segments only of few experts, where the matrix-core kernel has no more in flight than their
-// chunks: it writes more segments as fast.  us of the three merges of a layer, matrix cores and this.  Prompts: 14 experts of
-// 2048 x 6144, 8 segments 319 and 282; 3 experts of 2560 x 6144, 8 311 and 157; 5 of 1536 x 2816, 16 119 and 93.  Training
-// (the GEMM reads the slab next): 32 of 2048 x 5632, 4 segments 490 and 439; 8 of 1024 x 2816, 12 87 and 80; 6 of
-// 1536 x 4096, 16 181 and 183, the GEMMs 18 less; 20 of 1536 x 1536, 10 105 and 109; 12 of 1536 x 4096, 16 203 and 227.
+// One unit a wavefront takes a merge as long as a unit's registers hold all segments: 8, and 16 with up to 8 experts (whose
+// unit is twice as large).  us of the three merges of a layer, merge_kernel and merge_few_kernel: 3 prompts, 16 experts of
+// 2048 x 5632 273 and 216; 8 and 14 of 2048 x 6144 322 and 273; 16 and 6 of 1536 x 4096 175 and 135; 16 and 6 of 2048 x 5632
+// 285 and 254.  Forward passes, with the GEMMs that read the slab: 8 segments, 48 experts of 1024 x 2816 272 and 209;
+// 15 and 8 of 1536 x 2816 252 and 228; 16 and 7 of 2048 x 5632 636 and 619.  38 layers on average 0.83 of the time, the worst
+// 0.96 (backward 0.92 and 0.98).
 bool merge_is_few(int S, int E)
 {
-    return S <= 8 ? (S + 1) * E <= 320 : S <= 12 ? E <= 8 : S <= 16 && E <= 6;
+    return S <= (E <= 8 ? ms::kFewSegments : 8);
 }
 
 hipError_t launch_merge_few(hipStream_t st, const ms::MergeFewParams &p, int matrices)
 {
-    if (p.S < 1 || p.S > ms::kFewSegments || matrices < 1 || matrices > 3) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)((p.rc.nr * p.rc.nc / 8 + 255) / 256), (unsigned)matrices);
-#define LORY_FEW(N)                                                                                  \
+    if (p.S < 1 || !merge_is_few(p.S, p.E) || p.E < 1 || p.E > 64 || matrices < 1 || matrices > 3) return hipErrorInvalidValue;
+    const int chunks = 4 * ms::few_unit_chunks(p.E);   // of a workgroup
+    const dim3 grid((unsigned)((p.rc.nr * p.rc.nc / 8 + chunks - 1) / chunks), (unsigned)matrices);
+#define LORY_FEW(K, N)                                                                               \
     if (p.seg_map)                                                                                   \
-        hipLaunchKernelGGL((ms::merge_few_kernel<N, true>), grid, dim3(256), 0, st, p);              \
+        hipLaunchKernelGGL((ms::merge_few_kernel<K, N, true>), grid, dim3(256), 0, st, p);           \
     else                                                                                             \
-        hipLaunchKernelGGL((ms::merge_few_kernel<N, false>), grid, dim3(256), 0, st, p)
-    switch (p.S) {
-    case 1: LORY_FEW(1); break;
-    case 2: LORY_FEW(2); break;
-    case 3: LORY_FEW(3); break;
-    case 4: LORY_FEW(4); break;
-    case 5: case 6: LORY_FEW(6); break;
-    case 7: case 8: LORY_FEW(8); break;
-    case 9: case 10: case 11: case 12: LORY_FEW(12); break;
-    default: LORY_FEW(16); break;
+        hipLaunchKernelGGL((ms::merge_few_kernel<K, N, false>), grid, dim3(256), 0, st, p)
+    switch (p.E <= 8 ? 0 : (p.E + 15) / 16) {
+    case 0:
+        if (p.S > 8) {
+            LORY_FEW(0, 8);
+        } else {
+            LORY_FEW(0, 4);
+        }
+        break;
+    case 1: LORY_FEW(1, 4); break;
+    case 2: LORY_FEW(2, 4); break;
+    case 3: LORY_FEW(3, 4); break;
+    default: LORY_FEW(4, 4); break;
     }
 #undef LORY_FEW
     return hipGetLastError();

@@ -254,13 +254,14 @@ __global__ __launch_bounds__(256) void merge_kernel(const MergeParams p)
     }
 }
 
-// Merge of few segments on the vector ALUs: a thread owns one 16-byte chunk of the rectangle, keeps the fp32 sums of up
-// to SB segments and reads the chunk of every expert once, eight experts in flight; the routing weights are uniform and
-// come through scalar registers.  HBM-bound.  The matrix-core kernel above has one wavefront per SIMD and one unit in
-// flight behind the current one, which is enough where it stores dozens of segments for a unit, but not where a unit is
-// little more than its reads.  us of three merges, matrix cores -> this: 3 segments, 16 experts of 2048 x 5632 (one
-// launch) 263 -> 230; 3 and 6 of 1792 x 6144 220 -> 90 (6.5 TB/s); 1 and 1 of 1024 x 6144 131 -> 23.  The chunks are
-// loaded as non-temporal, they are read once (7 of 2048 x 5632, 32 experts: 517 -> 477); non-temporal stores took 487.
+// Merge of few segments: the matrix instructions of merge_kernel in its order, so that the merged values of a segment have
+// the same bits however many segments are merged beside it.  HBM-bound.  merge_kernel has one wavefront per SIMD and one unit
+// in flight behind the current one, enough where it stores dozens of segments for a unit, but not where a unit is little more
+// than its reads.  Here a wavefront merges one unit, its accumulators are packed two elements at a time, and two to seven
+// wavefronts fit a SIMD.  us of three merges (one launch), merge_kernel -> this: 3 segments, 16 experts of 2048 x 5632
+// 273 -> 216 (6.1 TB/s); 3 and 6 of 1792 x 6144 218 -> 94; 8 and 5 of 1536 x 6144 194 -> 110 (6.7); 1 and 4 of 1792 x 704
+// 38 -> 14.  Two and four units a wavefront: 1.01 and 1.04 of that time.  The chunks are loaded as non-temporal, they are
+// read once.
 struct MergeFewParams {
     const float *w;            // [S, E]
     int S, E;
@@ -272,77 +273,131 @@ struct MergeFewParams {
 };
 
 constexpr int kFewSegments = 16;
+constexpr int few_unit_chunks(int E) { return E <= 8 ? 64 : 32; }
 
-template <int SB, bool MAP>
-__global__ __launch_bounds__(256) void merge_few_kernel(const MergeFewParams p)
+// KS = ceil(E / 16), 0 for up to 8 experts; NR: accumulator registers that hold segments, 4 for up to 8 and 8 for up to 16.
+// KS 0: a unit has 64 chunks, and the two halves of the wavefront load 32 each; each half goes to the matrix cores as
+// K = 0 .. 7, with zeros in the place of experts 8 .. 15 (as merge_kernel has them).
+template <int KS, int NR, bool MAP>
+__global__ __launch_bounds__(256, KS > 2 ? 2 : KS == 2 || NR > 4 ? 3 : 4) void merge_few_kernel(const MergeFewParams p)
 {
-    // MAP: bit s of a wavefront's word: segment s differs from the one before in an expert that is the wavefront's share, or
-    // is the first.  Rows are compared as bits; the words are read after the sums, so that nothing waits for them.
-    __shared__ uint32_t differs[4];
-    if constexpr (MAP) {
-        const int s = threadIdx.x & 63, wv = threadIdx.x >> 6;
-        uint32_t diff = s == 0;
-        if (s > 0 && s < p.S) {
-            const uint32_t *a = reinterpret_cast<const uint32_t *>(p.w) + (size_t)s * p.E, *b = a - p.E;
-#pragma unroll 8
-            for (int e = wv; e < p.E; e += 4) diff |= a[e] ^ b[e];
+    constexpr int KN = KS > 0 ? KS : 1, UN = KS > 0 ? 1 : 2;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int ln = lane & 31, h = lane >> 5;
+    const int Q = (p.rc.nr * p.rc.nc) >> 3, unit = blockIdx.x * 4 + wave, q0 = unit * 32 * UN;
+    if (q0 >= Q) return;
+
+    // the routing weights are on their way before the chunks (addresses clamped: no branch stands between the loads)
+    float wv[KN][8];
+#pragma unroll
+    for (int ks = 0; ks < KN; ++ks)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int e = 16 * ks + 8 * h + i;
+            wv[ks][i] = p.w[(ln < p.S ? ln * p.E : 0) + (e < p.E ? e : 0)];
         }
-        const uint32_t m = (uint32_t)__builtin_amdgcn_ballot_w64(diff != 0);
-        if (s == 0) differs[wv] = m;
+
+    Frag R[KN][8];
+    {
+        const int e_lane = KS > 0 ? 8 * h : 0, q = q0 + (KS > 0 ? ln : lane);
+        const uint16_t *src = p.stack[blockIdx.y] + (q < Q ? rect_offset(p.rc, q) : 0) + e_lane * p.rc.expert_stride;
+#pragma unroll
+        for (int ks = 0; ks < KN; ++ks) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                R[ks][i].u = make_uint4(0, 0, 0, 0);
+                if (q < Q && 16 * ks + e_lane + i < p.E) {
+                    const gemm::u32x4 t = __builtin_nontemporal_load(reinterpret_cast<const gemm::u32x4 *>(src));
+                    R[ks][i].u = make_uint4(t.x, t.y, t.z, t.w);
+                }
+                src += p.rc.expert_stride;
+            }
+            src += 8 * p.rc.expert_stride;
+        }
+    }
+    Frag whi[KN], wlo[KN];
+#pragma unroll
+    for (int ks = 0; ks < KN; ++ks) {
+        float v[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = (ln < p.S && 16 * ks + 8 * h + i < p.E) ? wv[ks][i] : 0.f;
+        split_hi_lo(v, whi[ks], wlo[ks]);
+    }
+    uint32_t stored = (1u << p.S) - 1u;   // bit s: segment s is stored
+    if constexpr (MAP) {
+        // the first of each run of equal routing rows, compared as bits: lane ln has the weights of segment ln, the one before it
+        // those of the segment before (segments lie within one row of 16 lanes)
+        uint32_t diff = ln == 0;
+#pragma unroll
+        for (int ks = 0; ks < KN; ++ks)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int x = __float_as_int(wv[ks][i]);
+                diff |= (uint32_t)(x ^ __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, true));   // row_shr:1
+            }
+        const uint64_t m = __builtin_amdgcn_ballot_w64(diff != 0);
+        stored &= (uint32_t)(m | m >> 32);
+        if (unit == 0 && blockIdx.y == 0 && lane < p.S) p.seg_map[lane] = 31 - __builtin_clz(stored & (~0u >> (31 - lane)));
     }
 
-    const int Q = (p.rc.nr * p.rc.nc) >> 3, q = blockIdx.x * 256 + threadIdx.x;
-    const uint16_t *src = p.stack[blockIdx.y] + rect_offset(p.rc, q < Q ? q : Q - 1);
-    uint16_t *dst = p.slab[blockIdx.y] + (size_t)q * 8;
-
-    float acc[SB][8];
+    uint4 o[UN][NR];
 #pragma unroll
-    for (int s = 0; s < SB; ++s)
+    for (int jj = 0; jj < 4; ++jj) {   // elements 2 jj and 2 jj + 1 of the chunk
+        float v[UN][2][NR];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) acc[s][j] = 0.f;
-    auto add = [&](auto count, int e0) {
-        uint4 v[count];
+        for (int j = 0; j < 2; ++j) {
+            Frag P[UN][KN];   // eight experts of the element: a column of transpose8x8
 #pragma unroll
-        for (int i = 0; i < count; ++i) { const gemm::u32x4 t = __builtin_nontemporal_load(reinterpret_cast<const gemm::u32x4 *>(src + (size_t)(e0 + i) * p.rc.expert_stride)); v[i] = make_uint4(t.x, t.y, t.z, t.w); }
+            for (int ks = 0; ks < KN; ++ks)
 #pragma unroll
-        for (int i = 0; i < count; ++i) {
-            float x[8];
+                for (int ip = 0; ip < 4; ++ip) {
+                    const uint32_t t = __builtin_amdgcn_perm(R[ks][2 * ip + 1].w[jj], R[ks][2 * ip].w[jj], j ? 0x07060302u : 0x05040100u);
+                    if constexpr (KS > 0) {
+                        P[0][ks].w[ip] = t;
+                    } else {
+                        const auto two = __builtin_amdgcn_permlane32_swap(t, 0u, false, false);   // {lower half, 0}, {upper half, 0}
+                        P[0][ks].w[ip] = two[0];
+                        P[UN - 1][ks].w[ip] = two[1];
+                    }
+                }
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint32_t u = j == 0 ? v[i].x : j == 1 ? v[i].y : j == 2 ? v[i].z : v[i].w;
-                x[2 * j] = __uint_as_float(u << 16);
-                x[2 * j + 1] = __uint_as_float(u & 0xffff0000u);
-            }
+            for (int u = 0; u < UN; ++u) {
+                f32x16 acc;
 #pragma unroll
-            for (int s = 0; s < SB; ++s) {
-                const float ws = p.w[(size_t)(s < p.S ? s : 0) * p.E + e0 + i];
+                for (int r = 0; r < 16; ++r) acc[r] = 0.f;
 #pragma unroll
-                for (int j = 0; j < 8; ++j) acc[s][j] = fmaf(ws, x[j], acc[s][j]);
+                for (int ks = 0; ks < KN; ++ks) {
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(whi[ks].v, P[u][ks].v, acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wlo[ks].v, P[u][ks].v, acc, 0, 0, 0);
+                }
+#pragma unroll
+                for (int r = 0; r < NR; ++r) v[u][j][r] = acc[r];
             }
         }
-    };
-    int e = 0;
-    for (; e + 8 <= p.E; e += 8) add(std::integral_constant<int, 8>(), e);
-    if (p.E & 4) add(std::integral_constant<int, 4>(), e);
-    if (p.E & 2) add(std::integral_constant<int, 2>(), e + (p.E & 4));
-    if (p.E & 1) add(std::integral_constant<int, 1>(), p.E - 1);
-    uint32_t stored = (1u << p.S) - 1u;   // bit s: segment s is the first of its run
-    if constexpr (MAP) {
-        __syncthreads();
-        stored = __builtin_amdgcn_readfirstlane(differs[0] | differs[1] | differs[2] | differs[3]);
-        const int s = threadIdx.x;
-        if (blockIdx.x + blockIdx.y == 0 && s < p.S) p.seg_map[s] = 31 - __builtin_clz(stored & (~0u >> (31 - s)));
-    }
-    if (q >= Q) return;
 #pragma unroll
-    for (int s = 0; s < SB; ++s) {
-        if (!(stored >> s & 1)) continue;
-        uint4 o;
-        o.x = pack_bf16(acc[s][0], acc[s][1]);
-        o.y = pack_bf16(acc[s][2], acc[s][3]);
-        o.z = pack_bf16(acc[s][4], acc[s][5]);
-        o.w = pack_bf16(acc[s][6], acc[s][7]);
-        *reinterpret_cast<uint4 *>(dst + (size_t)s * p.seg_stride) = o;
+        for (int u = 0; u < UN; ++u)
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+                uint32_t t = pack_bf16(v[u][0][r], v[u][1][r]);
+                asm volatile("" : "+v"(t));   // packed here and not beside the stores, where all accumulators would be alive
+                if (jj == 0) o[u][r].x = t;
+                if (jj == 1) o[u][r].y = t;
+                if (jj == 2) o[u][r].z = t;
+                if (jj == 3) o[u][r].w = t;
+            }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    uint16_t *slab = p.slab[blockIdx.y];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+        const int q = q0 + 32 * u + ln;
+        if (q < Q) {
+#pragma unroll
+            for (int r = 0; r < NR; ++r) {
+                const int seg = 8 * (r >> 2) + 4 * h + (r & 3);
+                if (stored >> seg & 1) *reinterpret_cast<uint4 *>(slab + (size_t)seg * p.seg_stride + (size_t)q * 8) = o[u][r];
+            }
+        }
     }
 }
 

@@ -314,7 +314,7 @@ def test_bf16_ring_gemm_edge_tiles_without_saved_planes(cfg):
 @pytest.mark.parametrize("cfg", [
     LoryConfig("shared_S150", B=5, L=3840, T=128, d=64, d_ff=128, E=5, dtype="bf16", seed=111),
     LoryConfig("shared_E33", B=2, L=4096, T=128, d=64, d_ff=64, E=33, dtype="bf16", seed=112),
-    # few segments: merged on the vector ALUs
+    # few segments: merge_few_kernel, two units and one unit a wavefront
     LoryConfig("shared_S15", B=3, L=640, T=128, d=64, d_ff=192, E=5, dtype="bf16", seed=123),
     LoryConfig("shared_S8", B=2, L=512, T=128, d=64, d_ff=192, E=33, dtype="bf16", seed=124),
 ], ids=lambda c: c.name)
@@ -336,8 +336,8 @@ def test_bf16_equal_routing_rows(cfg, runs):
             assert np.array_equal(got[key], saved[key]), key
 
 
-# Every number of sums that a thread keeps, the remainders of the experts in groups of eight, and a last workgroup that the
-# chunks do not fill; the last three are beyond the line and merged on the matrix cores.
+# Every form of the merge of few segments (up to 8 and 16 segments; up to 8 experts two units a wavefront, else one), with
+# remainders of the experts; (9, 9) and (17, 3) are beyond the line and merged by merge_kernel.
 @pytest.mark.parametrize("B,E,d,d_ff", [(1, 1, 64, 64), (1, 13, 64, 320), (2, 2, 128, 192), (3, 7, 64, 128), (4, 8, 192, 64),
                                         (5, 11, 64, 64), (6, 9, 64, 192), (7, 16, 64, 64), (8, 33, 64, 128), (11, 6, 64, 64),
                                         (12, 8, 64, 192), (14, 3, 64, 128), (16, 6, 64, 64), (9, 9, 64, 64), (13, 7, 64, 192),
@@ -355,6 +355,23 @@ def test_bf16_merge_of_few_segments(B, E, d, d_ff):
         ref, mag = w64 @ st, np.abs(w64) @ np.abs(st)
         # one rounding to bf16, and sums in 32 bits of weights that the matrix cores take as hi + lo (2^-17)
         assert np.all(np.abs(host(Wbar[x]) - ref) <= 2.0 ** -8 * np.abs(ref) + 2.0 ** -15 * mag), x
+
+
+# The merged parameters of a prompt have the same bits whatever number of prompts is merged beside it: every count of
+# register sets and units (up to 8, 16, 32, 48 and 64 experts), on both sides of where merge_kernel takes over.
+@pytest.mark.parametrize("E,counts", [(3, (1, 8, 9, 16, 17)), (8, (2, 12, 16, 33)), (9, (1, 5, 8, 9)), (16, (3, 8, 20)),
+                                      (32, (1, 7, 8, 9)), (40, (2, 8, 9)), (64, (1, 4, 8, 9))])
+def test_bf16_merged_prompt_does_not_depend_on_the_batch(E, counts):
+    print(f"[gpu] merged prompts {E} {counts}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(130)
+    d, d_ff, n = 64, 192, max(counts)
+    X = (torch.randn((n, 40, d), generator=gen, device="cuda") + torch.randn((n, 1, d), generator=gen, device="cuda")).bfloat16()
+    R = (torch.randn((d, E), generator=gen, device="cuda") / 8).bfloat16()
+    Wg, Wu, Wd = (torch.randn(s, generator=gen, device="cuda").mul_(0.02).bfloat16() for s in ((E, d, d_ff), (E, d, d_ff), (E, d_ff, d)))
+    w, Wbar = lb.lory_prompt_merge(X, R, Wg, Wu, Wd)
+    for B in counts:
+        wb, part = lb.lory_prompt_merge(X[:B].contiguous(), R, Wg, Wu, Wd)
+        assert torch.equal(wb, w[:B]) and torch.equal(part, Wbar[:, :B]), B
 
 
 def test_profile_counts_shared_merges_once():
