@@ -109,9 +109,9 @@ int lory_set_slab_budget(size_t bytes);
  *      8, bf16 gradients that overwrite (other calls use the slab pipeline for
  *      this stage).  Measured slower than the slab pipeline at every shape tried;
  *      it exists to be measured
- * The LORY_FUSED environment variable sets the initial value.  Changes what
- * lory_workspace_bytes reports (forward pass), so set it before sizing a
- * workspace.  Returns LORY_ERR_SHAPE for other values.
+ * The LORY_FUSED environment variable sets the initial value.  Modes 2 and 3
+ * change what lory_workspace_bytes reports (forward pass), so set it before
+ * sizing a workspace.  Returns LORY_ERR_SHAPE for other values.
  */
 int lory_set_fused_merge(int mode);
 

@@ -107,20 +107,28 @@ bool fused_pays(const Dims &m, int N, int K, int mats, int nsrc)
     return fused < 0.92 * slab;
 }
 
+// The contractions of the layer have N and K in {d, d_ff}: parameters of the two products, for the shape conditions alone.
+fmg::Params fused_shape(const Dims &m, bool n_is_dff)
+{
+    const int N = n_is_dff ? m.dff : m.d, K = n_is_dff ? m.d : m.dff;
+    return fused_params(m, nullptr, nullptr, K, nullptr, nullptr, N, nullptr, N, K, nullptr, N);
+}
+
+// Whether the eight-wave kernel takes every contraction of the layer.
+bool eight_waves(const Dims &m)
+{
+    const fmg::Params a = fused_shape(m, true), b = fused_shape(m, false);
+    return m.tokens <= 0x7fffffffL && ((fmg::fits8<64>(a) && fmg::fits8<64>(b)) || (fmg::fits8<128>(a) && fmg::fits8<128>(b)));
+}
+
 Fused use_fused(const Dims &m)
 {
     const Fused none = {false, false, false, false}, all = {true, true, true, true};
     const int mode = fused_mode();
     if (mode == 0 || m.tokens > 0x7fffffffL) return none;
-    // every contraction of the layer has N and K in {d, d_ff}
-    const fmg::Params a = fused_params(m, nullptr, nullptr, m.d, nullptr, nullptr, m.dff, nullptr, m.dff, m.d,
-                                       nullptr, m.dff);
-    const fmg::Params b = fused_params(m, nullptr, nullptr, m.dff, nullptr, nullptr, m.d, nullptr, m.d, m.dff,
-                                       nullptr, m.d);
-    if (!k::fused_fits(a) || !k::fused_fits(b)) return none;
-    if (mode >= 2) return all;
+    if (mode >= 2) return k::fused_fits(fused_shape(m, true)) && k::fused_fits(fused_shape(m, false)) ? all : none;
     // longer segments, more experts and stacks of 2 GiB and more would run on the four-wave kernel
-    if (!(fmg::fits8<64>(a) && fmg::fits8<64>(b)) && !(fmg::fits8<128>(a) && fmg::fits8<128>(b))) return none;
+    if (!eight_waves(m)) return none;
     return {fused_pays(m, m.dff, m.d, 2, 1), fused_pays(m, m.d, m.dff, 1, 1), fused_pays(m, m.dff, m.d, 1, 1),
             fused_pays(m, m.d, m.dff, 2, 2)};
 }
@@ -375,26 +383,26 @@ size_t bf16_merged_save_bytes(const Dims &m)
 }
 
 // How the fused gate and up projections leave G and U in the workspace of a forward pass whose caller does not keep them:
-// in fp32 where that fits the slab, so that the activation rounds once as in the slab pipeline's epilogue; otherwise rounded,
-// for 64-token segments in whole row chunks, which report two planes at every slab budget.  Other calls take the slab:
-// they ask for no more workspace than it.  Error of Y against 64 bits, 1e-3, 11 segments of 64, 8 experts of 512 x 1408: slab
+// in fp32 where that fits the slab, so that the activation rounds once as in the slab pipeline's epilogue.  Otherwise the call
+// takes the slab, at every token count, and asks for no more workspace than it; only where the merge inside the GEMM is asked
+// for (modes 2 and 3) the planes are rounded.  Error of Y against 64 bits, 1e-3, 11 segments of 64, 8 experts of 512 x 1408: slab
 // 3.714, fp32 planes 3.713, rounded planes 4.46.  Their bytes cost 1.8 % of a forward pass on average (50 layers, T = 64 and
 // 128; 10 % at most, 192 segments of 64, 16 experts of 960 x 1792), which takes 0.85 of the slab's time on average all the same.
 enum class Planes { kNone, kF32, kBf16 };
 
 Planes gate_up_planes(const Dims &m, const Plan &p, bool explicitly)
 {
-    const bool eight_waves = m.E <= 16 && (m.T == 64 || m.T == 128) && m.D * m.E < (1L << 30);
-    if (eight_waves && 4 * p.act <= p.slab_fwd) return Planes::kF32;
-    return explicitly || (m.T <= 64 && m.tokens % fmg::kRows8 == 0) ? Planes::kBf16 : Planes::kNone;
+    if (eight_waves(m) && 4 * p.act <= p.slab_fwd) return Planes::kF32;
+    return explicitly ? Planes::kBf16 : Planes::kNone;
 }
 
 size_t bf16_workspace_bytes(const Dims &m, int pass)
 {
     const Plan p = make_plan(m);
     if (pass == LORY_PASS_FWD) {
-        // fused path: G and U of all tokens when the caller does not keep them
-        const size_t gu = use_fused(m).gate_up && gate_up_planes(m, p, fused_mode() > 1) == Planes::kBf16 ? 2 * p.act : 0;
+        // rounded G and U of all tokens when the caller does not keep them
+        const bool explicitly = fused_mode() > 1;
+        const size_t gu = explicitly && use_fused(m).gate_up && gate_up_planes(m, p, explicitly) == Planes::kBf16 ? 2 * p.act : 0;
         return p.act + (p.slab_fwd > gu ? p.slab_fwd : gu);
     }
     // dG, dU, Act, recomputed G and U, slabs, router-weight partial sums

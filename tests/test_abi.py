@@ -135,7 +135,9 @@ def test_inference_entry_points_validation():
 
 
 @pytest.mark.parametrize("T,L,d,d_ff,E", [(64, 192, 1216, 5632, 8), (64, 64, 1472, 5504, 16), (128, 384, 384, 4800, 8),
-                                          (128, 1024, 1152, 3520, 2), (128, 1024, 1600, 5120, 4)])
+                                          (128, 1024, 1152, 3520, 2), (128, 1024, 1600, 5120, 4),
+                                          # whole row chunks of 512 tokens
+                                          (64, 2048, 960, 4160, 8), (64, 512, 64, 704, 6), (64, 1024, 768, 2816, 16)])
 def test_lowered_budget_bounds_the_forward_workspace(T, L, d, d_ff, E):
     """Merging inside the GEMM where it is faster asks for no more workspace than the slab pipeline."""
     s = shape(dtype=lb.LORY_BF16, B=1, L=L, T=T, d=d, d_ff=d_ff, E=E)

@@ -623,10 +623,12 @@ def test_bf16_contractions_choose_for_themselves(d, d_ff, fused, slab, save, def
     compare(cfg, got, ref, ALL if save else ("Y", "dX", "dWg", "dWu", "dWd", "dw"), TOL["bf16"])
 
 
-# A lowered budget holds less than G and U of all tokens: a forward pass that does not keep them takes the slab, block by block.
+# A lowered budget holds less than G and U of all tokens: a forward pass that does not keep them takes the slab, block by
+# block, whether its tokens fill the row chunks or not.
 @pytest.mark.parametrize("save", [True, False], ids=["saved_GU", "recompute_GU"])
-def test_bf16_contractions_within_a_lowered_budget(save, default_budget):
-    cfg = LoryConfig("mixed_budget", B=3, L=192, T=64, d=64, d_ff=704, E=6, dtype="bf16", seed=125)
+@pytest.mark.parametrize("B,L", [(3, 192), (1, 512)])
+def test_bf16_contractions_within_a_lowered_budget(B, L, save, default_budget):
+    cfg = LoryConfig("mixed_budget", B=B, L=L, T=64, d=64, d_ff=704, E=6, dtype="bf16", seed=125)
     t = make_inputs(cfg, structured=True)
     print(f"[gpu] {cfg}", flush=True)
     lb.lory_set_slab_budget(1 << 20)
