@@ -146,7 +146,8 @@ int lory_profile_read(lory_kernel_stat *out, int max_out, int *n_out);
  * workspace holds only transient data (merged-weight slabs, per-segment
  * weight-gradient slabs, activations between the two projections, partial
  * router-weight gradients); its contents are undefined before and after a
- * call.  Host-only: touches no device.
+ * call.  Host-only: touches no device, except that LORY_PASS_DENSE for LORY_BF16
+ * asks the current device for its number of CUs (256 if there is none).
  */
 int lory_workspace_bytes(const lory_shape *shape, int pass, size_t *bytes_out);
 

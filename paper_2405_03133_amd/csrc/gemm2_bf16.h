@@ -738,7 +738,7 @@ inline int cu_count()
         int dev = 0, cus = 0;
         if (hipGetDevice(&dev) != hipSuccess ||
             hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 8)
-            cus = 256;
+            return 256;   // not kept: a later call may find the device
         n = cus / 8 * 8;
     }
     return n;

@@ -4,6 +4,8 @@ needed: every call below returns from validation."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -151,6 +153,44 @@ def test_lowered_budget_bounds_the_forward_workspace(T, L, d, d_ff, E):
     finally:
         lb.lory_set_fused_merge(1)
         lb.lory_set_slab_budget(6144 << 20)
+
+
+SHIM = r"""
+int asked, fail, cus;
+int hipGetDevice(int *dev) { ++asked; *dev = 0; return fail ? 100 : 0; }
+int hipDeviceGetAttribute(int *v, int attr, int dev) { ++asked; *v = cus; return fail ? 100 : 0; }
+"""
+QUERY = r"""
+import ctypes, sys
+shim = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+L = ctypes.CDLL(sys.argv[2])
+asked, fail, cus = (ctypes.c_int.in_dll(shim, n) for n in ("asked", "fail", "cus"))
+def size(p, *dims):
+    out = ctypes.c_size_t()
+    assert L.lory_workspace_bytes((ctypes.c_int32 * 7)(*dims, 1), p, ctypes.byref(out)) == 0
+    return out.value
+fail.value, cus.value = int(sys.argv[3]), 64
+for T in (64, 128, 256):
+    for p in (0, 1):
+        assert size(p, 2, 2048, T, 1024, 2816, 8) > 0
+assert asked.value == 0, asked.value
+first = size(2, 4, 64, 64, 512, 1408, 1)
+assert asked.value > 0
+fail.value = 0
+print(first, size(2, 4, 64, 64, 512, 1408, 1))
+"""
+
+
+def test_workspace_queries_and_the_device(tmp_path):
+    """Sizes of the training passes ask no device; those of the dense pass ask for its CUs, and an answer that failed is
+    not kept.  The two HIP calls come from a library loaded before HIP's own."""
+    src, shim = tmp_path / "shim.c", str(tmp_path / "shim.so")
+    src.write_text(SHIM)
+    subprocess.run(["gcc", "-shared", "-fPIC", "-o", shim, str(src)], check=True)
+    lb.lib()   # built
+    sizes = [tuple(map(int, subprocess.run([sys.executable, "-c", QUERY, shim, lb.LIB_PATH, fail], check=True,
+                                           stdout=subprocess.PIPE, text=True).stdout.split())) for fail in "01"]
+    assert sizes[0][0] == sizes[0][1] == sizes[1][1] != sizes[1][0]
 
 
 @pytest.mark.parametrize("dtype", [lb.LORY_F32, lb.LORY_BF16])
