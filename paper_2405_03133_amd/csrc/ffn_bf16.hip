@@ -85,26 +85,30 @@ struct Fused {
 
 // Whether the merge inside the GEMM is estimated to be faster for a contraction of `mats` expert matrices (two operand sets
 // or two sources) with N output columns and K per source: on the eight-wave kernel (segments of 64 or 128 tokens), against
-// the merges into the slab and the GEMM that reads it.  us: rounds of tasks over the CUs times their K steps, whose expert
-// chunks grow with E; the merges' and the GEMM's bytes.  Fitted to both forms of 700 layers of 64-token segments (2 .. 256
-// segments, 2 .. 16 experts, d = 768 .. 2560, d_ff = 704 .. 6144): off by 11 and 8 % (rms), and what is chosen takes 0.4 %
-// more than the faster form on average, where always the slab takes 24 .. 62 %.  400 layers of 128-token segments fit as
-// well; there the forms are closer (the slab takes 3 .. 11 % more), and 0.92 keeps the gain: 0.935 of the slab for
-// gate/up, 0.965 for dA, 0.99 for down and dX, 1.14 at worst.  us of slab and fused: gate/up of 82 segments of 64, 7 experts
-// of 1792 x 4160 1280 and 650; dX of 3 segments, 14 of 1792 x 5632 230 and 650.  One expert always takes the slab: its
-// segments share their merged values.
+// the merges into the slab and the GEMM that reads it.  us.  Fused: rounds of tasks over the CUs times their K steps, whose
+// expert chunks grow with E and are shared by up to eight row chunks; extra_us is added.  Slab: the bytes of the merges and of
+// the GEMM.  The first two segments of every sequence share their merged values: one of them is not stored, and read
+// from the cache in part.  Fitted to both forms of 600 layers each of 64- and 128-token segments (1 .. 120 sequences of 2 .. 240
+// segments, 2 .. 16 experts, d = 768 .. 2560, d_ff = 704 .. 6144): off by 9 and 8 % (rms).  The margins keep out what is not
+// clearly faster: 0.90, 17 of 2950 contractions take 3 % longer than through the slab, 1.12 at worst; merges of few segments
+// run at the memory's rate, and where their unevenly filled rounds of tasks are estimated well is within 0.76.  Time of the
+// slab's that is left, many segments, T = 64: gate/up 0.56, down 0.73, dA 0.61, dX 0.78; T = 128: 0.95, 0.99, 0.96, 1.00; few segments, T = 64:
+// 0.88, 1.00, 0.95, 1.00 (T = 128 0.98 for gate/up, 1.25 at worst: the slab).  us of slab and fused: gate/up of 82 segments of
+// 64, 7 experts of 1792 x 4160 1280 and 650; dX of 3 segments, 14 of 1792 x 5632 230 and 650; a backward pass of 16 sequences of two
+// 128-token segments, 4 of 2048 x 5632 1901 and 1997.  One expert always takes the slab: its segments share their merged values.
 // Layers of fewer parameters than measured stay on the slab with 128-token segments, where the two forms are close.
 constexpr long kFusedLeastD = 500000;
 
-bool fused_pays(const Dims &m, int N, int K, int mats, int nsrc)
+bool fused_pays(const Dims &m, int N, int K, int mats, int nsrc, double extra_us = 0.0)
 {
-    if (m.E < 2 || (m.T > 64 && m.D < kFusedLeastD)) return false;
-    const long cus = gemm2::cu_count(), tasks = (m.tokens + fmg::kRows8 - 1) / fmg::kRows8 * (N / fmg::BN) * (mats / nsrc);
-    const long rounds = ((tasks + 7) / 8 + cus / 8 - 1) / (cus / 8);
-    const double alone = m.tokens <= fmg::kRows8 ? 1.12 : 1.0;   // one row chunk shares its expert chunks with none
-    const double fused = 10.0 + alone * (double)rounds * nsrc * (K / fmg::BK) * (1.11 + 0.052 * m.E);
-    const double slab = 13.4 + mats * (7.1 + 2e-6 * m.D * (0.403 * m.S + 0.150 * m.E));
-    return fused < 0.92 * slab;
+    const bool few = k::merge_is_few(m.S, m.E), longer = m.T > 64;
+    if (m.E < 2 || (longer && (few || m.D < kFusedLeastD))) return false;
+    const long cus = gemm2::cu_count(), chunks = (m.tokens + fmg::kRows8 - 1) / fmg::kRows8;
+    const long tasks = chunks * (N / fmg::BN) * (mats / nsrc), rounds = ((tasks + 7) / 8 + cus / 8 - 1) / (cus / 8);
+    const double fused = 8.3 + extra_us + (double)rounds * nsrc * (K / fmg::BK) * (1.17 + m.E * (0.038 + 0.031 / (chunks < 8 ? chunks : 8)));
+    const long distinct = m.N > 1 ? m.S - m.B : m.S;
+    const double slab = 15.0 + mats * (6.9 + 2e-6 * m.D * (0.215 * distinct + (longer ? 0.215 : 0.172) * m.S + 0.165 * m.E));
+    return fused < (few ? 0.76 : 0.90) * slab;
 }
 
 // The contractions of the layer have N and K in {d, d_ff}: parameters of the two products, for the shape conditions alone.
@@ -121,7 +125,10 @@ bool eight_waves(const Dims &m)
     return m.tokens <= 0x7fffffffL && ((fmg::fits8<64>(a) && fmg::fits8<64>(b)) || (fmg::fits8<128>(a) && fmg::fits8<128>(b)));
 }
 
-Fused use_fused(const Dims &m)
+// keep_gu: the caller keeps G and U (or, in a backward pass, they are recomputed into bf16 planes).  Without, the fused kernel
+// writes them in fp32 and the activation is a pass of its own, 16 bytes an element more than the epilogue of the slab
+// pipeline moves.
+Fused use_fused(const Dims &m, bool keep_gu)
 {
     const Fused none = {false, false, false, false}, all = {true, true, true, true};
     const int mode = fused_mode();
@@ -129,7 +136,8 @@ Fused use_fused(const Dims &m)
     if (mode >= 2) return k::fused_fits(fused_shape(m, true)) && k::fused_fits(fused_shape(m, false)) ? all : none;
     // longer segments, more experts and stacks of 2 GiB and more would run on the four-wave kernel
     if (!eight_waves(m)) return none;
-    return {fused_pays(m, m.dff, m.d, 2, 1), fused_pays(m, m.d, m.dff, 1, 1), fused_pays(m, m.dff, m.d, 1, 1),
+    const bool gate_up = fused_pays(m, m.dff, m.d, 2, 1, keep_gu ? 0.0 : 3.4e-6 * m.tokens * m.dff);
+    return {gate_up, fused_pays(m, m.d, m.dff, 1, 1), fused_pays(m, m.dff, m.d, 1, 1),
             fused_pays(m, m.d, m.dff, 2, 2)};
 }
 
@@ -386,8 +394,7 @@ size_t bf16_merged_save_bytes(const Dims &m)
 // in fp32 where that fits the slab, so that the activation rounds once as in the slab pipeline's epilogue.  Otherwise the call
 // takes the slab, at every token count, and asks for no more workspace than it; only where the merge inside the GEMM is asked
 // for (modes 2 and 3) the planes are rounded.  Error of Y against 64 bits, 1e-3, 11 segments of 64, 8 experts of 512 x 1408: slab
-// 3.714, fp32 planes 3.713, rounded planes 4.46.  Their bytes cost 1.8 % of a forward pass on average (50 layers, T = 64 and
-// 128; 10 % at most, 192 segments of 64, 16 experts of 960 x 1792), which takes 0.85 of the slab's time on average all the same.
+// 3.714, fp32 planes 3.713, rounded planes 4.46.
 enum class Planes { kNone, kF32, kBf16 };
 
 Planes gate_up_planes(const Dims &m, const Plan &p, bool explicitly)
@@ -402,7 +409,7 @@ size_t bf16_workspace_bytes(const Dims &m, int pass)
     if (pass == LORY_PASS_FWD) {
         // rounded G and U of all tokens when the caller does not keep them
         const bool explicitly = fused_mode() > 1;
-        const size_t gu = explicitly && use_fused(m).gate_up && gate_up_planes(m, p, explicitly) == Planes::kBf16 ? 2 * p.act : 0;
+        const size_t gu = explicitly && use_fused(m, false).gate_up && gate_up_planes(m, p, explicitly) == Planes::kBf16 ? 2 * p.act : 0;
         return p.act + (p.slab_fwd > gu ? p.slab_fwd : gu);
     }
     // dG, dU, Act, recomputed G and U, slabs, router-weight partial sums
@@ -438,8 +445,8 @@ int bf16_ffn_fwd(const Dims &m, const void *Xv, const float *w, const void *Wgv,
     bf *slab = (bf *)((char *)ws + pl.act);
     const long TD = (long)m.T * m.d, TF = (long)m.T * m.dff;
 
-    Fused fused = Wbar || m.S > pl.Sc ? Fused{} : use_fused(m);
-    const Planes planes = G && U ? Planes::kBf16 : gate_up_planes(m, pl, fused_mode() > 1);
+    Fused fused = Wbar || m.S > pl.Sc ? Fused{} : use_fused(m, G != nullptr);
+    const Planes planes = G ? Planes::kBf16 : gate_up_planes(m, pl, fused_mode() > 1);
     if (planes == Planes::kNone) fused.gate_up = false;
     if (fused.gate_up) {
         // merged parameters never leave the chip: fused contractions and one SwiGLU pass
@@ -826,7 +833,7 @@ int bf16_ffn_bwd(const Dims &m, const void *Xv, const float *w, const void *Wgv,
     const int grad_f32 = (grad_dtype == LORY_F32) ? 1 : 0;
     // token contractions with the merge inside the GEMM (no re-merged slabs); the per-segment weight
     // gradients still pass through the slab
-    const Fused fused = Wbar || m.S > pl.Sc ? Fused{} : use_fused(m);
+    const Fused fused = Wbar || m.S > pl.Sc ? Fused{} : use_fused(m, true);
     // ... unless the expert-gradient kernel that keeps them on chip takes the shape (bf16 gradients
     // that overwrite; at most 16 experts)
     auto dw_params = [&](const bf *A, int lda, const bf *B, int ldb, const bf *W, void *dW, int M, int N) {

@@ -623,6 +623,41 @@ def test_bf16_contractions_choose_for_themselves(d, d_ff, fused, slab, save, def
     compare(cfg, got, ref, ALL if save else ("Y", "dX", "dWg", "dWu", "dWd", "dw"), TOL["bf16"])
 
 
+# The estimate behind the choice counts the merged values that segments share: the first two of every sequence.  Sixteen
+# sequences of two 128-token segments go through the slab, one sequence of as many segments is merged inside the GEMM.  A
+# forward pass that does not keep G and U counts their fp32 planes.  Reference: everything through the slab.
+@pytest.mark.parametrize("B,N,d,d_ff,fused,not_kept", [
+    (16, 2, 1024, 1408, set(), "gemm_gate_up"), (1, 32, 1024, 1408, {"fused_gate_up", "fused_dA"}, "gemm_gate_up"),
+    (20, 2, 768, 1408, {"fused_gate_up", "fused_dA"}, "gemm_gate_up"), (1, 40, 768, 1408, {"fused_gate_up", "fused_dA"}, "fused_gate_up"),
+])
+def test_bf16_choice_counts_shared_segments(B, N, d, d_ff, fused, not_kept, default_budget):
+    print(f"[gpu] shared segments {B} {N} {d} {d_ff}", flush=True)
+    T, E, gen = 128, 2, torch.Generator(device="cuda").manual_seed(131)
+    rand = lambda *s, sigma=1.0: torch.randn(s, generator=gen, device="cuda").mul_(sigma).bfloat16()
+    X, dY, W = rand(B, N * T, d), rand(B, N * T, d), [rand(E, d, d_ff, sigma=0.02), rand(E, d, d_ff, sigma=0.02), rand(E, d_ff, d, sigma=0.02)]
+    w = lb.lory_route(X, rand(d, E, sigma=d ** -0.5), T, d_ff=d_ff)
+    out = {}
+    lb.lory_profile_enable(True)
+    try:
+        for mode in (0, 1):
+            lb.lory_set_fused_merge(mode)
+            lb.lory_profile_read()
+            G, U = (torch.empty((B * N * T, d_ff), dtype=X.dtype, device="cuda") for _ in range(2))
+            Y = lb.lory_merged_ffn_fwd(X, w, *W, T, G_save=G, U_save=U)
+            grads = lb.lory_merged_ffn_bwd(X, w, *W, dY, T, G_save=G, U_save=U)
+            kept = {s["name"] for s in lb.lory_profile_read()}
+            Yn = lb.lory_merged_ffn_fwd(X, w, *W, T)
+            classes = {s["name"] for s in lb.lory_profile_read()}
+            out[mode] = (Y, Yn) + tuple(grads)
+            assert {c for c in kept if c.startswith("fused")} == (fused if mode else set()), kept
+            assert classes & {"gemm_gate_up", "fused_gate_up"} == {not_kept if mode else "gemm_gate_up"}, classes
+    finally:
+        lb.lory_profile_enable(False)
+        lb.lory_set_fused_merge(1)
+    for i, (a, b) in enumerate(zip(*out.values())):
+        check(f"output {i}", host(b), host(a), TOL["bf16"])
+
+
 # A lowered budget holds less than G and U of all tokens: a forward pass that does not keep them takes the slab, block by
 # block, whether its tokens fill the row chunks or not.
 @pytest.mark.parametrize("save", [True, False], ids=["saved_GU", "recompute_GU"])
