@@ -96,12 +96,12 @@ int lory_set_slab_budget(size_t bytes);
  *   0  never
  *   1  where it is estimated to be faster (default), for each of the layer's
  *      token contractions by itself: T = 64 or 128, 2 <= E <= 16, an expert stack
- *      below 2 GiB.  The fused kernel is bound by the L2 -> CU path at about the
- *      same rate for every segment length, while the slab pipeline's HBM
+ *      below 4 GiB if T = 128.  The fused kernel is bound by the L2 -> CU path at
+ *      about the same rate for every segment length, while the slab pipeline's HBM
  *      traffic grows with the number of segments
- *   2  wherever the shape fits the kernel: T in {64, 128} with E <= 16, else T in
- *      {64, 128, 256}, E <= 32, B*L a multiple of 1024 (512 for T <= 128); no
- *      Wbar_save given
+ *   2  wherever the shape fits the kernel: T in {64, 128} with E <= 16 and an
+ *      expert stack below 4 GiB, else T in {64, 128, 256}, E <= 32, B*L a multiple
+ *      of 1024 (512 for T <= 128); no Wbar_save given
  *   3  as 2, and the backward also keeps the per-segment weight gradients on
  *      chip (expert gradients and routing-weight inner products accumulated by
  *      the kernel that forms X_s^T dG_s; no gradient slab in HBM) where that

@@ -99,16 +99,33 @@ struct Fused {
 // Layers of fewer parameters than measured stay on the slab with 128-token segments, where the two forms are close.
 constexpr long kFusedLeastD = 500000;
 
+double slab_us(const Dims &m, int mats)
+{
+    const long distinct = m.N > 1 ? m.S - m.B : m.S;
+    return 15.0 + mats * (6.9 + 2e-6 * m.D * (0.215 * distinct + (m.T > 64 ? 0.215 : 0.172) * m.S + 0.165 * m.E));
+}
+
 bool fused_pays(const Dims &m, int N, int K, int mats, int nsrc, double extra_us = 0.0)
 {
-    const bool few = k::merge_is_few(m.S, m.E), longer = m.T > 64;
-    if (m.E < 2 || (longer && (few || m.D < kFusedLeastD))) return false;
+    const bool few = k::merge_is_few(m.S, m.E);
+    if (m.E < 2 || (m.T > 64 && (few || m.D < kFusedLeastD))) return false;
     const long cus = gemm2::cu_count(), chunks = (m.tokens + fmg::kRows8 - 1) / fmg::kRows8;
     const long tasks = chunks * (N / fmg::BN) * (mats / nsrc), rounds = ((tasks + 7) / 8 + cus / 8 - 1) / (cus / 8);
     const double fused = 8.3 + extra_us + (double)rounds * nsrc * (K / fmg::BK) * (1.17 + m.E * (0.038 + 0.031 / (chunks < 8 ? chunks : 8)));
-    const long distinct = m.N > 1 ? m.S - m.B : m.S;
-    const double slab = 15.0 + mats * (6.9 + 2e-6 * m.D * (0.215 * distinct + (longer ? 0.215 : 0.172) * m.S + 0.165 * m.E));
-    return fused < (few ? 0.76 : 0.90) * slab;
+    return fused < (few ? 0.76 : 0.90) * slab_us(m, mats);
+}
+
+// The same on the four-wave kernel, for stacks of 4 GiB and more, which the eight-wave kernel does not take.  Supertasks of 8
+// row chunks by 4 column blocks, one to an XCD at a time; with fewer than four row chunks hardly any expert chunk is shared.
+// A K step of K-slow stacks takes 2.3 us with 8 experts and 2.45 with 16, of K-contiguous ones (dA, dX) 2.2 and 3.5.
+// ms of slab and fused, 8192 tokens in segments of 64: gate/up, down of 16 experts of 8192 x 16384 28.5, 14.2 and 20.4, 10.2
+// (2048 tokens 8.3, 4.1 and 10.2, 5.1), dA + dX 42 and 44; backward pass of 16384 tokens, 8 of 16384 x 16384 378 and 318.
+bool fused_pays_four(const Dims &m, int N, int K, int mats, bool k_slow)
+{
+    const long chunks = (m.tokens + fmg::kRows8 - 1) / fmg::kRows8, super = (chunks + 7) / 8 * ((N / fmg::BN + 3) / 4);
+    const double step = k_slow ? 2.15 + 0.019 * m.E : 0.9 + 0.163 * m.E;
+    const double fused = mats * (10.0 + (double)((super + 7) / 8) * (K / fmg::BK) * step);
+    return m.T <= 64 && m.E >= 2 && m.E <= 16 && chunks >= 4 && fused < 0.90 * slab_us(m, mats);
 }
 
 // The contractions of the layer have N and K in {d, d_ff}: parameters of the two products, for the shape conditions alone.
@@ -133,9 +150,12 @@ Fused use_fused(const Dims &m, bool keep_gu)
     const Fused none = {false, false, false, false}, all = {true, true, true, true};
     const int mode = fused_mode();
     if (mode == 0 || m.tokens > 0x7fffffffL) return none;
-    if (mode >= 2) return k::fused_fits(fused_shape(m, true)) && k::fused_fits(fused_shape(m, false)) ? all : none;
-    // longer segments, more experts and stacks of 2 GiB and more would run on the four-wave kernel
-    if (!eight_waves(m)) return none;
+    const bool fits = k::fused_fits(fused_shape(m, true)) && k::fused_fits(fused_shape(m, false));
+    if (!fits || mode >= 2) return fits ? all : none;
+    // longer segments, more experts and stacks of 4 GiB and more run on the four-wave kernel, which does not write fp32 planes
+    if (!eight_waves(m))
+        return {keep_gu && fused_pays_four(m, m.dff, m.d, 2, true), fused_pays_four(m, m.d, m.dff, 1, true),
+                fused_pays_four(m, m.dff, m.d, 1, false), fused_pays_four(m, m.d, m.dff, 2, false)};
     const bool gate_up = fused_pays(m, m.dff, m.d, 2, 1, keep_gu ? 0.0 : 3.4e-6 * m.tokens * m.dff);
     return {gate_up, fused_pays(m, m.d, m.dff, 1, 1), fused_pays(m, m.dff, m.d, 1, 1),
             fused_pays(m, m.d, m.dff, 2, 2)};

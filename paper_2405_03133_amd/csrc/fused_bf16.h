@@ -537,7 +537,7 @@ __global__ __launch_bounds__(512, 1) void fmg8_kernel(const Params p)
         // expert chunks of a K step: lane (c16, kg) loads its chunk of unit kg >> 1 from experts
         // 8 (kg & 1) .. + 7.   W_NC: units = K rows 4 wave + 2 u + {0, 1}, chunk = 8 columns.
         // else: units = columns 8 wave + 4 u + {0..3}, chunk = 8 K values (64 bytes per column).
-        // (byte offsets from the K step's first element, 32 bits: the stack is smaller than 2 GiB)
+        // (byte offsets from the K step's first element, 32 bits without sign: the stack is smaller than 4 GiB)
         uint32_t w_off[8];
         {
             uint32_t w_lane;
@@ -557,7 +557,7 @@ __global__ __launch_bounds__(512, 1) void fmg8_kernel(const Params p)
             const int ks = (NSRC == 2) ? (g % ksteps) : g;
             const uint16_t *wk = p.W[src] + (W_NC ? (size_t)ks * BK * p.ldw : (size_t)ks * BK);
             // every offset lies inside the stack: the range is that of the offsets
-            const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(wk), 0, 0x7fffffff, 0x00027000);
+            const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(wk), 0, 0xffffffff, 0x00027000);
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(r, w_off[i], 0, 0);
@@ -748,7 +748,7 @@ template <int TSEG>
 inline bool fits8(const Params &p)
 {
     return p.T == TSEG && p.tokens >= TSEG && p.tokens % TSEG == 0 && p.N % BN == 0 && p.K % (2 * BK) == 0 && p.E <= 16 && p.E >= 1 &&
-           p.lda[0] == p.lda[1] && (size_t)p.E * (size_t)p.expert_stride * 2 < ((size_t)1 << 31);
+           p.lda[0] == p.lda[1] && (size_t)p.E * (size_t)p.expert_stride * 2 < ((size_t)1 << 32);
 }
 
 template <int TSEG, int NSRC, bool W_NC, bool PAIR, bool F32 = false>

@@ -679,6 +679,58 @@ def test_bf16_contractions_within_a_lowered_budget(B, L, save, default_budget):
     compare(cfg, got, ref, ALL if save else ("Y", "dX", "dWg", "dWu", "dWd", "dw"), TOL["bf16"])
 
 
+# Expert stacks of 2 GiB and more: byte offsets beyond 2^31 on the eight-wave kernel, and stacks that it does not take (4 GiB
+# and more), whose forward pass runs on the four-wave kernel where it keeps G and U.  Reference: everything through the slab.
+@pytest.mark.parametrize("d,d_ff,L,backward,classes", [
+    (4096, 16448, 192, True, {"fused_gate_up", "fused_down", "fused_dA", "fused_dX"}),
+    (8192, 16448, 8192, False, {"fused_gate_up", "fused_down"}),
+])
+def test_bf16_merge_inside_the_gemm_of_very_large_stacks(d, d_ff, L, backward, classes, default_budget):
+    print(f"[gpu] very large stacks {d} {d_ff} {L}", flush=True)
+    T, E, gen = 64, 16, torch.Generator(device="cuda").manual_seed(132)
+
+    def rand(*shape, sigma=1.0):
+        out = torch.empty(shape, dtype=torch.bfloat16, device="cuda")
+        for part in out:   # one matrix in fp32 at a time
+            part.copy_(torch.randn(part.shape, generator=gen, device="cuda") * sigma)
+        return out
+
+    def rel(a, b):
+        err, ref = 0.0, 0.0
+        for x, y in zip(a, b):
+            err += float((x.float() - y.float()).square().sum(dtype=torch.float64))
+            ref += float(y.float().square().sum(dtype=torch.float64))
+        return (err / ref) ** 0.5
+
+    X, dY = rand(1, L, d), rand(1, L, d)
+    W = [rand(E, d, d_ff, sigma=0.02), rand(E, d, d_ff, sigma=0.02), rand(E, d_ff, d, sigma=0.02)]
+    assert 2 * W[0].numel() >= (1 << 31 if backward else 1 << 32)
+    w = torch.softmax(torch.randn((L // T, E), generator=gen, device="cuda"), -1)
+    out = {}
+    lb.lory_profile_enable(True)
+    try:
+        for mode in (0, 2 if backward else 1):
+            lb.lory_set_fused_merge(mode)
+            lb.lory_profile_read()
+            G, U = (torch.empty((L, d_ff), dtype=X.dtype, device="cuda") for _ in range(2))
+            out[mode] = [lb.lory_merged_ffn_fwd(X, w, *W, T, G_save=G, U_save=U)]
+            if backward:
+                out[mode] += lb.lory_merged_ffn_bwd(X, w, *W, dY, T, G_save=G, U_save=U, grad_dtype=torch.bfloat16)
+            got = {s["name"] for s in lb.lory_profile_read()}
+            assert {c for c in got if c.startswith("fused")} == (classes if mode else set()), got
+        if not backward:   # without kept G and U the activation is rounded once, through the slab
+            out[1] += [lb.lory_merged_ffn_fwd(X, w, *W, T)]
+            out[0] += [out[0][0]]
+            assert {"gemm_gate_up", "fused_down"} <= {s["name"] for s in lb.lory_profile_read()}
+    finally:
+        lb.lory_profile_enable(False)
+        lb.lory_set_fused_merge(1)
+    for i, (a, b) in enumerate(zip(*out.values())):
+        err = rel(b, a)
+        print(f"[parity] output {i}: {err:.2e}", flush=True)
+        assert err <= TOL["bf16"], i
+
+
 # Without saved G and U the activation is formed from fp32 and rounded once, as through the slab.  Tensor-wide relative
 # rounding errors, 1.65e-3 each: weights of gate and up, activation, weights of down, output.  G and U rounded before would
 # add two more of that size (SwiGLU's slopes are near 1): 1.2 times the error; 1.03 allows for the scatter of its parts.
