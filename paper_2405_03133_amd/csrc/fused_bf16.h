@@ -675,7 +675,12 @@ __global__ __launch_bounds__(512, 1) void fmg8_kernel(const Params p)
             // tokens of step g + 2 before chunks of step g + 3, which step g + 2 consumes before it multiplies
             for (int g = 0; g < G; ++g) {
                 gemm2::ring_barrier();
-                if (g + 1 < G) produce(g + 1);
+                if (g + 1 < G) {
+                    produce(g + 1);
+                    // No barrier stands between produce's wait for the chunks of step g + 1 and the reads of token tile g, which
+                    // that wait covers: said here, for the reads to stay below it.  Only the NLD loads of tile g + 1 are in flight.
+                    gemm2::wait_vmcnt<NLD>();
+                }
                 if (g + 2 < G) load_ex(g + 2);
                 multiply(g, 0);
                 multiply(g, 1);
