@@ -823,6 +823,13 @@ ROUTE_BWD_CASES = [
     LoryConfig("f32_many_segments", B=2, L=640, T=4, d=40, d_ff=8, E=6, dtype="f32", seed=26),
     LoryConfig("bf16_route_bwd", B=2, L=512, T=64, d=192, d_ff=64, E=8, dtype="bf16", seed=41),
     LoryConfig("bf16_route_bwd_E33", B=3, L=384, T=128, d=320, d_ff=64, E=33, dtype="bf16", seed=42),
+    # more rows to a wavefront than it has in flight, with a remainder (41) and without (32), over several chunks of segments;
+    # several blocks of columns, the last one partly filled, with and without 16-byte accesses
+    LoryConfig("f32_route_bwd_rows", B=100, L=697, T=41, d=40, d_ff=8, E=6, dtype="f32", seed=43),
+    LoryConfig("bf16_route_bwd_rows", B=64, L=832, T=64, d=192, d_ff=64, E=5, dtype="bf16", seed=44),
+    LoryConfig("bf16_route_bwd_wide", B=1, L=192, T=64, d=2176, d_ff=64, E=9, dtype="bf16", seed=45),
+    LoryConfig("f32_route_bwd_wide", B=2, L=36, T=12, d=1100, d_ff=8, E=48, dtype="f32", seed=46),
+    LoryConfig("f32_route_bwd_wide_odd", B=2, L=36, T=12, d=1101, d_ff=8, E=5, dtype="f32", seed=47),
 ]
 
 
