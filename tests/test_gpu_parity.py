@@ -558,10 +558,11 @@ def test_bf16_saved_merged_parameters_match_remerge(idx, default_budget):
 FUSED_CASES = [
     # T = 256: one segment per wavefront; odd number of 64-column blocks, K not a multiple of 64
     LoryConfig("fused_T256", B=2, L=1024, T=256, d=192, d_ff=320, E=8, dtype="bf16", seed=91),
-    # T = 128 on the large tile (two segments per wavefront) and on the small one (512 tokens)
+    # T = 128 with more than 16 experts: the four-wave kernel on the large tile (two segments per wavefront); with at most 16
+    # the eight-wave kernel, like the T = 64 cases below
     LoryConfig("fused_T128", B=2, L=512, T=128, d=128, d_ff=192, E=32, dtype="bf16", seed=92),
     LoryConfig("fused_T128_small", B=1, L=512, T=128, d=128, d_ff=128, E=5, dtype="bf16", seed=93),
-    # T = 64: two segments per wavefront on the small tile; three tasks along the rows
+    # T = 64: three tasks along the rows
     LoryConfig("fused_T64", B=3, L=512, T=64, d=128, d_ff=256, E=16, dtype="bf16", seed=94),
     # T = 64 on the eight-wave kernel with the second group of eight experts partly and wholly absent
     LoryConfig("fused_T64_E11", B=2, L=256, T=64, d=128, d_ff=192, E=11, dtype="bf16", seed=97),
@@ -577,6 +578,11 @@ FUSED_CASES = [
     LoryConfig("fused_one_expert", B=1, L=1024, T=256, d=64, d_ff=64, E=1, dtype="bf16", seed=95),
     # more tasks than one round of workgroups per XCD block, several K steps per source
     LoryConfig("fused_many_tasks", B=4, L=2048, T=128, d=512, d_ff=1024, E=16, dtype="bf16", seed=96),
+    # the small tile of the four-wave kernel
+    LoryConfig("fused_T128_small_E17", B=1, L=512, T=128, d=128, d_ff=128, E=17, dtype="bf16", seed=133),
+    # many tasks on the four-wave kernel, with more than 16 experts and with the forms for at most 16
+    LoryConfig("fused_many_tasks_E20", B=4, L=2048, T=128, d=512, d_ff=1024, E=20, dtype="bf16", seed=134),
+    LoryConfig("fused_many_tasks_T256", B=4, L=2048, T=256, d=512, d_ff=1024, E=12, dtype="bf16", seed=135),
 ]
 
 
@@ -680,14 +686,11 @@ def test_bf16_contractions_within_a_lowered_budget(B, L, save, default_budget):
 
 
 # Expert stacks of 2 GiB and more: byte offsets beyond 2^31 on the eight-wave kernel, and stacks that it does not take (4 GiB
-# and more), whose forward pass runs on the four-wave kernel where it keeps G and U.  Reference: everything through the slab.
-@pytest.mark.parametrize("d,d_ff,L,backward,classes", [
-    (4096, 16448, 192, True, {"fused_gate_up", "fused_down", "fused_dA", "fused_dX"}),
-    (8192, 16448, 8192, False, {"fused_gate_up", "fused_down"}),
-])
-def test_bf16_merge_inside_the_gemm_of_very_large_stacks(d, d_ff, L, backward, classes, default_budget):
+# and more), which run on the four-wave kernel where a forward pass keeps G and U.  Reference: everything through the slab.
+@pytest.mark.parametrize("d,d_ff,E,L,mode", [(4096, 16448, 16, 192, 2), (8192, 32832, 8, 4096, 1)])
+def test_bf16_merge_inside_the_gemm_of_very_large_stacks(d, d_ff, E, L, mode, default_budget):
     print(f"[gpu] very large stacks {d} {d_ff} {L}", flush=True)
-    T, E, gen = 64, 16, torch.Generator(device="cuda").manual_seed(132)
+    T, gen = 64, torch.Generator(device="cuda").manual_seed(132)
 
     def rand(*shape, sigma=1.0):
         out = torch.empty(shape, dtype=torch.bfloat16, device="cuda")
@@ -704,21 +707,20 @@ def test_bf16_merge_inside_the_gemm_of_very_large_stacks(d, d_ff, L, backward, c
 
     X, dY = rand(1, L, d), rand(1, L, d)
     W = [rand(E, d, d_ff, sigma=0.02), rand(E, d, d_ff, sigma=0.02), rand(E, d_ff, d, sigma=0.02)]
-    assert 2 * W[0].numel() >= (1 << 31 if backward else 1 << 32)
+    assert 2 * W[0].numel() >= (1 << 31 if mode == 2 else 1 << 32)
     w = torch.softmax(torch.randn((L // T, E), generator=gen, device="cuda"), -1)
     out = {}
     lb.lory_profile_enable(True)
     try:
-        for mode in (0, 2 if backward else 1):
-            lb.lory_set_fused_merge(mode)
+        for m in (0, mode):
+            lb.lory_set_fused_merge(m)
             lb.lory_profile_read()
             G, U = (torch.empty((L, d_ff), dtype=X.dtype, device="cuda") for _ in range(2))
-            out[mode] = [lb.lory_merged_ffn_fwd(X, w, *W, T, G_save=G, U_save=U)]
-            if backward:
-                out[mode] += lb.lory_merged_ffn_bwd(X, w, *W, dY, T, G_save=G, U_save=U, grad_dtype=torch.bfloat16)
+            out[m] = [lb.lory_merged_ffn_fwd(X, w, *W, T, G_save=G, U_save=U)]
+            out[m] += lb.lory_merged_ffn_bwd(X, w, *W, dY, T, G_save=G, U_save=U, grad_dtype=torch.bfloat16)
             got = {s["name"] for s in lb.lory_profile_read()}
-            assert {c for c in got if c.startswith("fused")} == (classes if mode else set()), got
-        if not backward:   # without kept G and U the activation is rounded once, through the slab
+            assert {c for c in got if c.startswith("fused")} == ({"fused_gate_up", "fused_down", "fused_dA", "fused_dX"} if m else set()), got
+        if mode == 1:   # without kept G and U the activation is rounded once, through the slab
             out[1] += [lb.lory_merged_ffn_fwd(X, w, *W, T)]
             out[0] += [out[0][0]]
             assert {"gemm_gate_up", "fused_down"} <= {s["name"] for s in lb.lory_profile_read()}
