@@ -809,7 +809,8 @@ inline hipError_t launch_t(const Params &p, hipStream_t st)
 template <int WROWS, int SPW, int NSRC, bool W_NC>
 inline hipError_t launch(const Params &p, hipStream_t st)
 {
-    if constexpr (4 * SPW <= 8) {
+    // 128-token segments with at most 16 experts come here with stacks of 4 GiB and more alone, where only modes 2 and 3 send them
+    if constexpr (WROWS / SPW != 128) {
         if (p.E <= 16) {
             if constexpr (!W_NC && Smem<WROWS, SPW, true>::total <= 160 * 1024)
                 return launch_t<WROWS, SPW, NSRC, W_NC, true, true>(p, st);
