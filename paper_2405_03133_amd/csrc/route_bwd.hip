@@ -118,7 +118,11 @@ __device__ __forceinline__ float softmax_jacobian_row(const float *__restrict__ 
     return softmax_jacobian(e, de);
 }
 
-// Adds dhbar[s, :] / T to rows [rb * rows_per, ...) of segment s of dX, 64 VEC columns from c0: the work of one wavefront.
+// Columns of dX for a wavefront: 16 bytes a lane, or one where rows are not whole 16-byte pieces.
+template <typename T>
+__host__ __device__ constexpr int wave_cols(int d) { return d % (16 / (int)sizeof(T)) == 0 ? 64 * (16 / (int)sizeof(T)) : 64; }
+
+// Adds dhbar[s, :] / T to rows [rb * rows_per, ...) of segment s of dX, wave_cols columns from c0: the work of one wavefront.
 template <typename T>
 __device__ __forceinline__ void route_bwd_dx(const T *__restrict__ R, const float *__restrict__ w, const float *__restrict__ dw,
                                              T *__restrict__ dX, int Tseg, int d, int E, int rows_per, int s, int rb, int c0,
@@ -178,7 +182,8 @@ __device__ __forceinline__ void route_bwd_dx(const T *__restrict__ R, const floa
             }
         }
     } else {
-        for (int k = c0 + lane; k < d && k < c0 + 64 * VEC; k += 64) {
+        const int k = c0 + lane;
+        if (k < d) {
             const float dh = dot_row(R + (size_t)k * E, dz, E) * invT;
             for (int t = t0; t < t1; ++t) {
                 T *p = Xs + (size_t)t * d + k;
@@ -278,19 +283,18 @@ __global__ __launch_bounds__(kDxThreads) void route_bwd_kernel(const T *__restri
         route_bwd_dr(hbar, w, dw, dR, S, d, E, N, accumulate, id, dz);
         return;
     }
-    constexpr int kCols = 64 * (16 / (int)sizeof(T));
-    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int u = (id - dr_blocks) * kWaves + wave, col_blocks = (d + kCols - 1) / kCols;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), cols = wave_cols<T>(d);
+    const int u = (id - dr_blocks) * kWaves + wave, col_blocks = (d + cols - 1) / cols;
     const int seg_row = u / col_blocks, seg = seg_row / row_blocks;
     if (seg >= S / N * (N - 1)) return;
-    route_bwd_dx(R, w, dw, dX, Tseg, d, E, rows_per, seg / (N - 1) * N + seg % (N - 1), seg_row % row_blocks, u % col_blocks * kCols, dz[wave]);
+    route_bwd_dx(R, w, dw, dX, Tseg, d, E, rows_per, seg / (N - 1) * N + seg % (N - 1), seg_row % row_blocks, u % col_blocks * cols, dz[wave]);
 }
 
 template <typename T>
 int launch_route_bwd(const Dims &m, const void *R, const float *w, const float *hbar, const float *dw,
                      void *dX, float *dR, int accumulate, hipStream_t st)
 {
-    const int col_blocks = (m.d * (int)sizeof(T) + 1023) / 1024, segs = m.S - m.B;
+    const int col_blocks = (m.d + wave_cols<T>(m.d) - 1) / wave_cols<T>(m.d), segs = m.S - m.B;
     long rb = segs > 0 ? (kDxWaves + (long)segs * col_blocks - 1) / ((long)segs * col_blocks) : 1;
     if (rb > m.T / 8) rb = m.T / 8;
     if (rb < 1) rb = 1;
