@@ -279,7 +279,7 @@ constexpr int few_unit_chunks(int E) { return E <= 8 ? 64 : 32; }
 // KS 0: a unit has 64 chunks, and the two halves of the wavefront load 32 each; each half goes to the matrix cores as
 // K = 0 .. 7, with zeros in the place of experts 8 .. 15 (as merge_kernel has them).
 template <int KS, int NR, bool MAP>
-__global__ __launch_bounds__(256, KS > 2 ? 2 : KS == 2 || NR > 4 ? 3 : 4) void merge_few_kernel(const MergeFewParams p)
+__global__ __launch_bounds__(256, KS > 2 ? 2 : KS == 2 ? 3 : NR > 4 ? 4 : 5) void merge_few_kernel(const MergeFewParams p)
 {
     constexpr int KN = KS > 0 ? KS : 1, UN = KS > 0 ? 1 : 2;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -343,48 +343,45 @@ __global__ __launch_bounds__(256, KS > 2 ? 2 : KS == 2 || NR > 4 ? 3 : 4) void m
     uint4 o[UN][NR];
 #pragma unroll
     for (int jj = 0; jj < 4; ++jj) {   // elements 2 jj and 2 jj + 1 of the chunk
-        float v[UN][2][NR];
+        Frag P[UN][2][KN];   // eight experts of an element: a column of transpose8x8
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            Frag P[UN][KN];   // eight experts of the element: a column of transpose8x8
+        for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int ks = 0; ks < KN; ++ks)
 #pragma unroll
                 for (int ip = 0; ip < 4; ++ip) {
                     const uint32_t t = __builtin_amdgcn_perm(R[ks][2 * ip + 1].w[jj], R[ks][2 * ip].w[jj], j ? 0x07060302u : 0x05040100u);
                     if constexpr (KS > 0) {
-                        P[0][ks].w[ip] = t;
+                        P[0][j][ks].w[ip] = t;
                     } else {
                         const auto two = __builtin_amdgcn_permlane32_swap(t, 0u, false, false);   // {lower half, 0}, {upper half, 0}
-                        P[0][ks].w[ip] = two[0];
-                        P[UN - 1][ks].w[ip] = two[1];
+                        P[0][j][ks].w[ip] = two[0];
+                        P[UN - 1][j][ks].w[ip] = two[1];
                     }
                 }
 #pragma unroll
-            for (int u = 0; u < UN; ++u) {
-                f32x16 acc;
+        for (int u = 0; u < UN; ++u) {
+            f32x16 acc[2];
 #pragma unroll
-                for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+            for (int j = 0; j < 2; ++j) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[j][r] = 0.f;
 #pragma unroll
                 for (int ks = 0; ks < KN; ++ks) {
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(whi[ks].v, P[u][ks].v, acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wlo[ks].v, P[u][ks].v, acc, 0, 0, 0);
+                    acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(whi[ks].v, P[u][j][ks].v, acc[j], 0, 0, 0);
+                    acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wlo[ks].v, P[u][j][ks].v, acc[j], 0, 0, 0);
                 }
-#pragma unroll
-                for (int r = 0; r < NR; ++r) v[u][j][r] = acc[r];
             }
-        }
-#pragma unroll
-        for (int u = 0; u < UN; ++u)
 #pragma unroll
             for (int r = 0; r < NR; ++r) {
-                uint32_t t = pack_bf16(v[u][0][r], v[u][1][r]);
+                uint32_t t = pack_bf16(acc[0][r], acc[1][r]);
                 asm volatile("" : "+v"(t));   // packed here and not beside the stores, where all accumulators would be alive
                 if (jj == 0) o[u][r].x = t;
                 if (jj == 1) o[u][r].y = t;
                 if (jj == 2) o[u][r].z = t;
                 if (jj == 3) o[u][r].w = t;
             }
+        }
         __builtin_amdgcn_sched_barrier(0);
     }
     uint16_t *slab = p.slab[blockIdx.y];
