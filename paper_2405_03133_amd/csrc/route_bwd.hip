@@ -272,7 +272,7 @@ __device__ __forceinline__ void route_bwd_dr(const float *__restrict__ hbar, con
 // Workgroups 0 .. dr_blocks - 1: dR (they start first: a chain of loads, few bytes); the others: dX, a wavefront for 64 chunks
 // of columns in a block of rows of a segment that routes (all but the last of every sequence), columns first.
 template <typename T>
-__global__ __launch_bounds__(kDxThreads) void route_bwd_kernel(const T *__restrict__ R, const float *__restrict__ w,
+__global__ __launch_bounds__(kDxThreads) void route_bwd_dx_kernel(const T *__restrict__ R, const float *__restrict__ w,
                                                                const float *__restrict__ hbar, const float *__restrict__ dw,
                                                                T *__restrict__ dX, float *__restrict__ dR, int S, int Tseg, int d,
                                                                int E, int N, int rows_per, int row_blocks, int accumulate, int dr_blocks)
@@ -301,7 +301,7 @@ int launch_route_bwd(const Dims &m, const void *R, const float *w, const float *
     const int rows_per = (int)((m.T + rb - 1) / rb), row_blocks = (m.T + rows_per - 1) / rows_per;
     const int dr_blocks = (m.d + kDrRows - 1) / kDrRows;
     const long units = (long)segs * row_blocks * col_blocks;
-    hipLaunchKernelGGL((route_bwd_kernel<T>), dim3((unsigned)(dr_blocks + (units + kWaves - 1) / kWaves)), dim3(kDxThreads), 0, st, (const T *)R, w, hbar, dw,
+    hipLaunchKernelGGL((route_bwd_dx_kernel<T>), dim3((unsigned)(dr_blocks + (units + kWaves - 1) / kWaves)), dim3(kDxThreads), 0, st, (const T *)R, w, hbar, dw,
                        (T *)dX, dR, m.S, m.T, m.d, m.E, m.N, rows_per, row_blocks, accumulate, dr_blocks);
     return launch_status();
 }
