@@ -90,9 +90,10 @@ struct Fused {
 // the GEMM.  The first two segments of every sequence share their merged values: one of them is not stored, and read
 // from the cache in part.  Fitted to both forms of 600 layers each of 64- and 128-token segments (1 .. 120 sequences of 2 .. 240
 // segments, 2 .. 16 experts, d = 768 .. 2560, d_ff = 704 .. 6144): off by 9 and 8 % (rms).  The margins keep out what is not
-// clearly faster: 0.90, 17 of 2950 contractions take 3 % longer than through the slab, 1.12 at worst; merges of few segments
-// run at the memory's rate, and where their unevenly filled rounds of tasks are estimated well is within 0.76.  Time of the
-// slab's that is left, many segments, T = 64: gate/up 0.56, down 0.73, dA 0.61, dX 0.78; T = 128: 0.95, 0.99, 0.96, 1.00; few segments, T = 64:
+// clearly faster: 0.94 with 64- and 0.90 with 128-token segments, 38 of 3540 contractions take 3 % longer than through the slab,
+// 1.18 at worst (0.90 for both: 29, but 0.5 % of the gain is lost); with few segments the merges run at the memory's rate and
+// rounds of tasks are unevenly filled: 0.76.  Time of the slab's that is left,
+// many segments, T = 64: gate/up 0.56, down 0.72, dA 0.61, dX 0.78; T = 128: 0.95, 0.99, 0.96, 1.00; few segments, T = 64:
 // 0.88, 1.00, 0.95, 1.00 (T = 128 0.98 for gate/up, 1.25 at worst: the slab).  us of slab and fused: gate/up of 82 segments of
 // 64, 7 experts of 1792 x 4160 1280 and 650; dX of 3 segments, 14 of 1792 x 5632 230 and 650; a backward pass of 16 sequences of two
 // 128-token segments, 4 of 2048 x 5632 1901 and 1997.  One expert always takes the slab: its segments share their merged values.
@@ -112,7 +113,7 @@ bool fused_pays(const Dims &m, int N, int K, int mats, int nsrc, double extra_us
     const long cus = gemm2::cu_count(), chunks = (m.tokens + fmg::kRows8 - 1) / fmg::kRows8;
     const long tasks = chunks * (N / fmg::BN) * (mats / nsrc), rounds = ((tasks + 7) / 8 + cus / 8 - 1) / (cus / 8);
     const double fused = 8.3 + extra_us + (double)rounds * nsrc * (K / fmg::BK) * (1.17 + m.E * (0.038 + 0.031 / (chunks < 8 ? chunks : 8)));
-    return fused < (few ? 0.76 : 0.90) * slab_us(m, mats);
+    return fused < (few ? 0.76 : m.T > 64 ? 0.90 : 0.94) * slab_us(m, mats);
 }
 
 // The same on the four-wave kernel, for stacks of 4 GiB and more, which the eight-wave kernel does not take.  Supertasks of 8
